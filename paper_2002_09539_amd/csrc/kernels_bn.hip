@@ -34,9 +34,17 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;
 
-// pixel ranges per group: about 2048 pixels each, at most 256
-__host__ __device__ inline int bn_ranges(int P) {
+// Pixel ranges per group: about 2048 pixels each, at most 256 -- and where that leaves the chip idle, as many more as give
+// it four workgroups per compute unit, while a range keeps at least 64 pixels.  (3 workers x 3900 pixels x 128 channels:
+// two ranges per worker were six workgroups of 1950 pixels each, a serial chain of 75 us per backward call; 61 ranges
+// of 64 pixels take the call from 88 to 17 us.)
+__host__ __device__ inline int bn_ranges(int groups, int P) {
     int r = (P + 2047) / 2048;
+    int fill = (1024 + groups - 1) / groups;
+    const int most = (P + 63) / 64;
+    if (fill > most) fill = most;
+    if (fill > 64) fill = 64;
+    if (r < fill) r = fill;
     return r < 1 ? 1 : (r > 256 ? 256 : r);
 }
 
@@ -118,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void bn_stats_final_kernel(const float* _
 // the benchmark shape -- every workgroup touched all of a group's cache lines for an eighth of their bytes; with 4 x 64
 // 40 us.  The two levels take 10 + 5 us; 32 or 16 channels per workgroup and 10 - 19 parts in flight change nothing.)
 constexpr int kWaveStatChunks = 16, kWaveStatChannels = 64, kWaveStatStripes = kThreads / kWaveStatChannels, kWaveStatBatch = 12;
-__host__ __device__ inline int wave_stat_chunks(int P) { const int r = bn_ranges(P); return r < kWaveStatChunks ? r : kWaveStatChunks; }
+__host__ __device__ inline int wave_stat_chunks(int groups, int P) { const int r = bn_ranges(groups, P); return r < kWaveStatChunks ? r : kWaveStatChunks; }
 
 __device__ __forceinline__ void merge_moments(float& n, float& mean, float& m2, float nr, float mean_r, float m2_r) {
     if (nr > 0.0f) {
@@ -373,19 +381,33 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_partial_kernel(const float* _
     }
 }
 
-// sums[group][2][C] = the ranges' sums added in range order; d beta = sums[0], d gamma = sums[1] go to the gradient rows
+// sums[group][2][C] = the ranges' sums; d beta = sums[0], d gamma = sums[1] go to the gradient rows.  A workgroup owns 32
+// channels: each of its eight stripes adds every eighth range in range order (eight ranges requested at a time), and the
+// stripes' sums are added in stripe order.
+constexpr int kFinalChannels = 32, kFinalStripes = kThreads / kFinalChannels;
 __global__ __launch_bounds__(kThreads) void bn_bwd_final_kernel(const float* __restrict__ part, float* sums, float* g_out,
                                                                 int64_t ld, int64_t gamma_off, int64_t beta_off, int C,
                                                                 int ranges) {
-    const int c = blockIdx.x * kThreads + threadIdx.x;
-    if (c >= C) return;
+    __shared__ float lds[2][kThreads];
+    const int cl = threadIdx.x % kFinalChannels, stripe = threadIdx.x / kFinalChannels;
+    const int c = blockIdx.x * kFinalChannels + cl;
     const int g = blockIdx.y;
     float s1 = 0.0f, s2 = 0.0f;
+    if (c < C) {
+        const float* P = part + (int64_t)g * ranges * 2 * C + c;
 #pragma unroll 8
-    for (int r = 0; r < ranges; ++r) {
-        const float* o = part + (((int64_t)g * ranges + r) * 2) * C + c;
-        s1 += o[0];
-        s2 += o[C];
+        for (int r = stripe; r < ranges; r += kFinalStripes) {
+            s1 += P[(int64_t)r * 2 * C];
+            s2 += P[((int64_t)r * 2 + 1) * C];
+        }
+    }
+    lds[0][threadIdx.x] = s1;
+    lds[1][threadIdx.x] = s2;
+    __syncthreads();
+    if (stripe || c >= C) return;
+    for (int k = 1; k < kFinalStripes; ++k) {
+        s1 += lds[0][k * kFinalChannels + cl];
+        s2 += lds[1][k * kFinalChannels + cl];
     }
     sums[((int64_t)g * 2) * C + c] = s1;
     sums[((int64_t)g * 2 + 1) * C + c] = s2;
@@ -444,7 +466,7 @@ bool vec_grid(int64_t vecs, unsigned* blocks) {   // 31-bit vector indices (the 
 
 }  // namespace
 
-int64_t bn_partial_floats(int groups, int P, int C) { return (int64_t)groups * bn_ranges(P) * 3 * C; }
+int64_t bn_partial_floats(int groups, int P, int C) { return (int64_t)groups * bn_ranges(groups, P) * 3 * C; }
 
 hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
     if (!shape_ok(a.groups, a.P, a.C) || !a.z || (!a.out && !a.out_bf16 && !a.pool_part) || !a.stats || !a.part || !a.gamma || !a.beta) return hipErrorInvalidValue;
@@ -454,7 +476,7 @@ hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
     hipError_t e;
     if (a.wave_part) {   // the producer of z left per-wavefront statistics: z is not read for them
         if (a.waves < 1 || !aligned16(a.wave_part) || a.C % kWaveStatChannels) return hipErrorInvalidValue;
-        const int chunks = wave_stat_chunks(a.P);   // their results fit the ranges' buffer: chunks <= bn_ranges(P)
+        const int chunks = wave_stat_chunks(a.groups, a.P);   // their results fit the ranges' buffer: chunks <= bn_ranges(groups, P)
         bn_stats_waves_kernel<<<dim3((unsigned)chunks, (unsigned)a.groups, (unsigned)(a.C / kWaveStatChannels)), kThreads, 0, s>>>(
             a.wave_part, (int64_t)a.waves * 3 * a.C, a.part, a.C, a.waves, chunks);
         e = hipGetLastError();
@@ -463,7 +485,7 @@ hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     } else {
-        const int ranges = bn_ranges(a.P);
+        const int ranges = bn_ranges(a.groups, a.P);
         bn_stats_partial_kernel<<<dim3((unsigned)ranges, (unsigned)a.groups), kThreads, 0, s>>>(a.z, a.s_z, a.part, a.P, a.C, ranges);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -494,7 +516,7 @@ hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s) {
     if (!aligned16(a.z) || !aligned16(a.dy) || !aligned16(a.stats) || !aligned16(a.part) || !aligned16(a.sums) ||
         !aligned16(a.gamma) || a.s_z % 4 || a.s_dy % 4 || a.s_par % 4)
         return hipErrorInvalidValue;
-    const int ranges = bn_ranges(a.P);
+    const int ranges = bn_ranges(a.groups, a.P);
     PooledDelta pd = {};
     if (a.gate || a.sign) {
         if (!a.dpool || a.positions < 1 || a.P % a.positions != 0 || !aligned16(a.gate) || !aligned16(a.dpool) || a.s_gate % 4 || a.s_dp % 4)
@@ -510,7 +532,7 @@ hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s) {
     partial<<<dim3((unsigned)ranges, (unsigned)a.groups), kThreads, 0, s>>>(a.dy, a.s_dy, a.z, a.s_z, a.stats, a.part, a.P, a.C, ranges, pd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    bn_bwd_final_kernel<<<dim3((unsigned)((a.C + kThreads - 1) / kThreads), (unsigned)a.groups), kThreads, 0, s>>>(
+    bn_bwd_final_kernel<<<dim3((unsigned)((a.C + kFinalChannels - 1) / kFinalChannels), (unsigned)a.groups), kThreads, 0, s>>>(
         a.part, a.sums, a.g, a.ld, a.g_gamma_off, a.g_beta_off, a.C, ranges);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
