@@ -1,3 +1,4 @@
+// (Shapes that conv3x3_split_fits accepts run on the bf16 matrix cores instead, kernels_conv_split.hip.)
 // 3 x 3 convolutions (stride 1, zero padding 1) of the per-worker residual block as implicit GEMMs on the fp32
 // matrix cores (v_mfma_f32_32x32x2_f32), grouped over the m workers: forward, back-propagated delta, weight / bias
 // gradient; plus the global average pooling in front of the classifier and its backward.  The model is the first

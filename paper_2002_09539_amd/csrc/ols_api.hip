@@ -98,6 +98,7 @@ struct ols_ctx {
     float cv_eps = 1e-5f;
     int64_t off_a1 = 0, off_a2 = 0, off_dz1 = 0, off_dz2 = 0, off_pooled = 0, off_dpool = 0, off_cpartial = 0;
     int64_t off_z1 = 0, off_z2 = 0, off_bnstats = 0, off_bnsums = 0, off_bnpart = 0, off_dn = 0, off_wstat = 0;
+    int64_t off_wsplit = -1;   // fp32 block: split kernels (-1: the shape takes the fp32 matrix cores)
     const float* X = nullptr;
     const void* y = nullptr;
     int64_t xs = 0, ys = 0;
@@ -373,16 +374,21 @@ void plan_workspace(ols_ctx* c) {
         c->off_dz1 = take(act);
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
-        const int64_t splits = conv3x3_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
+        const bool split = conv3x3_split_fits(c->B, c->cv_H, c->cv_W, c->cv_C);
+        const int64_t splits = split ? conv3x3_split_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C)
+                                     : conv3x3_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
         c->off_cpartial = take(splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4);
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
+        c->off_wsplit = split ? take(3 * conv3x3_split_weight_bytes(c->m, c->cv_C)) : -1;
         if (c->cv_bn) {   // the convolution outputs stay for the backward pass, with their statistics
             c->off_z1 = take(act);
             c->off_z2 = take(act);
             c->off_bnstats = take(2 * m * 2 * c->cv_C * 4);
             c->off_bnsums = take(m * 2 * c->cv_C * 4);
             c->off_bnpart = take(bn_partial_floats(c->m, c->B * c->cv_H * c->cv_W, c->cv_C) * 4);
+            // the split convolutions leave partial statistics of their output (one convolution's at a time)
+            c->off_wstat = split && c->cv_C % 64 == 0 ? take(m * conv3x3_split_stat_parts(c->B, c->cv_H, c->cv_W) * 3 * c->cv_C * 4) : -1;
         }
     }
     c->ws_need = off;
@@ -644,6 +650,13 @@ int conv_gradients(ols_ctx* c) {
     base.groups = m; base.B = B; base.H = H; base.W = W; base.C = C;
     base.s_w = c->ld; base.s_bias = c->ld;
     base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
+    // shapes whose convolutions run on the bf16 matrix cores: the kernels of this step, split into three bf16 terms
+    const bool split = c->off_wsplit >= 0;
+    const int64_t wbytes = split ? conv3x3_split_weight_bytes(m, C) : 0;
+    uint8_t* ws_fa = (uint8_t*)(c->ws + c->off_wsplit);   // (not read unless split)
+    uint8_t *ws_fb = ws_fa + wbytes, *ws_db = ws_fa + 2 * wbytes;
+    float* wstat = bn && c->off_wstat >= 0 ? (float*)(c->ws + c->off_wstat) : nullptr;   // partial statistics of z1, then of z2
+    const int stat_parts = (int)conv3x3_split_stat_parts(B, H, W);
     BnArgs nbase = {};
     nbase.groups = m; nbase.P = B * H * W; nbase.C = C; nbase.eps = c->cv_eps;
     nbase.s_z = act; nbase.s_out = act; nbase.s_dy = act; nbase.s_par = c->ld;
@@ -662,25 +675,32 @@ int conv_gradients(ols_ctx* c) {
     {   // first convolution
         ConvArgs a = base;
         a.in = c->X; a.s_in = c->xs; a.w = xc + wa;
-        if (bn) { a.out = z1; a.relu = 0; } else { a.bias = xc + ba; a.out = a1; a.relu = 1; }
-        a.s_out = act;
-        if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_fwd(a, s); }))) return rc;
+        if (bn) { a.out = z1; a.relu = 0; a.stat_part = wstat; } else { a.bias = xc + ba; a.out = a1; a.relu = 1; }
+        a.s_out = act; a.w_split = ws_fa;
+        if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) {
+                 if (!split) return launch_conv3x3_fwd(a, s);
+                 hipError_t e = launch_conv3x3_split_weights(xc + wa, xc + wb, ws_fa, ws_fb, ws_db, c->ld, m, C, s);
+                 return e != hipSuccess ? e : launch_conv3x3_split_fwd(a, s);
+             })))
+            return rc;
     }
     if (bn) {
         BnArgs a = nbase;
-        a.z = z1; a.out = a1; a.stats = stats1; a.gamma = xc + ga; a.beta = xc + ba; a.relu = 1;
+        a.z = z1; a.out = a1; a.stats = stats1; a.gamma = xc + ga; a.beta = xc + ba; a.relu = 1; a.wave_part = wstat; a.waves = stat_parts;
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
     {   // second convolution, with the shortcut
         ConvArgs a = base;
         a.in = a1; a.s_in = act; a.w = xc + wb; a.s_out = act;
-        if (bn) { a.out = z2; a.relu = 0; }
+        if (bn) { a.out = z2; a.relu = 0; a.stat_part = wstat; }
         else { a.bias = xc + bb; a.residual = c->X; a.s_res = c->xs; a.out = a2; a.relu = 1; }
-        if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_fwd(a, s); }))) return rc;
+        a.w_split = ws_fb;
+        if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return split ? launch_conv3x3_split_fwd(a, s) : launch_conv3x3_fwd(a, s); }))) return rc;
     }
     if (bn) {
         BnArgs a = nbase;
         a.z = z2; a.out = a2; a.stats = stats2; a.gamma = xc + gb; a.beta = xc + bb; a.shortcut = c->X; a.s_sc = c->xs; a.relu = 1;
+        a.wave_part = wstat; a.waves = stat_parts;
         if (tail) { a.out = nullptr; a.sign = sign; a.s_sign = act / 4; a.pool_part = tail_part; a.positions = H * W; }
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
@@ -725,12 +745,13 @@ int conv_gradients(ols_ctx* c) {
     {   // delta at a1: transposed convolution of dz2 through Wb, gated by a1 > 0
         ConvArgs a = base;
         a.in = dz2; a.s_in = act; a.w = xc + wb; a.mask = a1; a.s_mask = act; a.out = dz1; a.s_out = act;
-        if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_dx(a, s); }))) return rc;
+        a.w_split_dx = ws_db;
+        if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return split ? launch_conv3x3_split_dx(a, s) : launch_conv3x3_dx(a, s); }))) return rc;
     }
     {   // gradients of the second convolution
         ConvArgs a = base;
         a.in = a1; a.s_in = act; a.dout = dz2; a.s_dout = act; a.g_w_off = wb; a.g_b_off = bn ? -1 : bb;
-        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_dw(a, s); }))) return rc;
+        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return split ? launch_conv3x3_split_dw(a, s) : launch_conv3x3_dw(a, s); }))) return rc;
     }
     if (bn) {   // through the first normalisation
         BnArgs a = nbase;
@@ -740,7 +761,7 @@ int conv_gradients(ols_ctx* c) {
     {   // gradients of the first convolution (its input is data: no delta beyond it)
         ConvArgs a = base;
         a.in = c->X; a.s_in = c->xs; a.dout = dz1; a.s_dout = act; a.g_w_off = wa; a.g_b_off = bn ? -1 : ba;
-        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_dw(a, s); }))) return rc;
+        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return split ? launch_conv3x3_split_dw(a, s) : launch_conv3x3_dw(a, s); }))) return rc;
     }
     return OLS_OK;
 }

@@ -186,11 +186,28 @@ struct ConvArgs {
     int64_t s_in, s_w, s_dout, s_out, s_bias, s_res, s_mask;   // group strides (elements)
     int groups, B, H, W, C;
     int relu;               // fwd: apply max(., 0)
+    // split kernels (launch_conv3x3_split_weights), set where conv3x3_split_fits: fwd resp. dx reads these in place of w
+    const uint8_t* w_split;
+    const uint8_t* w_split_dx;
+    // split fwd, optional, C a multiple of 64: [group][conv3x3_split_stat_parts(...)][3][C] statistics of the output per
+    // tile of pixels (count, mean, sum of squared deviations) for BnArgs::wave_part
+    float* stat_part;
 };
 hipError_t launch_conv3x3_fwd(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_dx(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_dw(const ConvArgs& a, hipStream_t s);   // weight + bias gradient (two launches)
 int conv3x3_dw_splits(int groups, int B, int H, int W, int C);   // pixel ranges the weight-gradient contraction is split into
+// The same products on the bf16 matrix cores with every fp32 operand split exactly into three bf16 terms (fp32 accuracy);
+// the kernels are split once per step: forward images of both, delta image of the second (dst: weight_bytes(groups) each).
+bool conv3x3_split_fits(int B, int H, int W, int C);
+int64_t conv3x3_split_weight_bytes(int groups, int C);
+int64_t conv3x3_split_stat_parts(int B, int H, int W);
+hipError_t launch_conv3x3_split_weights(const float* wa, const float* wb, uint8_t* fwd_a, uint8_t* fwd_b, uint8_t* dx_b,
+                                        int64_t s_w, int groups, int C, hipStream_t s);
+hipError_t launch_conv3x3_split_fwd(const ConvArgs& a, hipStream_t s);
+hipError_t launch_conv3x3_split_dx(const ConvArgs& a, hipStream_t s);
+hipError_t launch_conv3x3_split_dw(const ConvArgs& a, hipStream_t s);   // (two launches)
+int conv3x3_split_dw_splits(int groups, int B, int H, int W, int C);
 // second pass of the kernel gradient: sums the pixel ranges' parts [splits][groups][9 C C + C] in range order into g
 hipError_t launch_conv_dw_finish(const float* partial, int splits, int groups, int C, float* g, int64_t ld, int64_t w_off,
                                  int64_t b_off, hipStream_t s);
@@ -284,7 +301,7 @@ struct BnArgs {
     const float* dpool;
     int64_t s_gate, s_dp;
     int positions;
-    // Optional (fwd): per-wavefront statistics that the producer of z left (ConvBArgs::stat_part), [group][waves][3][C]:
+    // Optional (fwd): partial statistics that the producer of z left (ConvBArgs / ConvArgs::stat_part), [group][waves][3][C]:
     // the statistics are merged from them and z is read only once, by the normalisation itself.
     const float* wave_part;
     int waves;

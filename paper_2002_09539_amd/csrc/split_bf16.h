@@ -1,0 +1,95 @@
+// fp32 matrix products on the bf16 matrix cores without giving up fp32 accuracy.
+//
+// Every fp32 operand is split EXACTLY into three bf16 terms, x = hi + mid + lo: hi = bf16(x), mid = bf16(x - hi),
+// lo = bf16(x - hi - mid).  A bf16 carries 8 significant bits and each rounding to nearest leaves a remainder of at most
+// half a unit of the term before it, so three terms hold the 24 bits of an fp32 (as long as lo stays a normal number:
+// |x| >= 2^-109; below that the missing part is under 2^-133 in absolute value).  The product of two split numbers is
+// the sum of nine products of bf16 numbers, each exact in fp32; the six of them down to 2^-18 of the result's magnitude
+// are formed (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi), the three left out (mid lo, lo mid, lo lo) sum to at most
+// 2^-26 of |a b|, below the rounding of ONE fp32 addition (2^-24).  Six v_mfma_f32_32x32x16_bf16 take 192 cycles for 16
+// contraction indices, eight v_mfma_f32_32x32x2_f32 take 512, and a sum over K indices is rounded 6 K / 16 times
+// instead of K times.
+//
+// Infinities and the few finite numbers that round to a bf16 infinity (|x| >= 0x1.FFp127) take a separate path that
+// truncates hi and leaves no remainder behind an infinity, so that inf * finite stays inf as it is in fp32; a NaN makes
+// hi a NaN.
+#pragma once
+#include "gemm_bf16_tile.h"
+
+namespace ols {
+
+struct Split8 {
+    u4 hi, mid, lo;   // eight bf16 each, in element order
+};
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {   // round to nearest even (v_cvt_pk_bf16_f32)
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{a, b}, bf16x2));
+}
+__device__ __forceinline__ float bf16_lo(unsigned w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// Eight consecutive elements: 44 instructions for the split, four for the range check.
+__device__ __forceinline__ Split8 split8(f4 a, f4 b) {
+    constexpr float kRoundsToInf = 0x1.FFp127f;
+    float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    float top = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fabsf(x[2]));
+    top = fmaxf(fmaxf(top, fabsf(x[3])), fabsf(x[4]));
+    top = fmaxf(fmaxf(top, fabsf(x[5])), fabsf(x[6]));
+    top = fmaxf(top, fabsf(x[7]));
+    Split8 s;
+    float r[8];
+    if (__builtin_expect(top >= kRoundsToInf, 0)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float h[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float v = x[2 * e + t];
+                const bool huge = fabsf(v) >= kRoundsToInf;   // false for a NaN
+                h[t] = huge ? __uint_as_float(__float_as_uint(v) & 0xFFFF0000u) : v;
+            }
+            s.hi[e] = pack_bf16(h[0], h[1]);
+            r[2 * e] = __builtin_isinf(x[2 * e]) ? 0.0f : x[2 * e] - bf16_lo(s.hi[e]);
+            r[2 * e + 1] = __builtin_isinf(x[2 * e + 1]) ? 0.0f : x[2 * e + 1] - bf16_hi(s.hi[e]);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s.hi[e] = pack_bf16(x[2 * e], x[2 * e + 1]);
+            r[2 * e] = x[2 * e] - bf16_lo(s.hi[e]);
+            r[2 * e + 1] = x[2 * e + 1] - bf16_hi(s.hi[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        s.mid[e] = pack_bf16(r[2 * e], r[2 * e + 1]);
+        s.lo[e] = pack_bf16(r[2 * e] - bf16_lo(s.mid[e]), r[2 * e + 1] - bf16_hi(s.mid[e]));
+    }
+    return s;
+}
+
+// The six products of two split fragments.  The five small ones have a sum of their own (`low`), so that the large one is
+// rounded against the running sum once per 16 indices and the small ones against a sum 2^-8 of its size.  Gradients of the
+// residual block against 64 bits (relative 2-norm per worker, median over 24; 64 channels 32 x 32 / 128 channels 13 x 15 /
+// 32 channels 20 x 20): fp32 matrix cores 2.4e-7 / 2.4e-7 / 2.2e-7, one sum for all six products 2.7e-7 / 2.7e-7 /
+// 2.6e-7, two sums 1.1e-7 / 1.2e-7 / 1.2e-7.
+struct SplitFrag {
+    bf16x8 hi, mid, lo;
+};
+template <int J>
+__device__ __forceinline__ void mfma_split(f16v (&acc)[J], f16v (&low)[J], const SplitFrag (&a)[J], const SplitFrag& b) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].hi, b.hi, acc[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j) low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].lo, b.hi, low[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j) low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].hi, b.lo, low[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j) low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].mid, b.mid, low[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j) low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].mid, b.hi, low[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j) low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].hi, b.mid, low[j], 0, 0, 0);
+}
+
+}  // namespace ols
