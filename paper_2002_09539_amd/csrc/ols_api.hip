@@ -91,7 +91,7 @@ struct ols_ctx {
     int64_t ws_bytes = 0, ws_need = 0;
     // workspace sub-buffers (byte offsets)
     std::vector<int64_t> off_act, off_dz;
-    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_x0 = 0;
+    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_x0 = 0, off_flags = 0;
     // residual convolutional block: channels, image size, classes; workspace sub-buffers
     int cv_C = 0, cv_H = 0, cv_W = 0, cv_classes = 0;
     bool cv_bn = false;     // convolutions without bias, each followed by batch normalisation
@@ -297,6 +297,7 @@ void plan_workspace(ols_ctx* c) {
     if (c->model == MODEL_LSQ) {
         c->off_resid = take(m * B * 4);
         c->off_loss = take(m * B * 4);
+        c->off_flags = take(m * 8);
     } else if (c->model == MODEL_MLP) {
         const int L = (int)c->dims.size() - 1;
         const bool bf = c->gemm_dtype == 1;
@@ -779,9 +780,10 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
         if (upd) {   // small problem: one launch forms the gradient and applies the step
             const FusedUpdate u = *upd;
             if (int rc = wait_if_update_must(c)) return rc;
-            return enqueue(c, OLS_K_LSQ_STEP, 0, src_buf, dst_buf, [&](hipStream_t s) {
-                return launch_lsq_step(c->X, c->xs, (const float*)c->y, c->ys, loss, m, B, c->d, u, s);
-            });
+            LsqRoundArgs la = {};
+            la.A = c->X; la.a_stride = c->xs; la.y = (const float*)c->y; la.y_stride = c->ys;
+            la.nb = 1; la.steps = 1; la.loss_parts = loss; la.m = m; la.B = B; la.d = c->d;
+            return enqueue(c, OLS_K_LSQ_STEP, 0, src_buf, dst_buf, [&](hipStream_t s) { return launch_lsq_round(la, u, s); });
         }
         int rc = enqueue(c, OLS_K_LSQ_RESID, 0, c->cur, -1, [&](hipStream_t s) {
             return launch_lsq_resid(c->X, c->xs, (const float*)c->y, c->ys, xc, c->ld, resid, loss, m, B, c->d, s);
@@ -943,6 +945,24 @@ UpdateArgs update_args(ols_ctx* c, int src, int dst, bool pull) {
     u.alpha = c->alpha;
     u.nesterov = c->nesterov;
     u.pull = pull;
+    return u;
+}
+
+// The operands of an update fused into the gradient kernels.
+FusedUpdate fused_update(ols_ctx* c, int src, int dst, bool pull) {
+    FusedUpdate u = {};
+    u.x_in = c->x[src];
+    u.x_out = c->x[dst];
+    u.buf = c->mu != 0.0f ? c->buf : nullptr;
+    u.z = c->z;
+    u.shadow = shadow_ptr(c);
+    u.ld = c->ld;
+    u.gamma = c->gamma;
+    u.mu = c->mu;
+    u.alpha = c->alpha;
+    u.nesterov = c->nesterov ? 1 : 0;
+    u.pull = pull ? 1 : 0;
+    u.enabled = 1;
     return u;
 }
 
@@ -1299,19 +1319,7 @@ int ols_local_step(ols_handle c) {
         int src, dst;
         if (int rc = pick_buffers(c, &src, &dst, true)) return rc;
         if (boundary && paper_sync && c->anchor_inflight) c->wait_before_update = true;
-        FusedUpdate u = {};
-        u.x_in = c->x[src];
-        u.x_out = c->x[dst];
-        u.buf = c->mu != 0.0f ? c->buf : nullptr;
-        u.z = c->z;
-        u.shadow = shadow_ptr(c);
-        u.ld = c->ld;
-        u.gamma = c->gamma;
-        u.mu = c->mu;
-        u.alpha = c->alpha;
-        u.nesterov = c->nesterov ? 1 : 0;
-        u.pull = (boundary && paper_sync) ? 1 : 0;
-        u.enabled = 1;
+        const FusedUpdate u = fused_update(c, src, dst, boundary && paper_sync);
         if (int rc = compute_gradients(c, &u, src, dst)) return rc;
         if (int rc = wait_if_update_must(c)) return rc;   // (a model without an updating launch: nothing to defer to)
         c->cur = dst;
@@ -1457,6 +1465,46 @@ int ols_anchor_update_async(ols_handle c) {
     return OLS_OK;
 }
 
+namespace {
+// Whether the library-driven loop may run several local steps of a small least-squares problem in one launch: the
+// gradient kernel applies step and pull-back, the refresh is in line and its result is the plain average, nothing of an
+// earlier overlapped refresh is pending, and nobody counts or times the single launches.
+bool lsq_rounds_fit(const ols_ctx* c, const float* X, int64_t x_batch) {
+    return c->model == MODEL_LSQ && lsq_step_fits(c->B, c->d) && c->fuse_gemm_update && !c->fuse_mean && !c->mix_w && !c->snap &&
+           c->beta_z == 0.0f && c->anchor_delay_us == 0 && !c->dry && !c->trace && !c->timing && c->bound && c->inited && c->ws &&
+           (serialized(c) || c->stream[0] == c->stream[1]) && !c->anchor_inflight && !c->first_after_anchor && !c->pending_update &&
+           !(reinterpret_cast<uintptr_t>(X) & 15u) && x_batch % 4 == 0;   // what ols_set_batch asks of every batch
+}
+
+// Up to `most` local steps, at most to the end of the round; *done is how many.
+int lsq_round(ols_ctx* c, int64_t most, const float* X, const void* y, int nb, int64_t* done) {
+    constexpr int64_t kMostSteps = 64;   // bounds the launch's duration
+    const int64_t x_batch = (int64_t)c->B * c->d, to_sync = c->tau - c->k % c->tau;
+    const int64_t n = std::min(std::min(most, to_sync), kMostSteps);
+    const bool boundary = n == to_sync;
+    const int64_t b_last = (c->k + n - 1) % nb;
+    int rc = ols_set_batch(c, X + b_last * x_batch, (int64_t)nb * x_batch, (const float*)y + b_last * c->B, (int64_t)nb * c->B);
+    if (rc) return rc;
+    const FusedUpdate u = fused_update(c, c->cur, c->cur, boundary);
+    LsqRoundArgs la = {};
+    la.A = X; la.a_stride = (int64_t)nb * x_batch; la.y = (const float*)y; la.y_stride = (int64_t)nb * c->B;
+    la.nb = nb; la.first_batch = (int)(c->k % nb); la.steps = (int)n;
+    la.loss_parts = (float*)(c->ws + c->off_loss);
+    la.m = c->m; la.B = c->B; la.d = c->d;
+    la.with_mean = boundary && lsq_round_with_mean(c->m, c->ld);
+    la.mean_split = c->mean_split;
+    la.flags = (unsigned long long*)(c->ws + c->off_flags);
+    la.z = c->z;
+    if ((rc = enqueue(c, OLS_K_LSQ_STEP, 0, c->cur, c->cur, [&](hipStream_t s) { return launch_lsq_round(la, u, s); }))) return rc;
+    c->k += n;
+    *done = n;
+    if (!boundary || la.with_mean) return OLS_OK;
+    c->pull_due = c->pulled_in_step = true;
+    if ((rc = ols_sync_pull(c))) return rc;
+    return ols_anchor_update_async(c);
+}
+}  // namespace
+
 int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, int nb) {
     if (int rc = need(c)) return rc;
     if (c->model == MODEL_NONE) return fail(OLS_ESTATE, "ols_run_steps needs an attached model");
@@ -1466,6 +1514,12 @@ int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, in
     const int64_t x_batch = (int64_t)c->B * row, y_batch = c->B;   // elements per batch
     const size_t y_elem = 4;                                          // int32 labels and fp32 targets alike
     for (int64_t it = 0; it < steps; ++it) {
+        if (lsq_rounds_fit(c, X, x_batch)) {
+            int64_t done = 0;
+            if (int rc = lsq_round(c, steps - it, X, y, nb, &done)) return rc;
+            it += done - 1;
+            continue;
+        }
         const int64_t b = c->k % nb;
         int rc = ols_set_batch(c, X + b * x_batch, (int64_t)nb * x_batch, (const char*)y + (size_t)(b * y_batch) * y_elem,
                                (int64_t)nb * y_batch);

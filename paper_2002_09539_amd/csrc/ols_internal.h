@@ -110,10 +110,23 @@ __device__ __forceinline__ void fused_update_apply(const FusedUpdate& u, int64_t
 }
 #endif
 
-// least squares, small problems: residual, loss, gradient and the local step (+ pull-back) in one launch
+// least squares, small problems: residual, loss, gradient and the local step of one or several steps in one launch, with
+// the pull-back (u.pull) and the anchor average (with_mean) behind the last of them
 bool lsq_step_fits(int B, int64_t d);
-hipError_t launch_lsq_step(const float* A, int64_t a_stride, const float* y, int64_t y_stride, float* loss_parts, int m,
-                           int B, int64_t d, const FusedUpdate& u, hipStream_t s);
+bool lsq_round_with_mean(int m, int64_t ld);   // whether with_mean takes m replicas of ld parameters
+struct LsqRoundArgs {
+    const float* A;          // batch 0 of worker 0: [nb][B][d] per worker
+    const float* y;
+    int64_t a_stride, y_stride;   // elements between workers
+    int nb, first_batch, steps;   // step t reads batch (first_batch + t) mod nb
+    float* loss_parts;
+    int m, B;
+    int64_t d;
+    int with_mean, mean_split;
+    unsigned long long* flags;    // [m], any contents (with_mean)
+    float* z;                     // (with_mean)
+};
+hipError_t launch_lsq_round(const LsqRoundArgs& a, const FusedUpdate& u, hipStream_t s);
 
 struct HeadArgs;
 
