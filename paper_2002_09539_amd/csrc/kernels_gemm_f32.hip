@@ -541,6 +541,14 @@ __global__ __launch_bounds__(kThreads) void splitk_finish_kernel(const f4* __res
     *(f4*)(out + (int64_t)g * sc + (int64_t)row * ldc + 4 * c4) = r;
 }
 
+// second pass of a split-K forward GEMM: sum the partials, add the bias, apply the ReLU
+hipError_t launch_splitk_finish(const float* partial, int splits, const GemmArgs& g, hipStream_t s) {
+    const int64_t vecs = (int64_t)g.groups * g.M * (g.N / 4);
+    splitk_finish_kernel<<<(unsigned)((vecs + kThreads - 1) / kThreads), kThreads, 0, s>>>(
+        (const f4*)partial, splits, g.bias, g.sbias, (float*)g.c, g.sc, g.ldc, g.groups, g.M, g.N);
+    return hipGetLastError();
+}
+
 static bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH>
@@ -609,11 +617,7 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     if (!full) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false><<<grid, kThreads, 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits == 1) return e;
-    // second pass of a split-K forward GEMM: sum the partials, add the bias, apply the ReLU
-    const int64_t vecs = (int64_t)g.groups * g.M * (g.N / 4);
-    splitk_finish_kernel<<<(unsigned)((vecs + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-        (const f4*)p.partial, p.splits, g.bias, g.sbias, (float*)g.c, g.sc, g.ldc, g.groups, g.M, g.N);
-    return hipGetLastError();
+    return launch_splitk_finish(p.partial, p.splits, g, s);
 }
 
 // persistent workgroups per compute unit: measured 16 x (3072 x 512, K = 128): one 125 us, two 97.4 us, three 98.9 us,
@@ -690,7 +694,13 @@ static hipError_t dw_pipelined_launch(const GemmArgs& g, hipStream_t s) {
 // Where 64 x 64 tiles would give four or more workgroups per compute unit, 64 x 128 tiles (half as many, each
 // A slice loaded once for twice the columns) are faster: configuration 5 (M = 64, N = 1024, 64 groups) 232 us
 // against 238 us per launch, 0.8428 against 0.8504 ms per step.
+// Large launches run on the bf16 matrix cores with split operands (variant 32, kernels_gemm_split.hip: 234 -> 187 us and
+// 76 -> 61 us on configurations 5 and 2).  What is left is small: there a K range may be as short as 96 indices (5 workers
+// x (36 x 300 x 788): eight ranges 13.8 us, two 17.3), unless the contraction is too short for the second launch that
+// adds the ranges up.
 void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* splits) {
+    *variant = 32;
+    if (gemm_split_fwd_plan(groups, M, N, K, splits)) return;
     *variant = 2;
     int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 63) / 64);
     if (tiles >= 1024 && N >= 128) {
@@ -698,7 +708,7 @@ void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* split
         tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 127) / 128);
     }
     int s = 1;
-    while (tiles * s < 512 && K / (2 * s) >= 256 && s < 8) s *= 2;
+    while (K >= 512 && tiles * s < 512 && K / (2 * s) >= 96 && s < 8) s *= 2;
     *splits = s;
 }
 
@@ -708,6 +718,7 @@ hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant) {
         gemm_f32_fwd_plan(g.groups, g.M, g.N, g.K, &variant, &sp);
     }
     switch (variant) {
+        case 32: return launch_gemm_split_fwd(g, s);
         case 2: return gemm_launch<kFwd, 64, 64, 32, 2, 2, 2>(g, s);
         case 6: return gemm_launch<kFwd, 64, 128, 32, 2, 2, 2>(g, s);
 #ifdef OLS_TUNING_VARIANTS

@@ -157,6 +157,12 @@ hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant);
 void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* splits);
 hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_gemm_f32_da(const GemmArgs& g, hipStream_t s, int variant);
+hipError_t launch_splitk_finish(const float* partial, int splits, const GemmArgs& g, hipStream_t s);
+// forward on the bf16 matrix cores with every operand split exactly into three bf16 terms (fp32 accuracy): whether, and
+// over how many K ranges, a shape takes it
+bool gemm_split_fits(int64_t a_elems, int64_t b_elems);   // elements a group's operand spans
+bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits);
+hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s);
 // bf16 operands, fp32 accumulate.  fwd: A[M][K], W[K][N];  dw: A[K][M], B[K][N] (K = batch);  da: A[M][K], W[N][K]
 hipError_t launch_gemm_bf16_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant);

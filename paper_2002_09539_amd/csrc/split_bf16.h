@@ -28,20 +28,34 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {   // round to 
 __device__ __forceinline__ float bf16_lo(unsigned w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Eight consecutive elements: 44 instructions for the split, four for the range check.
-__device__ __forceinline__ Split8 split8(f4 a, f4 b) {
-    constexpr float kRoundsToInf = 0x1.FFp127f;
-    float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    float top = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fabsf(x[2]));
-    top = fmaxf(fmaxf(top, fabsf(x[3])), fabsf(x[4]));
-    top = fmaxf(fmaxf(top, fabsf(x[5])), fabsf(x[6]));
-    top = fmaxf(top, fabsf(x[7]));
+constexpr float kRoundsToInf = 0x1.FFp127f;
+
+// Eight consecutive elements without the separate path: 44 instructions, and four that keep the largest magnitude in
+// `top`.  Where top reaches kRoundsToInf the result is not to be used; callers that split many vectors look once.
+__device__ __forceinline__ Split8 split8_finite(f4 a, f4 b, float& top) {
+    const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) top = fmaxf(fmaxf(top, fabsf(x[e])), fabsf(x[e + 1]));
     Split8 s;
-    float r[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        s.hi[e] = pack_bf16(x[2 * e], x[2 * e + 1]);
+        const float r0 = x[2 * e] - bf16_lo(s.hi[e]), r1 = x[2 * e + 1] - bf16_hi(s.hi[e]);
+        s.mid[e] = pack_bf16(r0, r1);
+        s.lo[e] = pack_bf16(r0 - bf16_lo(s.mid[e]), r1 - bf16_hi(s.mid[e]));
+    }
+    return s;
+}
+
+// Eight consecutive elements of any value.
+__device__ __forceinline__ Split8 split8(f4 a, f4 b) {
+    const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    float top = 0.0f;
+    Split8 s = split8_finite(a, b, top);
     if (__builtin_expect(top >= kRoundsToInf, 0)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float h[2];
+            float h[2], r[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const float v = x[2 * e + t];
@@ -49,21 +63,11 @@ __device__ __forceinline__ Split8 split8(f4 a, f4 b) {
                 h[t] = huge ? __uint_as_float(__float_as_uint(v) & 0xFFFF0000u) : v;
             }
             s.hi[e] = pack_bf16(h[0], h[1]);
-            r[2 * e] = __builtin_isinf(x[2 * e]) ? 0.0f : x[2 * e] - bf16_lo(s.hi[e]);
-            r[2 * e + 1] = __builtin_isinf(x[2 * e + 1]) ? 0.0f : x[2 * e + 1] - bf16_hi(s.hi[e]);
+            r[0] = __builtin_isinf(x[2 * e]) ? 0.0f : x[2 * e] - bf16_lo(s.hi[e]);
+            r[1] = __builtin_isinf(x[2 * e + 1]) ? 0.0f : x[2 * e + 1] - bf16_hi(s.hi[e]);
+            s.mid[e] = pack_bf16(r[0], r[1]);
+            s.lo[e] = pack_bf16(r[0] - bf16_lo(s.mid[e]), r[1] - bf16_hi(s.mid[e]));
         }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            s.hi[e] = pack_bf16(x[2 * e], x[2 * e + 1]);
-            r[2 * e] = x[2 * e] - bf16_lo(s.hi[e]);
-            r[2 * e + 1] = x[2 * e + 1] - bf16_hi(s.hi[e]);
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        s.mid[e] = pack_bf16(r[2 * e], r[2 * e + 1]);
-        s.lo[e] = pack_bf16(r[2 * e] - bf16_lo(s.mid[e]), r[2 * e + 1] - bf16_hi(s.mid[e]));
     }
     return s;
 }
