@@ -1,15 +1,14 @@
 // Output layer of the per-worker MLP (class count C <= 32) with softmax cross-entropy, the delta it
-// sends back to the last hidden layer, and its own gradients.  The output width is far too small for
-// matrix cores, so these run on the vector ALUs.  They are a few MFLOP per worker: what they cost is
+// sends back to the last hidden layer, and its own gradients.  They are a few MFLOP per worker: what they cost is
 // (a) the chain of dependent memory round trips and (b) instruction fetch -- a launch this small runs
 // every instruction a handful of times, so long unrolled code is paid for line by line from a cold
-// instruction cache.  Hence the shape of both kernels: all global reads of a pass are issued together
-// and land in LDS, and the arithmetic runs in short rolled loops over LDS.
+// instruction cache.
 //
-//   head_fwd_kernel   logits, loss, dlogits AND the hidden delta dz in one launch.  Sixteen lanes (one
-//                     DPP row) share a sample; the 16 partial logits are combined with DPP row
-//                     rotations, every lane then evaluates the softmax redundantly, and the staged
-//                     activations (ReLU mask) and weights are reused for dz.
+//   head_fwd_kernel   logits, loss, dlogits AND the hidden delta dz in one launch.  Both products run on the fp32 matrix
+//                     cores (v_mfma_f32_16x16x4_f32) on fragments loaded straight into registers: a workgroup owns 16
+//                     samples, its wavefronts share the hidden units out, and everything the launch reads -- activations,
+//                     weights in both fragment orders, labels -- is requested in one round trip; the activations stay in
+//                     registers as the ReLU mask of dz.
 //   head_dw_kernel    dW = h^T dlogits, db = colsum(dlogits), consumed by the fused update or stored (body in
 //                     head_dw_body.h; by default it runs as guest workgroups of a weight-gradient GEMM instead).
 //
@@ -17,7 +16,8 @@
 // (the mini-batch loss whose gradient is the g_i of Section 2, arXiv 2002.09539):
 //   logits = h W + b;  loss_s = logsumexp(logits_s) - logits_s[y_s];  dlogits = (softmax - onehot) / B
 //   dW = h^T dlogits;  db = colsum(dlogits);  dz = (dlogits W^T) * [h > 0]
-// The class dimension is padded to CMAX (16 or 32) with zeros in LDS so that no inner loop branches on C.
+// The class dimension is padded to CMAX (16 or 32) with zeros so that no inner loop branches on C.
+#include "gemm_bf16_tile.h"
 #include "head_dw_body.h"
 #include "ols_internal.h"
 
@@ -25,10 +25,6 @@ namespace ols {
 
 constexpr int kRow = 16;     // lanes of one DPP row
 constexpr int kMaxC = 32;
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ unsigned int f32_to_bf16(float f) { return bf16_bits_rne(f); }
 // Sum over the 16 lanes of a DPP row, the same bits in every lane of the row (each step adds a lane's
@@ -66,204 +62,166 @@ struct HeadDev {
     int B, H, C;
 };
 
-// KC = hidden units staged per pass; THREADS / 16 samples per workgroup; activation rows are staged at pitch KC + 4
-__host__ __device__ constexpr int head_fwd_lds_floats(int CMAX, int KC, int THREADS) {
-    return KC * head_row_pitch(CMAX) + (THREADS / kRow) * (KC + 4) + (THREADS / kRow) * CMAX;
-}
+// Measured against a kernel that staged weights and activations in LDS and formed both products on the vector ALUs, us per
+// launch: 14.9 -> 12.0 (16 workers x 128 samples x 512 units), 27.9 -> 18.0 (64 x 64 x 1024), 52.7 -> 24.1 (16 x 256 x 2048, bf16),
+// 12.1 -> 8.5 (5 x 36 x 124).
+// A wavefront takes T tiles of 16 hidden units per pass; layers wider than WAVES T 16 units take several passes and read
+// activations and weights again for dz.
+// Fragment layout of the 16x16x4 product: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; register r of the result is
+// [4 (l / 16) + r][l % 16].  Logits: A = h (rows samples), B = W; product e of a tile contracts the units 4 (l / 16) + e, so
+// a lane's four products take one 4-wide vector of its sample.  dz: A = W (rows units), B = dlogits^T, so a lane's result is
+// four consecutive units of sample l % 16 -- the units whose activations it holds.
+constexpr unsigned kHeadNowhere = 0x80000000u;   // beyond every range, also with a tile's offset added
 
-// grid (ceil(B / (THREADS / 16)), m); dynamic LDS: head_fwd_lds_floats(CMAX, KC, THREADS) floats
-template <bool BF, int CMAX, int KC, int THREADS>
-__global__ __launch_bounds__(THREADS) void head_fwd_kernel(HeadDev p) {
-    constexpr int S = THREADS / kRow, HP = KC + 4;
-    static_assert(THREADS % 64 == 0 && (KC * CMAX) % THREADS == 0 && KC % 128 == 0, "staging shape");
-    constexpr int P = head_row_pitch(CMAX);         // LDS pitch of a weight row
-    constexpr int NW = KC * CMAX / THREADS;    // staged weights per lane, all in flight at once
-    constexpr int J = KC / (4 * kRow);         // 4-wide activation vectors per lane per pass (8)
-    extern __shared__ __attribute__((aligned(16))) float s_dyn[];
-    float* s_w = s_dyn;                        // [KC slots][P]
-    float* s_h = s_dyn + KC * P;               // [S][HP]
-    float* s_d = s_h + S * HP;                 // [S][CMAX] dlogits of the workgroup's samples
-
+// grid (ceil(B / 16), m)
+template <bool BF, int CMAX, int T, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void head_fwd_kernel(HeadDev p) {
+    constexpr int S = 16, CT = CMAX / 16, CS = CMAX / 4, kChunk = WAVES * T * 16;
+    __shared__ float s_part[WAVES][S * CMAX];   // the wavefronts' shares of the logits
+    __shared__ float s_d[S][CMAX + 1];
     const int C = p.C, H = p.H, B = p.B;
-    const int i = blockIdx.y;
-    const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
-    const int s0 = blockIdx.x * S, s = s0 + row;
-    const bool live = s < B;
-    const int cls = threadIdx.x % CMAX;
-    const float* W = p.x + (int64_t)i * p.ld + p.w_off;
+    const int i = blockIdx.y, s0 = blockIdx.x * S;
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, l16 = lane % 16, q = lane / 16;
+    const int rows = min(S, B - s0);
+    const unsigned es = BF ? 2u : 4u;
+    const rsrc_t h_rs = make_rsrc((const char*)p.h + ((int64_t)i * p.h_stride + (int64_t)s0 * H) * es, (unsigned)rows * (unsigned)H * es);
+    const rsrc_t w_rs = make_rsrc(p.x + (int64_t)i * p.ld + p.w_off, 4u * (unsigned)H * (unsigned)C);
+    auto w_at = [&](unsigned off) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w_rs, (int)off, 0, 0)); };
 
-    float bias[CMAX / kRow];   // lane sub owns class sub (and sub + 16)
+    // the softmax's operands: lane (sample threadIdx / 16, class threadIdx % 16) of the first four wavefronts
+    const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow, s = s0 + row;
+    const bool soft = threadIdx.x < S * kRow, live = soft && s < B;
+    float bias[CT];
 #pragma unroll
-    for (int c0 = 0; c0 < CMAX / kRow; ++c0)
-        bias[c0] = kRow * c0 + sub < C ? p.x[(int64_t)i * p.ld + p.b_off + kRow * c0 + sub] : 0.0f;
+    for (int c0 = 0; c0 < CT; ++c0) bias[c0] = soft && kRow * c0 + sub < C ? p.x[(int64_t)i * p.ld + p.b_off + kRow * c0 + sub] : 0.0f;
     const int label = live ? p.labels[(int64_t)i * p.label_stride + s] : 0;
 
-    // One pass: KC rows of W from k0 (zero beyond H and beyond C) and the same KC activations of the 16
-    // samples (zero beyond H and beyond the batch) into LDS; every load is issued before the first store.
-    // Weight row kl goes to slot (kl % 4) * (KC / 4) + kl / 4: element e of a lane's vector j then sits at
-    // slot e * (KC / 4) + sub + 16 j, consecutive across the lanes of a DPP row, and at pitch P their
-    // 16-byte reads fall into distinct banks.
-    auto stage = [&](int k0) {
-        const float* src = W + (int64_t)k0 * C + cls;
-        const int rows = H - k0;
-        float tw[NW];
+    f4 hv[BF ? 1 : T];
+    u2 hb[BF ? T : 1];
+    float w1[T][4][CT], w2[T][CS];
+    auto load_h = [&](int k0) {   // units k0 + 16 t + 4 q .. + 3 of sample l16 (zeros past the layer and past the batch)
 #pragma unroll
-        for (int u = 0; u < NW; ++u) {
-            const int kl = threadIdx.x / CMAX + u * (THREADS / CMAX);
-            tw[u] = (cls < C && kl < rows) ? src[kl * C] : 0.0f;
+        for (int t = 0; t < T; ++t) {
+            const int k = k0 + 16 * t + 4 * q;
+            const unsigned off = k < H ? ((unsigned)l16 * (unsigned)H + (unsigned)k) * es : kHeadNowhere;
+            if constexpr (BF) hb[t] = __builtin_bit_cast(u2, __builtin_amdgcn_raw_buffer_load_b64(h_rs, (int)off, 0, 0));
+            else hv[t] = __builtin_bit_cast(f4, buf_load(h_rs, off, 0u));
         }
-        if constexpr (BF) {
-            constexpr int NH = S * KC / 8 / THREADS;   // 16-byte vectors of 8 bf16 per lane (4)
-            u4 th[NH];
+    };
+    auto h_elem = [&](int t, int e) {
+        if constexpr (BF) return head_bf16_elem(e < 2 ? hb[t].x : hb[t].y, e);
+        else return hv[t][e];
+    };
+    auto load_w1 = [&](int k0) {   // W[k0 + 16 t + 4 q + e][16 j + l16]
 #pragma unroll
-            for (int u = 0; u < NH; ++u) {
-                const int f = threadIdx.x + u * THREADS, r = f / (KC / 8), kv = 8 * (f % (KC / 8));
-                th[u] = u4{0u, 0u, 0u, 0u};
-                if (s0 + r < B && k0 + kv < H)
-                    th[u] = *(const u4*)((const uint16_t*)p.h + (int64_t)i * p.h_stride + (int64_t)(s0 + r) * H + k0 + kv);
-            }
+        for (int j = 0; j < CT; ++j) {
+            const unsigned first = 16 * j + l16 < C ? 4u * ((unsigned)(k0 + 4 * q) * (unsigned)C + 16u * j + l16) : kHeadNowhere;
 #pragma unroll
-            for (int u = 0; u < NH; ++u) {
-                const int f = threadIdx.x + u * THREADS, r = f / (KC / 8), kv = 8 * (f % (KC / 8));
-                *(f4*)(s_h + r * HP + kv) = f4{head_bf16_elem(th[u].x, 0), head_bf16_elem(th[u].x, 1), head_bf16_elem(th[u].y, 0),
-                                               head_bf16_elem(th[u].y, 1)};
-                *(f4*)(s_h + r * HP + kv + 4) = f4{head_bf16_elem(th[u].z, 0), head_bf16_elem(th[u].z, 1), head_bf16_elem(th[u].w, 0),
-                                                   head_bf16_elem(th[u].w, 1)};
-            }
-        } else {
-            constexpr int NH = S * KC / 4 / THREADS;   // 16-byte vectors of 4 floats per lane (8)
-            f4 th[NH];
+            for (int t = 0; t < T; ++t)
 #pragma unroll
-            for (int u = 0; u < NH; ++u) {
-                const int f = threadIdx.x + u * THREADS, r = f / (KC / 4), kv = 4 * (f % (KC / 4));
-                th[u] = f4{0.f, 0.f, 0.f, 0.f};
-                if (s0 + r < B && k0 + kv < H)
-                    th[u] = *(const f4*)((const float*)p.h + (int64_t)i * p.h_stride + (int64_t)(s0 + r) * H + k0 + kv);
-            }
-#pragma unroll
-            for (int u = 0; u < NH; ++u) {
-                const int f = threadIdx.x + u * THREADS, r = f / (KC / 4), kv = 4 * (f % (KC / 4));
-                *(f4*)(s_h + r * HP + kv) = th[u];
-            }
+                for (int e = 0; e < 4; ++e) w1[t][e][j] = w_at(first + 4u * (unsigned)((16 * t + e) * C));
         }
+    };
+    auto load_w2 = [&](int k0) {   // W[k0 + 16 t + l16][4 c + q]
 #pragma unroll
-        for (int u = 0; u < NW; ++u) {
-            const int kl = threadIdx.x / CMAX + u * (THREADS / CMAX);
-            s_w[((kl % 4) * (KC / 4) + kl / 4) * P + cls] = tw[u];
+        for (int c = 0; c < CS; ++c) {
+            const unsigned first = 4 * c + q < C ? 4u * ((unsigned)(k0 + l16) * (unsigned)C + 4u * c + q) : kHeadNowhere;
+#pragma unroll
+            for (int t = 0; t < T; ++t) w2[t][c] = w_at(first + 64u * (unsigned)(t * C));
         }
     };
 
-    // Passes 0 .. n - 1 accumulate the logits over the chunks of H, the last of them ends with the softmax;
-    // passes n .. 2 n - 1 (only when dz is wanted) produce dz chunk by chunk.  One loop, so that the staging
-    // code exists once.  With a single chunk the weights and activations staged for the logits are still in
-    // LDS for dz; otherwise they are fetched again (they hit L2).
-    float acc[CMAX], d[CMAX];
+    const bool one_pass = H <= kChunk;
+    f4 acc[CT];
 #pragma unroll
-    for (int c = 0; c < CMAX; ++c) acc[c] = d[c] = 0.0f;
-    const int n = (H + KC - 1) / KC;
-    const int passes = p.dz ? 2 * n : n;
+    for (int j = 0; j < CT; ++j) acc[j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int pass = 0; pass < passes; ++pass) {
-        const bool backward = pass >= n;
-        const int k0 = (backward ? pass - n : pass) * KC;
-        if (!(backward && n == 1)) {
-            if (pass > 0) __syncthreads();   // the previous pass is no longer read
-            stage(k0);
-            __syncthreads();
+    for (int c0 = 0; c0 < H; c0 += kChunk) {
+        const int k0 = c0 + wave * T * 16;
+        load_h(k0);
+        load_w1(k0);
+        if (one_pass && p.dz) load_w2(k0);
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < CT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(h_elem(t, e), w1[t][e][j], acc[j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s_part[wave][(4 * q + r) * CMAX + 16 * j + l16] = acc[j][r];
+    __syncthreads();
+    if (soft) {
+        // Softmax with the classes spread over the 16 lanes of the row: lane sub owns class sub (and sub + 16 when CMAX =
+        // 32), so each lane evaluates one or two exponentials instead of CMAX.  The other classes' terms are summed
+        // separately from the label's: near convergence softmax[label] is within an ulp of 1, and both the loss log(1 +
+        // others / own) and the label's delta -(others / total) keep full relative accuracy this way, where log(total) -
+        // logit and softmax - 1 would cancel.
+        float logit[CT], ex[CT];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int c0 = 0; c0 < CT; ++c0) {
+            float v = 0.0f;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) v += s_part[w][row * CMAX + kRow * c0 + sub];
+            logit[c0] = kRow * c0 + sub < C ? v + bias[c0] : -INFINITY;
+            mx = fmaxf(mx, logit[c0]);
         }
-        if (!backward) {
-#pragma unroll 1
-            for (int j = 0; j < J; ++j) {
-                const f4 hv = *(const f4*)(s_h + row * HP + 4 * (sub + kRow * j));
+        mx = row_max(mx);
+        float others = 0.0f, own = 0.0f, picked = 0.0f;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float* wr = s_w + (e * (KC / 4) + sub + kRow * j) * P;
-#pragma unroll
-                    for (int c4 = 0; c4 < CMAX / 4; ++c4) {
-                        const f4 w = *(const f4*)(wr + 4 * c4);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) acc[4 * c4 + q] = __fmaf_rn(hv[e], w[q], acc[4 * c4 + q]);
-                    }
-                }
-            }
-            if (pass != n - 1) continue;
-            // Softmax with the classes spread over the 16 lanes of the row: lane sub owns class sub (and
-            // sub + 16 when CMAX = 32), so each lane evaluates one or two exponentials instead of CMAX.
-            // The other classes' terms are summed separately from the label's: near convergence
-            // softmax[label] is within an ulp of 1, and both the loss log(1 + others / own) and the
-            // label's delta -(others / total) keep full relative accuracy this way, where
-            // log(total) - logit and softmax - 1 would cancel.
-            float logit[CMAX / kRow], ex[CMAX / kRow];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int c0 = 0; c0 < CMAX / kRow; ++c0) {
-                float v = 0.0f;
-#pragma unroll
-                for (int c = 0; c < kRow; ++c) {
-                    const float full = row_sum(acc[kRow * c0 + c]);   // every lane takes part in every sum
-                    v = c == sub ? full : v;
-                }
-                logit[c0] = kRow * c0 + sub < C ? v + bias[c0] : -INFINITY;
-                mx = fmaxf(mx, logit[c0]);
-            }
-            mx = row_max(mx);
-            float others = 0.0f, own = 0.0f, picked = 0.0f;
-#pragma unroll
-            for (int c0 = 0; c0 < CMAX / kRow; ++c0) {
-                ex[c0] = expf(logit[c0] - mx);            // exp(-inf) = 0 for the padding
-                const bool is_label = kRow * c0 + sub == label;
-                own += is_label ? ex[c0] : 0.0f;
-                picked += is_label ? logit[c0] : 0.0f;
-                others += is_label ? 0.0f : ex[c0];
-            }
-            others = row_sum(others);
-            own = row_sum(own);          // one non-zero term
-            picked = row_sum(picked);    // one non-zero term
-            const float sum = others + own;
-            const float scale = 1.0f / (sum * (float)B);   // dlogits = (softmax - onehot) / B
-            if (live && sub == 0)
-                p.loss_parts[(int64_t)i * B + s] = own > 1e-30f ? log1pf(others / own) : (logf(sum) + mx) - picked;
-#pragma unroll
-            for (int c0 = 0; c0 < CMAX / kRow; ++c0) {
-                const int c = kRow * c0 + sub;
-                const float dv = (c == label ? -others : ex[c0]) * scale;   // 0 for the padding
-                s_d[row * CMAX + c] = dv;
-                if (live && c < C) p.dlogits[((int64_t)i * B + s) * C + c] = dv;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int c4 = 0; c4 < CMAX / 4; ++c4) {
-                const f4 v = *(const f4*)(s_d + row * CMAX + 4 * c4);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) d[4 * c4 + q] = v[q];
-            }
-            continue;
+        for (int c0 = 0; c0 < CT; ++c0) {
+            ex[c0] = expf(logit[c0] - mx);            // exp(-inf) = 0 for the padding
+            const bool is_label = kRow * c0 + sub == label;
+            own += is_label ? ex[c0] : 0.0f;
+            picked += is_label ? logit[c0] : 0.0f;
+            others += is_label ? 0.0f : ex[c0];
         }
-        // dz[s][k] = (sum_c dlogits[s][c] W[k][c]) * [h[s][k] > 0]
+        others = row_sum(others);
+        own = row_sum(own);          // one non-zero term
+        picked = row_sum(picked);    // one non-zero term
+        const float sum = others + own;
+        const float scale = 1.0f / (sum * (float)B);   // dlogits = (softmax - onehot) / B
+        if (live && sub == 0)
+            p.loss_parts[(int64_t)i * B + s] = own > 1e-30f ? log1pf(others / own) : (logf(sum) + mx) - picked;
+#pragma unroll
+        for (int c0 = 0; c0 < CT; ++c0) {
+            const int c = kRow * c0 + sub;
+            const float dv = (c == label ? -others : ex[c0]) * scale;   // 0 for the padding
+            s_d[row][c] = dv;
+            if (live && c < C) p.dlogits[((int64_t)i * B + s) * C + c] = dv;
+        }
+    }
+    if (!p.dz) return;
+    __syncthreads();
+    // dz[s][k] = (sum_c dlogits[s][c] W[k][c]) * [h[s][k] > 0]
+    float d[CS];
+#pragma unroll
+    for (int c = 0; c < CS; ++c) d[c] = s_d[l16][4 * c + q];
+    const rsrc_t dz_rs = make_rsrc((char*)p.dz + ((int64_t)i * B * H + (int64_t)s0 * H) * es, (unsigned)rows * (unsigned)H * es);
 #pragma unroll 1
-        for (int j = 0; j < J; ++j) {
-            const int kl = 4 * (sub + kRow * j), kv = k0 + kl;
-            const f4 hv = *(const f4*)(s_h + row * HP + kl);
-            f4 out;
+    for (int c0 = 0; c0 < H; c0 += kChunk) {
+        const int k0 = c0 + wave * T * 16;
+        if (!one_pass) {
+            load_h(k0);
+            load_w2(k0);
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float* wr = s_w + (e * (KC / 4) + sub + kRow * j) * P;
-                float a = 0.0f;
+        for (int t = 0; t < T; ++t) {
+            f4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int c4 = 0; c4 < CMAX / 4; ++c4) {
-                    const f4 w = *(const f4*)(wr + 4 * c4);
+            for (int c = 0; c < CS; ++c) o = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[t][c], d[c], o, 0, 0, 0);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) a = __fmaf_rn(d[4 * c4 + q], w[q], a);   // padding: d = 0, w = 0
-                }
-                out[e] = hv[e] > 0.0f ? a : 0.0f;
-            }
+            for (int e = 0; e < 4; ++e) o[e] = h_elem(t, e) > 0.0f ? o[e] : 0.0f;
+            const int k = k0 + 16 * t + 4 * q;
+            const unsigned off = k < H ? ((unsigned)l16 * (unsigned)H + (unsigned)k) * es : kHeadNowhere;   // samples past the batch are dropped as well
             if constexpr (BF) {
-                const unsigned int h0 = f32_to_bf16(out[0]), h1 = f32_to_bf16(out[1]), h2 = f32_to_bf16(out[2]),
-                                   h3 = f32_to_bf16(out[3]);
-                if (live && kv < H)
-                    *(u2*)((uint16_t*)p.dz + (int64_t)i * B * H + (int64_t)s * H + kv) = u2{h0 | (h1 << 16), h2 | (h3 << 16)};
+                const u2 w = {f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16), f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16)};
+                __builtin_amdgcn_raw_buffer_store_b64(w, dz_rs, (int)off, 0, 0);
             } else {
-                if (live && kv < H) *(f4*)((float*)p.dz + (int64_t)i * B * H + (int64_t)s * H + kv) = out;
+                buf_store(__builtin_bit_cast(u4, o), dz_rs, off);
             }
         }
     }
@@ -285,18 +243,25 @@ static bool head_args_ok(const HeadArgs& a) {
            (reinterpret_cast<uintptr_t>(a.h) & 15u) == 0 && a.h_stride % 4 == 0;
 }
 
-template <bool BF, int CMAX, int KC, int THREADS>
+template <bool BF, int CMAX, int T, int WAVES>
 static hipError_t head_fwd_launch(const HeadDev& p, int m, hipStream_t s) {
-    size_t lds = (size_t)head_fwd_lds_floats(CMAX, KC, THREADS) * sizeof(float);
-    auto kern = head_fwd_kernel<BF, CMAX, KC, THREADS>;
-    if (lds > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds((const void*)kern, lds);
-        if (e != hipSuccess) return e;
-    }
-    constexpr int kSamples = THREADS / kRow;
-    dim3 grid((unsigned)((p.B + kSamples - 1) / kSamples), (unsigned)m);
-    kern<<<grid, THREADS, lds, s>>>(p);
+    dim3 grid((unsigned)((p.B + 15) / 16), (unsigned)m);
+    head_fwd_kernel<BF, CMAX, T, WAVES><<<grid, 64 * WAVES, 0, s>>>(p);
     return hipGetLastError();
+}
+// One pass over the layer where the registers of up to 16 wavefronts hold it: T = 8 tiles of 16 units each, with fp32
+// activations beyond 1024 units or with more than 16 classes four (eight spill).
+template <bool BF>
+static hipError_t head_fwd_dispatch(const HeadDev& p, int m, hipStream_t s) {
+    if (p.C > 16) {
+        if (p.H <= 256) return head_fwd_launch<BF, 32, 4, 4>(p, m, s);
+        return head_fwd_launch<BF, 32, 4, 8>(p, m, s);
+    }
+    if (p.H <= 256) return head_fwd_launch<BF, 16, 4, 4>(p, m, s);
+    if (p.H <= 512) return head_fwd_launch<BF, 16, 4, 8>(p, m, s);
+    if (p.H <= 1024) return head_fwd_launch<BF, 16, 8, 8>(p, m, s);
+    if constexpr (BF) return head_fwd_launch<BF, 16, 8, 16>(p, m, s);
+    return head_fwd_launch<BF, 16, 4, 16>(p, m, s);
 }
 
 // logits, loss, dlogits, and (when a.dz is set) the delta of the last hidden layer
@@ -320,22 +285,8 @@ hipError_t launch_head_fwd(const HeadArgs& a, hipStream_t s) {
     p.B = a.B;
     p.H = a.H;
     p.C = a.C;
-    // Wider layers are staged 1024 hidden units at a time (146 KiB of LDS with 16 classes): half as many
-    // dependent passes, and up to H = 1024 the delta reuses what the logits staged.
-    // Workgroup size.  What a workgroup pays per pass is the staging of the weights, whatever the number of its
-    // samples: measured with 64 / 128 / 256 / 512 threads (4 to 32 samples) and 512 staged units, 16 workers x 128
-    // samples x 512 units: 19.5 / 17.0 / 15.4 / 14.0 us; 256 samples x 2048 units: 148 / 60 / 52 / 52 us.  So:
-    // 32 samples per workgroup where one pass covers the layer and the batch has them, 16 otherwise.
-    const bool wide = a.H > 512 && a.C <= 16;
-    const bool big = !wide && a.C <= 16 && a.B >= 32;
-    if (a.h_bf16) {
-        if (a.C > 16) return head_fwd_launch<true, 32, 512, 256>(p, a.m, s);
-        if (big) return head_fwd_launch<true, 16, 512, 512>(p, a.m, s);
-        return wide ? head_fwd_launch<true, 16, 1024, 256>(p, a.m, s) : head_fwd_launch<true, 16, 512, 256>(p, a.m, s);
-    }
-    if (a.C > 16) return head_fwd_launch<false, 32, 512, 256>(p, a.m, s);
-    if (big) return head_fwd_launch<false, 16, 512, 512>(p, a.m, s);
-    return wide ? head_fwd_launch<false, 16, 1024, 256>(p, a.m, s) : head_fwd_launch<false, 16, 512, 256>(p, a.m, s);
+    if (a.H >= (1 << 24)) return hipErrorInvalidValue;   // 32-bit byte offsets in the weights and in 16 samples' activations
+    return a.h_bf16 ? head_fwd_dispatch<true>(p, a.m, s) : head_fwd_dispatch<false>(p, a.m, s);
 }
 
 // Validates the arguments of the output layer's gradient pass and lays them out for the device.
