@@ -605,24 +605,35 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
 }
 
 // Tile choice.  Small problems (few rows per group) take 128 x 128 tiles: a 256-row tile would be mostly padding.
+// Where 128 x 128 tiles are fewer than the compute units, 64 x 64 ones shorten every workgroup's chain of slices and fill four
+// times as many units (forward / delta, us per launch averaged over the layers, batch x widths: 6 workers 72 x
+// 1032-520-264 18.1 -> 10.4 / 12.7 -> 7.7; 2 workers 64 x 512-256 13.3 -> 7.6; 16 workers 128 x 1024-512 15.4 -> 10.6; 4 workers 256 x
+// 3072-2048-1024 45.7 -> 23.3 / 20.9 -> 13.8; with exactly 256 tiles, 32 workers 128 x 1024-1024, 18.6 -> 22.9: not taken).
+// The contraction order is the same in every tile shape, and so are the bits.
+static bool few_tiles(const GemmArgs& g) { return (int64_t)g.groups * ((g.M + 127) / 128) * ((g.N + 127) / 128) < 256; }
 hipError_t launch_gemm_bf16_fwd(const GemmArgs& g, hipStream_t s) {
+    if (few_tiles(g)) return gemm_launch<kFwd, 64, 64, 64, 2>(g, s);
     if (g.M > 128) return gemm_launch<kFwd, 256, 128, 64, 2>(g, s);
     return gemm_launch<kFwd, 128, 128, 64, 2>(g, s);
 }
 hipError_t launch_gemm_bf16_da(const GemmArgs& g, hipStream_t s) {
+    if (few_tiles(g)) return gemm_launch<kDa, 64, 64, 64, 2>(g, s);
     if (g.M > 128) return gemm_launch<kDa, 256, 128, 64, 2>(g, s);
     return gemm_launch<kDa, 128, 128, 64, 2>(g, s);
 }
 hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant) {
     // Measured on configuration 3 (K = batch = 256, fused update): 64 x 128 x 32 tiles leave four workgroups per
     // compute unit and take 284 us per launch; 128 x 128: 309, 128 x 64: 294, 64 x 64: 295, BK = 64: 319-341.
+    // Up to 1024 of those tiles -- one round at four per compute unit -- 64 x 64 x 32 fills the chip better: 2 workers 64 x
+    // 512-256 10.6 -> 8.2 us, 8 workers 200 x 1000-136 15.5 -> 14.2, 16 workers 128 x 1024-512 37.8 -> 35.9; 4 workers 256 x
+    // 3072-2048-1024 (3072 tiles) 67.7 -> 71.5.
+    if (variant == 0) variant = (int64_t)g.groups * ((g.M + 63) / 64) * ((g.N + 127) / 128) <= 1024 ? 3 : 1;
     switch (variant) {
-        case 0:
         case 1: return gemm_launch<kDw, 64, 128, 32, 1>(g, s);
+        case 3: return gemm_launch<kDw, 64, 64, 32, 1>(g, s);
 #ifdef OLS_TUNING_VARIANTS
         case 6: return gemm_launch<kDw, 128, 128, 32, 1>(g, s);
         case 2: return gemm_launch<kDw, 128, 64, 32, 1>(g, s);
-        case 3: return gemm_launch<kDw, 64, 64, 32, 1>(g, s);
         case 4: return gemm_launch<kDw, 128, 128, 64, 1>(g, s);
         case 5: return gemm_launch<kDw, 64, 128, 64, 1>(g, s);
 #endif
