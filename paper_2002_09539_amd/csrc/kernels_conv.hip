@@ -556,7 +556,7 @@ int conv3x3_dw_splits(int groups, int B, int H, int W, int C) {
     const int64_t P = (int64_t)B * H * W;
     const int64_t tiles = (int64_t)groups * 3 * ((C + 63) / 64) * ((C + 63) / 64);   // one per kernel row and 64 x 64 block
     int64_t s = (1536 + tiles - 1) / tiles;                 // about six workgroups per compute unit
-    const int64_t most = (P + 1023) / 1024;                 // a range covers at least 1024 pixels
+    const int64_t most = (P + 255) / 256;                   // at least 256 pixels (1024: 52.4 against 29.2 us on 2 x 8 x 12 x 12 x 48)
     if (s > most) s = most;
     if (s > 32) s = 32;
     return s < 1 ? 1 : (int)s;
