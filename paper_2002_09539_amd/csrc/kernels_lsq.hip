@@ -47,6 +47,7 @@ __global__ __launch_bounds__(kThreads) void lsq_grad_kernel(const float* __restr
     if (j >= d) return;
     const float* col = A + (int64_t)i * a_stride + j;
     float acc = 0.0f;
+#pragma unroll 16   // independent loads ahead of the dependent chain of additions
     for (int s = 0; s < B; ++s) acc = __fmaf_rn(col[(int64_t)s * d], r_lds[s], acc);
     g[(int64_t)i * ld + j] = acc / (float)B;
 }
