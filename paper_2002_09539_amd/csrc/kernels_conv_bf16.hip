@@ -25,17 +25,17 @@
 // applies the ReLU, keeps the activation's sign (one bit per element) for the backward pass and the wavefront's channel
 // sums for the pooling -- neither the convolution's output nor the activation is ever stored.  (Images of fewer than 64
 // padded pixels take the unfused route: conv + bias in fp32, then one streaming pass.)
-// DW: one workgroup per (pixel range, 64 x 64 block of input x output channels) holds all nine taps' accumulators
-// (9 x 64 x 64 fp32 = 144 registers per lane); per 64 pixels the input strip (64 + 2 (W + 3) rows, row-contiguous,
-// read with the transpose load at nine row offsets) and the delta tile pass through LDS; ranges are summed in range
-// order by the finish pass shared with the fp32 kernels (no atomics).
+// DW: one workgroup per (pixel range, 64 x 64 block of input x output channels); each of twelve wavefronts holds the
+// three taps of a kernel row over 32 x 64 channels (96 registers per lane) for half of the contraction steps; per 96
+// pixels 96 new input rows enter a ring of LDS rows (read with the transpose load at nine row offsets) and 96 delta rows a
+// pair of buffers; ranges are summed in range order by the finish pass shared with the fp32 kernels (no atomics).
 // All three address global memory through buffer descriptors: the hardware's range check returns zeros for the rows a
 // strip reaches past either end of the tensor and drops the stores of a last tile's missing rows, so the loads and stores
 // carry no per-lane predicates, selects or 64-bit address arithmetic.
 //
 // Measured at the benchmark shape (16 workers x 128 samples x 32 x 32 x 64 channels, 154.6 GFLOP per launch): forward
 // 200 us (bf16 out), 240 us with the fused tail (208 us for conv + bias in fp32 alone, which then needed a 224 us
-// streaming pass), delta 204 us, kernel gradient 170 + 22 us, against 1390 - 1430 us for the fp32 kernels.
+// streaming pass), delta 204 us, kernel gradient 160 + 9 us, against 1390 - 1430 us for the fp32 kernels on their own units.
 // Timestamps (s_memrealtime) taken inside an instrumented copy of the forward kernel showed where a tile's 11.3 us went
 // before the descriptors: 2.8 us from the first instruction to the last load issued -- some 1100 instructions of
 // predicates and addresses, issued by one wavefront per SIMD at a few cycles each -- 1.3 us for the loads to arrive,
@@ -43,23 +43,25 @@
 // epilogue.  With one workgroup per compute unit a tile takes 7.2 us, so the second one hides a third of the latencies.
 // Buffer addressing took the kernel from 2150 to 1330 instructions and the tile to 9.4 us (forward 221 -> 197 us,
 // fp32 out 245 -> 208, delta 252 -> 204 with the gate activations requested three taps before the end instead of after
-// it).  The same treatment of the kernel gradient's slice loads: 0.70 -> 0.33 us of a slice's 2.36 us for the
-// requests, 0.43 -> 0.29 for the LDS stores (186 -> 170 us); its bias column sums now come from the delta fragments the
-// MFMAs use anyway instead of sixteen more LDS reads per slice.
+// it).
 // The fused tail's shortcut rows (fp32, 16 vectors per lane) are requested in two batches of eight, the first three
 // taps before the end and the second once the tile is staged, instead of both inside the epilogue's loop: 252 -> 241 us
 // (requesting the second batch before the staging as well: 248 us).
-// What moved the kernel gradient from 289 us before that: fragment reads issued a kernel row ahead of the MFMAs (258),
-// the bias column sums shared out over the four wavefronts instead of one wavefront summing while three wait at the
-// barrier (219), and 512 workgroups -- one round at two per compute unit -- instead of 768 (185; the finish pass 46 -> 22).
+// The kernel gradient had four wavefronts of 32 x 32 channels x nine taps, two workgroups per compute unit, 64 pixels and
+// a strip of 64 + 2 (W + 3) rows per slice: 170 us + 14 for the finish pass alone, 198 + 15 in a whole step.  Now 160 + 9
+// and 185 + 9: the ring fetches a row once instead of 2.1 times, the taps of a kernel row share three transpose reads
+// (seven reads feed six products, from twenty for nine), slices are requested two ahead, and the halves of the steps meet
+// in LDS, so that there are half as many partial sums.  Without its loads it takes 168 us in a step, without its fragment
+// reads 167, with one product of six 129: no single one bounds it, what is left is their overlap at 2.0 GHz.  The
+// descriptor and the choice of its tensor have to be in scalar registers: with a per-lane choice the compiler loops over
+// the lanes of every load (193).  Not kept: eight wavefronts with nine taps each, every fragment read a kernel row ahead
+// and across the slice's barrier (212); two workgroups of six wavefronts, 48 pixels per slice (232).
 // Tried and not kept: persistent workgroups that hold the whole kernel as 72 register fragments and walk the tiles of a
 // worker (one wavefront per SIMD, no barrier inside a tile: 280 - 400 us; with half the fragments per wavefront and two
 // workgroups per compute unit 308 - 397 us); the present forward kernel made persistent with the next tile's strip
 // requested a tile ahead (the 44 extra live registers spill: 308 - 366 us); all nine kernel slices requested at the
 // start of a tile (no change); in the kernel gradient two slices of loads in flight (400 registers, one wavefront per
-// SIMD: 349 us), fragment reads two kernel rows ahead (259 against 258 us), and an LDS ring of input rows that fetches
-// only the 64 new rows per slice three slices ahead (the wrap-around address arithmetic per fragment read costs more
-// than the loads it saves: 325 us); forward / delta tiles of 128 pixels (134 registers, 53 KB of LDS, three workgroups
+// SIMD: 349 us), fragment reads two kernel rows ahead (259 against 258 us); forward / delta tiles of 128 pixels (134 registers, 53 KB of LDS, three workgroups
 // per compute unit; the halo is then 1.55 x the tile: 260 / 291 / 271 us against 221 / 245 / 252); a raised wavefront
 // priority (s_setprio) outside or inside the tap loop (+-1 %); the bias loaded straight into the accumulators before the
 // first tap (the eight extra loads in the prologue cost what the epilogue's additions saved); a branch around the late
@@ -98,7 +100,7 @@ constexpr int kThreads = kTileThreads;
 constexpr int kXcds = 8;
 constexpr int kCB = 64;     // channel block: contraction chunk and output-channel tile
 constexpr int kBM = 256;    // padded pixels per forward / delta tile
-constexpr int kDwBK = 64;   // pixels per slice of the kernel-gradient contraction
+constexpr int kDwBK = 96;   // padded pixels per slice of the kernel-gradient contraction
 
 struct ConvBDev {
     const uint16_t* in;      // FWD: layer input; DX: delta of the layer output; DW: layer input   [groups][Pp][C] bf16
@@ -585,17 +587,24 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 3 : 2) void conv3x3_bf16_kern
 }
 
 // ---------------------------------------------------------------------------------------------
-// kernel / bias gradient
+// kernel / bias gradient.  One workgroup per (pixel range, 64 x 64 block of input x output channels): twelve wavefronts
+// (three per SIMD), (kernel row, 32 input channels, half of the contraction steps) each, with 32 x 64 channels x three taps in
+// 96 accumulators per lane; the halves are added through LDS at the end.  96 padded pixels per slice; the input rows live in
+// a ring of 512 LDS rows, so each is fetched once
+// although nine taps read it at nine offsets, and the delta's rows alternate between two buffers.  Rows are 128 bytes, their
+// halves exchanged by bit 1 of the row, so that the four rows of a transpose read cover the 64 banks.  A lane's fragments of
+// the three taps are eight of the pixels -1 .. 8 around its own eight: three transpose reads bring -1 .. 10 (the last two are
+// not used, and may be rows that are being written).
 // ---------------------------------------------------------------------------------------------
-template <int NV>   // strip vectors per lane (upper bound of (32 + 2 halo) * 8 / 256)
-__global__ __launch_bounds__(kThreads, 2) void conv3x3_dw_bf16_kernel(ConvBDev p) {
-    using TD = TileRC<kCB, kDwBK>;               // delta tile: [32 pixels][64 channels + 32]
-    constexpr int RP = TD::kPitch;               // the input strip uses the same pitch
-    extern __shared__ __attribute__((aligned(16))) uint16_t lds_all[];
-    const int strip_rows = kDwBK + 2 * p.halo;
-    const int strip_elems = strip_rows * RP;
-    auto lds_s = [&](int buf) { return lds_all + buf * strip_elems; };
-    auto lds_d = [&](int buf) { return lds_all + 2 * strip_elems + buf * TD::kElems; };
+constexpr int kDwThreads = 768, kDwRing = 512, kDwRow = 128, kDwVecs = 2;   // LDS rows in bytes; vectors per copying lane
+static_assert(kDwBK * 8 == kDwVecs * kDwThreads / 2, "half of the lanes copy input rows, half the delta's");
+constexpr int kDwFold = 6 * 64 * 96 * 4;   // bytes of one half's accumulators, which take the operands' place in LDS
+static_assert((kDwRing + 2 * kDwBK) * kDwRow <= kDwFold, "the larger of the two");
+static_assert(2 * kDwBK + 2 * (kConvBf16MaxWidth + 3) <= kDwRing, "the ring holds a slice's window and the next slice's rows");
+__global__ __launch_bounds__(kDwThreads, 3) void conv3x3_dw_bf16_kernel(ConvBDev p) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t dw_lds[];
+    uint8_t* ring = dw_lds;
+    auto delta = [&](int buf) { return dw_lds + kDwRing * kDwRow + buf * (kDwBK * kDwRow); };
 
     const int tile = xcd_tile(p.chunk, p.total_tiles);
     if (tile < 0) return;
@@ -606,109 +615,147 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_dw_bf16_kernel(ConvBDev p
     const int split = rest / (nb * nb);
     const int ci0 = ((rest / nb) % nb) * kCB, co0 = (rest % nb) * kCB;
     const int lo = split * p.k_chunk, hi = min(p.Pp, lo + p.k_chunk);
-    const uint16_t* IN = p.in + (int64_t)group * p.s_in;
-    const uint16_t* DO = p.dout + (int64_t)group * p.s_dout;
     const int C = p.C;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const int kh = wave / 4, wi = (wave / 2) % 2, khalf = wave % 2;
 
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int lane32 = lane % 32, half = lane / 32;
-    const int wi = wave / 2, wj = wave % 2;      // 32 x 32 block of the 64 x 64 (ci, co) tile
-
-    f16v acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
-    // bias gradient: column sums of the delta, taken from the delta fragments (a lane holds 8 pixels of one channel); the
-    // two wavefronts that read the same fragments share the k-steps
-    const bool col_sums = ci0 == 0;
-    float col_acc = 0.0f;
-
-    // Buffer addressing as in the forward kernel: lane t of the workgroup owns the 16-byte vector t % 8 of row t / 8 of a
-    // [rows][C] tensor, its further vectors lie 32 rows below.  Input rows outside the tensor read as zeros, and so do the
-    // delta's rows from the end of this workgroup's pixel range on (its descriptor ends there), which removes the pixels
-    // past the range from the sums.
-    static_assert(TD::kLineStep == 32 && TD::kPerThread == 2, "a lane's vectors are 32 rows apart in the strip and in the delta tile");
+    // Copying: lanes 0 .. 383 move input rows, 384 .. 767 delta rows; vector t % 8 of rows t / 8 and t / 8 + 48.  Input rows
+    // outside the tensor read as zeros, and so do the delta's rows from the end of the range on (its descriptor ends there).
+    const bool moves_in = wave < kDwThreads / 128;   // (in scalar registers, like the descriptor)
+    const int mt = moves_in ? threadIdx.x : threadIdx.x - kDwThreads / 2;
+    const int mrow = mt / 8, mv = mt % 8;
     const unsigned row_bytes = 2u * (unsigned)C;
-    const unsigned lane_off = (threadIdx.x / 8) * row_bytes + (threadIdx.x % 8) * 16u;
-    const unsigned step32 = 32u * row_bytes;
-    const rsrc_t in_rs = make_rsrc(IN, (unsigned)p.Pp * row_bytes);
-    const rsrc_t do_rs = make_rsrc(DO, (unsigned)hi * row_bytes);
-    const int nvec = strip_rows * (kCB / 8);
-    auto load_slice = [&](u4 (&r)[NV], u4 (&d)[TD::kPerThread], int k0) {
-        const unsigned first = (unsigned)(k0 - p.halo) * row_bytes + lane_off;
+    const uint16_t* src = moves_in ? p.in + (int64_t)group * p.s_in : p.dout + (int64_t)group * p.s_dout;
+    const rsrc_t rs = make_rsrc(src, (unsigned)(moves_in ? p.Pp : hi) * row_bytes);
+    const unsigned lane_off = 2u * (unsigned)(moves_in ? ci0 : co0) + mv * 16u;
+    auto load_rows = [&](u4 (&r)[kDwVecs], int q0) {   // (a negative row wraps to an offset beyond the range)
 #pragma unroll
-        for (int t = 0; t < NV; ++t) r[t] = buf_load(in_rs, first + t * step32, 2u * ci0);
-        const unsigned dfirst = (unsigned)k0 * row_bytes + lane_off;
-#pragma unroll
-        for (int t = 0; t < TD::kPerThread; ++t) d[t] = buf_load(do_rs, dfirst + t * step32, 2u * co0);
+        for (int t = 0; t < kDwVecs; ++t) r[t] = buf_load(rs, (unsigned)(q0 + mrow + 48 * t) * row_bytes + lane_off, 0u);
     };
-    auto store_slice = [&](int buf, const u4 (&r)[NV], const u4 (&d)[TD::kPerThread]) {
-        uint16_t* dst = lds_s(buf) + (threadIdx.x / 8) * RP + (threadIdx.x % 8) * 8;
+    // bias gradient: the delta's column sums, from the fragments of the first kernel row's wavefronts (a lane holds eight
+    // pixels of one channel)
+    const bool col_sums = ci0 == 0;
+    float col_acc[2] = {0.0f, 0.0f};
+    uint8_t* put_base = moves_in ? ring : delta(0);
+    auto put_rows = [&](const u4 (&r)[kDwVecs], int row0) {
 #pragma unroll
-        for (int t = 0; t < NV; ++t)
-            if ((int)threadIdx.x + t * kThreads < nvec) *(u4*)(dst + t * 32 * RP) = r[t];   // the strip ends inside one of them
-        uint16_t* dd = TD::lane_lds(lds_d(buf));
-#pragma unroll
-        for (int t = 0; t < TD::kPerThread; ++t) *(u4*)(dd + t * TD::kLdsLineStep) = d[t];
+        for (int t = 0; t < kDwVecs; ++t) {
+            const int row = (row0 + mrow + 48 * t) & (kDwRing - 1);
+            *(u4*)(put_base + row * kDwRow + (((mv / 4) ^ ((row >> 1) & 1)) * 64) + (mv % 4) * 16) = r[t];
+        }
     };
 
-    u4 rs[NV], rd[TD::kPerThread];
-    load_slice(rs, rd, lo);
-    store_slice(0, rs, rd);
-    __syncthreads();
-    const int nslices = (hi - lo + kDwBK - 1) / kDwBK;
-    for (int t = 0; t < nslices; ++t) {
-        const int cur = t & 1;
-        if (t + 1 < nslices) load_slice(rs, rd, lo + (t + 1) * kDwBK);
-        const uint16_t* S = lds_s(cur) + p.halo * RP;
-        const uint16_t* D = lds_d(cur);
-        // 4 k-steps x 9 taps = 12 groups of one kernel row: the fragments of group g + 1 are requested before the MFMAs
-        // of group g (a lone just-in-time read would expose the LDS latency on every MFMA)
-        constexpr int kGroups = (kDwBK / 16) * 3;
-        bf16x8 fi[2][3], fd[2];
-        auto load_group = [&](int g) {
-            const int s = g / 3, kh = g % 3;
-            if (kh == 0) fd[s & 1] = TD::frag(D, 32 * wj, s, lane);
+    const int blk = lane / 16, j = lane % 16;
+    const int frow = 8 * (blk / 2) + j / 4, fcol = (16 * (blk % 2) + 4 * (j % 4)) * 2;
+    typedef s4v __attribute__((address_space(3))) * lds_s4_ptr;
+    auto row_addr = [&](int row, int piece) { return row * kDwRow + ((piece ^ ((row >> 1) & 1)) * 64) + fcol; };
+    auto quad = [&](const uint8_t* a) { return __builtin_bit_cast(u2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)a)); };   // four pixels of a lane's channel
+    f16v acc[3][2];
 #pragma unroll
-            for (int kw = 0; kw < 3; ++kw) fi[g & 1][kw] = TD::frag(S + ((kh - 1) * p.Wp + (kw - 1)) * RP, 32 * wi, s, lane);
-        };
-        load_group(0);
+    for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            if (g + 1 < kGroups) load_group(g + 1);
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[t][c][e] = 0.0f;
+
+    // ring row of padded pixel q: (q - lo + halo) mod 512
+    const int nslices = hi > lo ? (hi - lo + kDwBK - 1) / kDwBK : 0;
+    if (nslices > 0) {
+        u4 r0[kDwVecs], r1[kDwVecs];
+        const int ahead = moves_in ? p.halo : 0;
+        if (moves_in) {
+            for (int d = 0; d < kDwBK + 2 * p.halo; d += kDwBK) {
+                load_rows(r0, lo - p.halo + d);
+                put_rows(r0, d);
+            }
+        } else {
+            load_rows(r0, lo);
+            put_rows(r0, 0);
+        }
+        load_rows(r0, lo + kDwBK + ahead);
+        __syncthreads();
+        auto slice = [&](int t, const u4 (&next)[kDwVecs], u4 (&after)[kDwVecs]) {
+            load_rows(after, lo + (t + 2) * kDwBK + ahead);       // (past the range: zeros that nothing reads)
             __builtin_amdgcn_sched_barrier(0);
+            const uint8_t* D = delta(t & 1);
+            const int base = t * kDwBK + p.halo + (kh - 1) * p.Wp + frow;
 #pragma unroll
-            for (int kw = 0; kw < 3; ++kw)
-                acc[3 * (g % 3) + kw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fi[g & 1][kw], fd[(g / 3) & 1], acc[3 * (g % 3) + kw], 0, 0, 0);
-            if (g % 3 == 0 && col_sums && (g / 3) / 2 == wi) {
-                const u4 w = __builtin_bit_cast(u4, fd[(g / 3) & 1]);
+            for (int s = 0; s < kDwBK / 32; ++s) {                // of this wavefront's half
+                const int k16 = 16 * (2 * s + khalf);
+                bf16x8 fd[2];
+                u2 w[3];                                          // input pixels -1 .. 10 of a lane's eight: the three taps
 #pragma unroll
-                for (int e = 0; e < 4; ++e) col_acc += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xFFFF0000u);
+                for (int q = 0; q < 3; ++q) w[q] = quad(ring + row_addr((base + k16 - 1 + 4 * q) & (kDwRing - 1), wi));
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const uint8_t* a = D + row_addr(k16 + frow, c);
+                    fd[c] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(quad(a), quad(a + 4 * kDwRow), 0, 1, 2, 3));   // four rows on: the same bit 1
+                }
+                const unsigned px[5] = {w[0].x, w[0].y, w[1].x, w[1].y, w[2].x};
+#pragma unroll
+                for (int kw = 0; kw < 3; ++kw) {
+                    u4 f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[e] = kw == 0 ? px[e] : kw == 1 ? __builtin_amdgcn_alignbit(px[e + 1], px[e], 16) : px[e + 1];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) acc[kw][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f), fd[c], acc[kw][c], 0, 0, 0);
+                }
+                if (col_sums && kh == 0 && wi == 0) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const u4 d = __builtin_bit_cast(u4, fd[c]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) col_acc[c] += __uint_as_float(d[e] << 16) + __uint_as_float(d[e] & 0xFFFF0000u);
+                    }
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
+            put_rows(next, moves_in ? (t + 1) * kDwBK + 2 * p.halo : ((t + 1) & 1) * kDwBK);   // behind the window; the other buffer
+            __syncthreads();
+        };
+        int t = 0;
+        for (; t + 1 < nslices; t += 2) {
+            slice(t, r0, r1);
+            slice(t + 1, r1, r0);
         }
-        if (t + 1 < nslices) store_slice(cur ^ 1, rs, rd);
-        __syncthreads();
+        if (t < nslices) slice(t, r0, r1);
     }
 
+    // the second half of the steps hands its sums over (the operand rows are no longer read)
+    float* fold = (float*)dw_lds + (wave / 2) * (64 * 96) + lane;
+    if (khalf == 1) {
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) fold[((2 * kw + c) * 16 + e) * 64] = acc[kw][c][e];
+    }
+    __syncthreads();
     const int64_t n_w = (int64_t)9 * C * C;
     float* PART = p.partial + ((int64_t)split * p.groups + group) * (n_w + C);
+    if (khalf == 0) {
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
+        for (int kw = 0; kw < 3; ++kw)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int ci = ci0 + 32 * wi + 8 * (r / 4) + 4 * half + (r % 4);
-            PART[((int64_t)tap * C + ci) * C + co0 + 32 * wj + lane32] = acc[tap][r];
-        }
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int ci = ci0 + 32 * wi + 8 * (e / 4) + 4 * (lane / 32) + (e % 4);
+                    PART[((int64_t)(3 * kh + kw) * C + ci) * C + co0 + 32 * c + lane % 32] = acc[kw][c][e] + fold[((2 * kw + c) * 16 + e) * 64];
+                }
     }
-    if (col_sums) {   // channel c: wavefronts (wi, wj = c / 32), both halves of their lanes, added in a fixed order
-        float* red = (float*)lds_all;
-        red[threadIdx.x] = col_acc;
+    if (ci0 == 0) {   // channel c: the two halves of the steps, both halves of the wavefronts' lanes, added in a fixed order
+        __syncthreads();
+        float* red = (float*)dw_lds;
+        if (kh == 0 && wi == 0) {
+            red[khalf * 128 + lane] = col_acc[0];
+            red[khalf * 128 + 64 + lane] = col_acc[1];
+        }
         __syncthreads();
         if (threadIdx.x < kCB) {
-            const float* r0 = red + 64 * (threadIdx.x / 32) + threadIdx.x % 32;   // wi = 0; wi = 1 is 128 lanes on
-            PART[n_w + co0 + threadIdx.x] = ((r0[0] + r0[32]) + r0[128]) + r0[160];
+            const float* r = red + 64 * (threadIdx.x / 32) + threadIdx.x % 32;
+            PART[n_w + co0 + threadIdx.x] = ((r[0] + r[32]) + r[128]) + r[160];
         }
     }
 }
@@ -999,10 +1046,9 @@ hipError_t launch_conv3x3_bf16_dx(const ConvBArgs& a, hipStream_t s) { return co
 int conv3x3_bf16_dw_splits(int groups, int B, int H, int W, int C) {
     const int64_t Pp = (int64_t)B * (H + 2) * (W + 2);
     const int64_t tiles = (int64_t)groups * (C / kCB) * (C / kCB);
-    int64_t s = (512 + tiles - 1) / tiles;                  // two workgroups per compute unit (registers and LDS allow two)
+    int64_t s = (256 + tiles - 1) / tiles;                  // one workgroup per compute unit (registers and LDS allow one)
     const int64_t most = (Pp + 511) / 512;                  // a range covers at least 512 padded pixels
     if (s > most) s = most;
-    if (s > 256) s = 256;
     return s < 1 ? 1 : (int)s;
 }
 
@@ -1020,20 +1066,11 @@ hipError_t launch_conv3x3_bf16_dw(const ConvBArgs& a, hipStream_t s) {
     if (total > (1 << 30)) return hipErrorInvalidValue;
     p.total_tiles = (int)total;
     p.chunk = (int)((total + kXcds - 1) / kXcds);
-    const int strip_rows = kDwBK + 2 * p.halo;
-    const size_t lds = (2 * (size_t)strip_rows * TileRC<kCB, kDwBK>::kPitch + 2 * TileRC<kCB, kDwBK>::kElems) * sizeof(uint16_t);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
-    const int nv = (strip_rows * (kCB / 8) + kThreads - 1) / kThreads;
-    void (*kern)(ConvBDev) = nullptr;
-    if (nv <= 5) kern = conv3x3_dw_bf16_kernel<5>;
-    else if (nv <= 11) kern = conv3x3_dw_bf16_kernel<11>;
-    else return hipErrorInvalidValue;
-    if (lds > 64 * 1024) {
-        hipError_t e = ensure_dynamic_lds((const void*)kern, 160 * 1024);
-        if (e != hipSuccess) return e;
-    }
-    kern<<<(unsigned)(p.chunk * kXcds), kThreads, lds, s>>>(p);
-    hipError_t e = hipGetLastError();
+    constexpr size_t lds = kDwFold;
+    hipError_t e = ensure_dynamic_lds((const void*)conv3x3_dw_bf16_kernel, lds);
+    if (e != hipSuccess) return e;
+    conv3x3_dw_bf16_kernel<<<(unsigned)(p.chunk * kXcds), kDwThreads, lds, s>>>(p);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_conv_dw_finish(a.partial, p.splits, a.groups, a.C, a.g, a.ld, a.g_w_off, a.g_b_off, s);
 }
