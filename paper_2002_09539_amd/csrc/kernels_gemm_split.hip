@@ -299,16 +299,17 @@ bool gemm_split_fits(int64_t a_elems, int64_t b_elems) {   // byte offsets of a 
     return a_elems < ((int64_t)1 << 29) - 65536 && b_elems < ((int64_t)1 << 29) - 65536;
 }
 
-// The rule: 64 x 128 tiles, where they give two workgroups per compute unit -- alone, or over up to four K ranges of at
-// least 512 indices.  Below that the fp32 kernel's smaller tiles fill the chip better: 8 workers x (128 x 1024 x 1024) 29 us
-// with it, 28 over four ranges here; 4 x (112 x 120 .. 280 x 1084 .. 120) 13 against 17 us.
+// The rule: 64 x 128 tiles, where they give two workgroups per compute unit, one with long contractions, or half of one over
+// four K ranges of at least 512 indices.  Below that the fp32 kernel's smaller tiles fill the chip better: 8 workers x (128 x
+// 1024 x 1024) 29 us with it, 28 over four ranges here; 4 x (112 x 120 .. 280 x 1084 .. 120) 13 against 17 us.  With 256 to
+// 511 tiles, the fp32 kernel's 64 x 64 tiles against this kernel: 32 x (128 x 512 x 1024) 49 and 47 us, 24 x (192 x 512 x
+// 2048) 116 and 107, 40 x (64 x 1024 x 1536) 99 and 95, 16 x (128 x 1024 x 3072) 135 and 135; two K ranges would take 48,
+// 105, 92 and 121 us but 64 MB and more of scratch, where these shapes need none.
 bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits) {
     if (N < 128 || !gemm_split_fits((int64_t)M * K, (int64_t)K * N)) return false;
     const int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 127) / 128);
-    int s = 1;
-    while (tiles * s < 512 && K / (2 * s) >= 512 && s < 4) s *= 2;
-    *splits = s;
-    return tiles * s >= 512;
+    *splits = tiles < 256 ? 4 : 1;
+    return tiles >= 512 || (tiles >= 256 && K >= 1024) || (tiles >= 128 && K >= 2048);
 }
 
 hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s) { return gemm_launch<64, 128, 4>(g, s); }

@@ -29,7 +29,8 @@ def one_step(cfg, dims, batch, X, labels, x0):
 
 @pytest.mark.parametrize("m,dims,batch", [
     (16, (2048, 512, 10), 124),         # 128 tiles over four K ranges; ragged rows
-    (32, (1060, 260, 5), 68),           # two K ranges, the last one short and no whole number of slices; ragged columns
+    (22, (2060, 260, 5), 68),           # 132 tiles, the last K range short and no whole number of slices; ragged columns
+    (32, (1060, 516, 5), 68),           # 320 tiles over one range
     (64, (36, 1028, 516, 3), 8),        # contractions of 36 (two slices, the second of four indices) and 1028
     (43, (128, 772, 7), 128),           # exactly one group of four slices; a last column tile of four
 ])
