@@ -338,15 +338,17 @@ OLS_API int ols_run_steps(ols_handle h, int64_t steps, const float* X_dev, const
  * caller-provided buffer.  The call allocates nothing (no hipMalloc / hipFree, no events); the handle must have
  * been bound and initialised beforehand, and state, data and streams remain the caller's.
  *   - The array holds ols_static_workspace_bytes() = 64 MiB, one copy per GPU, kept until the process ends;
- *     OLS_ENOMEM if ols_workspace_bytes(h) is larger.
- *   - fp32 models only (least squares, fp32 MLP): the bf16 MLP keeps weights in its workspace (OLS_EINVAL).
+ *     OLS_ENOMEM if ols_workspace_bytes(h) is larger -- except that an fp32 convolutional block which fits with the
+ *     kernels that need the least scratch takes those from then on (ols_workspace_bytes then says so; the same
+ *     results within the rounding of fp32 sums).
+ *   - fp32 models only (least squares, fp32 MLP, fp32 convolutional blocks): the bf16 MLP keeps weights in its workspace (OLS_EINVAL).
  *   - OLS_ESTATE while OLS_OPT_KERNEL_TIMING is on (timing creates events).
  *   - The handle's workspace becomes the static array (it replaces one bound with ols_bind_workspace); ols_get_loss
  *     afterwards reads the per-sample losses from it.  Nothing in it needs clearing between calls: every kernel
  *     writes what it later reads.
  *   - Every handle on one GPU shares the one array: calls (and the work they enqueue) that overlap on a GPU race;
  *     drain the streams (ols_sync) before another handle uses it.
- * Same launches, same results as ols_run_steps. */
+ * Otherwise the same launches and the same results as ols_run_steps. */
 OLS_API int ols_run_steps_static(ols_handle h, int64_t steps, const float* X_dev, const void* y_dev, int nb);
 OLS_API int64_t ols_static_workspace_bytes(void);
 

@@ -552,24 +552,24 @@ hipError_t conv_launch(const ConvArgs& a, hipStream_t s) {
 hipError_t launch_conv3x3_fwd(const ConvArgs& a, hipStream_t s) { return conv_launch<0>(a, s); }
 hipError_t launch_conv3x3_dx(const ConvArgs& a, hipStream_t s) { return conv_launch<1>(a, s); }
 
-int conv3x3_dw_splits(int groups, int B, int H, int W, int C) {
+int conv3x3_dw_splits(int groups, int B, int H, int W, int C, int least) {
     const int64_t P = (int64_t)B * H * W;
     const int64_t tiles = (int64_t)groups * 3 * ((C + 63) / 64) * ((C + 63) / 64);   // one per kernel row and 64 x 64 block
     int64_t s = (1536 + tiles - 1) / tiles;                 // about six workgroups per compute unit
-    const int64_t most = (P + 255) / 256;                   // at least 256 pixels (1024: 52.4 against 29.2 us on 2 x 8 x 12 x 12 x 48)
+    const int64_t most = (P + least - 1) / least;           // at least 256 pixels (1024: 52.4 against 29.2 us on 2 x 8 x 12 x 12 x 48)
     if (s > most) s = most;
     if (s > 32) s = 32;
     return s < 1 ? 1 : (int)s;
 }
 
 hipError_t launch_conv3x3_dw(const ConvArgs& a, hipStream_t s) {
-    if (!shape_ok(a) || !a.in || !a.dout || !a.partial || !a.g || !aligned16(a.in) || !aligned16(a.dout)) return hipErrorInvalidValue;
+    if (!shape_ok(a) || !a.in || !a.dout || !a.partial || a.dw_splits < 1 || !a.g || !aligned16(a.in) || !aligned16(a.dout)) return hipErrorInvalidValue;
     if (a.s_in % 4 || a.s_dout % 4) return hipErrorInvalidValue;
     ConvDev p = {};
     p.in = a.in; p.dout = a.dout; p.partial = a.partial;
     p.s_in = a.s_in; p.s_dout = a.s_dout;
     p.groups = a.groups; p.B = a.B; p.H = a.H; p.W = a.W; p.C = a.C; p.P = a.B * a.H * a.W;
-    p.splits = conv3x3_dw_splits(a.groups, a.B, a.H, a.W, a.C);
+    p.splits = a.dw_splits;
 #ifndef OLS_CONV_DW_BK
 #define OLS_CONV_DW_BK 16
 #endif

@@ -586,14 +586,14 @@ int conv3x3_split_dw_splits(int groups, int B, int H, int W, int C) {
 
 hipError_t launch_conv3x3_split_dw(const ConvArgs& a, hipStream_t s) {
     if (a.groups < 1 || a.groups > 65535 || !conv3x3_split_fits(a.B, a.H, a.W, a.C)) return hipErrorInvalidValue;
-    if (!a.in || !a.dout || !a.partial || !a.g || !aligned16(a.in) || !aligned16(a.dout) || a.s_in % 4 || a.s_dout % 4) return hipErrorInvalidValue;
+    if (!a.in || !a.dout || !a.partial || a.dw_splits < 1 || !a.g || !aligned16(a.in) || !aligned16(a.dout) || a.s_in % 4 || a.s_dout % 4) return hipErrorInvalidValue;
     ConvSDwDev p = {};
     p.in = a.in; p.dout = a.dout; p.partial = a.partial;
     p.s_in = a.s_in; p.s_dout = a.s_dout;
     p.groups = a.groups; p.B = a.B; p.H = a.H; p.W = a.W; p.C = a.C;
     p.V = a.B * (a.H + 1) * (a.W + 1);
     p.halo = a.W + 2;
-    p.splits = conv3x3_split_dw_splits(a.groups, a.B, a.H, a.W, a.C);
+    p.splits = a.dw_splits;
     p.k_chunk = (int)((((int64_t)p.V + p.splits - 1) / p.splits + kDwBK - 1) / kDwBK * kDwBK);
     p.blocks_n = (a.C + 63) / 64;
     p.tensor_bytes = (unsigned)a.B * a.H * a.W * 4u * (unsigned)a.C;

@@ -98,6 +98,8 @@ struct ols_ctx {
     float cv_eps = 1e-5f;
     int64_t off_a1 = 0, off_a2 = 0, off_dz1 = 0, off_dz2 = 0, off_pooled = 0, off_dpool = 0, off_cpartial = 0;
     int64_t off_z1 = 0, off_z2 = 0, off_bnstats = 0, off_bnsums = 0, off_bnpart = 0, off_dn = 0, off_wstat = 0;
+    int cv_dw_splits = 1;      // fp32 block: pixel ranges of the kernel gradients
+    bool cv_lean = false;      // fp32 block: the kernels that need the least scratch (see ols_run_steps_static)
     int64_t off_wsplit = -1;   // fp32 block: split kernels (-1: the shape takes the fp32 matrix cores)
     const float* X = nullptr;
     const void* y = nullptr;
@@ -375,10 +377,11 @@ void plan_workspace(ols_ctx* c) {
         c->off_dz1 = take(act);
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
-        const bool split = conv3x3_split_fits(c->B, c->cv_H, c->cv_W, c->cv_C);
-        const int64_t splits = split ? conv3x3_split_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C)
-                                     : conv3x3_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
-        c->off_cpartial = take(splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4);
+        const bool split = !c->cv_lean && conv3x3_split_fits(c->B, c->cv_H, c->cv_W, c->cv_C);
+        c->cv_dw_splits = split ? conv3x3_split_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C)
+                                : conv3x3_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->cv_lean ? 1024 : 256);
+        const int64_t cpartial = c->cv_dw_splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4;
+        c->off_cpartial = take(cpartial);
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_wsplit = split ? take(3 * conv3x3_split_weight_bytes(c->m, c->cv_C)) : -1;
@@ -387,7 +390,9 @@ void plan_workspace(ols_ctx* c) {
             c->off_z2 = take(act);
             c->off_bnstats = take(2 * m * 2 * c->cv_C * 4);
             c->off_bnsums = take(m * 2 * c->cv_C * 4);
-            c->off_bnpart = take(bn_partial_floats(c->m, c->B * c->cv_H * c->cv_W, c->cv_C) * 4);
+            // (lean: in the place of the kernel gradient's partial sums, which are read before the next normalisation's are written)
+            const int64_t bnpart = bn_partial_floats(c->m, c->B * c->cv_H * c->cv_W, c->cv_C) * 4;
+            c->off_bnpart = c->cv_lean && bnpart <= cpartial ? c->off_cpartial : take(bnpart);
             // the split convolutions leave partial statistics of their output (one convolution's at a time)
             c->off_wstat = split && c->cv_C % 64 == 0 ? take(m * conv3x3_split_stat_parts(c->B, c->cv_H, c->cv_W) * 3 * c->cv_C * 4) : -1;
         }
@@ -650,7 +655,7 @@ int conv_gradients(ols_ctx* c) {
     ConvArgs base = {};
     base.groups = m; base.B = B; base.H = H; base.W = W; base.C = C;
     base.s_w = c->ld; base.s_bias = c->ld;
-    base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
+    base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial); base.dw_splits = c->cv_dw_splits;
     // shapes whose convolutions run on the bf16 matrix cores: the kernels of this step, split into three bf16 terms
     const bool split = c->off_wsplit >= 0;
     const int64_t wbytes = split ? conv3x3_split_weight_bytes(m, C) : 0;
@@ -1232,6 +1237,7 @@ int attach_convblock(ols_ctx* c, int channels, int height, int width, int classe
     c->cv_classes = classes;
     c->cv_bn = bn;
     c->cv_eps = eps;
+    c->cv_lean = false;
     c->ws = nullptr;
     c->batch_set = false;
     plan_workspace(c);
@@ -1545,6 +1551,16 @@ int ols_run_steps_static(ols_handle c, int64_t steps, const float* X, const void
         return fail(OLS_EINVAL, "the bf16 model keeps its bf16 weights in the workspace, which must then outlive the call: "
                                 "bind a caller-owned workspace and use ols_run_steps");
     if (c->timing) return fail(OLS_ESTATE, "per-kernel timing creates events; switch OLS_OPT_KERNEL_TIMING off first");
+    if (c->ws_need > kStaticWorkspaceBytes && c->model == MODEL_CONV && !c->cv_lean) {
+        // the split kernels' images and their many partial sums are what may not fit (1 worker x 16 x 32 x 32 x 128: 71 MiB
+        // against 41 MiB): the fp32 matrix cores and fewer ranges then, for the rest of this model's life
+        c->cv_lean = true;
+        plan_workspace(c);
+        if (c->ws_need > kStaticWorkspaceBytes) {
+            c->cv_lean = false;
+            plan_workspace(c);
+        }
+    }
     if (c->ws_need > kStaticWorkspaceBytes)
         return fail(OLS_ENOMEM, "the attached model needs %lld bytes of workspace, the static workspace holds %lld",
                     (long long)c->ws_need, (long long)kStaticWorkspaceBytes);

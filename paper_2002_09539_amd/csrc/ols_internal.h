@@ -198,7 +198,8 @@ struct ConvArgs {
     const float* bias;      // fwd: [C] per group, or nullptr for a convolution without bias
     const float* residual;  // fwd: added before the activation (same shape as out), or nullptr
     const float* mask;      // dx: activations whose sign gates the result (same shape as out), or nullptr
-    float* partial;         // dw: scratch of conv3x3_dw_splits(...) * groups * (9 C C + C) floats
+    float* partial;         // dw: scratch of dw_splits * groups * (9 C C + C) floats
+    int dw_splits;          // dw: pixel ranges the contraction is split into
     float* g;               // dw: gradients [groups][ld]; kernel gradient at g_w_off, bias gradient at g_b_off of a row
                             // (g_b_off < 0: no bias, nothing written for it)
     int64_t ld, g_w_off, g_b_off;
@@ -215,7 +216,7 @@ struct ConvArgs {
 hipError_t launch_conv3x3_fwd(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_dx(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_dw(const ConvArgs& a, hipStream_t s);   // weight + bias gradient (two launches)
-int conv3x3_dw_splits(int groups, int B, int H, int W, int C);   // pixel ranges the weight-gradient contraction is split into
+int conv3x3_dw_splits(int groups, int B, int H, int W, int C, int least = 256);   // pixel ranges (of `least` at least) the weight-gradient contraction is split into
 // The same products on the bf16 matrix cores with every fp32 operand split exactly into three bf16 terms (fp32 accuracy);
 // the kernels are split once per step: forward images of both, delta image of the second (dst: weight_bytes(groups) each).
 bool conv3x3_split_fits(int B, int H, int W, int C);
