@@ -27,6 +27,10 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
+# fp32 products as six bf16 ones (every operand split exactly into three bf16 terms): the 3 x 3 convolutions and the
+# forward GEMMs of the fp32 workloads here
+SPLIT_PEAK_TFLOPS = MFMA_PEAK_TFLOPS["bf16"] / 6.0
+SPLIT_KERNELS = ("conv_fwd", "conv_dx", "conv_dw", "gemm_fwd")
 
 
 def parse():
@@ -360,7 +364,8 @@ def measure(idx, args, K, W, cpu_seconds, side):
                     entry.update(bound="hbm", achieved=rate / 1e9, peak=HBM_PEAK_GBS, unit="GB/s",
                                  frac=rate / 1e9 / HBM_PEAK_GBS, per_launch=amount)
                 else:
-                    peak = MFMA_PEAK_TFLOPS[cfg.gemm_dtype if cfg.kind in ("mlp", "conv") else "f32"]
+                    dtype = cfg.gemm_dtype if cfg.kind in ("mlp", "conv") else "f32"
+                    peak = SPLIT_PEAK_TFLOPS if dtype == "f32" and name in SPLIT_KERNELS else MFMA_PEAK_TFLOPS[dtype]
                     entry.update(bound="mfma", achieved=rate / 1e12, peak=peak, unit="TFLOP/s",
                                  frac=rate / 1e12 / peak, per_launch=amount)
                     if name + "_bytes" in work:   # fraction of min(matrix-core peak, arithmetic intensity x HBM peak)
