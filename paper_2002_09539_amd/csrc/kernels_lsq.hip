@@ -104,11 +104,13 @@ __device__ float lsq_column_mean(const float* x, int64_t ld, int j, int m, int G
     return anchor_mean_elem(part[0], (float)m);
 }
 
-// Behind the round's last step: publishes this workgroup's replica (its stores precede the barrier here), and the
-// workgroup that finds itself last averages all of them.  One release (the write-back of the XCD's L2) per workgroup; the
-// exchange has taken effect when it returns, so of two workgroups at least the later one reads both flags.
+// Behind the round's last step: publishes this workgroup's replica, and the workgroup that finds itself last averages all
+// of them.  A workgroup barrier does not wait for vector stores, so every wavefront first waits until its own have reached
+// the XCD's L2; one release (the write-back of that L2) per workgroup follows.  The exchange has taken effect when it
+// returns, so of two workgroups at least the later one reads both flags.
 __device__ void lsq_round_mean(const LsqRound& p, int i, int t) {
     const FusedUpdate& u = p.u;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (t == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
