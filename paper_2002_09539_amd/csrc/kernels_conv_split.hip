@@ -262,8 +262,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_split_kernel(ConvSDev p) 
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4)
             *(f4*)(stage + lane32 * kStagePitch + 32 * j + 8 * g4 + 4 * half) =
-                f4{acc[j][4 * g4] + low[j][4 * g4], acc[j][4 * g4 + 1] + low[j][4 * g4 + 1], acc[j][4 * g4 + 2] + low[j][4 * g4 + 2],
-                   acc[j][4 * g4 + 3] + low[j][4 * g4 + 3]};
+                f4{split_sum(acc[j][4 * g4], low[j][4 * g4]), split_sum(acc[j][4 * g4 + 1], low[j][4 * g4 + 1]),
+                   split_sum(acc[j][4 * g4 + 2], low[j][4 * g4 + 2]), split_sum(acc[j][4 * g4 + 3], low[j][4 * g4 + 3])};
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int cq = lane % 16, r0 = lane / 16;                 // channel quad and first row of this lane: rows r0 + 4 t
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kDwThreads, 3) void conv3x3_split_dw_kernel(ConvSDw
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int ci = ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
-            if (ci < C && co < C) PART[((int64_t)(3 * kh + kw) * C + ci) * C + co] = acc[kw][r] + low[kw][r];
+            if (ci < C && co < C) PART[((int64_t)(3 * kh + kw) * C + ci) * C + co] = split_sum(acc[kw][r], low[kw][r]);
         }
     if (col_sums) {   // rows added in order (the operand tiles are no longer read)
         float* red = (float*)lds;

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(GemmSDev p) {
             for (int r = 0; r < 16; ++r) {
                 const int row = m0 + wm0 + 32 * i + 8 * (r / 4) + 4 * half + (r % 4);
                 if (row >= p.M) continue;
-                float v = acc[j][i][r] + low[j][i][r];
+                float v = split_sum(acc[j][i][r], low[j][i][r]);
                 if (!raw) v = fmaxf(v + bias, 0.0f);
                 C[(int64_t)row * ldc + col] = v;
             }

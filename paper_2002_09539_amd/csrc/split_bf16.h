@@ -5,14 +5,18 @@
 // half a unit of the term before it, so three terms hold the 24 bits of an fp32 (as long as lo stays a normal number:
 // |x| >= 2^-109; below that the missing part is under 2^-133 in absolute value).  The product of two split numbers is
 // the sum of nine products of bf16 numbers, each exact in fp32; the six of them down to 2^-18 of the result's magnitude
-// are formed (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi), the three left out (mid lo, lo mid, lo lo) sum to at most
-// 2^-26 of |a b|, below the rounding of ONE fp32 addition (2^-24).  Six v_mfma_f32_32x32x16_bf16 take 192 cycles for 16
+// are formed (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi); the three left out (mid lo, lo mid, lo lo) sum to
+// less than 2^-23.9 of |a b| at worst (a remainder is at most 2^-8 of the term before it, and lo at most 2^-17 of the operand) and
+// to 2^-27.4 in the root mean square over normal operands, where the rounding of one fp32 product is 2^-24 and 2^-25.2.  Six
+// v_mfma_f32_32x32x16_bf16 take 192 cycles for 16
 // contraction indices, eight v_mfma_f32_32x32x2_f32 take 512, and a sum over K indices is rounded 6 K / 16 times
 // instead of K times.
 //
 // Infinities and the few finite numbers that round to a bf16 infinity (|x| >= 0x1.FFp127) take a separate path that
-// truncates hi and leaves no remainder behind an infinity, so that inf * finite stays inf as it is in fp32; a NaN makes
-// hi a NaN.
+// truncates hi and leaves no remainder behind an infinity; a NaN makes hi a NaN.  The products hi hi then carry the
+// infinity or the NaN that fp32 would, but those of an infinity with the other operand's remainders are NaN (a remainder of
+// zero) or of either sign, and so are those of finite operands whose product overflows: split_sum leaves the small products
+// out where the large ones' sum is not finite.
 #pragma once
 #include "gemm_bf16_tile.h"
 
@@ -95,5 +99,8 @@ __device__ __forceinline__ void mfma_split(f16v (&acc)[J], f16v (&low)[J], const
 #pragma unroll
     for (int j = 0; j < J; ++j) low[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j].hi, b.mid, low[j], 0, 0, 0);
 }
+
+// The result of a sum of split products: the large products' sum and the small ones'.
+__device__ __forceinline__ float split_sum(float acc, float low) { return __builtin_isfinite(acc) ? acc + low : acc; }
 
 }  // namespace ols

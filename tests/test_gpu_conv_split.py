@@ -98,3 +98,69 @@ def test_an_infinity_stays_with_its_worker():
     loss, grad = CO.convblock_loss_grad(x0, dims[0], dims[3], X[1, 0], labels[1, 0])
     assert abs(losses[1] - loss) <= 1e-5 * abs(loss)
     assert max_norm_ratio(g[1], grad) <= GRAD_TOL
+
+
+def tensor_of(s, index, m, dims, batch):
+    """Activation-sized tensor [m][batch][H][W][C] number `index` of the workspace: a1, a2, delta at z2, delta at z1."""
+    C, H, W, _ = dims
+    n = m * batch * H * W * C
+    first = index * (-(-4 * n // 256) * 256)
+    return s.ws[first:first + 4 * n].cpu().numpy().view(np.float32).reshape(m, batch, H, W, C)
+
+
+def test_every_activation_that_an_infinity_reaches():
+    """Per unit of the first layer: infinite where the weight of its one tap is positive, zero where it is negative, for weights
+    that are exact in bf16, that leave positive or negative remainders and that are generic."""
+    m, dims, batch = 2, (32, 6, 6, 4), 3
+    cfg, X, labels, x0 = conv_case(m, dims, batch, 1, seed=15)
+    C = dims[0]
+    X, x0 = X.copy(), x0.copy()
+    Wa = x0[:9 * C * C].reshape(3, 3, C, C)
+    kinds = np.array([1.0, 1.0 + 2.0 ** -9 + 2.0 ** -18, 2.0 - 2.0 ** -10, 1.7, -1.0, -1.3], np.float32)
+    Wa[:, :, 5, :] = kinds[np.arange(9 * C).reshape(3, 3, C) % len(kinds)]
+    X[0, 0, 1, 2, 3, 5] = np.inf
+    with make_session(m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+        s.attach_convblock(*dims, batch)
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        s.sync()
+        a1 = tensor_of(s, 0, m, dims, batch)
+    for dy in range(3):
+        for dx in range(3):       # output (y, x) reads input (y + dy - 1, x + dx - 1)
+            want = np.where(Wa[dy, dx, 5] > 0, np.inf, 0.0)
+            assert np.array_equal(a1[0, 1, 2 - (dy - 1), 3 - (dx - 1)], want), (dy, dx)
+    reached = np.zeros(a1.shape, bool)
+    reached[0, 1, 1:4, 2:5] = True
+    assert np.isfinite(a1[~reached]).all()
+
+
+def test_deltas_and_kernel_gradients_past_the_range():
+    """A block of positive numbers whose delta at z1 overflows: each of its elements is +inf, and so is the sum of the first
+    kernel's gradient that meets no padding (the centre tap)."""
+    m, dims, batch = 1, (32, 6, 6, 2), 2
+    cfg, X, labels, x0 = conv_case(m, dims, batch, 1, seed=16)
+    C, rng = dims[0], np.random.default_rng(16)
+    near_one = lambda shape: (1.0 + 0.9 * rng.random(shape)).astype(np.float32)   # noqa: E731
+    X = np.ldexp(near_one(X.shape), -36)
+    parts = groups_of(C, dims[3])
+    x0 = np.zeros_like(x0)
+    x0[np.ravel(parts["Wa"])] = near_one(9 * C * C) / (9 * C)
+    x0[np.ravel(parts["Wb"])] = np.ldexp(near_one(9 * C * C), 96)
+    Wh = np.zeros((C, 2), np.float32)
+    Wh[:, 0] = np.ldexp(near_one(C), 48)           # class 0 wins, every label is 1: its delta is 1 / batch
+    x0[np.ravel(parts["Wh"])] = Wh.ravel()
+    labels = np.ones_like(labels)
+    with make_session(m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+        s.attach_convblock(*dims, batch)
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        g = s.gradient()[0]
+        dz2, dz1 = (tensor_of(s, k, m, dims, batch) for k in (2, 3))
+    assert np.isfinite(dz2).all() and (dz2 > 0).all()
+    assert (dz1 == np.inf).all()
+    centre = g[np.ravel(parts["Wa"])].reshape(9, C, C)[4]
+    assert (centre == np.inf).all()

@@ -78,3 +78,40 @@ def test_an_infinity_stays_one():
         loss, grad = O.mlp_loss_grad(x0, dims, X[i, 0], labels[i, 0])
         assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
         assert max_norm_ratio(g[i], grad) <= GRAD_TOL
+
+
+def first_activations(cfg, dims, batch, X, labels, x0):
+    """The first hidden layer's activations [m][batch][dims[1]] of one step: they come first in the workspace."""
+    with make_session(cfg.m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+        s.attach_mlp(dims, batch, "f32")
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        s.sync()
+        n = cfg.m * batch * dims[1]
+        return s.ws[:4 * n].cpu().numpy().view(np.float32).reshape(cfg.m, batch, dims[1])
+
+
+@pytest.mark.parametrize("m,dims,batch", [(64, (64, 1024, 10), 16), (16, (2048, 512, 10), 124)])   # one K range, and four
+def test_every_unit_that_an_infinity_reaches(m, dims, batch):
+    """Per unit: infinite where the weight is positive, zero (ReLU of the negative infinity) where it is negative, for weights
+    that are exact in bf16, that leave positive or negative remainders and that are generic; likewise finite operands whose
+    product overflows.  Every other sample is as near to 64 bits as without."""
+    cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=414)
+    X, x0 = X.copy(), x0.copy()
+    W = x0[:dims[0] * dims[1]].reshape(dims[0], dims[1])
+    kinds = np.array([1.0, 1.0 + 2.0 ** -9 + 2.0 ** -18, 2.0 - 2.0 ** -10, 1.7, -1.0, -1.3], np.float32)
+    w = kinds[np.arange(dims[1]) % len(kinds)]
+    W[5], W[7] = w, np.ldexp(w, 40)
+    X[:, 0, :, 7] = 0.0
+    X[0, 0, 3, 5] = np.inf
+    X[1, 0, 2, 7] = 3e38
+    h = first_activations(cfg, dims, batch, X, labels, x0)
+    want = np.where(w > 0, np.inf, 0.0)
+    assert np.array_equal(h[0, 3], want) and np.array_equal(h[1, 2], want)
+    bias = x0[dims[0] * dims[1]:dims[0] * dims[1] + dims[1]].astype(np.float64)
+    for i in (0, 1, m - 1):
+        rows = [r for r in range(batch) if (i, r) not in ((0, 3), (1, 2))]
+        ref = np.maximum(X[i, 0, rows].astype(np.float64) @ W.astype(np.float64) + bias, 0.0)
+        assert max_norm_ratio(h[i, rows], ref) <= GRAD_TOL
