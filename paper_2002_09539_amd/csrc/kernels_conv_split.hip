@@ -360,6 +360,22 @@ struct ConvSDwDev {
     FastDiv div_s, div_w1;
 };
 
+// one element of the kernel gradient over the image pixels of a virtual range
+__device__ float pixel_sum(const ConvSDwDev& p, int group, int lo, int hi, int tap, int ci, int co) {
+    const float* IN = p.in + (int64_t)group * p.s_in;
+    const float* DOUT = p.dout + (int64_t)group * p.s_dout;
+    const int W1 = p.W + 1, S = (p.H + 1) * W1, dy = tap / 3 - 1, dx = tap % 3 - 1;
+    float sum = 0.0f;
+    for (int v = lo; v < hi; ++v) {
+        const int n = (int)fast_div((unsigned)v, p.div_s), rem = v - n * S;
+        const int y = (int)fast_div((unsigned)rem, p.div_w1) - 1, x = rem - (y + 1) * W1 - 1;
+        if (y < 0 || x < 0 || y + dy < 0 || y + dy >= p.H || x + dx < 0 || x + dx >= p.W) continue;
+        const int64_t pix = ((int64_t)n * p.H + y) * p.W + x;
+        sum = __fmaf_rn(IN[(pix + dy * p.W + dx) * p.C + ci], DOUT[pix * p.C + co], sum);
+    }
+    return sum;
+}
+
 __global__ __launch_bounds__(kDwThreads, 3) void conv3x3_split_dw_kernel(ConvSDwDev p) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     uint8_t* ring = lds;
@@ -473,13 +489,46 @@ __global__ __launch_bounds__(kDwThreads, 3) void conv3x3_split_dw_kernel(ConvSDw
     const int64_t n_w = (int64_t)9 * C * C;
     float* PART = p.partial + ((int64_t)split * p.groups + group) * (n_w + C);
     const int co = co0 + 32 * wj + lane % 32;
+    auto element = [&](int kw, int r) { return ((int64_t)(3 * kh + kw) * C + ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4) * C + co; };
+    auto inside = [&](int r) { return ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4 < C && co < C; };
+    bool finite = true;
 #pragma unroll
     for (int kw = 0; kw < 3; ++kw)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int ci = ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
-            if (ci < C && co < C) PART[((int64_t)(3 * kh + kw) * C + ci) * C + co] = split_sum(acc[kw][r], low[kw][r]);
+            const float v = split_sum(acc[kw][r], low[kw][r]);
+            finite = finite && __builtin_isfinite(v);
+            if (inside(r)) PART[element(kw, r)] = v;
         }
+    // An infinite or NaN input element has also been multiplied by the zeros that stand for the delta where there is no pixel
+    // and past the range.  Where the range's input holds one, the sums that are not finite are formed again, over the range's
+    // pixels alone.
+    int* flags = (int*)(lds + 16384);   // (behind the column sums below)
+    auto any_wave = [&](bool mine) {
+        const bool wave_any = __any(mine);
+        __syncthreads();
+        if (lane == 0) flags[wave] = wave_any;
+        __syncthreads();
+        bool any = false;
+        for (int w = 0; w < kDwThreads / 64; ++w) any = any || flags[w] != 0;
+        return any;
+    };
+    if (__builtin_expect(any_wave(!finite), 0)) {
+        float odd = 0.0f;    // NaN once a row held an infinity or a NaN
+        for (int v = lo - p.halo + mrow; moves_in && v < hi + p.halo; v += kDwBK) {
+            load_row(v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd = __fmaf_rn(r1[e], 0.0f, __fmaf_rn(r0[e], 0.0f, odd));
+        }
+        if (any_wave(!(odd == 0.0f))) {
+#pragma unroll 1
+            for (int t = 0; t < 48; ++t) {
+                const int kw = t / 16, r = t % 16;
+                if (!inside(r) || __builtin_isfinite(PART[element(kw, r)])) continue;
+                PART[element(kw, r)] = pixel_sum(p, group, lo, hi, 3 * kh + kw, ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4, co);
+            }
+        }
+    }
     if (col_sums) {   // rows added in order (the operand tiles are no longer read)
         float* red = (float*)lds;
         if (!moves_in) {

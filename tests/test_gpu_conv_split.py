@@ -164,3 +164,33 @@ def test_deltas_and_kernel_gradients_past_the_range():
     assert (dz1 == np.inf).all()
     centre = g[np.ravel(parts["Wa"])].reshape(9, C, C)[4]
     assert (centre == np.inf).all()
+
+
+def test_a_nan_pixel_stays_out_of_the_taps_that_never_read_it():
+    """A NaN in an image's corner leaves the ReLU as 0, so the loss is finite; the first kernel's gradient is NaN in the four
+    taps that read the corner from inside the image and nowhere else (where there is no pixel the delta counts as zero, and
+    NaN times that zero must not be added)."""
+    m, dims, batch = 1, (32, 13, 11, 4), 9        # eight pixel ranges
+    cfg, X, labels, x0 = conv_case(m, dims, batch, 1, seed=17)
+    C, H, W, _ = dims
+    X = X.copy()
+    X[0, 0, 4, 0, 0, 5] = np.nan
+    with make_session(m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+        s.attach_convblock(*dims, batch)
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        g, losses = s.gradient()[0], s.losses()
+        dz1 = tensor_of(s, 3, m, dims, batch)[0].astype(np.float64)
+    assert np.isfinite(losses[0]) and np.isfinite(dz1).all()
+    got = g[np.ravel(groups_of(C, dims[3])["Wa"])].reshape(3, 3, C, C)
+    pad = np.zeros((batch, H + 2, W + 2, C))
+    pad[:, 1:-1, 1:-1] = X[0, 0]
+    for i in range(3):
+        for j in range(3):
+            want = pad[:, i:i + H, j:j + W].reshape(-1, C).T @ dz1.reshape(-1, C)
+            assert np.array_equal(np.isnan(want[5]), np.full(C, i < 2 and j < 2))
+            assert np.array_equal(np.isnan(got[i, j]), np.isnan(want)), (i, j)
+            rows = ~np.isnan(want[:, 0])
+            assert max_norm_ratio(got[i, j][rows], want[rows]) <= GRAD_TOL
