@@ -339,8 +339,8 @@ OLS_API int ols_run_steps(ols_handle h, int64_t steps, const float* X_dev, const
  * been bound and initialised beforehand, and state, data and streams remain the caller's.
  *   - The array holds ols_static_workspace_bytes() = 64 MiB, one copy per GPU, kept until the process ends;
  *     OLS_ENOMEM if ols_workspace_bytes(h) is larger -- except that an fp32 convolutional block which fits with the
- *     kernels that need the least scratch takes those from then on (ols_workspace_bytes then says so; the same
- *     results within the rounding of fp32 sums).
+ *     kernels that need the least scratch takes those (the same results within the rounding of fp32 sums) until
+ *     ols_bind_workspace is given the bytes that ols_workspace_bytes asked for before; meanwhile it asks for the less.
  *   - fp32 models only (least squares, fp32 MLP, fp32 convolutional blocks): the bf16 MLP keeps weights in its workspace (OLS_EINVAL).
  *   - OLS_ESTATE while OLS_OPT_KERNEL_TIMING is on (timing creates events).
  *   - The handle's workspace becomes the static array (it replaces one bound with ols_bind_workspace); ols_get_loss

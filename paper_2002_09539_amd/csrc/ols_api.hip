@@ -1267,6 +1267,14 @@ int ols_bind_workspace(ols_handle c, void* ws, int64_t bytes) {
     if (int rc = need(c)) return rc;
     if (c->model == MODEL_NONE) return fail(OLS_ESTATE, "no model attached");
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u)) return fail(OLS_EINVAL, "workspace must be non-null and 256-byte aligned");
+    if (c->cv_lean) {   // chosen for the static workspace: one that holds the kernels ols_run_steps prefers takes them again
+        c->cv_lean = false;
+        plan_workspace(c);
+        if (bytes < c->ws_need) {
+            c->cv_lean = true;
+            plan_workspace(c);
+        }
+    }
     if (bytes < c->ws_need) return fail(OLS_ENOMEM, "workspace has %lld bytes, %lld needed", (long long)bytes,
                                         (long long)c->ws_need);
     if (c->inited && bf16_model(c))
@@ -1553,7 +1561,7 @@ int ols_run_steps_static(ols_handle c, int64_t steps, const float* X, const void
     if (c->timing) return fail(OLS_ESTATE, "per-kernel timing creates events; switch OLS_OPT_KERNEL_TIMING off first");
     if (c->ws_need > kStaticWorkspaceBytes && c->model == MODEL_CONV && !c->cv_lean) {
         // the split kernels' images and their many partial sums are what may not fit (1 worker x 16 x 32 x 32 x 128: 71 MiB
-        // against 41 MiB): the fp32 matrix cores and fewer ranges then, for the rest of this model's life
+        // against 41 MiB): the fp32 matrix cores and fewer ranges then, until a workspace that holds the others is bound
         c->cv_lean = true;
         plan_workspace(c);
         if (c->ws_need > kStaticWorkspaceBytes) {

@@ -48,6 +48,26 @@ def test_a_block_that_does_not_fit_either_way_is_refused_and_keeps_its_plan():
     B.ols_destroy(h)
 
 
+@pytest.mark.parametrize("bn", [False, True])
+def test_a_full_workspace_brings_the_other_kernels_back(bn):
+    h = dry(m=1, d=params(128, 10, bn), mu=0.9, tau=2)
+    attach(h, 128, 32, 10 if bn else 16, bn)
+    full = B.ols_workspace_bytes(h)
+    assert full > B.ols_static_workspace_bytes()
+    B.ols_init_params(h, FAKE)
+    for _ in range(2):
+        B.ols_run_steps_static(h, 2, FAKE, FAKE, 1)
+        lean = B.ols_workspace_bytes(h)
+        assert lean < full
+        assert code_of(B.ols_bind_workspace, h, FAKE, lean - 1) == B.OLS_ENOMEM
+        B.ols_bind_workspace(h, FAKE, full - 1)          # too little for the others: still accepted
+        assert B.ols_workspace_bytes(h) == lean
+        B.ols_bind_workspace(h, FAKE, full)
+        assert B.ols_workspace_bytes(h) == full
+        B.ols_run_steps(h, 2, FAKE, FAKE, 1)
+    B.ols_destroy(h)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dims,batch,bn", [((128, 32, 32, 10), 16, False), ((64, 16, 16, 10), 128, True)])
 def test_same_trajectory_as_with_the_full_workspace(dims, batch, bn):
