@@ -1677,7 +1677,7 @@ int ols_set_option(ols_handle c, int key, int64_t value) {
             c->mean_split = (int)value;
             break;
         case OLS_OPT_TUNING:   // unstable: 256 * which + variant
-            if (value < 0 || value / 256 > 2 || value % 256 > 63) return fail(OLS_EINVAL, "tuning value out of range");
+            if (value < 0 || value / 256 > 2 || value % 256 > 31) return fail(OLS_EINVAL, "tuning value out of range");
             c->gemm_variant[value / 256] = (int)(value % 256);
             break;
         case OLS_OPT_FUSE_GEMM_UPDATE:

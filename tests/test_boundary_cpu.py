@@ -93,6 +93,16 @@ def test_call_order_is_enforced():
     B.ols_destroy(h)
 
 
+def test_tuning_variants_have_a_range():
+    h = B.ols_create(4, 100, 2, 0.6, 0.1, 0.9)
+    for which in (B.TUNE_FWD, B.TUNE_DW, B.TUNE_DA):
+        B.ols_set_option(h, B.OLS_OPT_TUNING, which + 31)
+        assert code_of(B.ols_set_option, h, B.OLS_OPT_TUNING, which + 32) == B.OLS_EINVAL
+        assert code_of(B.ols_set_option, h, B.OLS_OPT_TUNING, which + 63) == B.OLS_EINVAL
+    assert code_of(B.ols_set_option, h, B.OLS_OPT_TUNING, -1) == B.OLS_EINVAL
+    B.ols_destroy(h)
+
+
 def kinds(trace):
     return [B.ols_kernel_name(t["kind"]) for t in trace]
 
