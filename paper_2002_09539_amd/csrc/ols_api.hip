@@ -1480,39 +1480,44 @@ int ols_anchor_update_async(ols_handle c) {
 }
 
 namespace {
-// Whether the library-driven loop may run several local steps of a small least-squares problem in one launch: the
-// gradient kernel applies step and pull-back, the refresh is in line and its result is the plain average, nothing of an
-// earlier overlapped refresh is pending, and nobody counts or times the single launches.
-bool lsq_rounds_fit(const ols_ctx* c, const float* X, int64_t x_batch) {
-    return c->model == MODEL_LSQ && lsq_step_fits(c->B, c->d) && c->fuse_gemm_update && !c->fuse_mean && !c->mix_w && !c->snap &&
-           c->beta_z == 0.0f && c->anchor_delay_us == 0 && !c->dry && !c->trace && !c->timing && c->bound && c->inited && c->ws &&
-           (serialized(c) || c->stream[0] == c->stream[1]) && !c->anchor_inflight && !c->first_after_anchor && !c->pending_update &&
-           !(reinterpret_cast<uintptr_t>(X) & 15u) && x_batch % 4 == 0;   // what ols_set_batch asks of every batch
+struct LsqRoundPlan {
+    int64_t steps = 0;                        // 0: a launch per step
+    bool boundary = false, with_mean = false;
+};
+// How many of the next `most` local steps, at most to the end of the round, the library-driven loop runs in one launch of a
+// small least-squares problem: the gradient kernel applies step and pull-back, the refresh is in line and its result is the
+// plain average, nothing of an earlier overlapped refresh is pending, and nobody counts or times the single launches.
+void lsq_round_plan(const ols_ctx* c, int64_t most, const float* X, int64_t x_batch, LsqRoundPlan* p) {
+    constexpr int64_t kMostSteps = 64;   // bounds the launch's duration
+    if (!(c->model == MODEL_LSQ && lsq_step_fits(c->B, c->d) && c->fuse_gemm_update && !c->fuse_mean && !c->mix_w && !c->snap &&
+          c->beta_z == 0.0f && c->anchor_delay_us == 0 && !c->dry && !c->trace && !c->timing && c->bound && c->inited && c->ws &&
+          (serialized(c) || c->stream[0] == c->stream[1]) && !c->anchor_inflight && !c->first_after_anchor && !c->pending_update &&
+          !(reinterpret_cast<uintptr_t>(X) & 15u) && x_batch % 4 == 0))   // what ols_set_batch asks of every batch
+        return;
+    const int64_t to_sync = c->tau - c->k % c->tau, n = std::min(std::min(most, to_sync), kMostSteps);
+    p->boundary = n == to_sync;
+    p->with_mean = p->boundary && lsq_round_with_mean(c->m, c->d, c->ld);
+    if (lsq_round_pays(c->B, c->d, n, p->with_mean)) p->steps = n;
 }
 
-// Up to `most` local steps, at most to the end of the round; *done is how many.
-int lsq_round(ols_ctx* c, int64_t most, const float* X, const void* y, int nb, int64_t* done) {
-    constexpr int64_t kMostSteps = 64;   // bounds the launch's duration
-    const int64_t x_batch = (int64_t)c->B * c->d, to_sync = c->tau - c->k % c->tau;
-    const int64_t n = std::min(std::min(most, to_sync), kMostSteps);
-    const bool boundary = n == to_sync;
+int lsq_round(ols_ctx* c, const LsqRoundPlan& plan, const float* X, const void* y, int nb) {
+    const int64_t x_batch = (int64_t)c->B * c->d, n = plan.steps;
     const int64_t b_last = (c->k + n - 1) % nb;
     int rc = ols_set_batch(c, X + b_last * x_batch, (int64_t)nb * x_batch, (const float*)y + b_last * c->B, (int64_t)nb * c->B);
     if (rc) return rc;
-    const FusedUpdate u = fused_update(c, c->cur, c->cur, boundary);
+    const FusedUpdate u = fused_update(c, c->cur, c->cur, plan.boundary);
     LsqRoundArgs la = {};
     la.A = X; la.a_stride = (int64_t)nb * x_batch; la.y = (const float*)y; la.y_stride = (int64_t)nb * c->B;
     la.nb = nb; la.first_batch = (int)(c->k % nb); la.steps = (int)n;
     la.loss_parts = (float*)(c->ws + c->off_loss);
     la.m = c->m; la.B = c->B; la.d = c->d;
-    la.with_mean = boundary && lsq_round_with_mean(c->m, c->ld);
+    la.with_mean = plan.with_mean;
     la.mean_split = c->mean_split;
     la.flags = (unsigned long long*)(c->ws + c->off_flags);
     la.z = c->z;
     if ((rc = enqueue(c, OLS_K_LSQ_STEP, 0, c->cur, c->cur, [&](hipStream_t s) { return launch_lsq_round(la, u, s); }))) return rc;
     c->k += n;
-    *done = n;
-    if (!boundary || la.with_mean) return OLS_OK;
+    if (!plan.boundary || plan.with_mean) return OLS_OK;
     c->pull_due = c->pulled_in_step = true;
     if ((rc = ols_sync_pull(c))) return rc;
     return ols_anchor_update_async(c);
@@ -1528,10 +1533,11 @@ int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, in
     const int64_t x_batch = (int64_t)c->B * row, y_batch = c->B;   // elements per batch
     const size_t y_elem = 4;                                          // int32 labels and fp32 targets alike
     for (int64_t it = 0; it < steps; ++it) {
-        if (lsq_rounds_fit(c, X, x_batch)) {
-            int64_t done = 0;
-            if (int rc = lsq_round(c, steps - it, X, y, nb, &done)) return rc;
-            it += done - 1;
+        LsqRoundPlan plan;
+        lsq_round_plan(c, steps - it, X, x_batch, &plan);
+        if (plan.steps) {
+            if (int rc = lsq_round(c, plan, X, y, nb)) return rc;
+            it += plan.steps - 1;
             continue;
         }
         const int64_t b = c->k % nb;

@@ -113,7 +113,9 @@ __device__ __forceinline__ void fused_update_apply(const FusedUpdate& u, int64_t
 // least squares, small problems: residual, loss, gradient and the local step of one or several steps in one launch, with
 // the pull-back (u.pull) and the anchor average (with_mean) behind the last of them
 bool lsq_step_fits(int B, int64_t d);
-bool lsq_round_with_mean(int m, int64_t ld);   // whether with_mean takes m replicas of ld parameters
+// whether the next `steps` steps are faster in one launch (which averages the replicas as well) than in one each
+bool lsq_round_pays(int B, int64_t d, int64_t steps, bool with_mean);
+bool lsq_round_with_mean(int m, int64_t d, int64_t ld);   // whether with_mean takes m replicas of d parameters, ld apart
 struct LsqRoundArgs {
     const float* A;          // batch 0 of worker 0: [nb][B][d] per worker
     const float* y;

@@ -32,6 +32,18 @@ def state_of(s):
     (1, 64, 8, 2, 0.9, (4,)),
     (40, 64, 4, 2, 0.9, (4,)),         # many replicas of few parameters: the average split sixteen ways
     (2, 128, 8, 70, 0.9, (141,)),      # a round longer than a launch takes
+    (32, 64, 33, 2, 0.9, (5, 3)),      # the most replicas that the last workgroup averages; a second pass over one sample
+    (33, 64, 4, 2, 0.9, (4,)),         # one more: the mean kernel
+    (3, 201, 12, 3, 0.9, (5, 4)),      # ragged rows of few columns: rounds by the wide kernel
+    (2, 1001, 40, 1, 0.0, (3,)),
+    (5, 1028, 32, 2, 0.9, (3, 4)),     # just half of the wide kernel's passes; pieces of one step take the step kernel
+    (5, 1028, 31, 2, 0.9, (4, 3)),     # ... and just less: rounds of two with their average
+    (20, 1028, 31, 2, 0.9, (4,)),      # ... too many replicas for it: a launch per step
+    (20, 1028, 12, 3, 0.9, (6,)),      # rounds of three
+    (4, 1540, 12, 4, 0.9, (4,)),       # wider than those: a launch per step
+    (4, 2048, 32, 2, 0.9, (4,)),       # the most columns of an in-launch average
+    (2, 2052, 32, 2, 0.9, (4,)),
+    (3, 1600, 32, 1, 0.9, (3,)),       # a single step filled well enough for the wide kernel
 ])
 def test_rounds_in_one_launch_leave_the_bits_of_single_steps(m, d, batch, tau, mu, pieces):
     cfg = I.get(1).scaled(m=m, d_flat=d, batch=batch, tau=tau, mu=mu, nb=5)

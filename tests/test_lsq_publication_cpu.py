@@ -20,7 +20,7 @@ def test_every_wavefront_completes_its_stores_before_the_replica_is_published(tm
                    check=True, capture_output=True)
     text = open(out).read()
     kernels = re.findall(r"^(\w*lsq_round\w*kernel\w*):.*?^\s*s_endpgm.*?^\.Lfunc_end", text, re.M | re.S)
-    assert len(kernels) == 3, kernels
+    assert len(kernels) == 5, kernels
     for name in kernels:
         lines = text[text.index("\n%s:" % name):].split(".Lfunc_end", 1)[0].splitlines()
         write_back = next(i for i, l in enumerate(lines) if "buffer_wbl2" in l)
