@@ -1043,13 +1043,27 @@ extern "C" __attribute__((visibility("default"))) int ols_debug_conv_phases(unsi
 hipError_t launch_conv3x3_bf16_fwd(const ConvBArgs& a, hipStream_t s) { return conv_launch<0>(a, s); }
 hipError_t launch_conv3x3_bf16_dx(const ConvBArgs& a, hipStream_t s) { return conv_launch<1>(a, s); }
 
+// One workgroup per compute unit (registers and LDS allow one), so as many ranges as fit one round of the 256 units: one
+// more starts a second round for a few workgroups (us per launch, rounded up before: 3 x 64 samples x 36 x 38 x 128, 22 ranges
+// 138, 21 83; 9 x 30 x 20 x 20 x 128 72 and 50; 7 x 77 x 2 x 2 x 256 42 and 33).  Past 128 blocks a second round can pay:
+// rounds x (slices of a range + what start and end of a workgroup cost, eight slices) + the parts to add up (17 x 14 x 20 x
+// 10 x 256, 272 blocks: one range 126, two 115, three 121).
 int conv3x3_bf16_dw_splits(int groups, int B, int H, int W, int C) {
     const int64_t Pp = (int64_t)B * (H + 2) * (W + 2);
     const int64_t tiles = (int64_t)groups * (C / kCB) * (C / kCB);
-    int64_t s = (256 + tiles - 1) / tiles;                  // one workgroup per compute unit (registers and LDS allow one)
     const int64_t most = (Pp + 511) / 512;                  // a range covers at least 512 padded pixels
-    if (s > most) s = most;
-    return s < 1 ? 1 : (int)s;
+    int64_t best = 1, best_cost = -1;
+    for (int64_t s : {256 / tiles, 512 / tiles, (512 + tiles - 1) / tiles}) {
+        if (s > most) s = most;
+        if (s < 1) s = 1;
+        const int64_t slices = (Pp + s * kDwBK - 1) / (s * kDwBK), rounds = (tiles * s + 255) / 256;
+        const int64_t cost = 40 * rounds * (slices + 8) + tiles * s;
+        if (best_cost < 0 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return (int)best;
 }
 
 hipError_t launch_conv3x3_bf16_dw(const ConvBArgs& a, hipStream_t s) {

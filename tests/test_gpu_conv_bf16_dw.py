@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (1, (64, 2, 128, 3), 5),       # 2600 pixels at the longest halo: the ring is nearly full
     (1, (64, 5, 61, 3), 6),        # 2646 pixels on six ranges of 480: the last is 246
     (1, (128, 10, 12, 3), 7),      # 2 x 2 blocks, 1176 pixels on three ranges
+    (5, (192, 6, 15, 3), 20),      # 45 blocks: five ranges fill one round of the compute units, a sixth would start a second
     (1, (64, 1, 1, 3), 171),       # 1539 pixels of which 171 are image: four ranges of 480, the last of 99
 ])
 def test_kernel_and_bias_gradients(m, dims, batch):
