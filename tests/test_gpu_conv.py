@@ -40,6 +40,7 @@ def groups_of(C, classes):
     (2, (48, 7, 9, 10), 4),       # 48 channels: 16-wide slices, column tile with a tail
     (2, (80, 6, 6, 7), 3),        # more than 64 channels: two column tiles, 2 x 2 blocks of the kernel gradient
     (2, (64, 32, 32, 10), 6),     # the benchmark's per-image shape (64 channels, 32 x 32), several pixel ranges
+    (14, (80, 5, 10, 4), 12),     # 168 blocks over two ranges of the kernel gradient: two workgroups on some units, one on others
     (1, (16, 1, 1, 3), 2),        # a single position: every tap but the centre falls outside
     (2, (16, 40, 3, 5), 2),       # narrow images: rows shorter than a K slice of the weight-gradient contraction
 ])
