@@ -360,6 +360,15 @@ struct ConvSDwDev {
     FastDiv div_s, div_w1;
 };
 
+// image pixels with a virtual index below v (clamped to the tensor)
+__device__ int image_pixels_before(const ConvSDwDev& p, int v) {
+    if (v <= 0) return 0;
+    if (v >= p.V) return p.B * p.H * p.W;
+    const int W1 = p.W + 1, S = (p.H + 1) * W1;
+    const int n = (int)fast_div((unsigned)v, p.div_s), rem = v - n * S;
+    const int y = (int)fast_div((unsigned)rem, p.div_w1) - 1, x = rem - (y + 1) * W1 - 1;
+    return (n * p.H + max(y, 0)) * p.W + (y < 0 ? 0 : max(x, 0));
+}
 // one element of the kernel gradient over the image pixels of a virtual range
 __device__ float pixel_sum(const ConvSDwDev& p, int group, int lo, int hi, int tap, int ci, int co) {
     const float* IN = p.in + (int64_t)group * p.s_in;
@@ -491,36 +500,25 @@ __global__ __launch_bounds__(kDwThreads, 3) void conv3x3_split_dw_kernel(ConvSDw
     const int co = co0 + 32 * wj + lane % 32;
     auto element = [&](int kw, int r) { return ((int64_t)(3 * kh + kw) * C + ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4) * C + co; };
     auto inside = [&](int r) { return ci0 + 32 * wi + 8 * (r / 4) + 4 * (lane / 32) + r % 4 < C && co < C; };
-    bool finite = true;
+    float odd = 0.0f;    // NaN once a sum is infinite or NaN
 #pragma unroll
     for (int kw = 0; kw < 3; ++kw)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const float v = split_sum(acc[kw][r], low[kw][r]);
-            finite = finite && __builtin_isfinite(v);
+            odd = __fmaf_rn(v, 0.0f, odd);
             if (inside(r)) PART[element(kw, r)] = v;
         }
     // An infinite or NaN input element has also been multiplied by the zeros that stand for the delta where there is no pixel
-    // and past the range.  Where the range's input holds one, the sums that are not finite are formed again, over the range's
-    // pixels alone.
-    int* flags = (int*)(lds + 16384);   // (behind the column sums below)
-    auto any_wave = [&](bool mine) {
-        const bool wave_any = __any(mine);
-        __syncthreads();
-        if (lane == 0) flags[wave] = wave_any;
-        __syncthreads();
-        bool any = false;
-        for (int w = 0; w < kDwThreads / 64; ++w) any = any || flags[w] != 0;
-        return any;
-    };
-    if (__builtin_expect(any_wave(!finite), 0)) {
-        float odd = 0.0f;    // NaN once a row held an infinity or a NaN
-        for (int v = lo - p.halo + mrow; moves_in && v < hi + p.halo; v += kDwBK) {
-            load_row(v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) odd = __fmaf_rn(r1[e], 0.0f, __fmaf_rn(r0[e], 0.0f, odd));
-        }
-        if (any_wave(!(odd == 0.0f))) {
+    // and past the range.  Where the wavefront's 32 input channels hold one in the range, its sums that are not finite are
+    // formed again, over the range's pixels alone.
+    if (__builtin_expect(__any(!(odd == 0.0f)), 0)) {
+        const float* IN = p.in + (int64_t)group * p.s_in + ci0 + 32 * wi;
+        const int64_t first = image_pixels_before(p, lo - p.halo), end = image_pixels_before(p, hi + p.halo);
+        odd = 0.0f;
+        for (int64_t q = first + lane / 32; q < end; q += 2)
+            if (ci0 + 32 * wi + lane % 32 < C) odd = __fmaf_rn(IN[q * C + lane % 32], 0.0f, odd);
+        if (__any(!(odd == 0.0f))) {
 #pragma unroll 1
             for (int t = 0; t < 48; ++t) {
                 const int kw = t / 16, r = t % 16;
@@ -627,7 +625,7 @@ hipError_t launch_conv3x3_split_weights(const float* wa, const float* wb, uint8_
 int conv3x3_split_dw_splits(int groups, int B, int H, int W, int C) {
     const int64_t V = (int64_t)B * (H + 1) * (W + 1);
     const int64_t blocks = (C + 63) / 64, tiles = groups * blocks * blocks;
-    int64_t s = (256 + tiles - 1) / tiles;             // one workgroup per compute unit (135 KB of LDS each)
+    int64_t s = 256 / tiles;                           // one workgroup per compute unit (135 KB of LDS each), in one round
     const int64_t most = (V + 4 * kDwBK - 1) / (4 * kDwBK);   // at least four slices (sixteen: 59.5 against 24.9 us on 1 x 2 x 32 x 32 x 64)
     if (s > most) s = most;
     return s < 1 ? 1 : (int)s;
