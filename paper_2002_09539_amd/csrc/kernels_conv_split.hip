@@ -22,9 +22,14 @@
 // and every tap's fragments requested after its barrier 900 us, three slices and the next fragments requested across the
 // barrier 710 us.  The forward epilogue leaves per-tile statistics for a batch normalisation that follows (two passes over
 // the 128 rows that the lanes still hold): the normalisation's forward calls 305 -> 195 us, the convolution + 10 us.
-// The rule (conv3x3_split_fits): channels in whole 32-channel chunks, and strips of at most 320 rows -- images up to 61
-// pixels wide unless they are tiny (1 x 1 .. 2 x 1) -- so that two workgroups share a compute unit's LDS (up to 256 rows) or one has it alone;
-// everything else keeps the fp32 kernels.
+// The rule (conv3x3_split_fits): channels in whole 32-channel chunks, strips of at most 320 rows, so that two workgroups share
+// a compute unit's LDS (up to 256 rows) or one has it alone, and a halo that the kernel gradient's ring holds.  Images up to
+// 61 pixels wide fit unless they are low and wide (1 x 20, 2 x 50) or tiny (1 x 1 .. 2 x 1); everything else keeps the fp32
+// kernels.  Output channels are padded to 64: with 32 half of a tile's products are wasted, with 96 a quarter, and the fp32
+// kernels waste as many.  Against them, us per two rounds of two steps: 16 workers x 32 samples x 32 x 32 x 32 channels 5348
+// and 2492, 4 x 8 x 20 x 20 x 32 899 and 425, 1 x 2 x 3 x 3 x 32 387 and 291; 16 x 16 x 16 x 16 x 96 3337 and 1768, 1 x 8 x 8 x 8 x
+// 96 1082 and 572, 16 x 4 x 6 x 6 x 96 normalised 1147 and 850; 1 x 4 x 4 x 4 x 256 1612 and 913; of 240 random shapes of up to
+// 60 x 60 pixels none of this route was slower.
 #include <algorithm>
 
 #include "fast_div.h"

@@ -304,7 +304,10 @@ bool gemm_split_fits(int64_t a_elems, int64_t b_elems) {   // byte offsets of a 
 // 1024 x 1024) 29 us with it, 28 over four ranges here; 4 x (112 x 120 .. 280 x 1084 .. 120) 13 against 17 us.  With 256 to
 // 511 tiles, the fp32 kernel's 64 x 64 tiles against this kernel: 32 x (128 x 512 x 1024) 49 and 47 us, 24 x (192 x 512 x
 // 2048) 116 and 107, 40 x (64 x 1024 x 1536) 99 and 95, 16 x (128 x 1024 x 3072) 135 and 135; two K ranges would take 48,
-// 105, 92 and 121 us but 64 MB and more of scratch, where these shapes need none.
+// 105, 92 and 121 us but 64 MB and more of scratch, where these shapes need none.  Contractions are rounded up to groups of
+// four slices (128 indices); short ones gain all the same (us per two rounds of two steps, fp32 kernels and these: 64 x (64 x
+// 1028 x 36) 367 and 289, 64 x (128 x 2048 x 36) 831 and 632, 64 x (16 x 1024 x 64) 244 and 208, 64 x (64 x 1024 x 132) 399
+// and 352).
 bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits) {
     if (N < 128 || !gemm_split_fits((int64_t)M * K, (int64_t)K * N)) return false;
     const int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 127) / 128);

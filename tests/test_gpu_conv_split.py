@@ -18,6 +18,9 @@ SHAPES = [
     (3, (64, 2, 2, 3), 40, 12),      # the smallest images: 32 of them in a tile
     (2, (64, 3, 60, 4), 1, 11),      # the widest strips
     (1, (64, 3, 62, 4), 1, 11),      # one column too wide: the fp32 matrix cores
+    (1, (32, 1, 30, 3), 3, 11),      # too low for its width: the fp32 matrix cores
+    (1, (32, 2, 50, 3), 2, 11),
+    (2, (32, 3, 30, 3), 2, 11),      # one row more: a strip of 259 rows
     (1, (64, 1, 1, 3), 4, 11),       # single positions: the fp32 matrix cores
     (1, (32, 31, 33, 4), 9, 11),     # 9207 pixels: thirteen ranges of the kernel gradient, ring wraps, ragged last slice
     (1, (160, 6, 5, 3), 2, 11),      # five chunks, three channel blocks
