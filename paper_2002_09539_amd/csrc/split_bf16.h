@@ -3,14 +3,15 @@
 // Every fp32 operand is split EXACTLY into three bf16 terms, x = hi + mid + lo: hi = bf16(x), mid = bf16(x - hi),
 // lo = bf16(x - hi - mid).  A bf16 carries 8 significant bits and each rounding to nearest leaves a remainder of at most
 // half a unit of the term before it, so three terms hold the 24 bits of an fp32 (as long as lo stays a normal number:
-// |x| >= 2^-109; below that the missing part is under 2^-133 in absolute value).  The product of two split numbers is
-// the sum of nine products of bf16 numbers, each exact in fp32; the six of them down to 2^-18 of the result's magnitude
-// are formed (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi); the three left out (mid lo, lo mid, lo lo) sum to
-// less than 2^-23.9 of |a b| at worst (a remainder is at most 2^-8 of the term before it, and lo at most 2^-17 of the operand) and
-// to 2^-27.4 in the root mean square over normal operands, where the rounding of one fp32 product is 2^-24 and 2^-25.2.  Six
-// v_mfma_f32_32x32x16_bf16 take 192 cycles for 16
-// contraction indices, eight v_mfma_f32_32x32x2_f32 take 512, and a sum over K indices is rounded 6 K / 16 times
-// instead of K times.
+// |x| >= 2^-109; below that the missing part is under 2^-133 in absolute value: a forward GEMM whose whole batch is of order
+// 2^-108 / 2^-112 / 2^-116 / 2^-120, with weights that bring its results back to one, is 5e-8 / 1.4e-7 / 2e-6 / 3e-5 from 64
+// bits where the fp32 matrix cores are 1.4e-7).  The product of two split numbers is
+// the sum of nine products of bf16 numbers, each exact in fp32; the six largest are formed (hi hi, hi mid, mid hi, mid mid,
+// hi lo, lo hi).  The three left out (mid lo, lo mid, lo lo) sum to less than 2^-23.9 of |a b| at worst (a remainder is at
+// most 2^-8 of the term before it, and lo at most 2^-17 of the operand) and to 2^-27.4 in the root mean square over normal
+// operands, where the rounding of one fp32 product is 2^-24 and 2^-25.2.  Six v_mfma_f32_32x32x16_bf16
+// take 192 cycles for 16 contraction indices, eight v_mfma_f32_32x32x2_f32 take 512, and a sum over K indices is rounded
+// 6 K / 16 times instead of K times.
 //
 // Infinities and the few finite numbers that round to a bf16 infinity (|x| >= 0x1.FFp127) take a separate path that
 // truncates hi and leaves no remainder behind an infinity; a NaN makes hi a NaN.  The products hi hi then carry the
