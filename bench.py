@@ -163,13 +163,14 @@ def algorithmic_work(cfg, ld, fused_update=True):
             second = sums + 2.0 + (1.0 / 16 if tail else 1.0)
             work["bn_fwd"] = ("hbm", (first + second) / 2 * act)
             # Backward, second layer: the gradient under pooling and ReLU is formed from the pooled gradient and a2 (or its
-            # sign bytes), so the sums read that and z, and the gradient at z reads both again and is written (half a
-            # tensor as a bf16 operand).  First layer: the stored gradient instead of the gate.
+            # sign bytes).  The sums read that and z -- or, with the tail, only what it left per sample -- and the gradient
+            # at z reads both and is written (half a tensor as a bf16 operand).  First layer: the stored gradient instead of
+            # the gate, read for the sums and for the gradient at z.
             gate = 1.0 / 16 if tail else 1.0
             out = 0.5 if bf else 1.0
-            work["bn_bwd"] = ("hbm", ((2 * (gate + 1.0) + out) + (4.0 + out)) / 2 * act)
+            work["bn_bwd"] = ("hbm", (((1 if tail else 2) * (gate + 1.0) + out) + (4.0 + out)) / 2 * act)
             if tail:   # the pooling is a pass over the sums per 64 pixels
-                work["pool"] = ("hbm", 4.0 * m * (-(-(cfg.batch * H * W) // 64) * 2 * C + cfg.batch * C))
+                work["pool"] = ("hbm", 4.0 * m * (-(-(cfg.batch * H * W) // 64) * 3 * C + 3 * cfg.batch * C))
             work.pop("pool_bwd", None)   # no such pass in the normalised blocks
     return work
 

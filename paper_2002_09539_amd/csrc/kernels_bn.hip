@@ -15,8 +15,8 @@
 // second moment, so nothing cancels when a channel's mean is large against its spread.
 // Options that take tensor passes out of the block: the statistics can be merged from per-wavefront parts that the
 // producing convolution left (z is then read once, not twice); the second normalisation can be the block's tail (sign
-// bytes and 64-pixel partial sums of the pooling instead of the stored activation); its backward pass can form the
-// gradient under pooling and ReLU on the fly from the pooled gradient and those sign bytes; and a result that becomes a
+// bytes and sums per 64 pixels instead of the stored activation); its backward pass can form the gradient under pooling
+// and ReLU on the fly from the pooled gradient and those sign bytes, and its two sums from the tail's; and a result that becomes a
 // bf16 convolution's operand can be written as bf16 straight into that operand's padded layout.
 // Measured and not kept: four vectors per lane in the two apply kernels (150 / 190 / 225 us either way); eight channels
 // per lane with one 16-byte store of the bf16 result instead of 8-byte stores (the backward apply kernels 10 us slower
@@ -244,22 +244,28 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
 }
 
 // The block's tail in the normalisation: a = relu(gamma (z - mean) inv_std + beta + shortcut) is not stored -- its sign
-// bytes and its channel sums per 64 consecutive pixels are (two slots per part: the sample of the part's first pixel and
-// the next one; H W >= 64, so there is no third).  A workgroup owns 64 pixels: lane = (channel quad, stripe), four
-// pixels per lane in flight, stripes combined in stripe order.
-constexpr int kTailPixels = 64;
+// bytes are, and three channel sums per 64 consecutive pixels: the activation's (for the pooling), the number of positive
+// activations, and xhat = (z - mean) inv_std over those (two slots per part: the sample of the part's first pixel and the
+// next one; H W >= 64, so there is no third, and a part inside one sample leaves the second slot unwritten).  The last two
+// are what the backward pass needs of z to sum the gradient: under the pooling that gradient is the same number for every
+// positive pixel of a sample, so sum dy and sum dy xhat are sums over samples (bn_bwd_pooled_kernel), and z and the sign
+// bytes are not read again for them (16 x 128 x 32 x 32 x 64: a pass of 104 us and a launch less per backward call).
+// A workgroup owns 64 pixels: lane = (channel quad, stripe), four pixels per lane in flight, stripes combined in stripe order.
+constexpr int kTailPixels = 64, kTailSums = 3;
 __global__ __launch_bounds__(kThreads) void bn_tail_kernel(const float* __restrict__ z, int64_t s_z, const float* __restrict__ stats,
                                                            const float* __restrict__ gamma, const float* __restrict__ beta,
                                                            int64_t s_par, const float* __restrict__ shortcut, int64_t s_sc,
                                                            uint8_t* sign, int64_t s_sign, float* pool_part, int P, int C, int relu,
                                                            int per, FastDiv div_per) {
-    __shared__ f4 lds[kThreads];
+    __shared__ f4 lds[kTailSums][kThreads];
     const int c4n = C / 4, stripes = kThreads / c4n;
     const int c4 = threadIdx.x % c4n, stripe = threadIdx.x / c4n;
     const int g = blockIdx.y, w = blockIdx.x;
     const int p0 = w * kTailPixels;
     const int next_sample = ((int)fast_div((unsigned)p0, div_per) + 1) * per;   // first pixel of the second slot's sample
-    f4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+    const bool two = next_sample < min(P, p0 + kTailPixels);                    // the same for the whole workgroup
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 s0[kTailSums] = {zero, zero, zero}, s1[kTailSums] = {zero, zero, zero};
     if (stripe < stripes) {
         const f4 mean = *(const f4*)(stats + ((int64_t)g * 2) * C + 4 * c4);
         const f4 istd = *(const f4*)(stats + ((int64_t)g * 2 + 1) * C + 4 * c4);
@@ -274,32 +280,46 @@ __global__ __launch_bounds__(kThreads) void bn_tail_kernel(const float* __restri
             for (int t = 0; t < 4; ++t) {
                 const int p = p0 + q0 + t * stripes;
                 const bool in = q0 + t * stripes < kTailPixels && p < P;
-                zv[t] = in ? __builtin_nontemporal_load((const f4*)(Z + (int64_t)p * C)) : f4{0.f, 0.f, 0.f, 0.f};
-                sv[t] = in && S ? __builtin_nontemporal_load((const f4*)(S + (int64_t)p * C)) : f4{0.f, 0.f, 0.f, 0.f};
+                zv[t] = in ? __builtin_nontemporal_load((const f4*)(Z + (int64_t)p * C)) : zero;
+                sv[t] = in && S ? __builtin_nontemporal_load((const f4*)(S + (int64_t)p * C)) : zero;
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int p = p0 + q0 + t * stripes;
                 if (q0 + t * stripes >= kTailPixels || p >= P) continue;
-                f4 o;
+                f4 o, on, xh;
                 unsigned bits = 0;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    o[e] = __fmaf_rn(ga[e], (zv[t][e] - mean[e]) * istd[e], be[e]) + sv[t][e];
+                    const float xhat = (zv[t][e] - mean[e]) * istd[e];
+                    o[e] = __fmaf_rn(ga[e], xhat, be[e]) + sv[t][e];
                     if (relu) o[e] = fmaxf(o[e], 0.0f);
                     bits |= o[e] > 0.0f ? (1u << e) : 0u;
+                    on[e] = o[e] > 0.0f ? 1.0f : 0.0f;
+                    xh[e] = on[e] * xhat;   // (a product: a NaN stays one where the activation is not positive)
                 }
                 SG[(int64_t)p * c4n] = (uint8_t)bits;
-                if (p < next_sample) s0 = s0 + o; else s1 = s1 + o;
+                if (p < next_sample) { s0[0] = s0[0] + o; s0[1] = s0[1] + on; s0[2] = s0[2] + xh; }
+                else { s1[0] = s1[0] + o; s1[1] = s1[1] + on; s1[2] = s1[2] + xh; }
             }
         }
     }
-    s0 = reduce_stripes(s0, lds, c4n, stripes);
-    s1 = reduce_stripes(s1, lds, c4n, stripes);
-    if ((int)threadIdx.x < c4n) {
-        float* o = pool_part + (((int64_t)g * gridDim.x + w) * 2) * C + 4 * c4;
-        *(f4*)o = s0;
-        *(f4*)(o + C) = s1;
+    // the stripes' sums of a slot, all three at once: thread = (sum, channel quad)
+    auto finish = [&](const f4 (&v)[kTailSums], int slot) {
+#pragma unroll
+        for (int k = 0; k < kTailSums; ++k) lds[k][threadIdx.x] = v[k];
+        __syncthreads();
+        for (int u = threadIdx.x; u < kTailSums * c4n; u += kThreads) {
+            const int k = u / c4n, c = u % c4n;
+            f4 acc = lds[k][c];
+            for (int s = 1; s < stripes; ++s) acc = acc + lds[k][s * c4n + c];
+            *(f4*)(pool_part + ((((int64_t)g * gridDim.x + w) * 2 + slot) * kTailSums + k) * C + 4 * c) = acc;
+        }
+    };
+    finish(s0, 0);
+    if (two) {
+        __syncthreads();
+        finish(s1, 1);
     }
 }
 
@@ -399,6 +419,42 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_final_kernel(const float* __r
         for (int r = stripe; r < ranges; r += kFinalStripes) {
             s1 += P[(int64_t)r * 2 * C];
             s2 += P[((int64_t)r * 2 + 1) * C];
+        }
+    }
+    lds[0][threadIdx.x] = s1;
+    lds[1][threadIdx.x] = s2;
+    __syncthreads();
+    if (stripe || c >= C) return;
+    for (int k = 1; k < kFinalStripes; ++k) {
+        s1 += lds[0][k * kFinalChannels + cl];
+        s2 += lds[1][k * kFinalChannels + cl];
+    }
+    sums[((int64_t)g * 2) * C + c] = s1;
+    sums[((int64_t)g * 2 + 1) * C + c] = s2;
+    g_out[(int64_t)g * ld + beta_off + c] = s1;
+    g_out[(int64_t)g * ld + gamma_off + c] = s2;
+}
+
+// The same sums where the gradient at the normalised output is dpool[sample][c] / positions on the pixels whose activation
+// is positive: with the number of those pixels and their sum of xhat per sample (which the forward pass left, see
+// bn_tail_kernel) both are sums over the samples.  (A sample without a positive pixel takes no part, whatever its dpool; its
+// zero is formed from the sum, so that a NaN there stays.)
+__global__ __launch_bounds__(kThreads) void bn_bwd_pooled_kernel(const float* __restrict__ sample_sums, const float* __restrict__ dpool,
+                                                                 int64_t s_dp, float scale, float* sums, float* g_out, int64_t ld,
+                                                                 int64_t gamma_off, int64_t beta_off, int C, int B) {
+    __shared__ float lds[2][kThreads];
+    const int cl = threadIdx.x % kFinalChannels, stripe = threadIdx.x / kFinalChannels;
+    const int c = blockIdx.x * kFinalChannels + cl;
+    const int g = blockIdx.y;
+    float s1 = 0.0f, s2 = 0.0f;
+    if (c < C) {
+        const float* N = sample_sums + (int64_t)g * 2 * B * C + c;   // [2][B][C]: number, sum of xhat
+        const float* D = dpool + (int64_t)g * s_dp + c;
+#pragma unroll 8
+        for (int n = stripe; n < B; n += kFinalStripes) {
+            const float num = N[(int64_t)n * C], xh = N[((int64_t)B + n) * C], d = num > 0.0f ? D[(int64_t)n * C] * scale : 0.0f;
+            s1 += d * num;
+            s2 += d * xh;
         }
     }
     lds[0][threadIdx.x] = s1;
@@ -516,7 +572,6 @@ hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s) {
     if (!aligned16(a.z) || !aligned16(a.dy) || !aligned16(a.stats) || !aligned16(a.part) || !aligned16(a.sums) ||
         !aligned16(a.gamma) || a.s_z % 4 || a.s_dy % 4 || a.s_par % 4)
         return hipErrorInvalidValue;
-    const int ranges = bn_ranges(a.groups, a.P);
     PooledDelta pd = {};
     if (a.gate || a.sign) {
         if (!a.dpool || a.positions < 1 || a.P % a.positions != 0 || !aligned16(a.gate) || !aligned16(a.dpool) || a.s_gate % 4 || a.s_dp % 4)
@@ -527,13 +582,21 @@ hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s) {
         pd.div_pos = make_div((unsigned)a.positions);
     }
     const int src = a.sign ? kFromSign : a.gate ? kFromGate : kFromDy;
-    auto partial = src == kFromSign ? bn_bwd_partial_kernel<kFromSign> : src == kFromGate ? bn_bwd_partial_kernel<kFromGate> : bn_bwd_partial_kernel<kFromDy>;
     auto apply = src == kFromSign ? bn_bwd_apply_kernel<kFromSign> : src == kFromGate ? bn_bwd_apply_kernel<kFromGate> : bn_bwd_apply_kernel<kFromDy>;
-    partial<<<dim3((unsigned)ranges, (unsigned)a.groups), kThreads, 0, s>>>(a.dy, a.s_dy, a.z, a.s_z, a.stats, a.part, a.P, a.C, ranges, pd);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    bn_bwd_final_kernel<<<dim3((unsigned)((a.C + kFinalChannels - 1) / kFinalChannels), (unsigned)a.groups), kThreads, 0, s>>>(
-        a.part, a.sums, a.g, a.ld, a.g_gamma_off, a.g_beta_off, a.C, ranges);
+    const dim3 final_grid((unsigned)((a.C + kFinalChannels - 1) / kFinalChannels), (unsigned)a.groups);
+    hipError_t e;
+    if (a.sign) {   // the forward pass's tail left what the sums need of z
+        if (!a.sample_sums) return hipErrorInvalidValue;
+        bn_bwd_pooled_kernel<<<final_grid, kThreads, 0, s>>>(a.sample_sums, a.dpool, a.s_dp, pd.scale, a.sums, a.g, a.ld, a.g_gamma_off,
+                                                             a.g_beta_off, a.C, a.P / a.positions);
+    } else {
+        const int ranges = bn_ranges(a.groups, a.P);
+        auto partial = src == kFromGate ? bn_bwd_partial_kernel<kFromGate> : bn_bwd_partial_kernel<kFromDy>;
+        partial<<<dim3((unsigned)ranges, (unsigned)a.groups), kThreads, 0, s>>>(a.dy, a.s_dy, a.z, a.s_z, a.stats, a.part, a.P, a.C, ranges, pd);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        bn_bwd_final_kernel<<<final_grid, kThreads, 0, s>>>(a.part, a.sums, a.g, a.ld, a.g_gamma_off, a.g_beta_off, a.C, ranges);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     unsigned blocks;

@@ -444,7 +444,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         a.xres = c->X; a.s_x = c->xs; a.sign = sign; a.s_sign = act / 4; a.pool_part = pool_part;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
         if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-                 return launch_pool_finish(pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), pooled, (int64_t)B * C, m, B, positions, C,
+                 return launch_pool_finish(pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), pooled, (int64_t)B * C, nullptr, m, B, positions, C,
                                            1.0f / (float)(H * W), s);
              })))
             return rc;
@@ -545,7 +545,9 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     const bool tail = H * W >= 64;
     const int64_t tail_units = ((int64_t)B * H * W + 63) / 64;
     uint8_t* sign = (uint8_t*)a2;
-    float* tail_part = a2 + ((int64_t)m * (act / 4) + 3) / 4;   // behind the sign bytes of all workers
+    // (all three fit: m act / 16 floats of sign bytes, at most 3 / 16 of m act for the parts and 1 / 32 for the samples' sums)
+    float* tail_part = a2 + round_up((int64_t)m * (act / 4), 16) / 4;   // behind the sign bytes of all workers
+    float* sample_sums = tail_part + m * tail_units * 6 * C;
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
              return launch_pad_cast_bf16(c->X, c->xs, xb, padded, m, B, H, W, C, s);
@@ -574,7 +576,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
     if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-             return tail ? launch_pool_finish(tail_part, tail_units * 2 * C, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s)
+             return tail ? launch_pool_finish(tail_part, tail_units * 6 * C, pooled, (int64_t)B * C, sample_sums, m, B, H * W, C, 1.0f / (float)(H * W), s)
                          : launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
          })))
         return rc;
@@ -603,7 +605,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
         // the bf16 operand dz2
         BnArgs a = nbase;
         a.z = z2; a.dpool = dpool; a.s_dp = (int64_t)B * C; a.positions = H * W;
-        if (tail) { a.sign = sign; a.s_sign = act / 4; } else { a.gate = a2; a.s_gate = act; }
+        if (tail) { a.sign = sign; a.s_sign = act / 4; a.sample_sums = sample_sums; } else { a.gate = a2; a.s_gate = act; }
         a.out_bf16 = dz2; a.stats = stats2; a.gamma = xc + gb; a.g_gamma_off = gb; a.g_beta_off = bb;
         if ((rc = enqueue(c, OLS_K_BN_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_backward(a, s); }))) return rc;
     }
@@ -676,7 +678,9 @@ int conv_gradients(ols_ctx* c) {
     const bool tail = bn && H * W >= 64;
     const int64_t tail_units = ((int64_t)B * H * W + 63) / 64;
     uint8_t* sign = (uint8_t*)a2;
-    float* tail_part = a2 + ((int64_t)m * (act / 4) + 3) / 4;   // behind the sign bytes of all workers
+    // (all three fit: m act / 16 floats of sign bytes, at most 3 / 16 of m act for the parts and 1 / 32 for the samples' sums)
+    float* tail_part = a2 + round_up((int64_t)m * (act / 4), 16) / 4;   // behind the sign bytes of all workers
+    float* sample_sums = tail_part + m * tail_units * 6 * C;
     int rc;
     {   // first convolution
         ConvArgs a = base;
@@ -711,7 +715,7 @@ int conv_gradients(ols_ctx* c) {
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
     if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-             return tail ? launch_pool_finish(tail_part, tail_units * 2 * C, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s)
+             return tail ? launch_pool_finish(tail_part, tail_units * 6 * C, pooled, (int64_t)B * C, sample_sums, m, B, H * W, C, 1.0f / (float)(H * W), s)
                          : launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
          })))
         return rc;
@@ -744,7 +748,7 @@ int conv_gradients(ols_ctx* c) {
                // (dpool / positions where a2 > 0) is formed on the fly; scale / shift gradients; dz2 = the gradient at z2
         BnArgs a = nbase;
         a.z = z2; a.dy = dz2; a.dpool = dpool; a.s_dp = (int64_t)B * C; a.positions = H * W;
-        if (tail) { a.sign = sign; a.s_sign = act / 4; } else { a.gate = a2; a.s_gate = act; }
+        if (tail) { a.sign = sign; a.s_sign = act / 4; a.sample_sums = sample_sums; } else { a.gate = a2; a.s_gate = act; }
         a.stats = stats2; a.gamma = xc + gb; a.g_gamma_off = gb; a.g_beta_off = bb;
         if ((rc = enqueue(c, OLS_K_BN_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_backward(a, s); }))) return rc;
     }

@@ -280,8 +280,8 @@ int64_t conv3x3_bf16_pool_part_floats(int B, int H, int W, int C);   // per grou
 int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C);   // per group
 // pooled[g][sample][c] = inv * the sum over the sample's positions, from partial sums [group][w][2][C] per 64 consecutive
 // pixels (slot 0: the sample of pixel 64 w, slot 1: the next one) with `per` (>= 64) pixels per sample
-hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, int groups, int B, int per, int C,
-                              float inv, hipStream_t s);
+hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, float* more, int groups, int B, int per,
+                              int C, float inv, hipStream_t s);
 // fp32 [groups][B H W][C] -> bf16 [groups][B (H+2) (W+2)][C] with a zero border
 hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, int64_t s_dst, int groups, int B, int H, int W,
                                 int C, hipStream_t s);
@@ -329,10 +329,13 @@ struct BnArgs {
     int waves;
     // Optional (fwd, with shortcut / relu as given; H * W >= 64): the block's tail.  The activation is not stored: `sign`
     // gets one byte per pixel and four channels ([group][P][C / 4], bit e set iff the activation is positive) and
-    // `pool_part` ([group][ceil(P / 64)][2][C] floats) the activation's sums per 64 pixels for launch_pool_finish.
-    // (bwd) `sign` in place of `gate`: the same bytes say where the activation was positive.
+    // `pool_part` ([group][ceil(P / 64)][2][3][C] floats) per 64 pixels the activation's sums, the number of positive
+    // activations and their sums of xhat, for launch_pool_finish (with `more`).
+    // (bwd) `sign` in place of `gate`: the same bytes say where the activation was positive; `sample_sums`
+    // ([group][2][sample][C]: numbers and sums of xhat, launch_pool_finish's `more`) then has to be given.
     uint8_t* sign;
     float* pool_part;
+    const float* sample_sums;
     int64_t s_sign;
 };
 hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s);    // statistics (two launches) + normalise
