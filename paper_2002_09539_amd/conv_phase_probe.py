@@ -36,7 +36,7 @@ def main():
     X, labels = G.conv_data(cfg)
     x0 = G.conv_init(cfg)
     C, H, W, _ = cfg.dims
-    tiles = cfg.m * (-(-(cfg.batch * (H + 2) * (W + 2)) // 256)) * (C // 64)
+    tiles = cfg.m * (-(-(cfg.batch * (H + 2) * (W + 2)) // 512)) * (C // 64)
     with Session(cfg.m, cfg.d, cfg.tau, cfg.alpha, cfg.gamma, cfg.mu) as s:
         s.attach_convblock(*cfg.dims, cfg.batch, batch_norm=cfg.batch_norm, gemm_dtype=cfg.gemm_dtype)
         Xd, yd = s.upload(X), s.upload(labels)
@@ -47,7 +47,7 @@ def main():
         rc = lib.ols_debug_conv_phases(buf.ctypes.data_as(ctypes.POINTER(ctypes.c_ulonglong)), tiles)
         if rc != 0:
             raise SystemExit("ols_debug_conv_phases failed: %d" % rc)
-    print("%s: %d tiles of 256 padded pixels x 64 channels per launch; times in microseconds, means over the tiles of the "
+    print("%s: %d tiles of 512 padded pixels x 64 channels per launch; times in microseconds, means over the tiles of the "
           "last launch" % (cfg.name, tiles))
     for k, name in enumerate(("forward, bf16 output", "forward, other output (fused tail / fp32)", "delta")):
         t = buf[k].astype(np.float64) / 100.0

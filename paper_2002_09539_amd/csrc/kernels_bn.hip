@@ -200,6 +200,8 @@ __global__ __launch_bounds__(kThreads) void bn_stats_chunks_kernel(const float* 
 // of the unpadded pixel v / (C / 4).
 struct PaddedOut {
     uint16_t* base;          // nullptr: the fp32 output is written instead
+    uint8_t* gate;           // optional: sign bytes of what is written, [pixel][C / 4] without a border
+    int64_t s_gate;
     int64_t stride;          // per group, bf16 elements
     FastDiv div_hw, div_w;
     int H, W;
@@ -212,6 +214,11 @@ __device__ __forceinline__ void store_padded_bf16(const PaddedOut& po, int g, un
     w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{o[0], o[1]}, bf16x2));
     w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{o[2], o[3]}, bf16x2));
     *(u2*)(po.base + (int64_t)g * po.stride + q * C + 4 * c4) = w;
+    if (po.gate) {   // a bf16 is positive iff its bits are in [0x0001, 0x7FFF]
+        const unsigned bits = ((w.x & 0xFFFFu) - 1u < 0x7FFFu ? 1u : 0u) | ((w.x >> 16) - 1u < 0x7FFFu ? 2u : 0u) |
+                              ((w.y & 0xFFFFu) - 1u < 0x7FFFu ? 4u : 0u) | ((w.y >> 16) - 1u < 0x7FFFu ? 8u : 0u);
+        po.gate[(int64_t)g * po.s_gate + (int64_t)pix * (C / 4) + c4] = (uint8_t)bits;
+    }
 }
 
 // out = act(gamma (z - mean) inv_std + beta (+ shortcut))
@@ -508,7 +515,7 @@ bool padded_out(const BnArgs& a, int64_t vecs, PaddedOut* po) {
     if (a.H < 1 || a.W < 1 || a.P % (a.H * a.W) != 0 || (reinterpret_cast<uintptr_t>(a.out_bf16) & 7u) || a.s_outb % 4 ||
         vecs >= ((int64_t)1 << 31) - kThreads)
         return false;
-    po->base = a.out_bf16; po->stride = a.s_outb; po->H = a.H; po->W = a.W;
+    po->base = a.out_bf16; po->stride = a.s_outb; po->gate = a.gate_out; po->s_gate = a.s_gate_out; po->H = a.H; po->W = a.W;
     po->div_hw = make_div((unsigned)(a.H * a.W)); po->div_w = make_div((unsigned)a.W);
     return true;
 }

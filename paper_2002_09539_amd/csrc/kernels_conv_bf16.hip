@@ -12,19 +12,20 @@
 //   DX   din[q][ci] = sum_{tap, co} dout[q - s_tap][co] w[tap][ci][co]
 //   DW   dw[tap][ci][co] = sum_q in[q + s_tap][ci] dout[q][co]
 // are plain GEMMs over shifted row windows with no per-pixel case analysis: interior pixels only ever reach their own
-// image's border, and every producer writes zeros to the border positions (the forward epilogue explicitly, the masks of
+// image's border, and every producer writes zeros to the border positions (the forward epilogue explicitly, the gates of
 // the backward pass by themselves, because a zero activation gates its delta).  Rows outside [0, Pp) are read as zeros.
 //
-// FWD / DX: one workgroup per 256 padded pixels x 64 output channels.  The input rows m0 - (W + 3) .. m0 + 256 + (W + 3)
-// of a 64-channel chunk are copied to LDS ONCE (a strip, K-contiguous, pitch 64 + 8); the nine taps read their A
-// fragments from it at nine row offsets, so the operand crosses the LDS write port once instead of nine times.  The
-// 64 x 64 kernel slice of each tap is double-buffered through registers.  Four wavefronts of 64 x 64; the MFMA takes the
-// kernel fragment first, so a lane's accumulators are four consecutive channels of one pixel, packed by the hardware
-// conversion and staged through LDS for 16-byte stores; every wavefront stages and stores its own 64 rows, so the
-// epilogue has no workgroup barrier.  The second convolution's epilogue is the block's tail: it adds the shortcut,
-// applies the ReLU, keeps the activation's sign (one bit per element) for the backward pass and the wavefront's channel
-// sums for the pooling -- neither the convolution's output nor the activation is ever stored.  (Images of fewer than 64
-// padded pixels take the unfused route: conv + bias in fp32, then one streaming pass.)
+// FWD / DX: one workgroup per 512 padded pixels x 64 output channels (256 x 64 or 256 x 32 in small launches, see conv_tile).
+// The input rows m0 - (W + 3) .. m0 + 512 + (W + 3) of a 64-channel chunk are loaded straight into LDS ONCE (a strip); the nine
+// taps read their pixel fragments from it at nine row offsets.  The kernels' fragments come from a copy in fragment order that
+// is made once per step (kernel_images, in the launch that converts the batch) straight into registers, four steps of 16
+// channels ahead: no barrier between the taps.  Four wavefronts of 128 x 64; the MFMA takes the kernel fragment first, so a
+// lane's accumulators are four consecutive channels of one pixel, packed by the hardware conversion and staged through LDS for
+// 16-byte stores; every wavefront stages and stores its own rows, 64 at a time, so the epilogue has no workgroup barrier.
+// The second convolution's epilogue is the block's tail: it adds the shortcut, applies the ReLU, keeps the activation's sign
+// (one bit per element) for the backward pass and channel sums per 64 pixels for the pooling -- neither the convolution's output
+// nor the activation is ever stored.  (Images of fewer than 64 padded pixels take the unfused route: conv + bias in fp32, then
+// one streaming pass.)
 // DW: one workgroup per (pixel range, 64 x 64 block of input x output channels); each of twelve wavefronts holds the
 // three taps of a kernel row over 32 x 64 channels (96 registers per lane) for half of the contraction steps; per 96
 // pixels 96 new input rows enter a ring of LDS rows (read with the transpose load at nine row offsets) and 96 delta rows a
@@ -33,20 +34,19 @@
 // strip reaches past either end of the tensor and drops the stores of a last tile's missing rows, so the loads and stores
 // carry no per-lane predicates, selects or 64-bit address arithmetic.
 //
-// Measured at the benchmark shape (16 workers x 128 samples x 32 x 32 x 64 channels, 154.6 GFLOP per launch): forward
-// 200 us (bf16 out), 240 us with the fused tail (208 us for conv + bias in fp32 alone, which then needed a 224 us
-// streaming pass), delta 204 us, kernel gradient 160 + 9 us, against 1390 - 1430 us for the fp32 kernels on their own units.
-// Timestamps (s_memrealtime) taken inside an instrumented copy of the forward kernel showed where a tile's 11.3 us went
-// before the descriptors: 2.8 us from the first instruction to the last load issued -- some 1100 instructions of
-// predicates and addresses, issued by one wavefront per SIMD at a few cycles each -- 1.3 us for the loads to arrive,
-// 4.6 us for the nine taps (1.9 us of MFMA issue; the other workgroup of the compute unit shares the pipe) and 2.7 us of
-// epilogue.  With one workgroup per compute unit a tile takes 7.2 us, so the second one hides a third of the latencies.
-// Buffer addressing took the kernel from 2150 to 1330 instructions and the tile to 9.4 us (forward 221 -> 197 us,
-// fp32 out 245 -> 208, delta 252 -> 204 with the gate activations requested three taps before the end instead of after
-// it).
-// The fused tail's shortcut rows (fp32, 16 vectors per lane) are requested in two batches of eight, the first three
-// taps before the end and the second once the tile is staged, instead of both inside the epilogue's loop: 252 -> 241 us
-// (requesting the second batch before the staging as well: 248 us).
+// Measured at the benchmark shape (16 workers x 128 samples x 32 x 32 x 64 channels, 154.6 GFLOP per launch), us per launch within
+// a step, before (256 x 64 tiles, kernel slices through LDS with a barrier per tap, the strip through registers) and now:
+// forward with bf16 out 208 and 187 (180 without the sign bytes that it now leaves), forward with fp32 out 231 and 205, delta
+// with bf16 out 214 and 179, with fp32 out 235 and 196 (206 and 240 while it read the bf16 activations for their sign: 0.3 GB
+// instead of 34 MB), forward with the fused tail 240 and 238; 3 x 20 x 13 x 15 x 128 alone, bf16 out, 12.1 and 7.9.
+// What bounds FWD / DX: energy.  Alone on the same inputs forward (bf16 out) takes 218 us; its taps without loads and epilogue
+// 108, everything but the taps 122 (0.64 GB at 5.3 TB/s): the two add although two workgroups share a compute unit.  With all
+// operands zero the whole takes 155 and the taps 87, and three other structures end at the same time: eight wavefronts that walk
+// tiles with their half of the kernel in 144 registers and the next strip on its way (231, its taps alone 136: 64 x 32 per
+// wavefront is bound by LDS reads), the same as two workgroups of four wavefronts (224), and four wavefronts with the whole
+// kernel in 288 registers (one per SIMD, the epilogue in the open; 14 % slower than eight).
+// The shortcut rows of the fused tail (fp32, 16 vectors per lane and half) are requested in batches of eight, the first two taps
+// before the end and each further one while the batch before it is consumed (two batches ahead: no change).
 // The kernel gradient had four wavefronts of 32 x 32 channels x nine taps, two workgroups per compute unit, 64 pixels and
 // a strip of 64 + 2 (W + 3) rows per slice: 170 us + 14 for the finish pass alone, 198 + 15 in a whole step.  Now 160 + 9
 // and 185 + 9: the ring fetches a row once instead of 2.1 times, the taps of a kernel row share three transpose reads
@@ -56,21 +56,11 @@
 // descriptor and the choice of its tensor have to be in scalar registers: with a per-lane choice the compiler loops over
 // the lanes of every load (193).  Not kept: eight wavefronts with nine taps each, every fragment read a kernel row ahead
 // and across the slice's barrier (212); two workgroups of six wavefronts, 48 pixels per slice (232).
-// Tried and not kept: persistent workgroups that hold the whole kernel as 72 register fragments and walk the tiles of a
-// worker (one wavefront per SIMD, no barrier inside a tile: 280 - 400 us; with half the fragments per wavefront and two
-// workgroups per compute unit 308 - 397 us); the present forward kernel made persistent with the next tile's strip
-// requested a tile ahead (the 44 extra live registers spill: 308 - 366 us); all nine kernel slices requested at the
-// start of a tile (no change); in the kernel gradient two slices of loads in flight (400 registers, one wavefront per
-// SIMD: 349 us), fragment reads two kernel rows ahead (259 against 258 us); forward / delta tiles of 128 pixels (134 registers, 53 KB of LDS, three workgroups
-// per compute unit; the halo is then 1.55 x the tile: 260 / 291 / 271 us against 221 / 245 / 252); a raised wavefront
-// priority (s_setprio) outside or inside the tap loop (+-1 %); the bias loaded straight into the accumulators before the
-// first tap (the eight extra loads in the prologue cost what the epilogue's additions saved); a branch around the late
-// requests of bias / gate activations (the compiler then makes every later wait on a kernel slice wait for them too:
-// +0.8 us per tile); the first MFMAs of a tile with a zero third operand instead of cleared accumulators (200 instructions
-// less, no change), and all kernel arguments fetched in one scalar round trip at the top instead of five dependent ones
-// (no change either): what remains of the prologue's 2 us is the issue of its 17 vector loads per lane, about 0.1 us
-// each -- with 68 KB per workgroup in flight and 7 - 8 TB/s crossing the L2 during a launch (strips, the 73 KB of
-// kernel slices every tile fetches again, the outputs), the memory pipeline itself is what the loads queue for.
+// Tried and not kept: in the kernel gradient two slices of loads in flight (400 registers, one wavefront per SIMD: 349 us),
+// fragment reads two kernel rows ahead (259 against 258 us); in forward / delta a raised wavefront priority (s_setprio)
+// outside or inside the tap loop (+-1 %), the bias loaded straight into the accumulators before the first tap, the first
+// MFMAs of a tile with a zero third operand instead of cleared accumulators (no change).
+#include <algorithm>
 #include <type_traits>
 
 #include "fast_div.h"
@@ -99,27 +89,29 @@ namespace {
 constexpr int kThreads = kTileThreads;
 constexpr int kXcds = 8;
 constexpr int kCB = 64;     // channel block: contraction chunk and output-channel tile
-constexpr int kBM = 256;    // padded pixels per forward / delta tile
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
 constexpr int kDwBK = 96;   // padded pixels per slice of the kernel-gradient contraction
 
 struct ConvBDev {
     const uint16_t* in;      // FWD: layer input; DX: delta of the layer output; DW: layer input   [groups][Pp][C] bf16
-    const uint16_t* w;       // FWD, DX: bf16 kernels [9][C][C]
+    const uint16_t* w;       // FWD, DX: bf16 kernels in fragment order (see kernel_images)
     const uint16_t* dout;    // DW: delta of the layer output
     void* out;               // FWD, DX: [Pp][C], bf16 or fp32
     const float* bias;       // FWD
-    const uint16_t* mask;    // DX: padded bf16 activations whose sign gates the result
+    uint8_t* gate;           // sign bytes, one per row of the output and four channels: DX, they gate the result; FWD with bf16
+                             // output, it leaves its own
     float* partial;          // DW
     const float* xres;       // FWD with the fused tail: the shortcut, fp32 [B H W][C]
     uint8_t* sign;           // FWD with the fused tail: [Pp][C / 4] sign bytes
-    float* pool_part;        // FWD with the fused tail: [groups][tiles_m * 4 wavefronts][2][C] partial sums of the pooling
-    float* stat_part;        // FWD with the unpadded fp32 output, optional: [groups][tiles_m * 4 wavefronts][3][C] per-wavefront
+    float* pool_part;        // FWD with the fused tail: [groups][units][2][C] partial sums of the pooling
+    float* stat_part;        // FWD with the unpadded fp32 output, optional: [groups][units][3][C]
                              // statistics of the output's image pixels (count, mean, sum of squared deviations)
     int64_t s_x, s_sign;
-    int64_t s_in, s_w, s_dout, s_out, s_bias, s_mask;
+    int64_t s_in, s_w, s_dout, s_out, s_bias, s_gate;
     int groups, B, H, W, C, Hp, Wp, Pp, halo;
-    int relu;
     int tiles_m, tiles_n, total_tiles, chunk;
+    int units;               // FWD, DX: parts of 64 padded pixels per group (pool_part, stat_part)
+    int strip_pieces, strip_bytes;   // FWD, DX: the strip in pieces of eight rows; its (or the staging's) place in LDS
     FastDiv div_per, div_wp; // division by (H + 2) (W + 2) and by W + 2
     FastDiv div_pg, div_tn;  // FWD, DX: division by tiles_m * tiles_n and by tiles_n
     int splits, k_chunk;
@@ -140,43 +132,40 @@ __device__ __forceinline__ bool interior(const ConvBDev& p, int q, int* unpadded
     return y >= 1 && y <= p.H && x >= 1 && x <= p.W;
 }
 
+// Two sign bytes of eight bf16 channels that are not negative (a ReLU's result): bit e of byte b is set iff channel 4 b + e is
+// positive.  The magnitude's 15 bits plus 0x7FFF carry into bit 15 unless they are all zero; the eight carries then close up.
+__device__ __forceinline__ unsigned short positive_bits(u4 v) {
+    u4 c;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) c[w] = ((v[w] & 0x7FFF7FFFu) + 0x7FFF7FFFu) & 0x80008000u;
+    const unsigned u = c[0] >> 15 | c[1] >> 13 | c[2] >> 7 | c[3] >> 5;   // channels 0, 2, 4, 6 at 0, 2, 8, 10; their successors 16 above
+    return (unsigned short)((u | u >> 15) & 0x0F0Fu);
+}
+
 // ---------------------------------------------------------------------------------------------
 // forward (MODE 0) and back-propagated delta (MODE 1)
 // ---------------------------------------------------------------------------------------------
-// LDS of the forward / delta kernel, in bf16 elements: the strip and two kernel slices -- or, if larger, the fp32 output
-// staging of the four wavefronts (BM / 4 rows of 64 + 4 floats each), which takes their place after the last tap.
-constexpr int kStagePitchF32 = kCB + 4;
 // What the epilogue produces: bf16 in the padded operand layout; conv + bias in fp32, padded; the fused tail; or fp32 in
 // the UNPADDED [B H W][C] layout (image pixels only) -- the input of a batch normalisation (forward) or of its backward
 // pass (delta, gated by the sign of the bf16 activation as usual).
 enum { kOutBf16 = 0, kOutF32 = 1, kOutTail = 2, kOutF32U = 3 };
-template <int BM, int OUT>
-__host__ __device__ constexpr int conv_main_elems(int strip_rows, int slice_elems) {
-    const int work = strip_rows * (kCB + 8) + 2 * slice_elems;
-    const int stage = OUT != kOutBf16 ? BM * kStagePitchF32 * 2 : 0;
-    return work > stage ? work : stage;
-}
+constexpr int kHalfRows = 64;             // rows that a wavefront's epilogue stages and moves at a time
+constexpr int kStripRow = 2 * kCB;        // bytes of a strip row (one pixel's 64 channels)
+__host__ __device__ constexpr int stage_pitch(int out, int bn) { return out == kOutBf16 ? 2 * (bn + 8) : 4 * (bn + 4); }   // bytes
+__host__ __device__ constexpr int stage_bytes(int out, int bn) { return 4 * kHalfRows * stage_pitch(out, bn); }            // of the four wavefronts
+constexpr bool row_index(int out) { return out == kOutTail || out == kOutF32U; }   // the epilogue needs the rows' unpadded pixel indices
 
-// NV: strip vectors per lane (upper bound of (BM + 2 halo) * 8 / 256); BM: pixels per tile.  OUT: bf16 activations /
-// deltas; the bare convolution + bias in fp32; or the residual block's tail fused into the epilogue (shortcut, ReLU,
-// sign bytes and partial sums of the global average pooling -- the second convolution's output is then never stored).
-template <int OUT>
-constexpr bool kRowIndex = OUT == kOutTail || OUT == kOutF32U;   // the epilogue needs the rows' unpadded pixel indices
-
-template <int MODE, int OUT, int NV, int BM>
-__global__ __launch_bounds__(kThreads, BM == 128 ? 3 : 2) void conv3x3_bf16_kernel(ConvBDev p) {
-    using TB = typename std::conditional<MODE == 0, TileRC<kCB, kCB>, TileKC<kCB, kCB>>::type;   // FWD w[k = ci][n = co]; DX w[n = ci][k = co]
-    constexpr int SP = kCB + 8;                  // strip pitch (bf16 elements): 144 bytes, conflict-free 16-byte reads
-    constexpr int TM = BM / 128, TN = 2, KS = kCB / 16; // a wavefront owns BM / 4 pixels x 64 channels
-    static_assert(TB::kLineStep == 32 && TB::kPerThread == 2, "a lane's vectors are 32 rows apart in the strip and in a kernel slice");
-    extern __shared__ __attribute__((aligned(16))) uint16_t lds_all[];
-    constexpr int kStripRows = NV * 32;          // every lane moves NV vectors: rows past BM + 2 halo are loaded and never read
-    uint16_t* strip = lds_all;
-    uint16_t* lds_b0 = lds_all + kStripRows * SP;
-    auto lds_b = [&](int buf) { return lds_b0 + buf * TB::kElems; };
-    // the fp32 output is staged over the strip and the kernel slices together (conv_main_elems)
-    uint8_t* row_flag = (uint8_t*)(lds_all + conv_main_elems<BM, OUT>(kStripRows, TB::kElems));   // [BM] 1: image pixel, 0: border
-    int* row_up = (int*)row_flag;   // fused tail / unpadded output instead: [BM] the pixel's index in the unpadded [B H W] order, -1 for the border
+// A workgroup's tile is 128 TM padded pixels x 32 TN output channels; a wavefront owns 32 TM pixels x 32 TN channels.
+// LDS: the strip (later the epilogue's staging), a table of the tile's rows, the bias.
+template <int MODE, int OUT, int TM, int TN>
+__global__ __launch_bounds__(kThreads, 2) void conv3x3_bf16_kernel(ConvBDev p) {
+    constexpr int BM = 128 * TM, WR = 32 * TM, BN = 32 * TN;
+    constexpr int KS = kCB / 16, kSteps = 9 * KS;       // contraction steps of a chunk: (tap, 16 channels)
+    constexpr int kAhead = 4;                           // kernel fragments are requested that many steps ahead
+    static_assert(WR % kHalfRows == 0, "the epilogue works on whole halves");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    int* row_up = (int*)(lds + p.strip_bytes);          // [BM] image pixel: its index in the unpadded [B H W] order; border: -1
+    float* bias_lds = (float*)(row_up + BM);            // [BN]
 
     const int tile = xcd_tile(p.chunk, p.total_tiles);
     if (tile < 0) return;
@@ -185,46 +174,34 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 3 : 2) void conv3x3_bf16_kern
     const int group = (int)fast_div((unsigned)tile, p.div_pg);
     const int in_group = tile - group * per_group;
     const int tm = (int)fast_div((unsigned)in_group, p.div_tn), tn = in_group - tm * p.tiles_n;
-    const int m0 = tm * BM, n0 = tn * kCB;
-    const uint16_t* IN = p.in + (int64_t)group * p.s_in;
-    const uint16_t* Wg = p.w + (int64_t)group * p.s_w;
-    const int C = p.C;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int C = p.C, nb = C / kCB;
 
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int lane32 = lane % 32, half = lane / 32;
-    const int wm0 = wave * (BM / 4);
+    const int wm0 = wave * WR;
 
-    // Byte offsets in a [rows][C] bf16 tensor: lane t of the workgroup owns the 16-byte vector t % 8 of row t / 8, and its
-    // further vectors lie 32 rows below.  The same lane offset serves the strip and the kernel slices.
     const unsigned row_bytes = 2u * (unsigned)C;
-    const unsigned lane_off = (threadIdx.x / 8) * row_bytes + (threadIdx.x % 8) * 16u;
-    const unsigned step32 = 32u * row_bytes;
-    const rsrc_t in_rs = make_rsrc(IN, (unsigned)p.Pp * row_bytes);
-    const rsrc_t w_rs = make_rsrc(Wg, 9u * (unsigned)C * row_bytes);
-    // rows m0 - halo .. of channels c0 .. c0 + 63: rows before the tensor wrap to offsets beyond its end, rows after it
-    // lie beyond it too -- both read as zeros.  Every lane requests all its vectors at once (one round trip), then
-    // writes them to LDS.
-    const unsigned strip_off = (unsigned)(m0 - p.halo) * row_bytes + lane_off;
-    uint16_t* strip_lane = strip + (threadIdx.x / 8) * SP + (threadIdx.x % 8) * 8;
-    auto load_strip = [&](u4 (&r)[NV], int c0) {
-#pragma unroll
-        for (int t = 0; t < NV; ++t) r[t] = buf_load(in_rs, strip_off + t * step32, 2u * c0);
+    const rsrc_t in_rs = make_rsrc(p.in + (int64_t)group * p.s_in, (unsigned)p.Pp * row_bytes);
+    const rsrc_t w_rs = make_rsrc(p.w + (int64_t)group * p.s_w, 9u * (unsigned)C * row_bytes);
+    // Rows m0 - halo .. of channels c0 .. c0 + 63, loaded straight into LDS: a wavefront's instruction fills eight rows
+    // (1 KiB, lane by lane), and a lane fetches the 16-byte vector that belongs at its place -- vector v of row r lies at
+    // place v ^ (r % 8), so that eight lanes reading one vector of eight consecutive rows cover all banks.  Rows before the
+    // tensor wrap to offsets beyond its end, rows after it lie beyond it too: both arrive as zeros.
+    const unsigned strip_lane = (unsigned)(m0 - p.halo + lane / 8) * row_bytes + ((lane % 8) ^ (lane / 8)) * 16u;
+    auto load_strip = [&](int c0) {
+        for (int t = wave; t < p.strip_pieces; t += 4)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(in_rs, (lds_void_ptr)(lds + t * 1024), 16, (int)(strip_lane + t * 8u * row_bytes), 2 * c0, 0, 0);
     };
-    auto store_strip = [&](const u4 (&r)[NV]) {
+    // Fragments of the kernels come in their own order (see kernel_images) straight into registers: no LDS, no barrier
+    // between the taps.  The last chunk's requests past its end lie outside the range and cost nothing.
+    bf16x8 fa[2][TM], fb[kAhead][TN];
+    const int jn = (n0 / 32) % 2;
+    auto load_fb = [&](int slot, int k, int c) {
+        const unsigned first = (unsigned)(((k / KS) * nb + c) * nb + n0 / kCB) * (kCB * kCB * 2u) + (2 * (k % KS) + jn) * 1024u;
+        const unsigned off = c < nb ? lane * 16u : 0x40000000u;
 #pragma unroll
-        for (int t = 0; t < NV; ++t) *(u4*)(strip_lane + t * 32 * SP) = r[t];
-    };
-    // the 64 x 64 kernel slice of one tap.  Memory [ci][co]: FWD (row-contiguous tile) k = ci, rows = co; DX
-    // (K-contiguous tile) rows = ci, k = co
-    auto load_b = [&](u4 (&r)[TB::kPerThread], int tap, int c0) {
-        const unsigned first = 2u * (unsigned)((tap * C + (MODE == 0 ? c0 : n0)) * C + (MODE == 0 ? n0 : c0));
-#pragma unroll
-        for (int t = 0; t < TB::kPerThread; ++t) r[t] = buf_load(w_rs, lane_off + t * step32, first);
-    };
-    auto store_b = [&](int buf, const u4 (&r)[TB::kPerThread]) {
-        uint16_t* dst = TB::lane_lds(lds_b(buf));
-#pragma unroll
-        for (int t = 0; t < TB::kPerThread; ++t) *(u4*)(dst + t * TB::kLdsLineStep) = r[t];
+        for (int j = 0; j < TN; ++j) fb[slot][j] = __builtin_bit_cast(bf16x8, buf_load(w_rs, off, first + j * 1024u));
     };
 
     // The MFMA takes the KERNEL fragment first and the pixel fragment second, so the accumulator tile is out^T:
@@ -237,350 +214,294 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 3 : 2) void conv3x3_bf16_kern
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    bf16x8 fa[2][TM], fb[2][TN];
-    auto load_frags = [&](int buf, const uint16_t* a_base, const uint16_t* b_tile, int s) {
+    int fa_row = 0;
+    auto load_fa = [&](int buf, int k) {
+        const int tap = k / KS, s = k % KS;
+        int row = wm0 + lane32 + p.halo + (MODE == 0 ? 1 : -1) * ((tap / 3 - 1) * p.Wp + tap % 3 - 1);
+        if (s == 0) asm("" : "+v"(row));   // (or the compiler keeps the addresses of all steps across the chunks: 40 registers)
+        else row = fa_row;
+        fa_row = row;
+        const uint8_t* a = lds + row * kStripRow + ((half ^ (row & 7) ^ (2 * s)) * 16);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-            fa[buf][i] = __builtin_bit_cast(bf16x8, *(const u4*)(a_base + (wm0 + 32 * i + lane32) * SP + 16 * s + 8 * half));
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[buf][j] = TB::frag(b_tile, 32 * j, s, lane);
-    };
-    auto mfmas = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[buf][j], fa[buf][i], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < TM; ++i) fa[buf][i] = __builtin_bit_cast(bf16x8, *(const u4*)(a + i * 32 * kStripRow));
     };
 
-    // Kernel slices travel kAhead taps ahead of their use (a tap's 16 MFMAs per wavefront are shorter than a round trip
-    // to L2): a ring of kAhead register sets, slice t in set t % kAhead.
-    constexpr int kAhead = 3;
-    u4 rb[kAhead][TB::kPerThread];
-    // Delta: the activations whose sign gates the result -- the 16-byte vectors of the wavefront's own rows that this
-    // lane will write -- are requested kMaskTap taps into a chunk, when no kernel slice is in flight any more (with the
-    // long strips of wide images the registers do not allow it: there they are requested after the last tap).
-    constexpr int kVecB = kCB / 8, kPerB = (BM / 4) * kVecB / 64, kMaskTap = NV <= 12 ? 6 : 9;
-    u4 mk[MODE == 1 && OUT == kOutBf16 ? kPerB : 1];
-    const uint16_t* Mk = MODE == 1 && p.mask ? p.mask + (int64_t)group * p.s_mask : nullptr;
-    const rsrc_t mk_rs = make_rsrc(Mk ? Mk : IN, Mk ? (unsigned)p.Pp * row_bytes : 0u);
-    // the wavefront's own rows of the [Pp][C] bf16 output: lane l moves the vector l % 8 of rows wm0 + l / 8 + 8 t
-    const unsigned own_off = (unsigned)(m0 + wm0 + lane / kVecB) * row_bytes + 2u * (unsigned)n0 + (lane % kVecB) * 16u;
-    const unsigned step8 = (64 / kVecB) * row_bytes;
-    // with the fp32 output a lane moves four channels at a time (vector l % 16 of rows wm0 + l / 16 + 4 t): 8-byte pieces of
-    // the gate
-    constexpr int kPerF = (BM / 4) * (kCB / 4) / 64;
-    u2 mkf[MODE == 1 && OUT == kOutF32U ? kPerF : 1];
-    auto load_mask = [&]() {
-        if constexpr (OUT == kOutF32U) {
-            const unsigned first = (unsigned)(m0 + wm0 + lane / (kCB / 4)) * row_bytes + 2u * (unsigned)n0 + (lane % (kCB / 4)) * 8u;
+    // What the epilogue reads from memory is requested two taps before the end: delta, the sign bytes that gate the result, a row
+    // of the wavefront per lane; fused tail, the shortcut's fp32 rows in batches of eight vectors per lane, the first then and
+    // each further one while the batch before it is consumed.
+    constexpr int kVecB = BN / 8, kVecF = BN / 4;       // vectors of a row: bf16 and fp32
+    constexpr int kRowsB = 64 / kVecB, kRowsF = 64 / kVecF;   // rows that a wavefront moves at a time
+    constexpr int kHalves = WR / kHalfRows, kTailBatch = 8, kBatches = kVecF / kTailBatch;
+    typedef typename std::conditional<TN == 2, u4, u2>::type gate_row;   // a row's sign bytes: BN / 4 of them
+    gate_row gates[MODE == 1 ? kHalves : 1];
+    const unsigned own_b = (unsigned)(m0 + wm0 + lane / kVecB) * row_bytes + 2u * (unsigned)n0 + (lane % kVecB) * 16u;
+    auto load_gates = [&]() {
+        const unsigned rows = OUT == kOutF32U ? (unsigned)(p.B * p.H * p.W) : (unsigned)p.Pp;   // of the output, like the bytes
+        const rsrc_t rs = make_rsrc(p.gate + (int64_t)group * p.s_gate, rows * (unsigned)(C / 4));
 #pragma unroll
-            for (int t = 0; t < kPerF; ++t) mkf[t] = __builtin_amdgcn_raw_buffer_load_b64(mk_rs, (int)(first + t * 4u * row_bytes), 0, 0);
-        } else {
-#pragma unroll
-            for (int t = 0; t < kPerB; ++t) mk[t] = buf_load(mk_rs, own_off + t * step8, 0u);
+        for (int h = 0; h < kHalves; ++h) {
+            const int r = wm0 + h * kHalfRows + lane;
+            const unsigned off = (unsigned)(OUT == kOutF32U ? row_up[r] : m0 + r) * (unsigned)(C / 4) + n0 / 4;   // border rows: -1, beyond the range
+            if constexpr (TN == 2) gates[h] = buf_load(rs, off, 0u);
+            else gates[h] = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
         }
     };
-    // Forward: the lane's channels of the bias (register quad g4 of block j: channels 32 j + 8 g4 + 4 (lane / 32) ..),
-    // requested at the same point and added in the epilogue.
-    f4 bq[MODE == 0 ? TN : 1][4];
-    // (an empty range without a bias: zeros, and no branch for the waits on the kernel slices to be merged over)
-    const rsrc_t bias_rs = make_rsrc(MODE == 0 && p.bias ? (const void*)(p.bias + (int64_t)group * p.s_bias + n0) : (const void*)IN,
-                                     MODE == 0 && p.bias ? kCB * 4u : 0u);
-    auto load_bias = [&]() {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) bq[j][g4] = __builtin_bit_cast(f4, buf_load(bias_rs, 16u * half + 128u * j + 32u * g4, 0u));
-    };
-    // Fused tail: the shortcut's fp32 rows that this lane will add (vector l % 16 of the unpadded rows behind the
-    // wavefront's padded rows l / 16 + 4 t) -- the first batch of eight is requested at the same point, the second in
-    // the epilogue while the first is consumed.
-    constexpr int kTailBatch = 8;
-    f4 xpre[OUT == kOutTail ? kTailBatch : 1];
-    int up_pre[OUT == kOutTail ? kTailBatch : 1];
-    const rsrc_t x_rs = make_rsrc(OUT == kOutTail ? (const void*)(p.xres + (int64_t)group * p.s_x) : (const void*)IN,
+    f4 xres[OUT == kOutTail ? kTailBatch : 1];
+    int up_res[OUT == kOutTail ? kTailBatch : 1];
+    const rsrc_t x_rs = make_rsrc(OUT == kOutTail ? (const void*)(p.xres + (int64_t)group * p.s_x) : (const void*)p.in,
                                   OUT == kOutTail ? (unsigned)(p.B * p.H * p.W) * 2u * row_bytes : 0u);
-    auto load_shortcut = [&]() {
-        if constexpr (OUT == kOutTail) {
+    auto load_shortcut = [&](int batch) {   // batch counts over both halves
 #pragma unroll
-            for (int t = 0; t < kTailBatch; ++t) up_pre[t] = row_up[wm0 + lane / (kCB / 4) + 4 * t];
+        for (int t = 0; t < kTailBatch; ++t) up_res[t] = row_up[wm0 + lane / kVecF + kRowsF * (kTailBatch * batch + t)];
 #pragma unroll
-            for (int t = 0; t < kTailBatch; ++t)   // border rows: -1 wraps to an offset beyond the tensor, zeros come back
-                xpre[t] = __builtin_bit_cast(f4, buf_load(x_rs, (unsigned)up_pre[t] * 2u * row_bytes + 4u * n0 + (lane % (kCB / 4)) * 16u, 0u));
-        }
+        for (int t = 0; t < kTailBatch; ++t)   // border rows: -1 wraps to an offset beyond the tensor, zeros come back
+            xres[t] = __builtin_bit_cast(f4, buf_load(x_rs, (unsigned)up_res[t] * 2u * row_bytes + 4u * n0 + (lane % kVecF) * 16u, 0u));
     };
-    for (int c0 = 0; c0 < C; c0 += kCB) {
-        // the previous chunk's last barrier has passed: nobody reads the strip or the kernel buffers any more
-        {
-            u4 rs[NV];
-            load_b(rb[0], 0, c0);   // what the first tap needs goes first
-            load_strip(rs, c0);
+
+    for (int c = 0; c < nb; ++c) {
+        // the previous chunk's last barrier has passed: nobody reads the strip any more
+        load_strip(kCB * c);
+        if (c == 0) {
 #pragma unroll
-            for (int t = 1; t < kAhead; ++t) load_b(rb[t], t, c0);
+            for (int k = 0; k < kAhead; ++k) load_fb(k, k, 0);
             OLS_TP(1);   // the chunk's loads are issued
-            if (c0 == 0) {
-                int up;   // which rows of the tile are image pixels (the others get the zero border)
-                const int q = m0 + threadIdx.x;
-                const bool img = q < p.Pp && interior(p, q, &up);
-                if (threadIdx.x < BM) {
-                    if constexpr (kRowIndex<OUT>) row_up[threadIdx.x] = img ? up : -1; else row_flag[threadIdx.x] = img ? 1 : 0;
-                }
+#pragma unroll
+            for (int r = threadIdx.x; r < BM; r += kThreads) {   // which rows of the tile are image pixels
+                int up;
+                row_up[r] = m0 + r < p.Pp && interior(p, m0 + r, &up) ? up : -1;
             }
-            store_b(0, rb[0]);
-            store_strip(rs);
+            if (MODE == 0 && threadIdx.x < BN) bias_lds[threadIdx.x] = p.bias ? p.bias[(int64_t)group * p.s_bias + n0 + threadIdx.x] : 0.0f;
         }
         __syncthreads();
         OLS_TP(2);   // the strip is in LDS
+        load_fa(0, 0);
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            if (tap + kAhead < 9) load_b(rb[tap % kAhead], tap + kAhead, c0);   // its slice is in LDS already
-            if (tap == kMaskTap) {   // in every chunk: a branch here would make the waits on the kernel slices wait for these too
-                if constexpr (MODE == 1) load_mask(); else load_bias();
-                load_shortcut();
+        for (int k = 0; k < kSteps; ++k) {
+            if (k == 7 * KS) {   // in every chunk: a branch here would make the waits on the fragments wait for these too
+                if constexpr (MODE == 1) load_gates();
+                if constexpr (OUT == kOutTail) load_shortcut(0);
             }
-            const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-            const int shift = (MODE == 0 ? 1 : -1) * (dy * p.Wp + dx);
-            const uint16_t* a_base = strip + (p.halo + shift) * SP;
-            const uint16_t* b_tile = lds_b(tap & 1);
-            load_frags(0, a_base, b_tile, 0);
+            if (k + 1 < kSteps) load_fa((k + 1) & 1, k + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                if (s + 1 < KS) load_frags((s + 1) & 1, a_base, b_tile, s + 1);
-                __builtin_amdgcn_sched_barrier(0);
-                mfmas(s & 1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (tap + 1 < 9) store_b((tap + 1) & 1, rb[(tap + 1) % kAhead]);
-            __syncthreads();
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[k % kAhead][j], fa[k & 1][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_fb(k % kAhead, (k + kAhead) % kSteps, k + kAhead < kSteps ? c : c + 1);
         }
+        __syncthreads();
     }
+    static_assert(kSteps % kAhead == 0, "a chunk's first fragments lie in the first slots");
 
     OLS_TP(3);   // the taps are done
-    if (kMaskTap >= 9) {
-        if constexpr (MODE == 1) load_mask(); else load_bias();
-        load_shortcut();
-    }
-    // Epilogue: the tile goes through LDS (the strip's place) so that every lane then moves 16-byte vectors.
-    if constexpr (OUT == kOutTail) {
-        // a2 = relu(convolution + bias + shortcut) on the image pixels: its sign bytes and, per wavefront (64 consecutive
-        // padded pixels, which touch at most two samples because a padded image has at least 64), the channel sums of its
-        // rows in the first and in the second of those samples.  A later pass adds the wavefronts' sums per sample in
-        // wavefront order.  Staging as for the fp32 output; lane l then owns the channel quad l % 16 of rows l / 16 + 4 t.
-        constexpr int FP = kStagePitchF32, WR = BM / 4;
-        constexpr int kVecPerRow = kCB / 4, kPer = WR * kVecPerRow / 64, kBatch = kTailBatch;
-        static_assert(WR == 64, "the partial sums are kept per 64 rows");
-        float* stage = (float*)lds_all + wave * WR * FP;
-        const int r0 = lane / kVecPerRow, cq = lane % kVecPerRow;
+    // Epilogue: the tile goes through LDS (the strip's place) so that every lane then moves 16-byte vectors.  A wavefront
+    // stages and moves its own rows, 64 at a time: its LDS operations complete in order, so no workgroup barrier is needed
+    // after the one that ended the last tap.
+    constexpr int kPitch = stage_pitch(OUT, BN);
+    uint8_t* stage = lds + wave * kHalfRows * kPitch;
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto put = [&](int h, auto store) {   // hands the half's accumulators out as quads (row, channel, values)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int g4 = 0; g4 < 4; ++g4) {
-                    const f4 o = {acc[i][j][4 * g4] + bq[j][g4][0], acc[i][j][4 * g4 + 1] + bq[j][g4][1], acc[i][j][4 * g4 + 2] + bq[j][g4][2],
-                                  acc[i][j][4 * g4 + 3] + bq[j][g4][3]};
-                    *(f4*)(stage + (32 * i + lane32) * FP + 32 * j + 8 * g4 + 4 * half) = o;
+                    const f16v& t = acc[2 * h + i][j];
+                    f4 o = {t[4 * g4], t[4 * g4 + 1], t[4 * g4 + 2], t[4 * g4 + 3]};
+                    const int n = 32 * j + 8 * g4 + 4 * half;
+                    if constexpr (MODE == 0 && OUT != kOutF32U) o = o + *(const f4*)(bias_lds + n);
+                    store(32 * i + lane32, n, o);
                 }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int q0 = m0 + wm0;                                    // the wavefront's first padded pixel
-        const int per = p.Hp * p.Wp;
-        const int next_sample = ((int)fast_div((unsigned)q0, p.div_per) + 1) * per;   // first pixel of the second sample
+    };
+    // Sign bytes of the half's rows, behind the staging areas: they cross memory a row per lane and are used, or made, where
+    // the lanes hold vectors (stored from there, 16 or 32 stores of a byte or two per lane, they cost the forward kernel 23 us)
+    uint8_t* gate_lds = lds + stage_bytes(OUT, BN) + wave * (kHalfRows * BN / 4);
+    auto store_gates = [&](rsrc_t rs, int h) {
+        const unsigned off = (unsigned)(m0 + wm0 + h * kHalfRows + lane) * (unsigned)(C / 4) + n0 / 4;   // rows past the tensor are dropped
+        const gate_row v = *(const gate_row*)(gate_lds + lane * (BN / 4));
+        if constexpr (TN == 2) buf_store(v, rs, off);
+        else __builtin_amdgcn_raw_buffer_store_b64(v, rs, (int)off, 0, 0);
+    };
+    auto put_gates = [&](int h) {
+        if constexpr (MODE == 1) *(gate_row*)(gate_lds + lane * (BN / 4)) = gates[h];
+    };
+    auto put_f32 = [&](int r, int n, f4 o) { *(f4*)(stage + r * kPitch + 4 * n) = o; };
+    const int r0 = lane / kVecF, cq = lane % kVecF;     // fp32 staging: lane owns the channel quad cq of rows r0 + kRowsF t
+    auto staged = [&](int t) { return *(const f4*)(stage + (r0 + kRowsF * t) * kPitch + cq * 16); };
+    // sum over the kRowsF lanes of a channel quad, in lane order, through 64 vectors of LDS that no lane needs any more
+    auto quad_sum = [&](f4* red, f4 v, int q) {
+        red[lane] = v;
+        wave_sync();
+        f4 o = red[q];
+#pragma unroll
+        for (int u = 1; u < kRowsF; ++u) o = o + red[u * kVecF + q];
+        return o;
+    };
+
+    if constexpr (OUT == kOutTail) {
+        // a2 = relu(convolution + bias + shortcut) on the image pixels: its sign bytes and, per 64 consecutive padded pixels
+        // (which touch at most two samples because a padded image has at least 64), the channel sums of its rows in the
+        // first and in the second of those samples.  A later pass adds these sums per sample in order.
         const rsrc_t sg_rs = make_rsrc(p.sign + (int64_t)group * p.s_sign, (unsigned)p.Pp * (unsigned)(C / 4));
-        f4 sum0 = {0.f, 0.f, 0.f, 0.f}, sum1 = {0.f, 0.f, 0.f, 0.f};
-        static_assert(kPer == 2 * kBatch, "two batches of shortcut rows per lane");
-        f4 xnext[kBatch];
-        int up_next[kBatch];
+        const int per = p.Hp * p.Wp;
 #pragma unroll
-        for (int t = 0; t < kBatch; ++t) up_next[t] = row_up[wm0 + r0 + 4 * (kBatch + t)];
+        for (int h = 0; h < kHalves; ++h) {
+            const int q0 = m0 + wm0 + h * kHalfRows;                    // the half's first padded pixel
+            const int next_sample = ((int)fast_div((unsigned)q0, p.div_per) + 1) * per;   // first pixel of the second sample
+            put(h, put_f32);
+            wave_sync();
+            f4 sum0 = {0.f, 0.f, 0.f, 0.f}, sum1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < kBatch; ++t)   // the second batch travels while the first is consumed
-            xnext[t] = __builtin_bit_cast(f4, buf_load(x_rs, (unsigned)up_next[t] * 2u * row_bytes + 4u * n0 + cq * 16u, 0u));
+            for (int b = 0; b < kBatches; ++b) {
+                f4 yv[kTailBatch], xv[kTailBatch];
+                int up[kTailBatch];
 #pragma unroll
-        for (int t0 = 0; t0 < kPer; t0 += kBatch) {
-            f4 yv[kBatch], xv[kBatch];
-            int up[kBatch];
+                for (int t = 0; t < kTailBatch; ++t) { up[t] = up_res[t]; xv[t] = xres[t]; }
+                if (h * kBatches + b + 1 < kHalves * kBatches) load_shortcut(h * kBatches + b + 1);   // travels while this one is consumed
 #pragma unroll
-            for (int t = 0; t < kBatch; ++t) {
-                up[t] = t0 == 0 ? up_pre[t] : up_next[t];
-                xv[t] = t0 == 0 ? xpre[t] : xnext[t];
-            }
+                for (int t = 0; t < kTailBatch; ++t) yv[t] = staged(kTailBatch * b + t);
 #pragma unroll
-            for (int t = 0; t < kBatch; ++t) yv[t] = *(const f4*)(stage + (r0 + 4 * (t0 + t)) * FP + cq * 4);
+                for (int t = 0; t < kTailBatch; ++t) {
+                    const int q = q0 + r0 + kRowsF * (kTailBatch * b + t);
+                    const bool img = up[t] >= 0;
+                    unsigned bits = 0;
+                    f4 a;
 #pragma unroll
-            for (int t = 0; t < kBatch; ++t) {
-                const int q = q0 + r0 + 4 * (t0 + t);
-                const bool img = up[t] >= 0;
-                unsigned bits = 0;
-                f4 a;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    a[e] = img ? fmaxf(yv[t][e] + xv[t][e], 0.0f) : 0.0f;
-                    bits |= a[e] > 0.0f ? (1u << e) : 0u;
+                    for (int e = 0; e < 4; ++e) {
+                        a[e] = img ? fmaxf(yv[t][e] + xv[t][e], 0.0f) : 0.0f;
+                        bits |= a[e] > 0.0f ? (1u << e) : 0u;
+                    }
+                    if (q < next_sample) sum0 = sum0 + a; else sum1 = sum1 + a;
+                    gate_lds[(r0 + kRowsF * (kTailBatch * b + t)) * (BN / 4) + cq] = (uint8_t)bits;
                 }
-                if (q < next_sample) sum0 = sum0 + a; else sum1 = sum1 + a;
-                __builtin_amdgcn_raw_buffer_store_b8((unsigned char)bits, sg_rs, (int)((unsigned)q * (unsigned)(C / 4) + n0 / 4 + cq), 0, 0);   // rows past the tensor are dropped
             }
-        }
-        // the four lanes of a channel quad, in lane order, through the staging area (all its reads are done)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        f4* red = (f4*)stage;
-        red[lane] = sum0;
-        red[64 + lane] = sum1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (lane < 2 * kVecPerRow) {   // lanes 0 .. 15: first sample, 16 .. 31: second
-            const f4* r = red + 64 * (lane / kVecPerRow) + lane % kVecPerRow;
-            const f4 o = ((r[0] + r[16]) + r[32]) + r[48];
-            float* PP = p.pool_part + ((((int64_t)group * p.tiles_m + tm) * 4 + wave) * 2 + lane / kVecPerRow) * C + n0;
-            *(f4*)(PP + 4 * (lane % kVecPerRow)) = o;
+            wave_sync();   // all reads of the staging area are done
+            store_gates(sg_rs, h);
+            const int unit = tm * (BM / kHalfRows) + wave * kHalves + h;
+            const f4 o0 = quad_sum((f4*)stage, sum0, cq), o1 = quad_sum((f4*)stage + 64, sum1, cq);
+            if (lane < kVecF && unit < p.units) {
+                float* PP = p.pool_part + ((int64_t)group * p.units + unit) * 2 * C + n0 + 4 * cq;
+                *(f4*)PP = o0;
+                *(f4*)(PP + C) = o1;
+            }
+            wave_sync();
         }
     } else if constexpr (OUT == kOutF32 || OUT == kOutF32U) {
         // Convolution + bias only (what follows it is another kernel's).  Padded output: border rows are written as
         // computed; their consumer skips them.  Unpadded output: a row goes to its pixel's place in the [B H W] order and a
-        // border row to offset -1, which the range check drops.  Every wavefront stages its own BM / 4 rows and moves them
-        // itself: the LDS operations of one wavefront complete in order, so no workgroup barrier is needed after the one
-        // that ended the last tap.
-        constexpr int FP = kStagePitchF32, WR = BM / 4;
-        constexpr int kVecPerRow = kCB / 4, kPer = WR * kVecPerRow / 64, kBatch = 8;
-        static_assert(kPer == kPerF, "vectors per lane");
-        float* stage = (float*)lds_all + wave * WR * FP;
+        // border row to offset -1, which the range check drops.
         const unsigned out_rows = OUT == kOutF32U ? (unsigned)(p.B * p.H * p.W) : (unsigned)p.Pp;
         const rsrc_t out_rs = make_rsrc((const float*)p.out + (int64_t)group * p.s_out, out_rows * 2u * row_bytes);
-        const unsigned col_off = 4u * (unsigned)n0 + (lane % kVecPerRow) * 16u;
-        const unsigned out_off = (unsigned)(m0 + wm0 + lane / kVecPerRow) * 2u * row_bytes + col_off;
-        const unsigned out_step = (64 / kVecPerRow) * 2u * row_bytes;
+        const unsigned col_off = 4u * (unsigned)n0 + cq * 16u;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int h = 0; h < kHalves; ++h) {
+            const int hr = wm0 + h * kHalfRows;
+            put_gates(h);
+            put(h, put_f32);
+            wave_sync();
+            f4 zv[kVecF];
+            int up[kVecF], bits[MODE == 1 ? kVecF : 1];
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    f4 o = {acc[i][j][4 * g4], acc[i][j][4 * g4 + 1], acc[i][j][4 * g4 + 2], acc[i][j][4 * g4 + 3]};
-                    if constexpr (MODE == 0) o = o + bq[j][g4];
-                    *(f4*)(stage + (32 * i + lane32) * FP + 32 * j + 8 * g4 + 4 * half) = o;
-                }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int t0 = 0; t0 < kPer; t0 += kBatch) {
-            u4 val[kBatch];
-            int up[kBatch];
-#pragma unroll
-            for (int t = 0; t < kBatch; ++t) {
-                const int v = lane + (t0 + t) * 64;
-                val[t] = *(const u4*)(stage + (v / kVecPerRow) * FP + (v % kVecPerRow) * 4);
-                if constexpr (OUT == kOutF32U) up[t] = row_up[wm0 + v / kVecPerRow];
+            for (int t = 0; t < kVecF; ++t) {
+                zv[t] = staged(t);
+                up[t] = row_up[hr + r0 + kRowsF * t];
+                if constexpr (MODE == 1) bits[t] = gate_lds[(r0 + kRowsF * t) * (BN / 4) + cq];
             }
 #pragma unroll
-            for (int t = 0; t < kBatch; ++t) {
-                u4 o = val[t];
-                if constexpr (MODE == 1 && OUT == kOutF32U) {
-                    if (Mk) {   // a bf16 is positive iff its bits are in [0x0001, 0x7FFF]
-                        const u2 g2 = mkf[t0 + t];
-                        o[0] = ((g2.x & 0xFFFFu) - 1u) < 0x7FFFu ? o[0] : 0u;
-                        o[1] = ((g2.x >> 16) - 1u) < 0x7FFFu ? o[1] : 0u;
-                        o[2] = ((g2.y & 0xFFFFu) - 1u) < 0x7FFFu ? o[2] : 0u;
-                        o[3] = ((g2.y >> 16) - 1u) < 0x7FFFu ? o[3] : 0u;
-                    }
+            for (int t = 0; t < kVecF; ++t) {
+                u4 o = __builtin_bit_cast(u4, zv[t]);
+                if constexpr (MODE == 1) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = ((unsigned)bits[t] >> e) & 1u ? o[e] : 0u;
                 }
                 if constexpr (OUT == kOutF32U) buf_store(o, out_rs, (unsigned)up[t] * 2u * row_bytes + col_off);   // border rows: dropped
-                else buf_store(o, out_rs, out_off + (t0 + t) * out_step);                                           // rows past the tensor are dropped
+                else buf_store(o, out_rs, (unsigned)(m0 + hr + r0 + kRowsF * t) * 2u * row_bytes + col_off);        // rows past the tensor are dropped
             }
-        }
-        if constexpr (MODE == 0 && OUT == kOutF32U) {
-            // Statistics of the wavefront's image pixels for the batch normalisation that follows (which then need not
-            // read the output again): count, mean, and the sum of squared deviations from that mean, per channel.  Two
-            // passes over the staged rows; the four lanes of a channel quad are combined through the staging area's
-            // tail in lane order.  A later pass merges the wavefronts in wavefront order (the parallel-variance rule).
-            if (p.stat_part) {
-                const int r0 = lane / kVecPerRow, cq = lane % kVecPerRow;
-                f4* red = (f4*)(stage + WR * FP) - 64;        // the last 64 vectors of the wavefront's staging rows ...
-                f4 sum = {0.f, 0.f, 0.f, 0.f};
-                float cnt = 0.0f;
-                f4 zv[kPer];
-                bool img[kPer];
+            wave_sync();
+            if constexpr (MODE == 0 && OUT == kOutF32U) {
+                // Statistics of these 64 padded pixels' image pixels for the batch normalisation that follows (which then
+                // need not read the output again): count, mean, and the sum of squared deviations from that mean, per
+                // channel.  A later pass merges the parts in order (the parallel-variance rule).
+                if (p.stat_part) {
+                    f4* red = (f4*)stage;
+                    f4 sum = {0.f, 0.f, 0.f, 0.f};
+                    float cnt = 0.0f;
 #pragma unroll
-                for (int t = 0; t < kPer; ++t) {
-                    zv[t] = *(const f4*)(stage + (r0 + 4 * t) * FP + cq * 4);
-                    img[t] = row_up[wm0 + r0 + 4 * t] >= 0;
-                    if (img[t]) { sum = sum + zv[t]; cnt += 1.0f; }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();              // ... which every lane has read by now
-                red[lane] = sum;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                const f4 tot = ((red[cq] + red[16 + cq]) + red[32 + cq]) + red[48 + cq];
-                const float n = ((__shfl(cnt, cq) + __shfl(cnt, 16 + cq)) + __shfl(cnt, 32 + cq)) + __shfl(cnt, 48 + cq);
-                const float inv_n = n > 0.0f ? 1.0f / n : 0.0f;
-                f4 mean;
+                    for (int t = 0; t < kVecF; ++t)
+                        if (up[t] >= 0) { sum = sum + zv[t]; cnt += 1.0f; }
+                    const f4 tot = quad_sum(red, sum, cq);
+                    float n = __shfl(cnt, cq);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mean[e] = tot[e] * inv_n;
-                f4 dev = {0.f, 0.f, 0.f, 0.f};
+                    for (int u = 1; u < kRowsF; ++u) n += __shfl(cnt, u * kVecF + cq);
+                    const float inv_n = n > 0.0f ? 1.0f / n : 0.0f;
+                    f4 mean;
 #pragma unroll
-                for (int t = 0; t < kPer; ++t)
-                    if (img[t]) { const f4 d = zv[t] - mean; dev = dev + d * d; }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                red[lane] = dev;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                if (lane < kVecPerRow) {
-                    const f4 m2 = ((red[lane] + red[16 + lane]) + red[32 + lane]) + red[48 + lane];
-                    float* SP3 = p.stat_part + ((((int64_t)group * p.tiles_m + tm) * 4 + wave) * 3) * C + n0 + 4 * lane;
-                    *(f4*)SP3 = f4{n, n, n, n};
-                    *(f4*)(SP3 + C) = mean;
-                    *(f4*)(SP3 + 2 * C) = m2;
+                    for (int e = 0; e < 4; ++e) mean[e] = tot[e] * inv_n;
+                    f4 dev = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int t = 0; t < kVecF; ++t)
+                        if (up[t] >= 0) { const f4 d = zv[t] - mean; dev = dev + d * d; }
+                    const f4 m2 = quad_sum(red + 64, dev, cq);
+                    const int unit = tm * (BM / kHalfRows) + wave * kHalves + h;
+                    if (lane < kVecF && unit < p.units) {
+                        float* SP3 = p.stat_part + ((int64_t)group * p.units + unit) * 3 * C + n0 + 4 * cq;
+                        *(f4*)SP3 = f4{n, n, n, n};
+                        *(f4*)(SP3 + C) = mean;
+                        *(f4*)(SP3 + 2 * C) = m2;
+                    }
+                    wave_sync();
                 }
             }
         }
     } else {
-        // wavefront-local like the fp32 epilogue: a wavefront stages and moves its own BM / 4 rows
         const rsrc_t out_rs = make_rsrc((const uint16_t*)p.out + (int64_t)group * p.s_out, (unsigned)p.Pp * row_bytes);
-        uint16_t* stage = lds_all + wm0 * SP;
-        const float floor_v = p.relu ? 0.0f : -__builtin_huge_valf();   // max(., 0) or nothing
+        const rsrc_t gate_rs = make_rsrc(p.gate + (int64_t)group * p.s_gate, (unsigned)p.Pp * (unsigned)(C / 4));
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int h = 0; h < kHalves; ++h) {
+            put_gates(h);
+            put(h, [&](int r, int n, f4 v) {
+                if constexpr (MODE == 0) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        v[e] = acc[i][j][4 * g4 + e];
-                        if constexpr (MODE == 0) v[e] = fmaxf(v[e] + bq[j][g4][e], floor_v);
-                    }
-                    u2 o;   // round to nearest even (v_cvt_pk_bf16_f32)
-                    o.x = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{v[0], v[1]}, bf16x2));
-                    o.y = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{v[2], v[3]}, bf16x2));
-                    *(u2*)(stage + (32 * i + lane32) * SP + 32 * j + 8 * g4 + 4 * half) = o;
+                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);   // ReLU
                 }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        u4 val[kPerB];
+                u2 o;   // round to nearest even (v_cvt_pk_bf16_f32)
+                o.x = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{v[0], v[1]}, bf16x2));
+                o.y = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{v[2], v[3]}, bf16x2));
+                *(u2*)(stage + r * kPitch + 2 * n) = o;
+            });
+            wave_sync();
+            u4 val[kVecB];
+            int flag[kVecB];   // FWD: < 0 in the border; DX: the two sign bytes
 #pragma unroll
-        for (int t = 0; t < kPerB; ++t) {
-            const int v = lane + t * 64;
-            val[t] = *(const u4*)(stage + (v / kVecB) * SP + (v % kVecB) * 8);
-        }
-#pragma unroll
-        for (int t = 0; t < kPerB; ++t) {
-            u4 o = val[t];
-            if (MODE == 0) {
-                if (!row_flag[wm0 + (lane + t * 64) / kVecB]) o = u4{0u, 0u, 0u, 0u};   // the zero border the next layer relies on
-            } else if (Mk) {
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {   // a bf16 is positive iff its bits are in [0x0001, 0x7FFF]
-                    const unsigned int lo = mk[t][w] & 0xFFFFu, hi = mk[t][w] >> 16;
-                    const unsigned int keep = ((lo - 1u) < 0x7FFFu ? 0xFFFFu : 0u) | ((hi - 1u) < 0x7FFFu ? 0xFFFF0000u : 0u);
-                    o[w] &= keep;
-                }
+            for (int t = 0; t < kVecB; ++t) {
+                const int r = lane / kVecB + kRowsB * t;
+                val[t] = *(const u4*)(stage + r * kPitch + (lane % kVecB) * 16);
+                flag[t] = MODE == 0 ? row_up[wm0 + h * kHalfRows + r] : *(const uint16_t*)(gate_lds + r * (BN / 4) + lane % kVecB * 2);
             }
-            buf_store(o, out_rs, own_off + t * step8);   // rows past the tensor are dropped
+#pragma unroll
+            for (int t = 0; t < kVecB; ++t) {
+                u4 o = val[t];
+                if constexpr (MODE == 0) {
+                    if (flag[t] < 0) o = u4{0u, 0u, 0u, 0u};   // the zero border the next layer relies on
+                    *(unsigned short*)(gate_lds + (lane / kVecB + kRowsB * t) * (BN / 4) + lane % kVecB * 2) = positive_bits(o);
+                } else {
+                    const unsigned bits = flag[t];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {   // channels 2 w and 2 w + 1: bits 2 w, 2 w + 1 of their byte
+                        const unsigned two = bits >> (w < 2 ? 2 * w : 8 + 2 * (w - 2));
+                        o[w] &= (two & 1u ? 0xFFFFu : 0u) | (two & 2u ? 0xFFFF0000u : 0u);
+                    }
+                }
+                buf_store(o, out_rs, own_b + (h * kHalfRows + t * kRowsB) * row_bytes);   // rows past the tensor are dropped
+            }
+            wave_sync();
+            if constexpr (MODE == 0) store_gates(gate_rs, h);
         }
     }
     OLS_TP(4);   // the tile's stores are issued
@@ -763,17 +684,53 @@ __global__ __launch_bounds__(kDwThreads, 3) void conv3x3_dw_bf16_kernel(ConvBDev
 // ---------------------------------------------------------------------------------------------
 // fp32 [B H W][C] -> bf16 [B (H+2) (W+2)][C] with a zero border; one lane per 8 channels of a padded pixel
 // ---------------------------------------------------------------------------------------------
+// The kernels of a step in the order in which the forward / delta kernel's lanes take their fragments: one 64 x 64 slice per
+// (tap, 64-channel chunk of the contraction, 64 output channels), in it [step of 16][32 output channels][lane][8]: lane l holds
+// contraction channels 16 s + 8 (l / 32) .. + 7 of output channel 32 j + l % 32.  Three images: the first convolution's
+// kernels, the second's, and the second's with its channel indices exchanged (for the delta).  One workgroup per slice.
+struct KernelImages {
+    const uint16_t* w[3];    // [9][C][C] per group
+    int64_t s_w;
+    uint16_t* dst;           // [3][groups][9 C C]
+    int groups, C;
+};
+__device__ __forceinline__ void kernel_images(const KernelImages& im, int unit, int group) {
+    const int nb = im.C / kCB, which = unit / (9 * nb * nb), slice = unit % (9 * nb * nb);
+    const int tap = slice / (nb * nb), c0 = (slice / nb % nb) * kCB, n0 = (slice % nb) * kCB;
+    const uint16_t* W = im.w[which] + (int64_t)group * im.s_w + (int64_t)tap * im.C * im.C;
+    u4* D = (u4*)(im.dst + ((int64_t)(which * im.groups + group) * 9 * nb * nb + slice) * (kCB * kCB));
+#pragma unroll
+    for (int v = threadIdx.x; v < kCB * kCB / 8; v += kThreads) {
+        const int l = v % 64, n = n0 + 32 * (v / 64 % 2) + l % 32, k = c0 + 16 * (v / 128) + 8 * (l / 32);
+        u4 o;
+        if (which == 2) {
+            o = *(const u4*)(W + (int64_t)n * im.C + k);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                o[e] = W[(int64_t)(k + 2 * e) * im.C + n] | (unsigned)W[(int64_t)(k + 2 * e + 1) * im.C + n] << 16;
+        }
+        D[v] = o;
+    }
+}
+
 constexpr int kPadCastFly = 2;   // 16-byte output vectors per lane
 __global__ __launch_bounds__(kThreads) void pad_cast_bf16_kernel(const float* __restrict__ src, int64_t s_src,
                                                                  uint16_t* __restrict__ dst, int64_t s_dst, unsigned vecs, int H,
-                                                                 int W, int C, FastDiv div_c8, FastDiv div_per, FastDiv div_wp) {
+                                                                 int W, int C, FastDiv div_c8, FastDiv div_per, FastDiv div_wp,
+                                                                 KernelImages im, unsigned image_blocks) {
     const int g = blockIdx.y;
+    if (blockIdx.x < image_blocks) {   // the step's kernels travel with its batch
+        kernel_images(im, blockIdx.x, g);
+        return;
+    }
+    const unsigned block = blockIdx.x - image_blocks;
     const unsigned c8 = (unsigned)C / 8, Wp = (unsigned)W + 2, per = (unsigned)(H + 2) * Wp;
     f4 lo[kPadCastFly], hi[kPadCastFly];
     bool img[kPadCastFly];
 #pragma unroll
     for (int t = 0; t < kPadCastFly; ++t) {   // the loads of all the lane's vectors before the first store
-        const unsigned v = (blockIdx.x * kPadCastFly + t) * kThreads + threadIdx.x;
+        const unsigned v = (block * kPadCastFly + t) * kThreads + threadIdx.x;
         const unsigned q = fast_div(v < vecs ? v : 0u, div_c8), cv = (v < vecs ? v : 0u) - q * c8;
         const unsigned n = fast_div(q, div_per), rem = q - n * per;
         const unsigned y = fast_div(rem, div_wp), x = rem - y * Wp;
@@ -786,7 +743,7 @@ __global__ __launch_bounds__(kThreads) void pad_cast_bf16_kernel(const float* __
     }
 #pragma unroll
     for (int t = 0; t < kPadCastFly; ++t) {
-        const unsigned v = (blockIdx.x * kPadCastFly + t) * kThreads + threadIdx.x;
+        const unsigned v = (block * kPadCastFly + t) * kThreads + threadIdx.x;
         if (v >= vecs) continue;
         u4 o = {0u, 0u, 0u, 0u};
         if (img[t]) {   // round to nearest even (v_cvt_pk_bf16_f32)
@@ -961,9 +918,23 @@ bool shape_ok(const ConvBArgs& a) {
 void fill(ConvBDev* p, const ConvBArgs& a) {
     p->groups = a.groups; p->B = a.B; p->H = a.H; p->W = a.W; p->C = a.C;
     p->Hp = a.H + 2; p->Wp = a.W + 2; p->Pp = a.B * p->Hp * p->Wp; p->halo = p->Wp + 1;
-    p->relu = a.relu;
     p->div_per = make_div((unsigned)(p->Hp * p->Wp));
     p->div_wp = make_div((unsigned)p->Wp);
+}
+
+// The tile of the forward / delta kernel.  512 pixels x 64 channels where the launch fills the 512 places that two workgroups
+// per compute unit make (once, or often enough for the last round not to matter); 256 x 32 where 256 x 64 would leave compute
+// units idle; 256 x 64 between them and for strips that do not fit twice (images wider than 49).  us per launch, bf16 output,
+// as 512 x 64 / 256 x 64 / 256 x 32:  3 x 20 x 13 x 15 x 128 (30 tiles of 512 pixels) 17.0 / 11.0 / 7.9;  8 x 16 x 24 x 24 x 64 (176)
+// 13.1 / 12.3 / 10.8;  4 x 40 x 30 x 30 x 64 (320) 20.9 / 19.1 / 19.8;  8 x 30 x 24 x 32 x 64 (416) 23.8 / 24.6 / 24.9;  12 x 24 x 28 x
+// 30 x 64 (540) 31.4 / 29.3 / 32.2;  12 x 60 x 10 x 20 x 128 (744) 55.1 / 58.2 / 63.5;  6 x 64 x 36 x 40 x 64 (1200) 55.1 / 55.3 / 61.1.
+struct ConvTile { int tm, tn; };
+int strip_pieces(int bm, int W) { return (bm + 2 * (W + 3) + 7) / 8; }
+ConvTile conv_tile(int groups, int Pp, int C, int W) {
+    const int64_t t512 = (int64_t)groups * ((Pp + 511) / 512) * (C / 64), t256 = (int64_t)groups * ((Pp + 255) / 256) * (C / 64);
+    const bool fits = 1024 * strip_pieces(512, W) + (512 + kCB) * 4 <= 80 * 1024;   // two workgroups per compute unit
+    if (fits && (t512 >= 680 || (t512 >= 400 && t512 <= 512))) return {4, 2};
+    return t256 < 800 ? ConvTile{2, 1} : ConvTile{2, 2};
 }
 
 template <int MODE>
@@ -971,9 +942,12 @@ hipError_t conv_launch(const ConvBArgs& a, hipStream_t s) {
     const bool tail = MODE == 0 && a.tail;
     if (!shape_ok(a) || !a.in || !a.w || !aligned16(a.in) || !aligned16(a.w)) return hipErrorInvalidValue;
     if (!tail && (!a.out || !aligned16(a.out) || a.s_out % 8)) return hipErrorInvalidValue;
-    if (a.s_in % 8 || a.s_w % 8 || (a.mask && (!aligned16(a.mask) || a.s_mask % 8))) return hipErrorInvalidValue;
+    if (a.s_in % 8 || a.s_w % 8) return hipErrorInvalidValue;
+    if (MODE == 1 || (!tail && !a.out_f32)) {   // the sign bytes go with a ReLU's bf16 result and with every delta
+        if (!a.gate || !aligned16(a.gate) || a.s_gate % 16 || (MODE == 0 && !a.relu)) return hipErrorInvalidValue;
+    }
     if (tail) {   // 16-byte vectors of the shortcut, 32-bit byte offsets in it, at most two samples per 64 padded pixels
-        if (a.out_f32 || a.relu || !a.xres || !a.sign || !a.pool_part || !aligned16(a.xres) || !aligned16(a.pool_part) || a.s_x % 4 ||
+        if (a.out_f32 || a.relu || !a.xres || !a.sign || !a.pool_part || !aligned16(a.xres) || !aligned16(a.pool_part) || !aligned16(a.sign) || a.s_x % 4 || a.s_sign % 16 ||
             (a.H + 2) * (a.W + 2) < 64 || (int64_t)a.B * a.H * a.W * a.C >= ((int64_t)1 << 30) - 1024)
             return hipErrorInvalidValue;
     }
@@ -985,48 +959,39 @@ hipError_t conv_launch(const ConvBArgs& a, hipStream_t s) {
     fill(&p, a);
     p.in = (const uint16_t*)a.in; p.w = (const uint16_t*)a.w; p.out = a.out;
     p.bias = MODE == 0 ? a.bias : nullptr;
-    p.mask = MODE == 1 ? (const uint16_t*)a.mask : nullptr;
-    p.s_in = a.s_in; p.s_w = a.s_w; p.s_out = a.s_out; p.s_bias = a.s_bias; p.s_mask = a.s_mask;
+    p.gate = a.gate;
+    p.s_in = a.s_in; p.s_w = a.s_w; p.s_out = a.s_out; p.s_bias = a.s_bias; p.s_gate = a.s_gate;
     if (tail) { p.xres = a.xres; p.s_x = a.s_x; p.sign = a.sign; p.s_sign = a.s_sign; p.pool_part = a.pool_part; }
     if (a.stat_part) {
         if (MODE != 0 || !a.out_unpadded || !aligned16(a.stat_part)) return hipErrorInvalidValue;
         p.stat_part = a.stat_part;
     }
-    constexpr int BM = kBM;   // 128 (three workgroups per compute unit, 134 registers) measured 8 - 19 % slower: halo 1.55x
+    const int out = tail ? kOutTail : a.out_unpadded ? kOutF32U : a.out_f32 ? kOutF32 : kOutBf16;
+    if (a.out_f32 && (int64_t)p.Pp * a.C >= ((int64_t)1 << 30)) return hipErrorInvalidValue;   // 32-bit byte offsets in the fp32 output
+    if ((int64_t)a.groups * ((p.Pp + 255) / 256) * (a.C / 32) > (1 << 30)) return hipErrorInvalidValue;
+    const ConvTile t = conv_tile(a.groups, p.Pp, a.C, a.W);
+    const int BM = 128 * t.tm, BN = 32 * t.tn;
     p.tiles_m = (p.Pp + BM - 1) / BM;
-    p.tiles_n = a.C / kCB;
+    p.tiles_n = a.C / BN;
+    p.units = (p.Pp + 255) / 256 * 4;
     p.div_pg = make_div((unsigned)(p.tiles_m * p.tiles_n));
     p.div_tn = make_div((unsigned)p.tiles_n);
-    const int64_t total = (int64_t)a.groups * p.tiles_m * p.tiles_n;
-    if (total > (1 << 30)) return hipErrorInvalidValue;
-    if (a.out_f32 && (int64_t)p.Pp * a.C >= ((int64_t)1 << 30)) return hipErrorInvalidValue;   // 32-bit byte offsets in the fp32 output
-    p.total_tiles = (int)total;
-    p.chunk = (int)((total + kXcds - 1) / kXcds);
-    const int strip_rows = BM + 2 * p.halo;
-    const size_t b_elems = MODE == 0 ? TileRC<kCB, kCB>::kElems : TileKC<kCB, kCB>::kElems;
-    constexpr int NV0 = ((BM + 2 * 35) * (kCB / 8) + kThreads - 1) / kThreads;                        // widths up to 32
-    constexpr int NV1 = ((BM + 2 * (kConvBf16MaxWidth + 3)) * (kCB / 8) + kThreads - 1) / kThreads;    // any width
-    const int nv = (strip_rows * (kCB / 8) + kThreads - 1) / kThreads;
-    if (nv > NV1) return hipErrorInvalidValue;
-    const int lds_rows = 32 * (nv <= NV0 ? NV0 : NV1);   // the kernel's strip holds all the vectors its lanes move
-    // the bf16 output tile is staged in the strip's place (BM x 72 bf16); the fp32 one is sized by conv_main_elems
-    const int out = tail ? kOutTail : a.out_unpadded ? kOutF32U : a.out_f32 ? kOutF32 : kOutBf16;
-    const size_t main_elems = out != kOutBf16 ? conv_main_elems<BM, kOutF32>(lds_rows, (int)b_elems) : conv_main_elems<BM, kOutBf16>(lds_rows, (int)b_elems);
-    const size_t lds = main_elems * sizeof(uint16_t) + (out == kOutTail || out == kOutF32U ? BM * sizeof(int) : BM);   // strip and kernel slices (or the fp32 staging), row flags / indices
+    p.total_tiles = a.groups * p.tiles_m * p.tiles_n;
+    p.chunk = (p.total_tiles + kXcds - 1) / kXcds;
+    p.strip_pieces = strip_pieces(BM, a.W);
+    p.strip_bytes = std::max(1024 * p.strip_pieces, stage_bytes(out, BN) + BN * kHalfRows);   // (the gates lie behind the staging)
+    const size_t lds = p.strip_bytes + BM * sizeof(int) + BN * sizeof(float);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    void (*kern)(ConvBDev);
-    if (nv <= NV0)
-        kern = MODE == 1 ? (out == kOutF32U ? conv3x3_bf16_kernel<1, kOutF32U, NV0, BM> : conv3x3_bf16_kernel<1, kOutBf16, NV0, BM>)
-               : out == kOutTail ? conv3x3_bf16_kernel<0, kOutTail, NV0, BM>
-               : out == kOutF32U ? conv3x3_bf16_kernel<0, kOutF32U, NV0, BM>
-               : out == kOutF32  ? conv3x3_bf16_kernel<0, kOutF32, NV0, BM>
-                                 : conv3x3_bf16_kernel<0, kOutBf16, NV0, BM>;
-    else
-        kern = MODE == 1 ? (out == kOutF32U ? conv3x3_bf16_kernel<1, kOutF32U, NV1, BM> : conv3x3_bf16_kernel<1, kOutBf16, NV1, BM>)
-               : out == kOutTail ? conv3x3_bf16_kernel<0, kOutTail, NV1, BM>
-               : out == kOutF32U ? conv3x3_bf16_kernel<0, kOutF32U, NV1, BM>
-               : out == kOutF32  ? conv3x3_bf16_kernel<0, kOutF32, NV1, BM>
-                                 : conv3x3_bf16_kernel<0, kOutBf16, NV1, BM>;
+    auto pick = [&](auto tm, auto tn) -> void (*)(ConvBDev) {
+        constexpr int TM = decltype(tm)::value, TN = decltype(tn)::value;
+        if constexpr (MODE == 1) return out == kOutF32U ? conv3x3_bf16_kernel<1, kOutF32U, TM, TN> : conv3x3_bf16_kernel<1, kOutBf16, TM, TN>;
+        else return out == kOutTail ? conv3x3_bf16_kernel<0, kOutTail, TM, TN> : out == kOutF32U ? conv3x3_bf16_kernel<0, kOutF32U, TM, TN>
+                  : out == kOutF32 ? conv3x3_bf16_kernel<0, kOutF32, TM, TN> : conv3x3_bf16_kernel<0, kOutBf16, TM, TN>;
+    };
+    typedef std::integral_constant<int, 1> i1;
+    typedef std::integral_constant<int, 2> i2;
+    typedef std::integral_constant<int, 4> i4;
+    void (*kern)(ConvBDev) = t.tm == 4 ? pick(i4(), i2()) : t.tn == 2 ? pick(i2(), i2()) : pick(i2(), i1());
     if (lds > 64 * 1024) {
         hipError_t e = ensure_dynamic_lds((const void*)kern, 160 * 1024);
         if (e != hipSuccess) return e;
@@ -1100,16 +1065,18 @@ hipError_t launch_conv3x3_bf16_dw(const ConvBArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, int64_t s_dst, int groups, int B, int H, int W,
-                                int C, hipStream_t s) {
-    if (!src || !dst || groups < 1 || groups > 65535 || B < 1 || H < 1 || W < 1 || C < 8 || C % 8 || !aligned16(src) ||
-        !aligned16(dst) || s_src % 4 || s_dst % 8)
+                                int C, const uint16_t* wa, const uint16_t* wb, int64_t s_w, uint16_t* images, hipStream_t s) {
+    if (!src || !dst || groups < 1 || groups > 65535 || B < 1 || H < 1 || W < 1 || C < kCB || C % kCB || !aligned16(src) ||
+        !aligned16(dst) || s_src % 4 || s_dst % 8 || !wa || !wb || !images || !aligned16(wa) || !aligned16(wb) || !aligned16(images) || s_w % 8)
         return hipErrorInvalidValue;
     const int64_t vecs = (int64_t)B * (H + 2) * (W + 2) * (C / 8);
     if (vecs >= ((int64_t)1 << 31) - kPadCastFly * kThreads) return hipErrorInvalidValue;   // the divisions by multiplication take 31-bit dividends
     const int64_t blocks = (vecs + kPadCastFly * kThreads - 1) / (kPadCastFly * kThreads);
-    pad_cast_bf16_kernel<<<dim3((unsigned)blocks, (unsigned)groups), kThreads, 0, s>>>(
+    KernelImages im = {{wa, wb, wb}, s_w, images, groups, C};
+    const int64_t image_blocks = 3 * 9 * (int64_t)(C / kCB) * (C / kCB);
+    pad_cast_bf16_kernel<<<dim3((unsigned)(blocks + image_blocks), (unsigned)groups), kThreads, 0, s>>>(
         src, s_src, dst, s_dst, (unsigned)vecs, H, W, C, make_div((unsigned)(C / 8)), make_div((unsigned)((H + 2) * (W + 2))),
-        make_div((unsigned)(W + 2)));
+        make_div((unsigned)(W + 2)), im, (unsigned)image_blocks);
     return hipGetLastError();
 }
 
@@ -1126,12 +1093,12 @@ hipError_t launch_shortcut_relu_pool(const float* y, int64_t s_y, const float* X
 
 int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C) {
     const int64_t Pp = (int64_t)B * (H + 2) * (W + 2);
-    return ((Pp + kBM - 1) / kBM) * 4 * 3 * C;   // per group
+    return ((Pp + 255) / 256) * 4 * 3 * C;   // per group
 }
 
 int64_t conv3x3_bf16_pool_part_floats(int B, int H, int W, int C) {
     const int64_t Pp = (int64_t)B * (H + 2) * (W + 2);
-    return ((Pp + kBM - 1) / kBM) * 4 * 2 * C;   // per group
+    return ((Pp + 255) / 256) * 4 * 2 * C;   // per group
 }
 
 hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, float* more, int groups, int B, int per,

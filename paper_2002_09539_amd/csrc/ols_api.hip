@@ -91,7 +91,7 @@ struct ols_ctx {
     int64_t ws_bytes = 0, ws_need = 0;
     // workspace sub-buffers (byte offsets)
     std::vector<int64_t> off_act, off_dz;
-    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_x0 = 0, off_flags = 0;
+    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_wimages = 0, off_gate = 0, off_x0 = 0, off_flags = 0;
     // residual convolutional block: channels, image size, classes; workspace sub-buffers
     int cv_C = 0, cv_H = 0, cv_W = 0, cv_classes = 0;
     bool cv_bn = false;     // convolutions without bias, each followed by batch normalisation
@@ -352,6 +352,8 @@ void plan_workspace(ols_ctx* c) {
         c->off_bnpart = take(bn_partial_floats(c->m, c->B * c->cv_H * c->cv_W, c->cv_C) * 4);
         c->off_wstat = take(m * conv3x3_bf16_stat_part_floats(c->B, c->cv_H, c->cv_W, c->cv_C) * 4);
         c->off_shadow = take(m * c->ld * 2);
+        c->off_wimages = take(3 * m * 9 * c->cv_C * c->cv_C * 2);
+        c->off_gate = take(padded / 4);   // sign bytes of a1
     } else if (c->model == MODEL_CONV && c->gemm_dtype == 1) {
         // operand tensors are bf16 and carry their zero border; a2's place holds the pooling's partial sums (or, for
         // images of fewer than 64 padded pixels, the second convolution's fp32 output with the border)
@@ -369,6 +371,8 @@ void plan_workspace(ols_ctx* c) {
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_shadow = take(m * c->ld * 2);
+        c->off_wimages = take(3 * m * 9 * c->cv_C * c->cv_C * 2);
+        c->off_gate = take(padded / 4);   // sign bytes of a1
     } else if (c->model == MODEL_CONV) {
         const int64_t act = m * B * c->cv_H * c->cv_W * c->cv_C * 4;   // one activation / delta tensor
         c->off_a1 = take(act);
@@ -423,16 +427,19 @@ int conv_gradients_bf16(ols_ctx* c) {
     float* dpool = (float*)(c->ws + c->off_dpool);
     ConvBArgs base = {};
     base.groups = m; base.B = B; base.H = H; base.W = W; base.C = C;
-    base.s_w = c->ld; base.s_bias = c->ld;
+    base.s_w = n_w; base.s_bias = c->ld;
     base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
+    uint16_t* images = (uint16_t*)(c->ws + c->off_wimages);   // of the kernels: first convolution, second, second for the delta
+    uint8_t* gate = (uint8_t*)(c->ws + c->off_gate);          // sign of a1 for the delta, a byte per pixel and four channels
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-             return launch_pad_cast_bf16(c->X, c->xs, xb, act, m, B, H, W, C, s);
+             return launch_pad_cast_bf16(c->X, c->xs, xb, act, m, B, H, W, C, shadow + wa, shadow + wb, c->ld, images, s);
          })))
         return rc;
     {   // a1 = bf16(relu(conv(X; Wa) + ba))
         ConvBArgs a = base;
-        a.in = xb; a.s_in = act; a.w = shadow + wa; a.bias = xc + ba; a.out = a1; a.s_out = act; a.relu = 1;
+        a.in = xb; a.s_in = act; a.w = images; a.bias = xc + ba; a.out = a1; a.s_out = act; a.relu = 1;
+        a.gate = gate; a.s_gate = act / 4;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
     }
     if (positions >= 64) {
@@ -440,7 +447,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         // partial sums of the pooling are (the partial sums take the place the fp32 output has without the fusion)
         ConvBArgs a = base;
         float* pool_part = y2;
-        a.in = a1; a.s_in = act; a.w = shadow + wb; a.bias = xc + bb; a.tail = 1;
+        a.in = a1; a.s_in = act; a.w = images + m * n_w; a.bias = xc + bb; a.tail = 1;
         a.xres = c->X; a.s_x = c->xs; a.sign = sign; a.s_sign = act / 4; a.pool_part = pool_part;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
         if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
@@ -451,7 +458,7 @@ int conv_gradients_bf16(ols_ctx* c) {
     } else {   // images too small for the fused tail's two-samples-per-wavefront bookkeeping
         {   // y = conv(a1; Wb) + bb, fp32
             ConvBArgs a = base;
-            a.in = a1; a.s_in = act; a.w = shadow + wb; a.bias = xc + bb; a.out = y2; a.s_out = act; a.out_f32 = 1;
+            a.in = a1; a.s_in = act; a.w = images + m * n_w; a.bias = xc + bb; a.out = y2; a.s_out = act; a.out_f32 = 1;
             if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
         }
         // a2 = relu(y + X), pooled = its mean over the positions, and the sign of a2 for the backward pass, in one pass
@@ -486,7 +493,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         return rc;
     {   // delta at a1, gated by a1 > 0
         ConvBArgs a = base;
-        a.in = dz2; a.s_in = act; a.w = shadow + wb; a.mask = a1; a.s_mask = act; a.out = dz1; a.s_out = act;
+        a.in = dz2; a.s_in = act; a.w = images + 2 * m * n_w; a.gate = gate; a.s_gate = act / 4; a.out = dz1; a.s_out = act;
         if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }
     {
@@ -528,13 +535,15 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     float* dpool = (float*)(c->ws + c->off_dpool);
     ConvBArgs base = {};
     base.groups = m; base.B = B; base.H = H; base.W = W; base.C = C;
-    base.s_w = c->ld; base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
+    base.s_w = n_w; base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
     BnArgs nbase = {};
     nbase.groups = m; nbase.P = B * H * W; nbase.C = C; nbase.eps = c->cv_eps;
     nbase.s_z = act; nbase.s_out = act; nbase.s_dy = act; nbase.s_par = c->ld;
     nbase.ld = c->ld; nbase.g = c->g; nbase.H = H; nbase.W = W; nbase.s_outb = padded;
     nbase.part = (float*)(c->ws + c->off_bnpart);
     nbase.sums = (float*)(c->ws + c->off_bnsums);
+    uint16_t* images = (uint16_t*)(c->ws + c->off_wimages);   // of the kernels: first convolution, second, second for the delta
+    uint8_t* gate = (uint8_t*)(c->ws + c->off_gate);          // sign of a1 for the delta, a byte per pixel and four channels
     float* stats1 = (float*)(c->ws + c->off_bnstats);
     float* stats2 = stats1 + (int64_t)m * 2 * C;
     // the convolutions leave the statistics of their output per wavefront (64 padded pixels): the normalisations merge those
@@ -550,22 +559,23 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     float* sample_sums = tail_part + m * tail_units * 6 * C;
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-             return launch_pad_cast_bf16(c->X, c->xs, xb, padded, m, B, H, W, C, s);
+             return launch_pad_cast_bf16(c->X, c->xs, xb, padded, m, B, H, W, C, shadow + wa, shadow + wb, c->ld, images, s);
          })))
         return rc;
     {   // z1 = conv(X; Wa)
         ConvBArgs a = base;
-        a.in = xb; a.s_in = padded; a.w = shadow + wa; a.out = z1; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
+        a.in = xb; a.s_in = padded; a.w = images; a.out = z1; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
     }
     {   // a1 = bf16(relu(bn(z1)))
         BnArgs a = nbase;
         a.z = z1; a.out_bf16 = a1; a.stats = stats1; a.gamma = xc + ga; a.beta = xc + ba; a.relu = 1; a.wave_part = wstat; a.waves = waves;
+        a.gate_out = gate; a.s_gate_out = act / 4;
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
     {   // z2 = conv(a1; Wb)
         ConvBArgs a = base;
-        a.in = a1; a.s_in = padded; a.w = shadow + wb; a.out = z2; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
+        a.in = a1; a.s_in = padded; a.w = images + m * n_w; a.out = z2; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
     }
     {   // a2 = relu(bn(z2) + X)
@@ -611,7 +621,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     }
     {   // gradient at the first normalised output: transposed convolution of dz2 through Wb, gated by a1 > 0
         ConvBArgs a = base;
-        a.in = dz2; a.s_in = padded; a.w = shadow + wb; a.mask = a1; a.s_mask = padded; a.out = dn; a.s_out = act;
+        a.in = dz2; a.s_in = padded; a.w = images + 2 * m * n_w; a.gate = gate; a.s_gate = act / 4; a.out = dn; a.s_out = act;
         a.out_f32 = 1; a.out_unpadded = 1;
         if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }

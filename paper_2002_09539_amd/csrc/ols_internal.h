@@ -241,11 +241,11 @@ hipError_t launch_pool_bwd(const float* dpool, int64_t s_dp, const float* a, int
                            int groups, int B, int HW, int C, hipStream_t s);
 
 // The same convolutions with bf16 operands.  Operand tensors carry their zero border: [group][B (H+2) (W+2)][C] bf16,
-// channel contiguous; kernels [group][9][C][C] bf16.  C a multiple of 64, W at most kConvBf16MaxWidth.
+// channel contiguous.  C a multiple of 64, W at most kConvBf16MaxWidth.
 constexpr int kConvBf16MaxWidth = 128;
 struct ConvBArgs {
     const void* in;         // fwd: layer input; dx: delta of the layer output; dw: layer input (bf16, padded)
-    const void* w;          // fwd, dx: bf16 kernels
+    const void* w;          // fwd, dx: bf16 kernels, an image of launch_pad_cast_bf16 (s_w = 9 C C)
     const void* dout;       // dw: delta of the layer output (bf16, padded)
     void* out;              // fwd: layer output; dx: delta of the layer input; padded, bf16 -- or, fwd with out_f32, the
                             // bare convolution + bias in fp32 with border rows as computed (their consumer skips them)
@@ -255,13 +255,14 @@ struct ConvBArgs {
                             // padded pixels (count, mean, sum of squared deviations) [3][C] of the output's image pixels,
                             // which launch_bn_forward takes instead of reading the output for its statistics
     const float* bias;      // fwd: [C] per group, or nullptr
-    const void* mask;       // dx: padded bf16 activations whose sign gates the result, or nullptr
+    uint8_t* gate;          // dx: [row of the output][C / 4] sign bytes (bit e set: channel 4 c + e stays, else 0); fwd with
+                            // bf16 output: where the output leaves its own (bit e set iff it is positive)
     float* partial;         // dw: scratch of conv3x3_bf16_dw_splits(...) * groups * (9 C C + C) floats
     float* g;               // dw: gradients [groups][ld]
     int64_t ld, g_w_off, g_b_off;   // g_b_off < 0: no bias
-    int64_t s_in, s_w, s_dout, s_out, s_bias, s_mask;   // group strides (elements of the tensor's own type)
+    int64_t s_in, s_w, s_dout, s_out, s_bias, s_gate;   // group strides (elements of the tensor's own type)
     int groups, B, H, W, C;
-    int relu;               // fwd with bf16 output: apply max(., 0)
+    int relu;               // fwd with bf16 output: max(., 0) is applied, and has to be asked for
     // fwd with the residual block's tail fused in (tail != 0; out unused, no relu, padded images of at least 64 pixels):
     // a2 = relu(convolution + bias + xres) is never stored -- sign[padded pixel][C / 4] gets one byte per four channels
     // with bit e set iff a2 > 0 (border: 0), and pool_part (conv3x3_bf16_pool_part_floats(...) floats per group) the
@@ -282,9 +283,11 @@ int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C);   // per grou
 // pixels (slot 0: the sample of pixel 64 w, slot 1: the next one) with `per` (>= 64) pixels per sample
 hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, float* more, int groups, int B, int per,
                               int C, float inv, hipStream_t s);
-// fp32 [groups][B H W][C] -> bf16 [groups][B (H+2) (W+2)][C] with a zero border
+// fp32 [groups][B H W][C] -> bf16 [groups][B (H+2) (W+2)][C] with a zero border; and the step's kernels (bf16 [9][C][C] per
+// group, wa of the first convolution and wb of the second) -> images[3][groups][9 C C]: the first convolution's, the second's
+// and the second's for the delta, in the order that launch_conv3x3_bf16_fwd / _dx take as ConvBArgs::w
 hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, int64_t s_dst, int groups, int B, int H, int W,
-                                int C, hipStream_t s);
+                                int C, const uint16_t* wa, const uint16_t* wb, int64_t s_w, uint16_t* images, hipStream_t s);
 // The block's tail: a2 = relu(y + X) on the image pixels (y fp32 padded, X fp32 not padded), pooled = its mean over the
 // positions, sign[padded pixel][C / 4] = one byte per four channels with bit e set iff a2 > 0 (border: 0).  a2 is not stored.
 hipError_t launch_shortcut_relu_pool(const float* y, int64_t s_y, const float* X, int64_t s_x, float* pooled, int64_t s_p,
@@ -313,9 +316,12 @@ struct BnArgs {
     // Optional: the result (fwd: the activation; bwd: the gradient at z) goes out as bf16, to nearest even, in the padded
     // operand layout of the bf16 convolutions, [B (H + 2) (W + 2)][C] per group with P = B H W -- only the image pixels
     // are written (the border is zero from the start and stays so); `out` / the in-place update of dy are then skipped.
+    // (fwd) `gate_out`, with out_bf16: [P][C / 4] sign bytes of the bf16 result (bit e set iff channel 4 c + e is positive).
     uint16_t* out_bf16;
     int64_t s_outb;
     int H, W;
+    uint8_t* gate_out;
+    int64_t s_gate_out;
     // Optional (bwd): the normalised output sits under a ReLU and global average pooling, so the gradient on entry is
     // dpool[group][sample][c] / positions where gate (the activation, [group][P][C]) is positive and 0 elsewhere; it is
     // formed on the fly and dy is only written (the gradient at z), or not touched at all with out_bf16.
