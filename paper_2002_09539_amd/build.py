@@ -21,6 +21,7 @@ SOURCES = [
     "kernels_lsq.hip",
     "kernels_mlp_head.hip",
     "kernels_gemm_f32.hip",
+    "kernels_gemm_small.hip",
     "kernels_gemm_split.hip",
     "kernels_gemm_bf16.hip",
     "kernels_conv.hip",

@@ -697,10 +697,13 @@ static hipError_t dw_pipelined_launch(const GemmArgs& g, hipStream_t s) {
 // Large launches run on the bf16 matrix cores with split operands (variant 32, kernels_gemm_split.hip: 234 -> 187 us and
 // 76 -> 61 us on configurations 5 and 2).  What is left is small: there a K range may be as short as 96 indices (5 workers
 // x (36 x 300 x 788): eight ranges 13.8 us, two 17.3), unless the contraction is too short for the second launch that
-// adds the ranges up.
+// adds the ranges up.  Smaller launches still have a kernel without slices (variant 33, kernels_gemm_small.hip).
 void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* splits) {
     *variant = 32;
     if (gemm_split_fwd_plan(groups, M, N, K, splits)) return;
+    *variant = 33;
+    *splits = 1;
+    if (gemm_small_fwd_fits(groups, M, N, K)) return;
     *variant = 2;
     int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 63) / 64);
     if (tiles >= 1024 && N >= 128) {
@@ -719,6 +722,7 @@ hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant) {
     }
     switch (variant) {
         case 32: return launch_gemm_split_fwd(g, s);
+        case 33: return launch_gemm_small_fwd(g, s);
         case 2: return gemm_launch<kFwd, 64, 64, 32, 2, 2, 2>(g, s);
         case 6: return gemm_launch<kFwd, 64, 128, 32, 2, 2, 2>(g, s);
 #ifdef OLS_TUNING_VARIANTS
@@ -767,6 +771,7 @@ hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant) {
     }
 }
 hipError_t launch_gemm_f32_da(const GemmArgs& g, hipStream_t s, int variant) {
+    if (variant == 0 && gemm_small_da_fits(g.groups, g.M, g.N, g.K)) return launch_gemm_small_da(g, s);
     switch (variant) {
         case 0: return gemm_launch<kDa, 64, 64, 64, 2, 2, 2>(g, s);
 #ifdef OLS_TUNING_VARIANTS

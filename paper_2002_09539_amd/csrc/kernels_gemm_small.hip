@@ -1,0 +1,202 @@
+// Grouped fp32 GEMMs of small launches: forward and back-propagated delta of the per-worker MLPs (whose gradients are the
+// g_i of Section 2, arXiv 2002.09539) where 64 x 64 tiles are too few for the chip, so that a launch's time is one tile's chain
+// of K slices -- load, LDS, barrier, fragments -- and not throughput.
+//
+//   FWD  C[M][N] = relu(A[M][K] W[K][N] + bias[N])
+//   DA   C[M][N] = (A[M][K] B[N][K]^T) * [mask > 0]
+//
+// A workgroup owns a 32 x 16 tile (32 x 32 in larger launches); its four wavefronts share out the contraction (wavefront w
+// takes steps w, w + 4, .. of 16 indices) and load their MFMA fragments (v_mfma_f32_16x16x4_f32) straight from memory, up to
+// eight steps in one round trip: no LDS and no barrier before the wavefronts' sums meet in LDS, in wavefront order.  Lane l of
+// a fragment holds indices 4 (l / 16) .. + 3 of its step, one per MFMA, for both operands: 16-byte loads where the contraction
+// index is contiguous, four dwords of 64 contiguous bytes per 16 lanes where it is not.  Buffer descriptors return zeros past
+// the operands' ends.  How many steps a round trip takes is a template parameter, so that no load is issued for nothing (with
+// twelve always requested, 5 x (36 x 124 x 300) took 8.0 us instead of 4.0); eight or sixteen wavefronts per tile are no
+// faster on any of 70 shapes by more than 8 % and slower on most.
+//
+// us per launch, 64 x 64 tiles (forward with the pass that adds their K ranges) / here:
+//   workers x (M x N x K)     forward       delta
+//   4 x (32 x 96 x 64)        6.2 / 2.8     7.7 / 2.7
+//   5 x (36 x 124 x 300)     11.8 / 4.0    12.9 / 3.5
+//   5 x (36 x 300 x 788)     11.6 / 6.8    23.9 / 6.1
+//   11 x (100 x 312 x 188)    9.0 / 5.3    10.5 / 5.2
+//   34 x (60 x 188 x 412)    15.1 / 9.1    16.1 / 10.6
+//   6 x (220 x 608 x 604)    28.4 / 19.1   20.7 / 19.9
+//   7 x (92 x 824 x 1580)    35.6 / 38.7 (not taken)   43.1 / 41.6
+#include "gemm_bf16_tile.h"
+#include "ols_internal.h"
+
+namespace ols {
+
+namespace {
+
+enum { kFwd = 0, kDa = 1 };
+constexpr int kXcds = 8;
+constexpr int kW = 4, kThreads = 64 * kW;          // wavefronts that share a tile's contraction
+
+struct SmallDev {
+    const float* a;
+    const float* b;
+    float* c;
+    const float* bias;
+    const float* mask;
+    int64_t sa, sb, sc, sbias, smask;
+    int M, N, K, lda, ldb, ldc;
+    int tiles_m, tiles_n, total_tiles, chunk;
+};
+
+template <int MODE, int TM, int TN, int S>
+__global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
+    constexpr int BM = 16 * TM, BN = 16 * TN, kOut = BM * BN, kPer = kOut / kThreads;
+    __shared__ float red[kW][kOut];
+    // a group's tiles stay on one XCD (workgroups are dealt to the XCDs in turn), whose L2 then holds its weights
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    const int tile = xcd * p.chunk + slot;
+    if (tile >= p.total_tiles) return;
+    const int per_group = p.tiles_m * p.tiles_n, group = tile / per_group;
+    const int m0 = tile % per_group / p.tiles_n * BM, n0 = tile % p.tiles_n * BN;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, l16 = lane % 16, k4 = lane / 16 * 4;
+
+    // the epilogue's inputs come first: output o = thread + u kThreads of the tile lies in block o / 256 (see the accumulators' layout)
+    float extra[kPer];
+    auto row_of = [&](int o) { return m0 + 16 * (o / 256 / TN) + 4 * (o % 64 / 16) + o % 256 / 64; };
+    auto col_of = [&](int o) { return n0 + 16 * (o / 256 % TN) + l16; };
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int o = threadIdx.x + u * kThreads, row = row_of(o), col = col_of(o);
+        extra[u] = 0.0f;
+        if (row < p.M && col < p.N)
+            extra[u] = MODE == kFwd ? p.bias[(int64_t)group * p.sbias + col] : p.mask[(int64_t)group * p.smask + (int64_t)row * p.ldc + col];
+    }
+
+    const rsrc_t a_rs = make_rsrc(p.a + (int64_t)group * p.sa, (unsigned)((p.M - 1) * p.lda + p.K) * 4u);
+    const rsrc_t b_rs = make_rsrc(p.b + (int64_t)group * p.sb, (unsigned)(MODE == kFwd ? (p.K - 1) * p.ldb + p.N : (p.N - 1) * p.ldb + p.K) * 4u);
+    constexpr unsigned kOutside = 0x80000000u;   // beyond every range
+    struct Step { f4 a[TM], b[TN]; };
+    auto load = [&](Step& r, int step) {
+        const int k = 16 * step + k4;
+        const bool in = k < p.K;                 // K is a multiple of four
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {          // (rows past M: beyond the range, or the next row's -- not stored)
+            const int row = m0 + 16 * i + l16;
+            r.a[i] = __builtin_bit_cast(f4, buf_load(a_rs, in && row < p.M ? 4u * (unsigned)(row * p.lda + k) : kOutside, 0u));
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = n0 + 16 * j + l16;
+            if constexpr (MODE == kFwd) {
+                const unsigned off = in && col < p.N ? 4u * (unsigned)(k * p.ldb + col) : kOutside;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r.b[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b_rs, (int)(off + 4u * (unsigned)(e * p.ldb)), 0, 0));
+            } else {
+                r.b[j] = __builtin_bit_cast(f4, buf_load(b_rs, in && col < p.N ? 4u * (unsigned)(col * p.ldb + k) : kOutside, 0u));
+            }
+        }
+    };
+    f4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    auto mfma = [&](const Step& r) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[i][e], r.b[j][e], acc[i][j], 0, 0, 0);
+    };
+    const int steps = (p.K + 15) / 16;
+    for (int s0 = wave; s0 < steps; s0 += S * kW) {
+        Step r[S];
+#pragma unroll
+        for (int t = 0; t < S; ++t) load(r[t], s0 + t * kW);   // (steps past the end: zeros, no traffic)
+#pragma unroll
+        for (int t = 0; t < S; ++t) mfma(r[t]);
+    }
+    // Accumulator register r of a lane: row 4 (lane / 16) + r, column lane % 16 of its 16 x 16 block; kept as [block][r][lane]
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave][256 * (i * TN + j) + 64 * r + lane] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int o = threadIdx.x + u * kThreads, row = row_of(o), col = col_of(o);
+        if (row >= p.M || col >= p.N) continue;
+        float v = red[0][o];
+#pragma unroll
+        for (int w = 1; w < kW; ++w) v += red[w][o];
+        v = MODE == kFwd ? fmaxf(v + extra[u], 0.0f) : extra[u] > 0.0f ? v : 0.0f;
+        p.c[(int64_t)group * p.sc + (int64_t)row * p.ldc + col] = v;
+    }
+}
+
+bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
+
+}  // namespace
+
+// The rule, from both sides measured on 110 shapes (2 - 64 workers, M 16 - 252, N 64 - 2000, K 64 - 3072): work in steps of 16
+// indices of a 32 x 16 tile.  Forward up to 80,000 (faster on all but three, 2 - 5 % slower there; beyond, 64 x 64 tiles read less),
+// long contractions only up to 25,000 (their K ranges spread better: 3 x (40 x 532 x 2236) 16.2 and 18.8).  Delta, whose 64 x 64
+// tiles have no K ranges, the same without that and up to 160,000 from K = 1024 on (7 x (76 x 1348 x 1396) 63.0 and 54.5;
+// 22 x (64 x 536 x 2256), 211,000: 56.9 and 66.4).
+static int64_t small_tiles(int groups, int M, int N) { return (int64_t)groups * ((M + 31) / 32) * ((N + 15) / 16); }
+static bool small_offsets(int64_t a_elems, int64_t b_elems) { return a_elems < (1 << 28) && b_elems < (1 << 28); }   // 32-bit byte offsets
+bool gemm_small_fwd_fits(int groups, int M, int N, int K) {
+    const int64_t work = small_tiles(groups, M, N) * ((K + 15) / 16);
+    return work <= (K <= 2048 ? 80000 : 25000) && small_offsets((int64_t)M * K, (int64_t)K * N);
+}
+bool gemm_small_da_fits(int groups, int M, int N, int K) {
+    const int64_t work = small_tiles(groups, M, N) * ((K + 15) / 16);
+    return work <= (K >= 1024 ? 160000 : 80000) && small_offsets((int64_t)M * K, (int64_t)K * N);
+}
+
+template <int MODE, int TN>
+static void small_start(const SmallDev& p, int steps, hipStream_t s) {
+    // as few round trips of up to eight steps as there have to be, and as short as they then can be
+    const int per = (steps + kW - 1) / kW, trips = (per + 7) / 8;
+    const unsigned grid = (unsigned)(p.chunk * kXcds);
+    switch ((per + trips - 1) / trips) {
+        case 1: gemm_f32_small_kernel<MODE, 2, TN, 1><<<grid, kThreads, 0, s>>>(p); break;
+        case 2: gemm_f32_small_kernel<MODE, 2, TN, 2><<<grid, kThreads, 0, s>>>(p); break;
+        case 3: gemm_f32_small_kernel<MODE, 2, TN, 3><<<grid, kThreads, 0, s>>>(p); break;
+        case 4: gemm_f32_small_kernel<MODE, 2, TN, 4><<<grid, kThreads, 0, s>>>(p); break;
+        case 5: gemm_f32_small_kernel<MODE, 2, TN, 5><<<grid, kThreads, 0, s>>>(p); break;
+        case 6: gemm_f32_small_kernel<MODE, 2, TN, 6><<<grid, kThreads, 0, s>>>(p); break;
+        case 7: gemm_f32_small_kernel<MODE, 2, TN, 7><<<grid, kThreads, 0, s>>>(p); break;
+        default: gemm_f32_small_kernel<MODE, 2, TN, 8><<<grid, kThreads, 0, s>>>(p); break;
+    }
+}
+
+static hipError_t small_launch(int mode, const GemmArgs& g, hipStream_t s) {
+    const bool fwd = mode == kFwd;
+    if (!g.a || !g.b || !g.c || g.groups < 1 || g.M < 1 || g.N < 1 || g.K < 1 || (fwd ? !g.bias : !g.mask)) return hipErrorInvalidValue;
+    if (!aligned16(g.a) || !aligned16(g.b) || g.lda % 4 || g.ldb % 4 || g.sa % 4 || g.sb % 4 || g.K % 4 || (fwd && g.N % 4)) return hipErrorInvalidValue;
+    if (g.lda < g.K || g.ldb < (fwd ? g.N : g.K) || g.ldc < g.N) return hipErrorInvalidValue;
+    SmallDev p = {};
+    p.a = (const float*)g.a; p.b = (const float*)g.b; p.c = (float*)g.c; p.bias = g.bias; p.mask = (const float*)g.mask;
+    p.sa = g.sa; p.sb = g.sb; p.sc = g.sc; p.sbias = g.sbias; p.smask = g.smask;
+    p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
+    // 32 x 32 tiles (forward only: they halve its many dword loads) once 32 x 16 ones keep the compute units busy for a while:
+    // 32 x (24 x 444 x 360), 20,600: 8.8 and 8.0; 4 x (28 x 1924 x 1872), 56,600: 23.0 and 19.3; 4 x (224 x 124 x 1192), 224 tiles: 8.9 and 11.5
+    const int steps = (g.K + 15) / 16;
+    const int64_t t16 = small_tiles(g.groups, g.M, g.N);
+    const bool wide = fwd && t16 >= 256 && t16 * steps >= 16000;
+    p.tiles_m = (g.M + 31) / 32;
+    p.tiles_n = wide ? (g.N + 31) / 32 : (g.N + 15) / 16;
+    const int64_t total = (int64_t)g.groups * p.tiles_m * p.tiles_n;
+    if (total > (1 << 30) || !small_offsets((int64_t)g.M * g.lda, (int64_t)(fwd ? g.K : g.N) * g.ldb)) return hipErrorInvalidValue;
+    p.total_tiles = (int)total;
+    p.chunk = (int)((total + kXcds - 1) / kXcds);
+    if (!fwd) small_start<kDa, 1>(p, steps, s);
+    else if (wide) small_start<kFwd, 2>(p, steps, s);
+    else small_start<kFwd, 1>(p, steps, s);
+    return hipGetLastError();
+}
+hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s) { return small_launch(kFwd, g, s); }
+hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s) { return small_launch(kDa, g, s); }
+
+}  // namespace ols

@@ -160,6 +160,11 @@ void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* split
 hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_gemm_f32_da(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_splitk_finish(const float* partial, int splits, const GemmArgs& g, hipStream_t s);
+// forward and delta of small launches (kernels_gemm_small.hip), and whether a shape takes them
+bool gemm_small_fwd_fits(int groups, int M, int N, int K);
+bool gemm_small_da_fits(int groups, int M, int N, int K);
+hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s);
 // forward on the bf16 matrix cores with every operand split exactly into three bf16 terms (fp32 accuracy): whether, and
 // over how many K ranges, a shape takes it
 bool gemm_split_fits(int64_t a_elems, int64_t b_elems);   // elements a group's operand spans

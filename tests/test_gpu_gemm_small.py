@@ -1,0 +1,52 @@
+"""GPU parity of the fp32 MLP where its forward and delta GEMMs take the kernel of small launches: tiles, contraction steps and
+round trips of steps that are whole or not, both tile widths, and an infinite weight."""
+import numpy as np
+import pytest
+
+from ols_inputs import generate as G
+from oracle import ols_oracle as O
+from tests.helpers import max_norm_ratio
+from tests.test_gpu_gemm_split import GRAD_TOL, one_step
+from tests.test_gpu_mlp import small_mlp_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,dims,batch", [
+    (2, (4, 4, 4, 3), 4),                # a quarter of one step, four rows
+    (3, (128, 36, 20, 5), 36),           # two steps per wavefront; four rows and four columns more than a tile
+    (2, (132, 300, 124, 7), 36),         # one step of four indices more
+    (1, (512, 16, 516, 3), 32),          # a whole round trip of eight steps; contractions of one step and of 33
+    (2, (520, 48, 16, 3), 20),           # nine steps per wavefront: two round trips of five
+    (2, (2060, 24, 8, 4), 20),           # 33 steps per wavefront: five round trips of seven
+    (32, (360, 444, 8, 4), 24),          # 32 x 32 tiles, the last with 28 columns
+    (9, (760, 384, 92, 6), 164),         # 32 x 32 tiles over two round trips, rows no multiple of a tile
+])
+def test_gradient_and_loss_match_oracle(m, dims, batch):
+    cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=421)
+    x0 = x0 + G.generic_normal(3, 1, x0.shape, sigma=0.02)
+    g, losses = one_step(cfg, dims, batch, X, labels, x0)
+    for i in sorted({0, m // 2, m - 1}):
+        loss, grad = O.mlp_loss_grad(x0, dims, X[i, 0], labels[i, 0])
+        assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
+        assert max_norm_ratio(g[i], grad) <= GRAD_TOL
+
+
+def test_infinite_weight_stays_in_its_column():
+    """Lanes past the contraction's end (20 indices: a second step of four) and past the last row or column hold zeros, not a
+    neighbour's value: an infinite weight reaches its own unit only."""
+    m, dims, batch = 2, (20, 20, 20, 4), 4
+    cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=422)
+    inf = 20 * 20 + 20                   # second layer's weight [0][0], right behind the first layer's bias
+    x0 = x0.copy()
+    x0[20 * 20:inf] = -100.0             # first layer: no unit is active ..
+    x0[20 * 20 + 1:inf] = 1.0            # .. but those after the first
+    x0[inf] = np.inf
+    g, losses = one_step(cfg, dims, batch, X, labels, x0)
+    # 0 * inf is a NaN in the second layer's first unit, which the ReLU takes to 0 as before; everything else stays finite
+    ref = x0.copy()
+    ref[inf] = 0.0
+    ref[inf + 20 * 20] = -1e6            # that unit inactive
+    for i in range(m):
+        loss, grad = O.mlp_loss_grad(ref, dims, X[i, 0], labels[i, 0])
+        assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
