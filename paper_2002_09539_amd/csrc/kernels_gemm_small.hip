@@ -45,7 +45,7 @@ struct SmallDev {
     int tiles_m, tiles_n, total_tiles, chunk;
 };
 
-template <int MODE, int TM, int TN, int S>
+template <int MODE, int TM, int TN, int S, bool MORE>
 __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
     constexpr int BM = 16 * TM, BN = 16 * TN, kOut = BM * BN, kPer = kOut / kThreads;
     __shared__ float red[kW][kOut];
@@ -107,12 +107,28 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
                 for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[i][e], r.b[j][e], acc[i][j], 0, 0, 0);
     };
     const int steps = (p.K + 15) / 16;
-    for (int s0 = wave; s0 < steps; s0 += S * kW) {
-        Step r[S];
+    Step r0[S], r1[MORE ? S : 1];
+    auto load_trip = [&](Step (&r)[S], int s0) {
 #pragma unroll
         for (int t = 0; t < S; ++t) load(r[t], s0 + t * kW);   // (steps past the end: zeros, no traffic)
+    };
+    auto mfma_trip = [&](const Step (&r)[S]) {
 #pragma unroll
         for (int t = 0; t < S; ++t) mfma(r[t]);
+    };
+    if constexpr (MORE) {   // the next round trip under way during this one's products
+        load_trip(r0, wave);
+        for (int s0 = wave; s0 < steps; s0 += 2 * S * kW) {
+            load_trip(r1, s0 + S * kW);
+            mfma_trip(r0);
+            load_trip(r0, s0 + 2 * S * kW);
+            mfma_trip(r1);
+        }
+    } else {
+        for (int s0 = wave; s0 < steps; s0 += S * kW) {
+            load_trip(r0, s0);
+            mfma_trip(r0);
+        }
     }
     // Accumulator register r of a lane: row 4 (lane / 16) + r, column lane % 16 of its 16 x 16 block; kept as [block][r][lane]
 #pragma unroll
@@ -140,14 +156,14 @@ bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) ==
 
 // The rule, from both sides measured on 110 shapes (2 - 64 workers, M 16 - 252, N 64 - 2000, K 64 - 3072): work in steps of 16
 // indices of a 32 x 16 tile.  Forward up to 80,000 (faster on all but three, 2 - 5 % slower there; beyond, 64 x 64 tiles read less),
-// long contractions only up to 25,000 (their K ranges spread better: 3 x (40 x 532 x 2236) 16.2 and 18.8).  Delta, whose 64 x 64
+// long contractions only up to 30,000 (their K ranges spread better: 13 x (40 x 476 x 2612), 128,000, 40.5 and 45.4).  Delta, whose 64 x 64
 // tiles have no K ranges, the same without that and up to 160,000 from K = 1024 on (7 x (76 x 1348 x 1396) 63.0 and 54.5;
 // 22 x (64 x 536 x 2256), 211,000: 56.9 and 66.4).
 static int64_t small_tiles(int groups, int M, int N) { return (int64_t)groups * ((M + 31) / 32) * ((N + 15) / 16); }
 static bool small_offsets(int64_t a_elems, int64_t b_elems) { return a_elems < (1 << 28) && b_elems < (1 << 28); }   // 32-bit byte offsets
 bool gemm_small_fwd_fits(int groups, int M, int N, int K) {
     const int64_t work = small_tiles(groups, M, N) * ((K + 15) / 16);
-    return work <= (K <= 2048 ? 80000 : 25000) && small_offsets((int64_t)M * K, (int64_t)K * N);
+    return work <= (K <= 2048 ? 80000 : 30000) && small_offsets((int64_t)M * K, (int64_t)K * N);
 }
 bool gemm_small_da_fits(int groups, int M, int N, int K) {
     const int64_t work = small_tiles(groups, M, N) * ((K + 15) / 16);
@@ -157,18 +173,31 @@ bool gemm_small_da_fits(int groups, int M, int N, int K) {
 template <int MODE, int TN>
 static void small_start(const SmallDev& p, int steps, hipStream_t s) {
     // as few round trips of up to eight steps as there have to be, and as short as they then can be
-    const int per = (steps + kW - 1) / kW, trips = (per + 7) / 8;
+    const int per = (steps + kW - 1) / kW, trips = (per + 7) / 8, S = (per + trips - 1) / trips;
     const unsigned grid = (unsigned)(p.chunk * kXcds);
-    switch ((per + trips - 1) / trips) {
-        case 1: gemm_f32_small_kernel<MODE, 2, TN, 1><<<grid, kThreads, 0, s>>>(p); break;
-        case 2: gemm_f32_small_kernel<MODE, 2, TN, 2><<<grid, kThreads, 0, s>>>(p); break;
-        case 3: gemm_f32_small_kernel<MODE, 2, TN, 3><<<grid, kThreads, 0, s>>>(p); break;
-        case 4: gemm_f32_small_kernel<MODE, 2, TN, 4><<<grid, kThreads, 0, s>>>(p); break;
-        case 5: gemm_f32_small_kernel<MODE, 2, TN, 5><<<grid, kThreads, 0, s>>>(p); break;
-        case 6: gemm_f32_small_kernel<MODE, 2, TN, 6><<<grid, kThreads, 0, s>>>(p); break;
-        case 7: gemm_f32_small_kernel<MODE, 2, TN, 7><<<grid, kThreads, 0, s>>>(p); break;
-        default: gemm_f32_small_kernel<MODE, 2, TN, 8><<<grid, kThreads, 0, s>>>(p); break;
+#define OLS_SMALL(S, MORE) gemm_f32_small_kernel<MODE, 2, TN, S, MORE><<<grid, kThreads, 0, s>>>(p)
+    // Round trips one behind the other leave room for more workgroups; with hardly one per compute unit and three trips or more
+    // (five to eight steps each) they overlap: forward 3 x (32 x 960 x 1836), 180 tiles, 16.0 -> 12.1, 3 x (40 x 532 x 2236), 204, 18.7 ->
+    // 15.1; but 4 x (224 x 124 x 1192), 224 tiles, 8.9 -> 9.8, 17 x (128 x 248 x 1372) 34.3 -> 48.1, and no delta gains.
+    if constexpr (MODE == kFwd && TN == 1) {
+        if (trips > 2 && p.total_tiles <= 216) {
+            if (S <= 6) OLS_SMALL(6, true);
+            else if (S == 7) OLS_SMALL(7, true);
+            else OLS_SMALL(8, true);
+            return;
+        }
     }
+    switch (S) {
+        case 1: OLS_SMALL(1, false); break;
+        case 2: OLS_SMALL(2, false); break;
+        case 3: OLS_SMALL(3, false); break;
+        case 4: OLS_SMALL(4, false); break;
+        case 5: OLS_SMALL(5, false); break;
+        case 6: OLS_SMALL(6, false); break;
+        case 7: OLS_SMALL(7, false); break;
+        default: OLS_SMALL(8, false); break;
+    }
+#undef OLS_SMALL
 }
 
 static hipError_t small_launch(int mode, const GemmArgs& g, hipStream_t s) {
