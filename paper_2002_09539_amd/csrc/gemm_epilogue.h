@@ -27,18 +27,21 @@ struct DwOut {
 
 __device__ __forceinline__ unsigned int ep_bf16(float f) { return bf16_bits_rne(f); }
 
-#ifndef OLS_EPILOGUE_NONTEMPORAL
-#define OLS_EPILOGUE_NONTEMPORAL 1
-#endif
-#if OLS_EPILOGUE_NONTEMPORAL
-__device__ __forceinline__ ep_f4 ep_load_stream(const ep_f4* p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ void ep_store_stream(ep_f4* p, ep_f4 v) { __builtin_nontemporal_store(v, p); }
-#else
-__device__ __forceinline__ ep_f4 ep_load_stream(const ep_f4* p) { return *p; }
-__device__ __forceinline__ void ep_store_stream(ep_f4* p, ep_f4 v) { *p = v; }
-#endif
+// State accesses.  Larger than the memory-side cache (256 MiB), the state streams through once per step: non-temporal
+// accesses keep it from displacing the operands in L2, and do not fill that cache either.  State that fits it (state_cached)
+// is better left there from one step to the next: plain accesses.  us per launch, non-temporal / plain (parameters and momentum
+// in place; workers x (in x out, batch), MB of both): 25 x (896 x 412, 48), 74: 47 / 30; 16 x (1144 x 988, 32), 145: 88 / 47; 12 x (2000
+// x 1000, 64), 192: 111 / 70; 16 x (3072 x 512, 128), 201: 107 / 96; 64 x (3072 x 1024, 64), 1611: 603 / 641.
+template <bool STREAM>
+__device__ __forceinline__ ep_f4 ep_load(const ep_f4* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+template <bool STREAM>
+__device__ __forceinline__ void ep_store(ep_f4* p, ep_f4 v) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 
 // One vector of 4 gradient entries at (row, col .. col + 3) of the layer's weight matrix.
+template <bool STREAM>
 __device__ __forceinline__ void dw_consume(const DwOut& o, int N, int row, int col, ep_f4 g, ep_f4 x, ep_f4 b, ep_f4 z) {
     const FusedUpdate& u = o.upd;
     const int64_t off = (int64_t)row * N + col;
@@ -50,9 +53,8 @@ __device__ __forceinline__ void dw_consume(const DwOut& o, int N, int row, int c
         xn[e] = local_step_elem(g[e], x[e], be, z[e], u.gamma, u.mu, u.alpha, mom, nest, pull);
         bn[e] = be;
     }
-    // the state streams through once per step: non-temporal accesses keep it from displacing the operands in L2
-    ep_store_stream((ep_f4*)(u.x_out + o.upd_base + off), xn);
-    if (u.mu != 0.0f) ep_store_stream((ep_f4*)(u.buf + o.upd_base + off), bn);
+    ep_store<STREAM>((ep_f4*)(u.x_out + o.upd_base + off), xn);
+    if (u.mu != 0.0f) ep_store<STREAM>((ep_f4*)(u.buf + o.upd_base + off), bn);
     if (u.shadow) {
         ep_u2 pk;
         pk.x = ep_bf16(xn[0]) | (ep_bf16(xn[1]) << 16);
@@ -73,7 +75,7 @@ template <int NVEC>
 struct DwState {
     ep_f4 x[NVEC], b[NVEC];
 };
-template <int BM, int BN, int RP, int THREADS, int PF>
+template <int BM, int BN, int RP, int THREADS, int PF, bool STREAM>
 __device__ __forceinline__ void dw_prefetch_state(DwState<BM * BN / 4 / THREADS>& st, const DwOut& o, int m0, int n0, int M, int N) {
     constexpr int kVecPerRow = BN / 4, kIters = RP * kVecPerRow / THREADS;
     if (PF == 0 || !o.upd.enabled) return;
@@ -83,14 +85,13 @@ __device__ __forceinline__ void dw_prefetch_state(DwState<BM * BN / 4 / THREADS>
         const int v = threadIdx.x + (k % kIters) * THREADS;
         const int row = m0 + (k / kIters) * RP + v / kVecPerRow, col = n0 + 4 * (v % kVecPerRow);
         const int64_t off = (row < M && col < N) ? (int64_t)row * N + col : 0;
-        st.x[k] = ep_load_stream((const ep_f4*)(o.upd.x_in + o.upd_base + off));
-        if (PF >= 2 && mom) st.b[k] = ep_load_stream((const ep_f4*)(o.upd.buf + o.upd_base + off));
+        st.x[k] = ep_load<STREAM>((const ep_f4*)(o.upd.x_in + o.upd_base + off));
+        if (PF >= 2 && mom) st.b[k] = ep_load<STREAM>((const ep_f4*)(o.upd.buf + o.upd_base + off));
     }
 }
-
 // stage: LDS scratch of at least RP * (BN + 4) floats, RP a multiple of 32 dividing BM.
 // (m0, n0): tile origin; (wm0, wn0): this wavefront's origin inside the tile; M, N: matrix extents.
-template <int BM, int BN, int TM, int TN, int RP, int THREADS, int PF = 0>
+template <int BM, int BN, int TM, int TN, int RP, int THREADS, bool STREAM, int PF = 0>
 __device__ __forceinline__ void dw_epilogue_staged(float* stage, const ep_f16 (&acc)[TM][TN], const DwOut& o, int m0,
                                                    int n0, int wm0, int wn0, int M, int N,
                                                    const DwState<BM * BN / 4 / THREADS>* st = nullptr) {
@@ -135,10 +136,10 @@ __device__ __forceinline__ void dw_epilogue_staged(float* stage, const ep_f16 (&
                     const int64_t off = ok ? (int64_t)rows[u] * N + cols[u] : 0;
                     const int k = (p0 / RP) * kIters + it + u;
                     if (PF >= 1) xv[u] = st->x[k];
-                    else xv[u] = ep_load_stream((const ep_f4*)(o.upd.x_in + o.upd_base + off));
+                    else xv[u] = ep_load<STREAM>((const ep_f4*)(o.upd.x_in + o.upd_base + off));
                     if (mom) {
                         if (PF >= 2) bv[u] = st->b[k];
-                        else bv[u] = ep_load_stream((const ep_f4*)(o.upd.buf + o.upd_base + off));
+                        else bv[u] = ep_load<STREAM>((const ep_f4*)(o.upd.buf + o.upd_base + off));
                     }
                     if (pull) zv[u] = *(const ep_f4*)(o.upd.z + o.col_base + off);
                 }
@@ -146,7 +147,7 @@ __device__ __forceinline__ void dw_epilogue_staged(float* stage, const ep_f16 (&
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 if (rows[u] < 0) continue;
-                if (fused) dw_consume(o, N, rows[u], cols[u], gv[u], xv[u], bv[u], zv[u]);
+                if (fused) dw_consume<STREAM>(o, N, rows[u], cols[u], gv[u], xv[u], bv[u], zv[u]);
                 else *(ep_f4*)(o.g + (int64_t)rows[u] * o.ldg + cols[u]) = gv[u];
             }
         }

@@ -79,7 +79,7 @@ struct GemmShape {
     static constexpr size_t kLdsBytes = (size_t)kLdsElems * sizeof(uint16_t);
 };
 
-template <int MODE, int BM, int BN, int BK, int DEPTH>
+template <int MODE, int BM, int BN, int BK, int DEPTH, bool STREAM>   // STREAM: DW, non-temporal accesses to the state
 __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
     constexpr int WM = BM / 2, WN = BN / 2;     // 2 x 2 wavefronts
     constexpr int TM = WM / 32, TN = WN / 32;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
         dw_out.upd = p.upd;
         dw_out.upd_base = (int64_t)group * p.upd.ld + p.upd_w_off;
         dw_out.col_base = p.upd_w_off;
-        dw_prefetch_state<BM, BN, kDwRP, kThreads, kDwPf>(dw_state, dw_out, m0, n0, p.M, p.N);
+        dw_prefetch_state<BM, BN, kDwRP, kThreads, kDwPf, STREAM>(dw_state, dw_out, m0, n0, p.M, p.N);
     }
 
     // DW only: the tiles of the first tile row also sum each column of B (a delta column over the batch),
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
         }
         // the gradient tile is staged through the (now idle) operand LDS, as many rows per pass as it holds
         static_assert(kDwFit >= 32 && BM % kDwRP == 0, "operand LDS too small to stage the gradient tile");
-        dw_epilogue_staged<BM, BN, TM, TN, kDwRP, kThreads, kDwPf>((float*)lds_all, acc, dw_out, m0, n0, wm0, wn0, p.M, p.N, &dw_state);
+        dw_epilogue_staged<BM, BN, TM, TN, kDwRP, kThreads, STREAM, kDwPf>((float*)lds_all, acc, dw_out, m0, n0, wm0, wn0, p.M, p.N, &dw_state);
     } else {
         // Epilogue of FWD / DA: the bf16 tile goes through LDS so that every lane then moves 16-byte vectors
         // of 8 consecutive columns (output, and the activations whose sign gates the delta).  Accumulator
@@ -580,7 +580,8 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     p.chunk = (int)((total + kXcds - 1) / kXcds);
     constexpr size_t lds = GemmShape<MODE, BM, BN, BK>::kLdsBytes;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    void (*kern)(GemmDevB) = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH>;
+    void (*kern)(GemmDevB) = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH, true>;
+    if (MODE == kDw && p.upd.cached) kern = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH, MODE != kDw>;
     unsigned threads = kThreads;
     if constexpr (MODE != kDw && BK == 64) {
         // full tiles and 32-bit lane offsets: the branch-free, interleaved kernel

@@ -48,7 +48,7 @@ struct GemmDev {
     HeadDwDev guest;     // DW: output-layer gradients computed by the first guest.blocks workgroups (0: none)
 };
 
-template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH, bool FULL>
+template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH, bool FULL, bool STREAM>
 __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDev p) {
     constexpr bool A_KC = MODE != kDw;   // FWD, DA: A[M][K];  DW: A[K][M]
     constexpr bool B_KC = MODE == kDa;   // DA: B[N][K];  FWD, DW: B[K][N]
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDev p) {
         o.upd = p.upd;
         o.upd_base = (int64_t)group * p.upd.ld + p.upd_w_off;
         o.col_base = p.upd_w_off;
-        dw_epilogue_staged<BM, BN, TM, TN, RP, kThreads>(lds_all, acc, o, m0, n0, wm0, wn0, p.M, p.N);
+        dw_epilogue_staged<BM, BN, TM, TN, RP, kThreads, STREAM>(lds_all, acc, o, m0, n0, wm0, wn0, p.M, p.N);
         return;
     }
 
@@ -339,7 +339,7 @@ struct DwFlag {
 // overlap, and the matrix work hides all but 6 us.  The cost of the operand loads is not their L2 traffic: a
 // generalisation of this kernel to 128 x 64 tiles (a quarter less operand traffic, two workgroups per compute unit,
 // identical bits) measured 96.8 us against 96.4 us for 64 x 64 tiles and is not in the tree.
-template <int SPG, bool PULL, bool MOM>
+template <int SPG, bool PULL, bool MOM, bool STREAM>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(OLS_DWP_WAVES)))
 void gemm_f32_dw_pipelined_kernel(GemmDev p) {
     constexpr int RING = 2;   // register sets of the operand ring
@@ -402,8 +402,8 @@ void gemm_f32_dw_pipelined_kernel(GemmDev p) {
     f4 sx[2], sb[MOM ? 2 : 1], sz[PULL ? 2 : 1];
     auto issue = [&](int set, const DwTile& d, int v) {
         const unsigned o = my_off + (unsigned)v * vec_step;
-        sx[set] = ep_load_stream((const ep_f4*)((const char*)(u.x_in + d.upd_base) + o));
-        if (MOM) sb[MOM ? set : 0] = ep_load_stream((const ep_f4*)((const char*)(u.buf + d.upd_base) + o));
+        sx[set] = ep_load<STREAM>((const ep_f4*)((const char*)(u.x_in + d.upd_base) + o));
+        if (MOM) sb[MOM ? set : 0] = ep_load<STREAM>((const ep_f4*)((const char*)(u.buf + d.upd_base) + o));
         if (PULL) sz[PULL ? set : 0] = *(const ep_f4*)((const char*)(u.z + d.col_base) + o);
     };
     auto consume = [&](int set, const DwTile& d, int v) {
@@ -417,8 +417,8 @@ void gemm_f32_dw_pipelined_kernel(GemmDev p) {
                                     u.nesterov != 0, PULL);
             bn[e] = be;
         }
-        ep_store_stream((ep_f4*)((char*)(u.x_out + d.upd_base) + o), xn);
-        if (MOM) ep_store_stream((ep_f4*)((char*)(u.buf + d.upd_base) + o), bn);
+        ep_store<STREAM>((ep_f4*)((char*)(u.x_out + d.upd_base) + o), xn);
+        if (MOM) ep_store<STREAM>((ep_f4*)((char*)(u.buf + d.upd_base) + o), bn);
     };
 
     f16v acc;
@@ -612,9 +612,13 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
                       (g.K % p.k_chunk) % q == 0 && g.lda < (1 << 22) && g.ldb < (1 << 22);
     const unsigned grid = (unsigned)(p.guest.blocks + p.chunk * kXcds);
     if constexpr (kCanFull) {
-        if (full) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, true><<<grid, kThreads, 0, s>>>(p);
+        if (full) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, true, true><<<grid, kThreads, 0, s>>>(p);
     }
-    if (!full) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false><<<grid, kThreads, 0, s>>>(p);
+    if (!full) {
+        // (only the weight gradient touches state)
+        if (MODE == kDw && p.upd.cached) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false, MODE != kDw><<<grid, kThreads, 0, s>>>(p);
+        else gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false, true><<<grid, kThreads, 0, s>>>(p);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_splitk_finish(p.partial, p.splits, g, s);
@@ -664,7 +668,12 @@ static hipError_t dw_pipelined_launch(const GemmArgs& g, hipStream_t s) {
     const int per_cu = g.K >= 128 ? OLS_DWP_WGS_PER_CU : 2 * OLS_DWP_WGS_PER_CU;
     p.wgs_per_xcd = p.chunk < 32 * per_cu ? p.chunk : 32 * per_cu;   // 32 compute units per XCD
     const unsigned grid = (unsigned)(p.guest.blocks + p.wgs_per_xcd * kXcds);
-#define OLS_DWP2(SPG, PULL, MOM) gemm_f32_dw_pipelined_kernel<SPG, PULL, MOM><<<grid, kThreads, 0, s>>>(p)
+// (with the pull-back the state streams through in any case: 5 - 10 x (3072 x 512, 128), tau 1, 2 % slower otherwise)
+#define OLS_DWP2(SPG, PULL, MOM)                                                                               \
+    do {                                                                                                       \
+        if (g.upd.cached) gemm_f32_dw_pipelined_kernel<SPG, PULL, MOM, PULL><<<grid, kThreads, 0, s>>>(p);     \
+        else gemm_f32_dw_pipelined_kernel<SPG, PULL, MOM, true><<<grid, kThreads, 0, s>>>(p);                  \
+    } while (0)
 #define OLS_DWP(SPG)                                                      \
     do {                                                                  \
         const bool mom = g.upd.mu != 0.0f;                                \

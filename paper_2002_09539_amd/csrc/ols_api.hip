@@ -982,6 +982,7 @@ FusedUpdate fused_update(ols_ctx* c, int src, int dst, bool pull) {
     u.nesterov = c->nesterov ? 1 : 0;
     u.pull = pull ? 1 : 0;
     u.enabled = 1;
+    u.cached = state_cached(c->m * c->ld, (u.buf ? 4 : 0) + (u.shadow ? 2 : 0), src == dst && c->tau >= 4);
     return u;
 }
 

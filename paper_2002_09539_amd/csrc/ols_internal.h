@@ -87,7 +87,18 @@ struct FusedUpdate {
     float gamma, mu, alpha;
     int nesterov, pull;
     int enabled;
+    int cached;         // the state is left in the memory-side cache (state_cached)
 };
+// Whether the arrays that an update reads and writes stay in the 256 MiB memory-side cache until the next one does: both replica
+// buffers and `more` bytes per element in 205 MB, which leaves room for the batch and the activations -- or, where rounds of four
+// steps or more rewrite one buffer in place most of the time, that buffer and the rest in 185 MB.  (Two arrays in place, alone:
+// plain accesses 8.4 - 8.5 TB/s up to 2 x 128 MiB and 5.4 from 2 x 192 MiB on, non-temporal ones 6.1 at every size.)  Two rounds, us,
+// non-temporal / plain, batch 64:  9 x (1024-1024-10, bf16), tau 4, 95 MB in place, 551 / 516;  14 x (784-800-400-10), 107 MB, tau 1
+// 304 / 283, tau 2 569 / 523, tau 4 1096 / 993;  21 of them, 160 MB, tau 4 1418 / 1363, tau 2 (not taken) 720 / 728;  26 x
+// (1024-1024-10), 220 MB (not taken), tau 4 1202 / 1193, 35 of them 1471 / 1514.
+inline bool state_cached(int64_t elements, int more, bool in_place) {
+    return elements * (8 + more) <= (int64_t)205000000 || (in_place && elements * (4 + more) <= (int64_t)185000000);
+}
 
 #if defined(__HIPCC__)
 }  // namespace ols
