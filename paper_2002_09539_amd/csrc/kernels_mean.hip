@@ -158,7 +158,7 @@ hipError_t launch_mean(const MeanArgs& a, hipStream_t s) {
 #define OLS_SPM_ROWS 16
 #endif
 constexpr int kSpmThreads = OLS_SPM_THREADS;
-template <bool WITH_STEP, bool MOM, bool NEST, bool ANCHOR_MOM>
+template <bool WITH_STEP, bool MOM, bool NEST, bool ANCHOR_MOM, bool STREAM>   // STREAM: non-temporal accesses to the rows (state_streams)
 __global__ __launch_bounds__(kSpmThreads) void step_pull_mean_kernel(const f4* __restrict__ g, const f4* x_in, f4* x_out,
                                                                   f4* buf, const f4* z_in, f4* z_out, f4* v, int m,
                                                                   int64_t n4, float gamma, float mu, float alpha,
@@ -174,9 +174,9 @@ __global__ __launch_bounds__(kSpmThreads) void step_pull_mean_kernel(const f4* _
         for (int r = 0; r < R; ++r) {
             if (i0 + r < m) {
                 const int64_t o = (int64_t)(i0 + r) * n4 + c;
-                vx[r] = __builtin_nontemporal_load(x_in + o);
-                if (WITH_STEP) vg[r] = __builtin_nontemporal_load(g + o);
-                if (WITH_STEP && MOM) vb[r] = __builtin_nontemporal_load(buf + o);
+                vx[r] = STREAM ? __builtin_nontemporal_load(x_in + o) : x_in[o];
+                if (WITH_STEP) vg[r] = STREAM ? __builtin_nontemporal_load(g + o) : g[o];
+                if (WITH_STEP && MOM) vb[r] = STREAM ? __builtin_nontemporal_load(buf + o) : buf[o];
             }
         }
 #pragma unroll
@@ -194,8 +194,12 @@ __global__ __launch_bounds__(kSpmThreads) void step_pull_mean_kernel(const f4* _
                         xo[e] = pull_back_elem(vx[r][e], zo[e], alpha);
                     }
                 }
-                __builtin_nontemporal_store(xo, x_out + o);
-                if (WITH_STEP && MOM) __builtin_nontemporal_store(bo, buf + o);
+                if (STREAM) __builtin_nontemporal_store(xo, x_out + o);
+                else x_out[o] = xo;
+                if (WITH_STEP && MOM) {
+                    if (STREAM) __builtin_nontemporal_store(bo, buf + o);
+                    else buf[o] = bo;
+                }
                 acc = acc + xo;
             }
         }
@@ -224,14 +228,13 @@ static void spm_dispatch(const StepPullMeanArgs& a, hipStream_t s) {
     const UpdateArgs& u = a.u;
     const int64_t n4 = u.ld / 4;
     const unsigned grid = (unsigned)((n4 + kSpmThreads - 1) / kSpmThreads);
-    if (a.v)
-        step_pull_mean_kernel<WITH_STEP, MOM, NEST, true><<<grid, kSpmThreads, 0, s>>>(
-            (const f4*)u.g, (const f4*)u.x_in, (f4*)u.x_out, (f4*)u.buf, (const f4*)u.z, (f4*)a.z_out, (f4*)a.v, u.m, n4,
-            u.gamma, u.mu, u.alpha, a.beta_z);
-    else
-        step_pull_mean_kernel<WITH_STEP, MOM, NEST, false><<<grid, kSpmThreads, 0, s>>>(
-            (const f4*)u.g, (const f4*)u.x_in, (f4*)u.x_out, (f4*)u.buf, (const f4*)u.z, (f4*)a.z_out, nullptr, u.m, n4,
-            u.gamma, u.mu, u.alpha, 0.0f);
+    auto start = [&](auto kern) {
+        kern<<<grid, kSpmThreads, 0, s>>>((const f4*)u.g, (const f4*)u.x_in, (f4*)u.x_out, (f4*)u.buf, (const f4*)u.z, (f4*)a.z_out, (f4*)a.v,
+                                          u.m, n4, u.gamma, u.mu, u.alpha, a.v ? a.beta_z : 0.0f);
+    };
+    const bool stream = state_streams(u.m, u.ld);
+    if (a.v) stream ? start(step_pull_mean_kernel<WITH_STEP, MOM, NEST, true, true>) : start(step_pull_mean_kernel<WITH_STEP, MOM, NEST, true, false>);
+    else stream ? start(step_pull_mean_kernel<WITH_STEP, MOM, NEST, false, true>) : start(step_pull_mean_kernel<WITH_STEP, MOM, NEST, false, false>);
 }
 
 // Emulated communication latency ahead of the anchor refresh (the delay that Section 2, arXiv 2002.09539 argues

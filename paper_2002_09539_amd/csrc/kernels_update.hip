@@ -24,9 +24,6 @@ typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 #ifndef OLS_UPDATE_UNROLL
 #define OLS_UPDATE_UNROLL 1
 #endif
-#ifndef OLS_UPDATE_NONTEMPORAL
-#define OLS_UPDATE_NONTEMPORAL 1
-#endif
 constexpr int kThreads = OLS_UPDATE_THREADS;
 // Workgroup size and 16-byte vectors per lane per array.  Measured on the d = 11.2 M, m = 16 stream (local
 // step, us): 64 threads x 1 -> 552, 128 x 1 -> 584, 256 x 1 -> 599, 256 x 2 -> 628, 256 x 4 -> 618,
@@ -34,13 +31,16 @@ constexpr int kThreads = OLS_UPDATE_THREADS;
 // Single-wavefront workgroups stream best: 6.5 TB/s.
 constexpr int kUnroll = OLS_UPDATE_UNROLL;
 
-#if OLS_UPDATE_NONTEMPORAL
-__device__ __forceinline__ f4 ld_stream(const f4* p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ void st_stream(f4* p, f4 v) { __builtin_nontemporal_store(v, p); }
-#else
-__device__ __forceinline__ f4 ld_stream(const f4* p) { return *p; }
-__device__ __forceinline__ void st_stream(f4* p, f4 v) { *p = v; }
-#endif
+// Non-temporal accesses where the arrays exceed the memory-side cache (STREAM, see state_streams), plain ones below.
+template <bool STREAM>
+__device__ __forceinline__ f4 ld_state(const f4* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+template <bool STREAM>
+__device__ __forceinline__ void st_state(f4* p, f4 v) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+__device__ __forceinline__ f4 ld_stream(const f4* p) { return ld_state<true>(p); }
+__device__ __forceinline__ void st_stream(f4* p, f4 v) { st_state<true>(p, v); }
 
 __device__ __forceinline__ unsigned int bf16_rne(float f) { return bf16_bits_rne(f); }
 __device__ __forceinline__ u2 pack_bf16x4(f4 v) {
@@ -58,7 +58,7 @@ __device__ __forceinline__ u2 pack_bf16x4(f4 v) {
 // workgroup looping over all replicas with z in registers reaches the algorithmic traffic but takes
 // 677 us -- row-wise streaming is what the memory system rewards, the extra z fetches are served by the
 // last-level cache.
-template <bool MOM, bool NEST, bool PULL, bool SHADOW>
+template <bool MOM, bool NEST, bool PULL, bool SHADOW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void step_kernel(const f4* __restrict__ g, const f4* x_in, f4* x_out,
                                                         f4* buf, const f4* __restrict__ z, u2* __restrict__ shadow,
                                                         int64_t n4, int m, float gamma, float mu, float alpha) {
@@ -70,9 +70,9 @@ __global__ __launch_bounds__(kThreads) void step_kernel(const f4* __restrict__ g
     for (int u = 0; u < kUnroll; ++u) {
         const int64_t c = c0 + u * kThreads;
         if (c < n4) {
-            vg[u] = ld_stream(g + row + c);
-            vx[u] = ld_stream(x_in + row + c);
-            if (MOM) vb[u] = ld_stream(buf + row + c);
+            vg[u] = ld_state<STREAM>(g + row + c);
+            vx[u] = ld_state<STREAM>(x_in + row + c);
+            if (MOM) vb[u] = ld_state<STREAM>(buf + row + c);
             if (PULL) vz[u] = z[c];
         }
     }
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(kThreads) void step_kernel(const f4* __restrict__ g
                 xo[e] = local_step_elem(vg[u][e], vx[u][e], b, PULL ? vz[u][e] : 0.0f, gamma, mu, alpha, MOM, NEST, PULL);
                 bo[e] = b;
             }
-            st_stream(x_out + row + c, xo);
-            if (MOM) st_stream(buf + row + c, bo);
+            st_state<STREAM>(x_out + row + c, xo);
+            if (MOM) st_state<STREAM>(buf + row + c, bo);
             if (SHADOW) shadow[row + c] = pack_bf16x4(xo);
         }
     }
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kThreads) void pull_kernel(f4* x, const f4* __restr
 
 // Stale-average synchronisation ("Related Works": a round's local updates are applied to the average of the models
 // of tau iterations before): x <- z + (x - snap), snap <- the new x; z is the average of the old snapshots.
-template <bool SHADOW>
+template <bool SHADOW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void stale_sync_kernel(f4* x, f4* snap, const f4* __restrict__ z,
                                                               u2* __restrict__ shadow, int64_t n4, int m) {
     const int64_t spans = (n4 + kThreads * kUnroll - 1) / (kThreads * kUnroll);
@@ -135,8 +135,8 @@ __global__ __launch_bounds__(kThreads) void stale_sync_kernel(f4* x, f4* snap, c
     for (int u = 0; u < kUnroll; ++u) {
         const int64_t c = c0 + u * kThreads;
         if (c < n4) {
-            vx[u] = ld_stream(x + row + c);
-            vs[u] = ld_stream(snap + row + c);
+            vx[u] = ld_state<STREAM>(x + row + c);
+            vs[u] = ld_state<STREAM>(snap + row + c);
             vz[u] = z[c];
         }
     }
@@ -147,8 +147,8 @@ __global__ __launch_bounds__(kThreads) void stale_sync_kernel(f4* x, f4* snap, c
             f4 xo;
 #pragma unroll
             for (int e = 0; e < 4; ++e) xo[e] = __fadd_rn(vz[u][e], __fsub_rn(vx[u][e], vs[u][e]));
-            st_stream(x + row + c, xo);
-            st_stream(snap + row + c, xo);
+            st_state<STREAM>(x + row + c, xo);
+            st_state<STREAM>(snap + row + c, xo);
             if (SHADOW) shadow[row + c] = pack_bf16x4(xo);
         }
     }
@@ -177,15 +177,13 @@ static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 template <bool MOM, bool NEST, bool PULL>
 static void dispatch_shadow(const UpdateArgs& a, unsigned grid, hipStream_t s) {
-    const int64_t n4 = a.ld / 4;
-    if (a.shadow)
-        step_kernel<MOM, NEST, PULL, true><<<grid, kThreads, 0, s>>>((const f4*)a.g, (const f4*)a.x_in, (f4*)a.x_out,
-                                                                    (f4*)a.buf, (const f4*)a.z, (u2*)a.shadow, n4,
-                                                                    a.m, a.gamma, a.mu, a.alpha);
-    else
-        step_kernel<MOM, NEST, PULL, false><<<grid, kThreads, 0, s>>>((const f4*)a.g, (const f4*)a.x_in,
-                                                                     (f4*)a.x_out, (f4*)a.buf, (const f4*)a.z,
-                                                                     nullptr, n4, a.m, a.gamma, a.mu, a.alpha);
+    auto start = [&](auto kern) {
+        kern<<<grid, kThreads, 0, s>>>((const f4*)a.g, (const f4*)a.x_in, (f4*)a.x_out, (f4*)a.buf, (const f4*)a.z, (u2*)a.shadow, a.ld / 4,
+                                       a.m, a.gamma, a.mu, a.alpha);
+    };
+    const bool stream = state_streams(a.m, a.ld);
+    if (a.shadow) stream ? start(step_kernel<MOM, NEST, PULL, true, true>) : start(step_kernel<MOM, NEST, PULL, true, false>);
+    else stream ? start(step_kernel<MOM, NEST, PULL, false, true>) : start(step_kernel<MOM, NEST, PULL, false, false>);
 }
 
 static bool grid_for(int m, int64_t ld, unsigned* grid) {
@@ -237,9 +235,10 @@ hipError_t launch_stale_sync(float* x, float* snap, const float* z, uint16_t* sh
     if (!aligned16(x) || !aligned16(snap) || !aligned16(z) || !aligned16(shadow)) return hipErrorInvalidValue;
     unsigned grid;
     if (!grid_for(m, ld, &grid)) return hipErrorInvalidValue;
-    const int64_t n4 = ld / 4;
-    if (shadow) stale_sync_kernel<true><<<grid, kThreads, 0, s>>>((f4*)x, (f4*)snap, (const f4*)z, (u2*)shadow, n4, m);
-    else stale_sync_kernel<false><<<grid, kThreads, 0, s>>>((f4*)x, (f4*)snap, (const f4*)z, nullptr, n4, m);
+    auto start = [&](auto kern) { kern<<<grid, kThreads, 0, s>>>((f4*)x, (f4*)snap, (const f4*)z, (u2*)shadow, ld / 4, m); };
+    const bool stream = state_streams(m, ld);
+    if (shadow) stream ? start(stale_sync_kernel<true, true>) : start(stale_sync_kernel<true, false>);
+    else stream ? start(stale_sync_kernel<false, true>) : start(stale_sync_kernel<false, false>);
     return hipGetLastError();
 }
 

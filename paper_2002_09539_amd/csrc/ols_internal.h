@@ -12,6 +12,13 @@ namespace ols {
 // themselves live in the matching kernels_*.hip file.  All pointers are device pointers.
 // ---------------------------------------------------------------------------------------------
 
+// Whether the kernels that stream over [m][ld] state use non-temporal accesses.  Up to 25 million elements, parameters, momenta
+// and gradients are worth leaving in the 256 MiB memory-side cache.  Two rounds, non-temporal over plain, by millions of elements
+// (8 workers, momentum; steps alone with pull-back and refresh | stale-average rule):
+//   tau 1   3: 1.10 | 1.06   9: 1.07 | 1.10   18: 1.06 | 1.09   25: 1.00 | 0.98   36: 1.02 | 0.97
+//   tau 4   3: 1.10 | 1.06   9: 1.09 | 1.11   18: 1.07 | 1.08   25: 1.07 | 1.05   36: 0.93 | 0.92
+inline bool state_streams(int64_t m, int64_t ld) { return m * ld > 25000000; }
+
 struct UpdateArgs {
     const float* g;     // [m][ld] gradients
     const float* x_in;  // [m][ld] parameters read
