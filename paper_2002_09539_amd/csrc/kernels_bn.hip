@@ -23,6 +23,8 @@
 // each); the first
 // normalisation's backward sums formed in the epilogue of the delta convolution that produces its gradient (the
 // convolution grows by the 86 us that the saved pass over gradient and input took beyond its own share).
+#include <type_traits>
+
 #include "fast_div.h"
 #include "gemm_bf16_tile.h"
 #include "ols_internal.h"
@@ -47,6 +49,11 @@ __host__ __device__ inline int bn_ranges(int groups, int P) {
     if (r < fill) r = fill;
     return r < 1 ? 1 : (r > 256 ? 256 : r);
 }
+
+// Loads of the streamed tensors: non-temporal where they exceed what the memory-side cache holds on to from one kernel of the
+// block to the next (STREAM, see tensors_stream), plain below.
+template <bool STREAM>
+__device__ __forceinline__ f4 ld_tensor(const f4* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
 
 // Sums over the stripes of a workgroup, in stripe order; result valid for stripe 0.
 __device__ __forceinline__ f4 reduce_stripes(f4 v, f4* lds, int c4n, int stripes) {
@@ -222,6 +229,7 @@ __device__ __forceinline__ void store_padded_bf16(const PaddedOut& po, int g, un
 }
 
 // out = act(gamma (z - mean) inv_std + beta (+ shortcut))
+template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restrict__ z, int64_t s_z,
                                                             const float* __restrict__ stats, const float* __restrict__ gamma,
                                                             const float* __restrict__ beta, int64_t s_par,
@@ -237,11 +245,11 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
     const f4 istd = *(const f4*)(stats + ((int64_t)g * 2 + 1) * C + c);
     const f4 ga = *(const f4*)(gamma + (int64_t)g * s_par + c);
     const f4 be = *(const f4*)(beta + (int64_t)g * s_par + c);
-    const f4 zv = __builtin_nontemporal_load((const f4*)(z + (int64_t)g * s_z) + v);
+    const f4 zv = ld_tensor<STREAM>((const f4*)(z + (int64_t)g * s_z) + v);
     f4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = __fmaf_rn(ga[e], (zv[e] - mean[e]) * istd[e], be[e]);
-    if (shortcut) o = o + __builtin_nontemporal_load((const f4*)(shortcut + (int64_t)g * s_sc) + v);
+    if (shortcut) o = o + ld_tensor<STREAM>((const f4*)(shortcut + (int64_t)g * s_sc) + v);
     if (relu) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = fmaxf(o[e], 0.0f);
@@ -259,6 +267,7 @@ __global__ __launch_bounds__(kThreads) void bn_apply_kernel(const float* __restr
 // bytes are not read again for them (16 x 128 x 32 x 32 x 64: a pass of 104 us and a launch less per backward call).
 // A workgroup owns 64 pixels: lane = (channel quad, stripe), four pixels per lane in flight, stripes combined in stripe order.
 constexpr int kTailPixels = 64, kTailSums = 3;
+template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void bn_tail_kernel(const float* __restrict__ z, int64_t s_z, const float* __restrict__ stats,
                                                            const float* __restrict__ gamma, const float* __restrict__ beta,
                                                            int64_t s_par, const float* __restrict__ shortcut, int64_t s_sc,
@@ -287,8 +296,8 @@ __global__ __launch_bounds__(kThreads) void bn_tail_kernel(const float* __restri
             for (int t = 0; t < 4; ++t) {
                 const int p = p0 + q0 + t * stripes;
                 const bool in = q0 + t * stripes < kTailPixels && p < P;
-                zv[t] = in ? __builtin_nontemporal_load((const f4*)(Z + (int64_t)p * C)) : zero;
-                sv[t] = in && S ? __builtin_nontemporal_load((const f4*)(S + (int64_t)p * C)) : zero;
+                zv[t] = in ? ld_tensor<STREAM>((const f4*)(Z + (int64_t)p * C)) : zero;
+                sv[t] = in && S ? ld_tensor<STREAM>((const f4*)(S + (int64_t)p * C)) : zero;
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -344,10 +353,10 @@ struct PooledDelta {
 // Where the backward kernels take the gradient at the normalised output from (a template parameter: a branch inside
 // their loops would serialise the loads of one pixel behind the other's)
 enum { kFromDy = 0, kFromGate = 1, kFromSign = 2 };
-template <int SRC>
+template <int SRC, bool STREAM>
 __device__ __forceinline__ f4 delta_at(const float* __restrict__ D, const PooledDelta& pd, int g, unsigned pixel, int C, int c4) {
     if constexpr (SRC == kFromDy) {
-        return __builtin_nontemporal_load((const f4*)(D + (int64_t)pixel * C + 4 * c4));
+        return ld_tensor<STREAM>((const f4*)(D + (int64_t)pixel * C + 4 * c4));
     } else {
         const f4 d = *(const f4*)(pd.dpool + (int64_t)g * pd.s_dp + (int64_t)fast_div(pixel, pd.div_pos) * C + 4 * c4);
         f4 o;
@@ -356,7 +365,7 @@ __device__ __forceinline__ f4 delta_at(const float* __restrict__ D, const Pooled
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = (bits >> e) & 1u ? d[e] * pd.scale : 0.0f;
         } else {
-            const f4 a = __builtin_nontemporal_load((const f4*)(pd.gate + (int64_t)g * pd.s_gate + (int64_t)pixel * C + 4 * c4));
+            const f4 a = ld_tensor<STREAM>((const f4*)(pd.gate + (int64_t)g * pd.s_gate + (int64_t)pixel * C + 4 * c4));
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = a[e] > 0.0f ? d[e] * pd.scale : 0.0f;
         }
@@ -365,7 +374,7 @@ __device__ __forceinline__ f4 delta_at(const float* __restrict__ D, const Pooled
 }
 
 // part[group][range][2][C]: sum dy, sum dy xhat over the range
-template <int SRC>
+template <int SRC, bool STREAM>
 __global__ __launch_bounds__(kThreads) void bn_bwd_partial_kernel(const float* __restrict__ dy, int64_t s_dy,
                                                                   const float* __restrict__ z, int64_t s_z,
                                                                   const float* __restrict__ stats, float* part, int P, int C,
@@ -388,8 +397,8 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_partial_kernel(const float* _
             for (int t = 0; t < 4; ++t) {
                 const int p = p0 + t * stripes;
                 const unsigned pc = (unsigned)(p < p_hi ? p : p0);       // a lane past the range re-reads its first pixel
-                d[t] = delta_at<SRC>(D, pd, g, pc, C, c4);
-                zv[t] = __builtin_nontemporal_load((const f4*)(Z + (int64_t)pc * C + 4 * c4));
+                d[t] = delta_at<SRC, STREAM>(D, pd, g, pc, C, c4);
+                zv[t] = ld_tensor<STREAM>((const f4*)(Z + (int64_t)pc * C + 4 * c4));
             }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -479,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_pooled_kernel(const float* __
 }
 
 // dz = gamma inv_std (dy - s1 / P - xhat s2 / P), written over dy -- or as a bf16 operand (see PaddedOut)
-template <int SRC>
+template <int SRC, bool STREAM>
 __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(float* dy, int64_t s_dy, const float* __restrict__ z,
                                                                 int64_t s_z, const float* __restrict__ stats,
                                                                 const float* __restrict__ sums,
@@ -496,8 +505,8 @@ __global__ __launch_bounds__(kThreads) void bn_bwd_apply_kernel(float* dy, int64
     const f4 s2 = *(const f4*)(sums + ((int64_t)g * 2 + 1) * C + c);
     const f4 ga = *(const f4*)(gamma + (int64_t)g * s_par + c);
     f4* D = (f4*)(dy + (int64_t)g * s_dy) + v;
-    const f4 d = delta_at<SRC>(dy + (int64_t)g * s_dy, pd, g, pixel, C, c / 4);
-    const f4 xh = (__builtin_nontemporal_load((const f4*)(z + (int64_t)g * s_z) + v) - mean) * istd;
+    const f4 d = delta_at<SRC, STREAM>(dy + (int64_t)g * s_dy, pd, g, pixel, C, c / 4);
+    const f4 xh = (ld_tensor<STREAM>((const f4*)(z + (int64_t)g * s_z) + v) - mean) * istd;
     f4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = ga[e] * istd[e] * (d[e] - s1[e] * inv_count - xh[e] * (s2[e] * inv_count));
@@ -536,6 +545,7 @@ hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
     if (!aligned16(a.z) || !aligned16(a.out) || !aligned16(a.stats) || !aligned16(a.part) || !aligned16(a.gamma) ||
         !aligned16(a.beta) || !aligned16(a.shortcut) || a.s_z % 4 || a.s_out % 4 || a.s_par % 4 || a.s_sc % 4)
         return hipErrorInvalidValue;
+    const bool stream = tensors_stream(a.groups, (int64_t)a.P * a.C);
     hipError_t e;
     if (a.wave_part) {   // the producer of z left per-wavefront statistics: z is not read for them
         if (a.waves < 1 || !aligned16(a.wave_part) || a.C % kWaveStatChannels) return hipErrorInvalidValue;
@@ -559,7 +569,8 @@ hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
     }
     if (a.pool_part) {   // the block's tail: sign bytes and partial sums instead of the activation
         if (!a.sign || a.positions < kTailPixels || a.P % a.positions != 0 || !aligned16(a.pool_part) || a.C > 4 * kThreads) return hipErrorInvalidValue;
-        bn_tail_kernel<<<dim3((unsigned)((a.P + kTailPixels - 1) / kTailPixels), (unsigned)a.groups), kThreads, 0, s>>>(
+        auto kern = stream ? bn_tail_kernel<true> : bn_tail_kernel<false>;
+        kern<<<dim3((unsigned)((a.P + kTailPixels - 1) / kTailPixels), (unsigned)a.groups), kThreads, 0, s>>>(
             a.z, a.s_z, a.stats, a.gamma, a.beta, a.s_par, a.shortcut, a.s_sc, a.sign, a.s_sign, a.pool_part, a.P, a.C, a.relu, a.positions,
             make_div((unsigned)a.positions));
         return hipGetLastError();
@@ -569,7 +580,8 @@ hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
     if (!vec_grid(vecs, &blocks)) return hipErrorInvalidValue;
     PaddedOut po = {};
     if (!padded_out(a, vecs, &po)) return hipErrorInvalidValue;
-    bn_apply_kernel<<<dim3(blocks, (unsigned)a.groups), kThreads, 0, s>>>(a.z, a.s_z, a.stats, a.gamma, a.beta, a.s_par, a.shortcut,
+    auto kern = stream ? bn_apply_kernel<true> : bn_apply_kernel<false>;
+    kern<<<dim3(blocks, (unsigned)a.groups), kThreads, 0, s>>>(a.z, a.s_z, a.stats, a.gamma, a.beta, a.s_par, a.shortcut,
                                                                           a.s_sc, a.out, a.s_out, (unsigned)vecs, a.C, a.relu, make_div((unsigned)(a.C / 4)), po);
     return hipGetLastError();
 }
@@ -589,7 +601,16 @@ hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s) {
         pd.div_pos = make_div((unsigned)a.positions);
     }
     const int src = a.sign ? kFromSign : a.gate ? kFromGate : kFromDy;
-    auto apply = src == kFromSign ? bn_bwd_apply_kernel<kFromSign> : src == kFromGate ? bn_bwd_apply_kernel<kFromGate> : bn_bwd_apply_kernel<kFromDy>;
+    auto pick = [&](auto st) {
+        constexpr bool S = decltype(st)::value;
+        return src == kFromSign ? bn_bwd_apply_kernel<kFromSign, S> : src == kFromGate ? bn_bwd_apply_kernel<kFromGate, S> : bn_bwd_apply_kernel<kFromDy, S>;
+    };
+    auto pick_partial = [&](auto st) {
+        constexpr bool S = decltype(st)::value;
+        return src == kFromGate ? bn_bwd_partial_kernel<kFromGate, S> : bn_bwd_partial_kernel<kFromDy, S>;
+    };
+    const bool stream = tensors_stream(a.groups, (int64_t)a.P * a.C);
+    auto apply = stream ? pick(std::true_type()) : pick(std::false_type());
     const dim3 final_grid((unsigned)((a.C + kFinalChannels - 1) / kFinalChannels), (unsigned)a.groups);
     hipError_t e;
     if (a.sign) {   // the forward pass's tail left what the sums need of z
@@ -598,7 +619,7 @@ hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s) {
                                                              a.g_beta_off, a.C, a.P / a.positions);
     } else {
         const int ranges = bn_ranges(a.groups, a.P);
-        auto partial = src == kFromGate ? bn_bwd_partial_kernel<kFromGate> : bn_bwd_partial_kernel<kFromDy>;
+        auto partial = stream ? pick_partial(std::true_type()) : pick_partial(std::false_type());
         partial<<<dim3((unsigned)ranges, (unsigned)a.groups), kThreads, 0, s>>>(a.dy, a.s_dy, a.z, a.s_z, a.stats, a.part, a.P, a.C, ranges, pd);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

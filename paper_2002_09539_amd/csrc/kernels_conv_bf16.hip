@@ -715,6 +715,7 @@ __device__ __forceinline__ void kernel_images(const KernelImages& im, int unit, 
 }
 
 constexpr int kPadCastFly = 2;   // 16-byte output vectors per lane
+template <bool STREAM>   // non-temporal loads of the batch (tensors_stream)
 __global__ __launch_bounds__(kThreads) void pad_cast_bf16_kernel(const float* __restrict__ src, int64_t s_src,
                                                                  uint16_t* __restrict__ dst, int64_t s_dst, unsigned vecs, int H,
                                                                  int W, int C, FastDiv div_c8, FastDiv div_per, FastDiv div_wp,
@@ -737,8 +738,8 @@ __global__ __launch_bounds__(kThreads) void pad_cast_bf16_kernel(const float* __
         img[t] = v < vecs && y >= 1 && y <= (unsigned)H && x >= 1 && x <= (unsigned)W;
         if (img[t]) {
             const f4* S = (const f4*)(src + (int64_t)g * s_src + ((int64_t)(n * H + y - 1) * W + (x - 1)) * C) + 2 * cv;
-            lo[t] = __builtin_nontemporal_load(S);
-            hi[t] = __builtin_nontemporal_load(S + 1);
+            lo[t] = STREAM ? __builtin_nontemporal_load(S) : S[0];
+            hi[t] = STREAM ? __builtin_nontemporal_load(S + 1) : S[1];
         }
     }
 #pragma unroll
@@ -1074,7 +1075,8 @@ hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, 
     const int64_t blocks = (vecs + kPadCastFly * kThreads - 1) / (kPadCastFly * kThreads);
     KernelImages im = {{wa, wb, wb}, s_w, images, groups, C};
     const int64_t image_blocks = 3 * 9 * (int64_t)(C / kCB) * (C / kCB);
-    pad_cast_bf16_kernel<<<dim3((unsigned)(blocks + image_blocks), (unsigned)groups), kThreads, 0, s>>>(
+    auto kern = tensors_stream(groups, (int64_t)B * H * W * C) ? pad_cast_bf16_kernel<true> : pad_cast_bf16_kernel<false>;
+    kern<<<dim3((unsigned)(blocks + image_blocks), (unsigned)groups), kThreads, 0, s>>>(
         src, s_src, dst, s_dst, (unsigned)vecs, H, W, C, make_div((unsigned)(C / 8)), make_div((unsigned)((H + 2) * (W + 2))),
         make_div((unsigned)(W + 2)), im, (unsigned)image_blocks);
     return hipGetLastError();

@@ -213,6 +213,11 @@ struct HeadArgs {
 };
 hipError_t launch_head_fwd(const HeadArgs& a, hipStream_t s);
 hipError_t launch_head_bwd(const HeadArgs& a, hipStream_t s);
+// Whether the block's streaming kernels read activation tensors of groups x elements floats non-temporally: above 48 MB each.
+// Two rounds, non-temporal over plain, bf16 normalised blocks by MB per tensor: 8: 1.05, 14: 1.06, 16: 1.06, 29: 1.06, 35: 1.05, 42:
+// 1.01, 57: 0.99, 76: 1.01, 120: 1.00.
+inline bool tensors_stream(int64_t groups, int64_t elements) { return groups * elements * 4 > 48000000; }
+
 // 3 x 3 convolutions (stride 1, zero padding 1) grouped over the workers; activations [group][B H W][C] (channel
 // contiguous), kernels [group][9][C][C] as (tap, input channel, output channel).  C a multiple of 16.
 struct ConvArgs {
