@@ -610,14 +610,17 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
 // times as many units (forward / delta, us per launch averaged over the layers, batch x widths: 6 workers 72 x
 // 1032-520-264 18.1 -> 10.4 / 12.7 -> 7.7; 2 workers 64 x 512-256 13.3 -> 7.6; 16 workers 128 x 1024-512 15.4 -> 10.6; 4 workers 256 x
 // 3072-2048-1024 45.7 -> 23.3 / 20.9 -> 13.8; with exactly 256 tiles, 32 workers 128 x 1024-1024, 18.6 -> 22.9: not taken).
-// The contraction order is the same in every tile shape, and so are the bits.
+// The contraction order is the same in every tile shape, and so are the bits.  The smallest launches take the kernel without LDS
+// tiles (kernels_gemm_small.hip), whose sums of four K shares round differently in their last bits.
 static bool few_tiles(const GemmArgs& g) { return (int64_t)g.groups * ((g.M + 127) / 128) * ((g.N + 127) / 128) < 256; }
 hipError_t launch_gemm_bf16_fwd(const GemmArgs& g, hipStream_t s) {
+    if (gemm_small_bf16_fits(g, true)) return launch_gemm_small_bf16_fwd(g, s);
     if (few_tiles(g)) return gemm_launch<kFwd, 64, 64, 64, 2>(g, s);
     if (g.M > 128) return gemm_launch<kFwd, 256, 128, 64, 2>(g, s);
     return gemm_launch<kFwd, 128, 128, 64, 2>(g, s);
 }
 hipError_t launch_gemm_bf16_da(const GemmArgs& g, hipStream_t s) {
+    if (gemm_small_bf16_fits(g, false)) return launch_gemm_small_bf16_da(g, s);
     if (few_tiles(g)) return gemm_launch<kDa, 64, 64, 64, 2>(g, s);
     if (g.M > 128) return gemm_launch<kDa, 256, 128, 64, 2>(g, s);
     return gemm_launch<kDa, 128, 128, 64, 2>(g, s);

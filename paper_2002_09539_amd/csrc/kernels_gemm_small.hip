@@ -150,6 +150,139 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
     }
 }
 
+// The same for bf16 operands, fp32 accumulation and bf16 results (v_mfma_f32_16x16x32_bf16: lane l of a fragment holds indices
+// 8 (l / 16) .. + 7 of a step of 32).  A tile is 32 x 32; its two column blocks are interleaved (columns 2 (l % 16) and + 1), so
+// that the forward pass, whose weights are contiguous along the columns, takes both blocks' fragments from eight dwords of
+// neighbouring columns and puts them together with byte permutations, and results leave as pairs.  Up to six steps a round trip
+// (a step is ten loads in the forward pass).
+//
+// us per launch, 64 x 64 tiles of kernels_gemm_bf16.hip, whose time is their chain of slices through LDS / here:
+//   workers x (M x N x K)     forward       delta
+//   6 x (24 x 88 x 112)       3.5 / 2.7     3.3 / 2.8
+//   6 x (72 x 264 x 520)      6.4 / 4.0     6.0 / 3.7
+//   6 x (72 x 520 x 264)      5.1 / 3.9     4.9 / 3.8
+//   6 x (72 x 520 x 1032)     9.2 / 6.7     8.2 / 7.4
+//   2 x (32 x 168 x 2224)    15.1 / 7.0    12.6 / 8.0
+//   24 x (224 x 168 x 120)    4.4 / 3.9     4.4 / 3.8
+struct SmallDevB {
+    const uint16_t* a;
+    const uint16_t* b;
+    uint16_t* c;
+    const float* bias;
+    const uint16_t* mask;
+    int64_t sa, sb, sc, sbias, smask;
+    int M, N, K, lda, ldb, ldc;
+    int tiles_m, tiles_n, total_tiles, chunk;
+};
+
+template <int MODE, int S>
+__global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) {
+    __shared__ float red[kW][2][2][256];   // [wavefront][row block][column block][register, lane]
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    const int tile = xcd * p.chunk + slot;
+    if (tile >= p.total_tiles) return;
+    const int per_group = p.tiles_m * p.tiles_n, group = tile / per_group;
+    const int m0 = tile % per_group / p.tiles_n * 32, n0 = tile % p.tiles_n * 32;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, l16 = lane % 16, k8 = lane / 16 * 8;
+    const int col = n0 + 2 * l16;   // N is a multiple of eight: the pair is inside or outside together
+
+    // the epilogue's inputs come first: thread t finishes the pairs of row blocks 0 and 1 at (register t / 64, lane t % 64)
+    const int row0 = m0 + 4 * (lane / 16) + wave;
+    float bias[2] = {0.0f, 0.0f};
+    unsigned gate[2] = {0u, 0u};
+    if (col < p.N) {
+        if constexpr (MODE == kFwd) {
+            bias[0] = p.bias[(int64_t)group * p.sbias + col];
+            bias[1] = p.bias[(int64_t)group * p.sbias + col + 1];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (row0 + 16 * i < p.M) gate[i] = *(const unsigned*)(p.mask + (int64_t)group * p.smask + (int64_t)(row0 + 16 * i) * p.ldc + col);
+        }
+    }
+
+    const rsrc_t a_rs = make_rsrc(p.a + (int64_t)group * p.sa, (unsigned)((p.M - 1) * p.lda + p.K) * 2u);
+    const rsrc_t b_rs = make_rsrc(p.b + (int64_t)group * p.sb, (unsigned)(MODE == kFwd ? (p.K - 1) * p.ldb + p.N : (p.N - 1) * p.ldb + p.K) * 2u);
+    constexpr unsigned kOutside = 0x80000000u;   // beyond every range
+    struct Step { u4 a[2], b[2]; };   // b: FWD, rows k .. k + 7 of the column pair; DA, eight indices of either column
+    auto load = [&](Step& r, int step) {
+        const int k = 32 * step + k8;
+        const bool in = k < p.K;                 // K is a multiple of eight
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int row = m0 + 16 * i + l16;
+            r.a[i] = buf_load(a_rs, in && row < p.M ? 2u * (unsigned)(row * p.lda + k) : kOutside, 0u);
+        }
+        if constexpr (MODE == kFwd) {
+            const unsigned off = in && col < p.N ? 2u * (unsigned)(k * p.ldb + col) : kOutside;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r.b[e / 4][e % 4] = __builtin_amdgcn_raw_buffer_load_b32(b_rs, (int)(off + 2u * (unsigned)(e * p.ldb)), 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) r.b[j] = buf_load(b_rs, in && col < p.N ? 2u * (unsigned)((col + j) * p.ldb + k) : kOutside, 0u);
+        }
+    };
+    f4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    auto mfma = [&](const Step& r) {
+        u4 fb[2];
+        if constexpr (MODE == kFwd) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const unsigned lo = r.b[w / 2][2 * (w % 2)], hi = r.b[w / 2][2 * (w % 2) + 1];   // rows k + 2 w and k + 2 w + 1
+                fb[0][w] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+                fb[1][w] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+            }
+        } else {
+            fb[0] = r.b[0];
+            fb[1] = r.b[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.a[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0, 0);
+    };
+    const int steps = (p.K + 31) / 32;
+    for (int s0 = wave; s0 < steps; s0 += S * kW) {
+        Step r[S];
+#pragma unroll
+        for (int t = 0; t < S; ++t) load(r[t], s0 + t * kW);   // (steps past the end: zeros, no traffic)
+#pragma unroll
+        for (int t = 0; t < S; ++t) mfma(r[t]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave][i][j][64 * r + lane] = acc[i][j][r];
+    __syncthreads();
+    if (col >= p.N) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = row0 + 16 * i;
+        if (row >= p.M) continue;
+        float v[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            v[j] = red[0][i][j][threadIdx.x];
+#pragma unroll
+            for (int w = 1; w < kW; ++w) v[j] += red[w][i][j][threadIdx.x];
+            if constexpr (MODE == kFwd) v[j] = fmaxf(v[j] + bias[j], 0.0f);
+        }
+        unsigned o = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{v[0], v[1]}, bf16x2));   // to nearest even
+        if constexpr (MODE == kDa) {   // a bf16 is positive iff its sign bit is clear and it is not zero
+            const unsigned lo = gate[i] & 0xFFFFu, hi = gate[i] >> 16;
+            o &= (lo != 0u && lo < 0x8000u ? 0xFFFFu : 0u) | (hi != 0u && hi < 0x8000u ? 0xFFFF0000u : 0u);
+        }
+        *(unsigned*)(p.c + (int64_t)group * p.sc + (int64_t)row * p.ldc + col) = o;
+    }
+}
+
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 }  // namespace
@@ -227,5 +360,52 @@ static hipError_t small_launch(int mode, const GemmArgs& g, hipStream_t s) {
 }
 hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s) { return small_launch(kFwd, g, s); }
 hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s) { return small_launch(kDa, g, s); }
+
+// The bf16 rule, from both sides measured on 120 shapes (2 - 61 workers, M 16 - 250, N 64 - 2000, K 64 - 3000): work in steps of 32
+// indices of a 32 x 32 tile.  Forward up to 8,000, where it is faster on every shape (1.07 - 2.3 times), and up to 15,000 from K = 640
+// on (1.01 - 1.44 times; shorter contractions of that size lose: 14 x (168 x 536 x 192), 8,570, 5.5 and 6.0; a step of
+// 3 x 2016-512-1264-4 at batch 208, whose second layer is 13,440 with K = 512, 2 % of its time).
+// Delta up to 7,000 (1.02 - 1.7 times), up to 15,000 from K = 1024 on (6 x (72 x 520 x 1032), 10,100: 8.2 and 7.4; 4 x (32 x 1928 x
+// 1872), 14,400: 11.4 and 7.8; but 6 x (224 x 608 x 608), 15,200: 6.3 and 9.3).
+static int64_t small_tiles_bf16(int groups, int M, int N) { return (int64_t)groups * ((M + 31) / 32) * ((N + 31) / 32); }
+bool gemm_small_bf16_fits(const GemmArgs& g, bool fwd) {
+    const int64_t work = small_tiles_bf16(g.groups, g.M, g.N) * ((g.K + 31) / 32);
+    const int64_t most = fwd ? (g.K >= 640 ? 15000 : 8000) : (g.K >= 1024 ? 15000 : 7000);
+    return work <= most && small_offsets((int64_t)g.M * g.lda, (int64_t)(fwd ? g.K : g.N) * g.ldb);
+}
+
+template <int MODE>
+static hipError_t small_bf16(const GemmArgs& g, hipStream_t s) {
+    constexpr bool fwd = MODE == kFwd;
+    if (!g.a || !g.b || !g.c || g.groups < 1 || g.M < 1 || g.N < 1 || g.K < 1 || (fwd ? !g.bias : !g.mask)) return hipErrorInvalidValue;
+    if (!aligned16(g.a) || !aligned16(g.b) || !aligned16(g.c) || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || g.sa % 8 || g.sb % 8 || g.sc % 8 || g.K % 8 || g.N % 8)
+        return hipErrorInvalidValue;
+    if (!fwd && (!aligned16(g.mask) || g.smask % 8)) return hipErrorInvalidValue;
+    if (g.lda < g.K || g.ldb < (fwd ? g.N : g.K) || g.ldc < g.N) return hipErrorInvalidValue;
+    if (!small_offsets((int64_t)g.M * g.lda, (int64_t)(fwd ? g.K : g.N) * g.ldb)) return hipErrorInvalidValue;
+    SmallDevB p = {};
+    p.a = (const uint16_t*)g.a; p.b = (const uint16_t*)g.b; p.c = (uint16_t*)g.c; p.bias = g.bias; p.mask = (const uint16_t*)g.mask;
+    p.sa = g.sa; p.sb = g.sb; p.sc = g.sc; p.sbias = g.sbias; p.smask = g.smask;
+    p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
+    p.tiles_m = (g.M + 31) / 32;
+    p.tiles_n = (g.N + 31) / 32;
+    const int64_t total = small_tiles_bf16(g.groups, g.M, g.N);
+    if (total > (1 << 30)) return hipErrorInvalidValue;
+    p.total_tiles = (int)total;
+    p.chunk = (int)((total + kXcds - 1) / kXcds);
+    const unsigned grid = (unsigned)(p.chunk * kXcds);
+    const int per = ((g.K + 31) / 32 + kW - 1) / kW, trips = (per + 5) / 6;
+    switch ((per + trips - 1) / trips) {
+        case 1: gemm_bf16_small_kernel<MODE, 1><<<grid, kThreads, 0, s>>>(p); break;
+        case 2: gemm_bf16_small_kernel<MODE, 2><<<grid, kThreads, 0, s>>>(p); break;
+        case 3: gemm_bf16_small_kernel<MODE, 3><<<grid, kThreads, 0, s>>>(p); break;
+        case 4: gemm_bf16_small_kernel<MODE, 4><<<grid, kThreads, 0, s>>>(p); break;
+        case 5: gemm_bf16_small_kernel<MODE, 5><<<grid, kThreads, 0, s>>>(p); break;
+        default: gemm_bf16_small_kernel<MODE, 6><<<grid, kThreads, 0, s>>>(p); break;
+    }
+    return hipGetLastError();
+}
+hipError_t launch_gemm_small_bf16_fwd(const GemmArgs& g, hipStream_t s) { return small_bf16<kFwd>(g, s); }
+hipError_t launch_gemm_small_bf16_da(const GemmArgs& g, hipStream_t s) { return small_bf16<kDa>(g, s); }
 
 }  // namespace ols

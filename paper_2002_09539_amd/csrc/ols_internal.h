@@ -183,6 +183,9 @@ bool gemm_small_fwd_fits(int groups, int M, int N, int K);
 bool gemm_small_da_fits(int groups, int M, int N, int K);
 hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s);
+bool gemm_small_bf16_fits(const GemmArgs& g, bool fwd);
+hipError_t launch_gemm_small_bf16_fwd(const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_small_bf16_da(const GemmArgs& g, hipStream_t s);
 // forward on the bf16 matrix cores with every operand split exactly into three bf16 terms (fp32 accuracy): whether, and
 // over how many K ranges, a shape takes it
 bool gemm_split_fits(int64_t a_elems, int64_t b_elems);   // elements a group's operand spans
