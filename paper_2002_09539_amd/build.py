@@ -28,6 +28,7 @@ SOURCES = [
     "kernels_conv_split.hip",
     "kernels_bn.hip",
     "kernels_conv_bf16.hip",
+    "kernels_conv_bf16_slices.hip",
 ]
 
 # packed-fp32 VALU forms stay disabled for every device translation unit

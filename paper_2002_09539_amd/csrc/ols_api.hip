@@ -431,25 +431,30 @@ int conv_gradients_bf16(ols_ctx* c) {
     base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
     uint16_t* images = (uint16_t*)(c->ws + c->off_wimages);   // of the kernels: first convolution, second, second for the delta
     uint8_t* gate = (uint8_t*)(c->ws + c->off_gate);          // sign of a1 for the delta, a byte per pixel and four channels
+    const bool slices = conv3x3_bf16_slices_fits(m, B, H, W, C);   // takes the kernels as they are and a1 for the delta's gate
+    auto conv_fwd = [&](ConvBArgs a, const uint16_t* w, const uint16_t* image) {
+        if (slices) { a.w = w; a.s_w = c->ld; } else a.w = image;
+        return enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return slices ? launch_conv3x3_bf16_slices_fwd(a, s) : launch_conv3x3_bf16_fwd(a, s); });
+    };
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-             return launch_pad_cast_bf16(c->X, c->xs, xb, act, m, B, H, W, C, shadow + wa, shadow + wb, c->ld, images, s);
+             return launch_pad_cast_bf16(c->X, c->xs, xb, act, m, B, H, W, C, shadow + wa, shadow + wb, c->ld, slices ? nullptr : images, s);
          })))
         return rc;
     {   // a1 = bf16(relu(conv(X; Wa) + ba))
         ConvBArgs a = base;
-        a.in = xb; a.s_in = act; a.w = images; a.bias = xc + ba; a.out = a1; a.s_out = act; a.relu = 1;
+        a.in = xb; a.s_in = act; a.bias = xc + ba; a.out = a1; a.s_out = act; a.relu = 1;
         a.gate = gate; a.s_gate = act / 4;
-        if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
+        if ((rc = conv_fwd(a, shadow + wa, images))) return rc;
     }
     if (positions >= 64) {
         // conv(a1; Wb) + bb with the block's tail in its epilogue: a2 = relu(. + X) is never stored -- its sign bytes and
         // partial sums of the pooling are (the partial sums take the place the fp32 output has without the fusion)
         ConvBArgs a = base;
         float* pool_part = y2;
-        a.in = a1; a.s_in = act; a.w = images + m * n_w; a.bias = xc + bb; a.tail = 1;
+        a.in = a1; a.s_in = act; a.bias = xc + bb; a.tail = 1;
         a.xres = c->X; a.s_x = c->xs; a.sign = sign; a.s_sign = act / 4; a.pool_part = pool_part;
-        if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
+        if ((rc = conv_fwd(a, shadow + wb, images + m * n_w))) return rc;
         if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
                  return launch_pool_finish(pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), pooled, (int64_t)B * C, nullptr, m, B, positions, C,
                                            1.0f / (float)(H * W), s);
@@ -458,8 +463,8 @@ int conv_gradients_bf16(ols_ctx* c) {
     } else {   // images too small for the fused tail's two-samples-per-wavefront bookkeeping
         {   // y = conv(a1; Wb) + bb, fp32
             ConvBArgs a = base;
-            a.in = a1; a.s_in = act; a.w = images + m * n_w; a.bias = xc + bb; a.out = y2; a.s_out = act; a.out_f32 = 1;
-            if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
+            a.in = a1; a.s_in = act; a.bias = xc + bb; a.out = y2; a.s_out = act; a.out_f32 = 1;
+            if ((rc = conv_fwd(a, shadow + wb, images + m * n_w))) return rc;
         }
         // a2 = relu(y + X), pooled = its mean over the positions, and the sign of a2 for the backward pass, in one pass
         if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
@@ -493,8 +498,10 @@ int conv_gradients_bf16(ols_ctx* c) {
         return rc;
     {   // delta at a1, gated by a1 > 0
         ConvBArgs a = base;
-        a.in = dz2; a.s_in = act; a.w = images + 2 * m * n_w; a.gate = gate; a.s_gate = act / 4; a.out = dz1; a.s_out = act;
-        if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dx(a, s); }))) return rc;
+        a.in = dz2; a.s_in = act; a.out = dz1; a.s_out = act;
+        if (slices) { a.w = shadow + wb; a.s_w = c->ld; a.mask = a1; a.s_mask = act; }
+        else { a.w = images + 2 * m * n_w; a.gate = gate; a.s_gate = act / 4; }
+        if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return slices ? launch_conv3x3_bf16_slices_dx(a, s) : launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }
     {
         ConvBArgs a = base;

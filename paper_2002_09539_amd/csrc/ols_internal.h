@@ -288,10 +288,11 @@ struct ConvBArgs {
     const float* bias;      // fwd: [C] per group, or nullptr
     uint8_t* gate;          // dx: [row of the output][C / 4] sign bytes (bit e set: channel 4 c + e stays, else 0); fwd with
                             // bf16 output: where the output leaves its own (bit e set iff it is positive)
+    const void* mask;       // launch_conv3x3_bf16_slices_dx: the padded bf16 activations whose sign gates the result
     float* partial;         // dw: scratch of conv3x3_bf16_dw_splits(...) * groups * (9 C C + C) floats
     float* g;               // dw: gradients [groups][ld]
     int64_t ld, g_w_off, g_b_off;   // g_b_off < 0: no bias
-    int64_t s_in, s_w, s_dout, s_out, s_bias, s_gate;   // group strides (elements of the tensor's own type)
+    int64_t s_in, s_w, s_dout, s_out, s_bias, s_gate, s_mask;   // group strides (elements of the tensor's own type)
     int groups, B, H, W, C;
     int relu;               // fwd with bf16 output: max(., 0) is applied, and has to be asked for
     // fwd with the residual block's tail fused in (tail != 0; out unused, no relu, padded images of at least 64 pixels):
@@ -307,6 +308,11 @@ struct ConvBArgs {
 hipError_t launch_conv3x3_bf16_fwd(const ConvBArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_bf16_dx(const ConvBArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_bf16_dw(const ConvBArgs& a, hipStream_t s);
+// the plain block's forward (bf16 output or fused tail) and delta in launches of middling size, and whether a shape takes them:
+// w is the bf16 kernels themselves, there are no sign bytes of the output, and the delta is gated by `mask`
+bool conv3x3_bf16_slices_fits(int groups, int B, int H, int W, int C);
+hipError_t launch_conv3x3_bf16_slices_fwd(const ConvBArgs& a, hipStream_t s);
+hipError_t launch_conv3x3_bf16_slices_dx(const ConvBArgs& a, hipStream_t s);
 int conv3x3_bf16_dw_splits(int groups, int B, int H, int W, int C);
 int64_t conv3x3_bf16_pool_part_floats(int B, int H, int W, int C);   // per group
 int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C);   // per group
@@ -316,7 +322,7 @@ hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, 
                               int C, float inv, hipStream_t s);
 // fp32 [groups][B H W][C] -> bf16 [groups][B (H+2) (W+2)][C] with a zero border; and the step's kernels (bf16 [9][C][C] per
 // group, wa of the first convolution and wb of the second) -> images[3][groups][9 C C]: the first convolution's, the second's
-// and the second's for the delta, in the order that launch_conv3x3_bf16_fwd / _dx take as ConvBArgs::w
+// and the second's for the delta, in the order that launch_conv3x3_bf16_fwd / _dx take as ConvBArgs::w (images nullptr: none)
 hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, int64_t s_dst, int groups, int B, int H, int W,
                                 int C, const uint16_t* wa, const uint16_t* wb, int64_t s_w, uint16_t* images, hipStream_t s);
 // The block's tail: a2 = relu(y + X) on the image pixels (y fp32 padded, X fp32 not padded), pooled = its mean over the
