@@ -129,37 +129,37 @@ def algorithmic_work(cfg, ld, fused_update=True):
         work["pool"] = ("hbm", act)
         work["pool_bwd"] = ("hbm", 2 * act)
         if cfg.gemm_dtype == "bf16" and cfg.batch_norm:
-            # convolutions: bf16 operands in, fp32 out (the normalisations' input); the delta also reads the bf16 gate
+            # convolutions: bf16 operands in, fp32 out (the normalisations' input); the delta also reads a1's sign bytes
             work["cast_bf16"] = ("hbm", 1.5 * act)
             work["conv_fwd_bytes"] = 1.5 * act
-            work["conv_dx_bytes"] = 2.0 * act
+            work["conv_dx_bytes"] = (1.5 + 1.0 / 16) * act
             work["conv_dw_bytes"] = 1.0 * act
         elif cfg.gemm_dtype == "bf16":
             # bytes of the tensors each launch has to touch once (bf16 operands are half an fp32 tensor; the border the
             # kernels store with them is overhead, not work): 288 flop per byte for a bf16-in, bf16-out convolution,
             # just below the 312 flop per byte ridge, so min(matrix peak, AI x HBM peak) is reported beside the peak
             work["cast_bf16"] = ("hbm", 1.5 * act)                      # fp32 batch in, bf16 batch out
-            work["conv_dx_bytes"] = 1.5 * act                           # bf16 delta in, bf16 mask in, bf16 delta out
+            work["conv_dx_bytes"] = (1.0 + 1.0 / 16) * act              # bf16 delta in, a1's sign bytes in, bf16 delta out
             work["conv_dw_bytes"] = 1.0 * act                           # bf16 input and bf16 delta
             if (H + 2) * (W + 2) >= 64:
-                # the block's tail runs in the second convolution's epilogue: bf16 in, fp32 shortcut in, sign bytes out;
+                # the block's tail runs in the second convolution's epilogue: bf16 in, fp32 shortcut in, sign bytes out (the first one's too);
                 # what is left of the pooling is a pass over the wavefronts' partial sums (8 C floats per 256 padded pixels)
-                work["conv_fwd_bytes"] = (1.0 * act + (1.5 + 1.0 / 16) * act) / 2
+                work["conv_fwd_bytes"] = ((1.0 + 1.0 / 16) * act + (1.5 + 1.0 / 16) * act) / 2
                 tiles = -(-(cfg.batch * (H + 2) * (W + 2)) // 256)
                 work["pool"] = ("hbm", 4.0 * m * (tiles * 8 * C + cfg.batch * C))
             else:
-                work["conv_fwd_bytes"] = (1.0 * act + 1.5 * act) / 2    # first: bf16 in, bf16 out; second: bf16 in, fp32 out
+                work["conv_fwd_bytes"] = ((1.0 + 1.0 / 16) * act + 1.5 * act) / 2   # first: bf16 in, bf16 and sign bytes out; second: bf16 in, fp32 out
                 work["pool"] = ("hbm", 2.0 * act + act / 16)            # shortcut + ReLU + pooling: conv output and shortcut in, sign bytes out
             work["pool_bwd"] = ("hbm", 0.5 * act + act / 16)            # sign bytes in, bf16 delta out
         if cfg.batch_norm:
             bf = cfg.gemm_dtype == "bf16"
             tail = H * W >= 64
             # Forward, first layer: the statistics come from what the convolution's epilogue left (channels in whole tiles of
-            # 64; else they read z), the normalisation reads z and writes a1 (half a tensor as a bf16 operand).  Second
+            # 64; else they read z), the normalisation reads z and writes a1 (as a bf16 operand half a tensor and its sign bytes).  Second
             # layer: the statistics as before; the normalisation reads z and the shortcut and writes a2 -- or, as the
             # block's tail (images of at least 64 pixels), only a2's sign bytes.  bench.py reports the mean of the two launches.
             sums = 0.0 if C % 64 == 0 else 1.0
-            first = sums + 1.0 + (0.5 if bf else 1.0)
+            first = sums + 1.0 + (0.5 + 1.0 / 16 if bf else 1.0)
             second = sums + 2.0 + (1.0 / 16 if tail else 1.0)
             work["bn_fwd"] = ("hbm", (first + second) / 2 * act)
             # Backward, second layer: the gradient under pooling and ReLU is formed from the pooled gradient and a2 (or its
