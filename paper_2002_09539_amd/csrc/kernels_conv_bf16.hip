@@ -691,15 +691,15 @@ __global__ __launch_bounds__(kDwThreads, 3) void conv3x3_dw_bf16_kernel(ConvBDev
 // kernels, the second's, and the second's with its channel indices exchanged (for the delta).  One workgroup per slice.
 struct KernelImages {
     const uint16_t* w[3];    // [9][C][C] per group
-    int64_t s_w;
-    uint16_t* dst;           // [3][groups][9 C C]
-    int groups, C;
+    uint16_t* dst[3];        // [9 C C] per group
+    int64_t s_w, s_dst;
+    int C;
 };
 __device__ __forceinline__ void kernel_images(const KernelImages& im, int unit, int group) {
     const int nb = im.C / kCB, which = unit / (9 * nb * nb), slice = unit % (9 * nb * nb);
     const int tap = slice / (nb * nb), c0 = (slice / nb % nb) * kCB, n0 = (slice % nb) * kCB;
     const uint16_t* W = im.w[which] + (int64_t)group * im.s_w + (int64_t)tap * im.C * im.C;
-    u4* D = (u4*)(im.dst + ((int64_t)(which * im.groups + group) * 9 * nb * nb + slice) * (kCB * kCB));
+    u4* D = (u4*)(im.dst[which] + (int64_t)group * im.s_dst + (int64_t)slice * (kCB * kCB));
 #pragma unroll
     for (int v = threadIdx.x; v < kCB * kCB / 8; v += kThreads) {
         const int l = v % 64, n = n0 + 32 * (v / 64 % 2) + l % 32, k = c0 + 16 * (v / 128) + 8 * (l / 32);
@@ -1067,15 +1067,18 @@ hipError_t launch_conv3x3_bf16_dw(const ConvBArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, int64_t s_dst, int groups, int B, int H, int W,
-                                int C, const uint16_t* wa, const uint16_t* wb, int64_t s_w, uint16_t* images, hipStream_t s) {
+                                int C, const ConvBImages& images, hipStream_t s) {
     if (!src || !dst || groups < 1 || groups > 65535 || B < 1 || H < 1 || W < 1 || C < kCB || C % kCB || !aligned16(src) ||
-        !aligned16(dst) || s_src % 4 || s_dst % 8 || !wa || !wb || !aligned16(wa) || !aligned16(wb) || !aligned16(images) || s_w % 8)
+        !aligned16(dst) || s_src % 4 || s_dst % 8)
+        return hipErrorInvalidValue;
+    if (images.fwd_a && (!images.wa || !images.wb || !images.fwd_b || !images.dx_b || !aligned16(images.wa) || !aligned16(images.wb) ||
+                         !aligned16(images.fwd_a) || !aligned16(images.fwd_b) || !aligned16(images.dx_b) || images.s_w % 8 || images.s_image % 8))
         return hipErrorInvalidValue;
     const int64_t vecs = (int64_t)B * (H + 2) * (W + 2) * (C / 8);
     if (vecs >= ((int64_t)1 << 31) - kPadCastFly * kThreads) return hipErrorInvalidValue;   // the divisions by multiplication take 31-bit dividends
     const int64_t blocks = (vecs + kPadCastFly * kThreads - 1) / (kPadCastFly * kThreads);
-    KernelImages im = {{wa, wb, wb}, s_w, images, groups, C};
-    const int64_t image_blocks = images ? 3 * 9 * (int64_t)(C / kCB) * (C / kCB) : 0;
+    KernelImages im = {{images.wa, images.wb, images.wb}, {images.fwd_a, images.fwd_b, images.dx_b}, images.s_w, images.s_image, C};
+    const int64_t image_blocks = images.fwd_a ? 3 * 9 * (int64_t)(C / kCB) * (C / kCB) : 0;
     auto kern = tensors_stream(groups, (int64_t)B * H * W * C) ? pad_cast_bf16_kernel<true> : pad_cast_bf16_kernel<false>;
     kern<<<dim3((unsigned)(blocks + image_blocks), (unsigned)groups), kThreads, 0, s>>>(
         src, s_src, dst, s_dst, (unsigned)vecs, H, W, C, make_div((unsigned)(C / 8)), make_div((unsigned)((H + 2) * (W + 2))),

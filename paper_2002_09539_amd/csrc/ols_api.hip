@@ -91,7 +91,7 @@ struct ols_ctx {
     int64_t ws_bytes = 0, ws_need = 0;
     // workspace sub-buffers (byte offsets)
     std::vector<int64_t> off_act, off_dz;
-    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_wimages = 0, off_gate = 0, off_x0 = 0, off_flags = 0;
+    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_gate = 0, off_x0 = 0, off_flags = 0;
     // residual convolutional block: channels, image size, classes; workspace sub-buffers
     int cv_C = 0, cv_H = 0, cv_W = 0, cv_classes = 0;
     bool cv_bn = false;     // convolutions without bias, each followed by batch normalisation
@@ -330,7 +330,8 @@ void plan_workspace(ols_ctx* c) {
     }
     if (c->model == MODEL_CONV && c->gemm_dtype == 1 && c->cv_bn) {
         // bf16 operand tensors with their zero border (batch, a1, both deltas); what the normalisations read and write is
-        // fp32 without a border (both convolution outputs, a2, the gradients at the normalised outputs)
+        // fp32 without a border (both convolution outputs, a2).  The gradient at the first normalised output takes the place of
+        // the second convolution's output, whose last reader runs before the delta that writes it.
         const int64_t padded = m * B * (c->cv_H + 2) * (c->cv_W + 2) * c->cv_C;
         const int64_t act = m * B * c->cv_H * c->cv_W * c->cv_C * 4;
         c->off_x0 = take(padded * 2);
@@ -340,7 +341,8 @@ void plan_workspace(ols_ctx* c) {
         c->off_z1 = take(act);
         c->off_z2 = take(act);
         c->off_a2 = take(act);
-        c->off_dn = take(act);            // gradient at a normalised output (second block, then first)
+        c->off_dn = c->off_z2;
+        c->off_gate = take(act / 16);     // sign of a1: a byte per pixel and four channels
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
         const int64_t splits = conv3x3_bf16_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
@@ -352,18 +354,19 @@ void plan_workspace(ols_ctx* c) {
         c->off_bnpart = take(bn_partial_floats(c->m, c->B * c->cv_H * c->cv_W, c->cv_C) * 4);
         c->off_wstat = take(m * conv3x3_bf16_stat_part_floats(c->B, c->cv_H, c->cv_W, c->cv_C) * 4);
         c->off_shadow = take(m * c->ld * 2);
-        c->off_wimages = take(3 * m * 9 * c->cv_C * c->cv_C * 2);
-        c->off_gate = take(padded / 4);   // sign bytes of a1
     } else if (c->model == MODEL_CONV && c->gemm_dtype == 1) {
         // operand tensors are bf16 and carry their zero border; a2's place holds the pooling's partial sums (or, for
-        // images of fewer than 64 padded pixels, the second convolution's fp32 output with the border)
+        // images of fewer than 64 padded pixels, the second convolution's fp32 output with the border) until they are
+        // added up, and the delta at a1 afterwards
         const int64_t padded = m * B * (c->cv_H + 2) * (c->cv_W + 2) * c->cv_C;
         c->off_x0 = take(padded * 2);
         c->off_a1 = take(padded * 2);
         c->off_a2 = take(padded * 4);
         c->off_z1 = take(padded / 4);     // sign bytes of a2
         c->off_dz2 = take(padded * 2);
-        c->off_dz1 = take(padded * 2);
+        c->off_dz1 = c->off_a2;
+        // sign bytes of a1, where a kernel reads them
+        if (!conv3x3_bf16_slices_fits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C)) c->off_gate = take(padded / 4);
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
         const int64_t splits = conv3x3_bf16_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
@@ -371,8 +374,6 @@ void plan_workspace(ols_ctx* c) {
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_shadow = take(m * c->ld * 2);
-        c->off_wimages = take(3 * m * 9 * c->cv_C * c->cv_C * 2);
-        c->off_gate = take(padded / 4);   // sign bytes of a1
     } else if (c->model == MODEL_CONV) {
         const int64_t act = m * B * c->cv_H * c->cv_W * c->cv_C * 4;   // one activation / delta tensor
         c->off_a1 = take(act);
@@ -404,6 +405,22 @@ void plan_workspace(ols_ctx* c) {
     c->ws_need = off;
 }
 
+// Where the bf16 blocks keep the images of a step's kernels: in the kernels' gradients, which are written later in the step --
+// the second convolution's by its weight-gradient launch, behind both forward launches, and the first's at the step's end,
+// behind the delta.  (A kernel's gradient holds two images: 9 C C floats.)
+ConvBImages kernel_images(ols_ctx* c, const uint16_t* shadow, int64_t wa, int64_t wb) {
+    const int64_t n_w = (int64_t)9 * c->cv_C * c->cv_C;
+    ConvBImages im = {};
+    im.wa = shadow + wa;
+    im.wb = shadow + wb;
+    im.fwd_a = (uint16_t*)(c->g + wb);
+    im.fwd_b = im.fwd_a + n_w;
+    im.dx_b = (uint16_t*)(c->g + wa);
+    im.s_w = c->ld;
+    im.s_image = 2 * c->ld;
+    return im;
+}
+
 // The plain residual block with bf16 operands: the input batch is converted (and given its zero border) first, the
 // kernels come from the bf16 copy of the parameters, a1 and both deltas are written as bf16; biases, shortcut, a2,
 // pooling and classifier stay fp32.  The second convolution's epilogue adds the shortcut, applies the ReLU and keeps
@@ -427,25 +444,26 @@ int conv_gradients_bf16(ols_ctx* c) {
     float* dpool = (float*)(c->ws + c->off_dpool);
     ConvBArgs base = {};
     base.groups = m; base.B = B; base.H = H; base.W = W; base.C = C;
-    base.s_w = n_w; base.s_bias = c->ld;
+    base.s_bias = c->ld;
     base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
-    uint16_t* images = (uint16_t*)(c->ws + c->off_wimages);   // of the kernels: first convolution, second, second for the delta
-    uint8_t* gate = (uint8_t*)(c->ws + c->off_gate);          // sign of a1 for the delta, a byte per pixel and four channels
     const bool slices = conv3x3_bf16_slices_fits(m, B, H, W, C);   // takes the kernels as they are and a1 for the delta's gate
+    const ConvBImages images = slices ? ConvBImages{} : kernel_images(c, shadow, wa, wb);
+    base.s_w = slices ? c->ld : images.s_image;
+    uint8_t* gate = slices ? nullptr : (uint8_t*)(c->ws + c->off_gate);   // sign of a1 for the delta, a byte per pixel and four channels
     auto conv_fwd = [&](ConvBArgs a, const uint16_t* w, const uint16_t* image) {
-        if (slices) { a.w = w; a.s_w = c->ld; } else a.w = image;
+        a.w = slices ? w : image;
         return enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return slices ? launch_conv3x3_bf16_slices_fwd(a, s) : launch_conv3x3_bf16_fwd(a, s); });
     };
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-             return launch_pad_cast_bf16(c->X, c->xs, xb, act, m, B, H, W, C, shadow + wa, shadow + wb, c->ld, slices ? nullptr : images, s);
+             return launch_pad_cast_bf16(c->X, c->xs, xb, act, m, B, H, W, C, images, s);
          })))
         return rc;
     {   // a1 = bf16(relu(conv(X; Wa) + ba))
         ConvBArgs a = base;
         a.in = xb; a.s_in = act; a.bias = xc + ba; a.out = a1; a.s_out = act; a.relu = 1;
         a.gate = gate; a.s_gate = act / 4;
-        if ((rc = conv_fwd(a, shadow + wa, images))) return rc;
+        if ((rc = conv_fwd(a, shadow + wa, images.fwd_a))) return rc;
     }
     if (positions >= 64) {
         // conv(a1; Wb) + bb with the block's tail in its epilogue: a2 = relu(. + X) is never stored -- its sign bytes and
@@ -454,7 +472,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         float* pool_part = y2;
         a.in = a1; a.s_in = act; a.bias = xc + bb; a.tail = 1;
         a.xres = c->X; a.s_x = c->xs; a.sign = sign; a.s_sign = act / 4; a.pool_part = pool_part;
-        if ((rc = conv_fwd(a, shadow + wb, images + m * n_w))) return rc;
+        if ((rc = conv_fwd(a, shadow + wb, images.fwd_b))) return rc;
         if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
                  return launch_pool_finish(pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), pooled, (int64_t)B * C, nullptr, m, B, positions, C,
                                            1.0f / (float)(H * W), s);
@@ -464,7 +482,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         {   // y = conv(a1; Wb) + bb, fp32
             ConvBArgs a = base;
             a.in = a1; a.s_in = act; a.bias = xc + bb; a.out = y2; a.s_out = act; a.out_f32 = 1;
-            if ((rc = conv_fwd(a, shadow + wb, images + m * n_w))) return rc;
+            if ((rc = conv_fwd(a, shadow + wb, images.fwd_b))) return rc;
         }
         // a2 = relu(y + X), pooled = its mean over the positions, and the sign of a2 for the backward pass, in one pass
         if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
@@ -499,8 +517,8 @@ int conv_gradients_bf16(ols_ctx* c) {
     {   // delta at a1, gated by a1 > 0
         ConvBArgs a = base;
         a.in = dz2; a.s_in = act; a.out = dz1; a.s_out = act;
-        if (slices) { a.w = shadow + wb; a.s_w = c->ld; a.mask = a1; a.s_mask = act; }
-        else { a.w = images + 2 * m * n_w; a.gate = gate; a.s_gate = act / 4; }
+        if (slices) { a.w = shadow + wb; a.mask = a1; a.s_mask = act; }
+        else { a.w = images.dx_b; a.gate = gate; a.s_gate = act / 4; }
         if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return slices ? launch_conv3x3_bf16_slices_dx(a, s) : launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }
     {
@@ -537,19 +555,19 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     float* z1 = (float*)(c->ws + c->off_z1);
     float* z2 = (float*)(c->ws + c->off_z2);
     float* a2 = (float*)(c->ws + c->off_a2);
-    float* dn = (float*)(c->ws + c->off_dn);
+    float* dn = (float*)(c->ws + c->off_dn);          // over z2
     float* pooled = (float*)(c->ws + c->off_pooled);
     float* dpool = (float*)(c->ws + c->off_dpool);
     ConvBArgs base = {};
     base.groups = m; base.B = B; base.H = H; base.W = W; base.C = C;
-    base.s_w = n_w; base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
+    const ConvBImages images = kernel_images(c, shadow, wa, wb);
+    base.s_w = images.s_image; base.ld = c->ld; base.g = c->g; base.partial = (float*)(c->ws + c->off_cpartial);
     BnArgs nbase = {};
     nbase.groups = m; nbase.P = B * H * W; nbase.C = C; nbase.eps = c->cv_eps;
     nbase.s_z = act; nbase.s_out = act; nbase.s_dy = act; nbase.s_par = c->ld;
     nbase.ld = c->ld; nbase.g = c->g; nbase.H = H; nbase.W = W; nbase.s_outb = padded;
     nbase.part = (float*)(c->ws + c->off_bnpart);
     nbase.sums = (float*)(c->ws + c->off_bnsums);
-    uint16_t* images = (uint16_t*)(c->ws + c->off_wimages);   // of the kernels: first convolution, second, second for the delta
     uint8_t* gate = (uint8_t*)(c->ws + c->off_gate);          // sign of a1 for the delta, a byte per pixel and four channels
     float* stats1 = (float*)(c->ws + c->off_bnstats);
     float* stats2 = stats1 + (int64_t)m * 2 * C;
@@ -566,12 +584,12 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     float* sample_sums = tail_part + m * tail_units * 6 * C;
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-             return launch_pad_cast_bf16(c->X, c->xs, xb, padded, m, B, H, W, C, shadow + wa, shadow + wb, c->ld, images, s);
+             return launch_pad_cast_bf16(c->X, c->xs, xb, padded, m, B, H, W, C, images, s);
          })))
         return rc;
     {   // z1 = conv(X; Wa)
         ConvBArgs a = base;
-        a.in = xb; a.s_in = padded; a.w = images; a.out = z1; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
+        a.in = xb; a.s_in = padded; a.w = images.fwd_a; a.out = z1; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
     }
     {   // a1 = bf16(relu(bn(z1)))
@@ -582,7 +600,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     }
     {   // z2 = conv(a1; Wb)
         ConvBArgs a = base;
-        a.in = a1; a.s_in = padded; a.w = images + m * n_w; a.out = z2; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
+        a.in = a1; a.s_in = padded; a.w = images.fwd_b; a.out = z2; a.s_out = act; a.out_f32 = 1; a.out_unpadded = 1; a.stat_part = wstat;
         if ((rc = enqueue(c, OLS_K_CONV_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_fwd(a, s); }))) return rc;
     }
     {   // a2 = relu(bn(z2) + X)
@@ -628,7 +646,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     }
     {   // gradient at the first normalised output: transposed convolution of dz2 through Wb, gated by a1 > 0
         ConvBArgs a = base;
-        a.in = dz2; a.s_in = padded; a.w = images + 2 * m * n_w; a.gate = gate; a.s_gate = act / 4; a.out = dn; a.s_out = act;
+        a.in = dz2; a.s_in = padded; a.w = images.dx_b; a.gate = gate; a.s_gate = act / 4; a.out = dn; a.s_out = act;
         a.out_f32 = 1; a.out_unpadded = 1;
         if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }

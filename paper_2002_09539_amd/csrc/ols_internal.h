@@ -276,7 +276,7 @@ hipError_t launch_pool_bwd(const float* dpool, int64_t s_dp, const float* a, int
 constexpr int kConvBf16MaxWidth = 128;
 struct ConvBArgs {
     const void* in;         // fwd: layer input; dx: delta of the layer output; dw: layer input (bf16, padded)
-    const void* w;          // fwd, dx: bf16 kernels, an image of launch_pad_cast_bf16 (s_w = 9 C C)
+    const void* w;          // fwd, dx: bf16 kernels, an image of launch_pad_cast_bf16
     const void* dout;       // dw: delta of the layer output (bf16, padded)
     void* out;              // fwd: layer output; dx: delta of the layer input; padded, bf16 -- or, fwd with out_f32, the
                             // bare convolution + bias in fp32 with border rows as computed (their consumer skips them)
@@ -320,11 +320,16 @@ int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C);   // per grou
 // pixels (slot 0: the sample of pixel 64 w, slot 1: the next one) with `per` (>= 64) pixels per sample
 hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, float* more, int groups, int B, int per,
                               int C, float inv, hipStream_t s);
-// fp32 [groups][B H W][C] -> bf16 [groups][B (H+2) (W+2)][C] with a zero border; and the step's kernels (bf16 [9][C][C] per
-// group, wa of the first convolution and wb of the second) -> images[3][groups][9 C C]: the first convolution's, the second's
-// and the second's for the delta, in the order that launch_conv3x3_bf16_fwd / _dx take as ConvBArgs::w (images nullptr: none)
+// The step's kernels in fragment order, which launch_conv3x3_bf16_fwd / _dx take as ConvBArgs::w: 9 C C values per group for the
+// first convolution, the second, and the second's delta.  All nullptr: none are made.
+struct ConvBImages {
+    const uint16_t *wa, *wb;             // bf16 kernels [9][C][C] per group
+    uint16_t *fwd_a, *fwd_b, *dx_b;
+    int64_t s_w, s_image;                // group strides
+};
+// fp32 [groups][B H W][C] -> bf16 [groups][B (H+2) (W+2)][C] with a zero border; and the images of the step's kernels
 hipError_t launch_pad_cast_bf16(const float* src, int64_t s_src, uint16_t* dst, int64_t s_dst, int groups, int B, int H, int W,
-                                int C, const uint16_t* wa, const uint16_t* wb, int64_t s_w, uint16_t* images, hipStream_t s);
+                                int C, const ConvBImages& images, hipStream_t s);
 // The block's tail: a2 = relu(y + X) on the image pixels (y fp32 padded, X fp32 not padded), pooled = its mean over the
 // positions, sign[padded pixel][C / 4] = one byte per four channels with bit e set iff a2 > 0 (border: 0).  a2 is not stored.
 hipError_t launch_shortcut_relu_pool(const float* y, int64_t s_y, const float* X, int64_t s_x, float* pooled, int64_t s_p,
