@@ -45,7 +45,7 @@ struct SmallDev {
     int tiles_m, tiles_n, total_tiles, chunk;
 };
 
-template <int MODE, int TM, int TN, int S, bool MORE>
+template <int MODE, int TM, int TN, int S, int CHAINS, bool MORE>
 __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
     constexpr int BM = 16 * TM, BN = 16 * TN, kOut = BM * BN, kPer = kOut / kThreads;
     __shared__ float red[kW][kOut];
@@ -93,18 +93,21 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
             }
         }
     };
-    f4 acc[TM][TN];
+    // A wavefront's steps alternate between CHAINS sums (see small_start)
+    f4 acc[CHAINS][TM][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    auto mfma = [&](const Step& r) {
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[c][i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    auto mfma = [&](const Step& r, int c) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[i][e], r.b[j][e], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < TN; ++j) acc[c][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[i][e], r.b[j][e], acc[c][i][j], 0, 0, 0);
     };
     const int steps = (p.K + 15) / 16;
     Step r0[S], r1[MORE ? S : 1];
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
     };
     auto mfma_trip = [&](const Step (&r)[S]) {
 #pragma unroll
-        for (int t = 0; t < S; ++t) mfma(r[t]);
+        for (int t = 0; t < S; ++t) mfma(r[t], t % CHAINS);
     };
     if constexpr (MORE) {   // the next round trip under way during this one's products
         load_trip(r0, wave);
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[wave][256 * (i * TN + j) + 64 * r + lane] = acc[i][j][r];
+            for (int r = 0; r < 4; ++r) red[wave][256 * (i * TN + j) + 64 * r + lane] = CHAINS == 1 ? acc[0][i][j][r] : acc[0][i][j][r] + acc[CHAINS - 1][i][j][r];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -308,27 +311,41 @@ static void small_start(const SmallDev& p, int steps, hipStream_t s) {
     // as few round trips of up to eight steps as there have to be, and as short as they then can be
     const int per = (steps + kW - 1) / kW, trips = (per + 7) / 8, S = (per + trips - 1) / trips;
     const unsigned grid = (unsigned)(p.chunk * kXcds);
-#define OLS_SMALL(S, MORE) gemm_f32_small_kernel<MODE, 2, TN, S, MORE><<<grid, kThreads, 0, s>>>(p)
+#define OLS_SMALL(S, CHAINS, MORE) gemm_f32_small_kernel<MODE, 2, TN, S, CHAINS, MORE><<<grid, kThreads, 0, s>>>(p)
     // Round trips one behind the other leave room for more workgroups; with hardly one per compute unit and three trips or more
     // (five to eight steps each) they overlap: forward 3 x (32 x 960 x 1836), 180 tiles, 16.0 -> 12.1, 3 x (40 x 532 x 2236), 204, 18.7 ->
     // 15.1; but 4 x (224 x 124 x 1192), 224 tiles, 8.9 -> 9.8, 17 x (128 x 248 x 1372) 34.3 -> 48.1, and no delta gains.
+    //
+    // The error of a sum grows with the length of its chain, and the 64 x 64 tiles add forward contractions of 768 indices or more in
+    // up to eight K ranges: from there on the four wavefronts have two sums each.  Error of the activations against 64 bits over
+    // that of the tiles, 60 shapes: with one sum per wavefront 1.34 (up to 1.40) where they take eight ranges, 1.00 with four,
+    // 0.54 with one (like every delta); with two sums 0.96 (up to 1.01) of eight ranges.  The registers of the second sum cost
+    // nothing on most shapes (1 % on 4 x (28 x 1924 x 1872)), but 9 % on 6 x (220 x 608 x 604), which does not need it.
     if constexpr (MODE == kFwd && TN == 1) {
         if (trips > 2 && p.total_tiles <= 216) {
-            if (S <= 6) OLS_SMALL(6, true);
-            else if (S == 7) OLS_SMALL(7, true);
-            else OLS_SMALL(8, true);
+            if (S <= 6) OLS_SMALL(6, 2, true);
+            else if (S == 7) OLS_SMALL(7, 2, true);
+            else OLS_SMALL(8, 2, true);
+            return;
+        }
+    }
+    if constexpr (MODE == kFwd) {
+        if (p.K >= 768) {   // (twelve steps per wavefront or more: two trips of six to eight at least)
+            if (S <= 6) OLS_SMALL(6, 2, false);
+            else if (S == 7) OLS_SMALL(7, 2, false);
+            else OLS_SMALL(8, 2, false);
             return;
         }
     }
     switch (S) {
-        case 1: OLS_SMALL(1, false); break;
-        case 2: OLS_SMALL(2, false); break;
-        case 3: OLS_SMALL(3, false); break;
-        case 4: OLS_SMALL(4, false); break;
-        case 5: OLS_SMALL(5, false); break;
-        case 6: OLS_SMALL(6, false); break;
-        case 7: OLS_SMALL(7, false); break;
-        default: OLS_SMALL(8, false); break;
+        case 1: OLS_SMALL(1, 1, false); break;
+        case 2: OLS_SMALL(2, 1, false); break;
+        case 3: OLS_SMALL(3, 1, false); break;
+        case 4: OLS_SMALL(4, 1, false); break;
+        case 5: OLS_SMALL(5, 1, false); break;
+        case 6: OLS_SMALL(6, 1, false); break;
+        case 7: OLS_SMALL(7, 1, false); break;
+        default: OLS_SMALL(8, 1, false); break;
     }
 #undef OLS_SMALL
 }

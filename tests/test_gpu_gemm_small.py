@@ -5,8 +5,8 @@ import pytest
 
 from ols_inputs import generate as G
 from oracle import ols_oracle as O
-from tests.helpers import max_norm_ratio
-from tests.test_gpu_gemm_split import GRAD_TOL, one_step
+from tests.helpers import l2_ratio, max_norm_ratio
+from tests.test_gpu_gemm_split import GRAD_TOL, first_activations, one_step
 from tests.test_gpu_mlp import small_mlp_case
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +50,23 @@ def test_infinite_weight_stays_in_its_column():
     for i in range(m):
         loss, grad = O.mlp_loss_grad(ref, dims, X[i, 0], labels[i, 0])
         assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
+
+
+@pytest.mark.parametrize("m,batch,width,features", [
+    (8, 24, 236, 2936),      # 32 x 16 tiles, round trips that overlap
+    (3, 32, 1200, 912),      # 32 x 16 tiles, round trips one behind the other
+    (4, 28, 1924, 1872),     # 32 x 32 tiles
+])
+def test_long_contractions_are_added_in_eight_parts(m, batch, width, features):
+    """A sum of n terms of random sign in one chain has an error of 0.3 u sqrt(n) of its own root mean square: each addition rounds a
+    partial sum that has grown to sqrt(k) of a term by 0.42 u of it in the root mean square, u = 2^-24.  P chains of K / P terms
+    leave 0.3 u sqrt(K / P), the additions that follow less than u.  The 64 x 64 tiles add these contractions in eight ranges;
+    the bound lies a fifth above eight chains and a sixth below four."""
+    dims = (features, width, 4)
+    cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=423)
+    X = G.generic_normal(11, 2, X.shape)          # (class means would lengthen the sums)
+    h = first_activations(cfg, dims, batch, X, labels, x0)
+    W = x0[:features * width].reshape(features, width).astype(np.float64)
+    ref = np.maximum(X[:, 0].astype(np.float64) @ W + x0[features * width:features * width + width], 0.0)
+    bound = 2.0 ** -24 * (1.2 * 0.3 * np.sqrt(features / 8) + 0.42)
+    assert l2_ratio(h, ref) <= bound
