@@ -286,6 +286,24 @@ uint16_t* shadow_ptr(ols_ctx* c) {
     return (bf16_model(c) && c->ws) ? (uint16_t*)(c->ws + c->off_shadow) : nullptr;
 }
 
+// The normalised block on images of at least 64 pixels never stores a2: its place holds a2's sign (a byte per pixel and four
+// channels), three sums per 64 pixels and sample part, and two sums per sample, in floats from its start.  (They fill at most
+// 9 / 32 of it: m act / 16 for the signs, 3 / 16 of m act for the parts and 1 / 32 for the samples' sums.)
+struct BnTail {
+    int64_t units;                   // parts of 64 pixels per worker
+    int64_t part, sums, floats;      // the parts, the samples' sums, the end
+};
+bool bn_has_tail(const ols_ctx* c) { return c->cv_H * c->cv_W >= 64; }
+BnTail bn_tail_layout(const ols_ctx* c) {
+    const int64_t m = c->m, pixels = (int64_t)c->B * c->cv_H * c->cv_W;
+    BnTail t;
+    t.units = (pixels + 63) / 64;
+    t.part = round_up(m * (pixels * c->cv_C / 4), 16) / 4;
+    t.sums = t.part + m * t.units * 6 * c->cv_C;
+    t.floats = t.sums + m * 2 * c->B * c->cv_C;
+    return t;
+}
+
 void plan_workspace(ols_ctx* c) {
     int64_t off = 0;
     auto take = [&](int64_t bytes) {
@@ -330,8 +348,7 @@ void plan_workspace(ols_ctx* c) {
     }
     if (c->model == MODEL_CONV && c->gemm_dtype == 1 && c->cv_bn) {
         // bf16 operand tensors with their zero border (batch, a1, both deltas); what the normalisations read and write is
-        // fp32 without a border (both convolution outputs, a2).  The gradient at the first normalised output takes the place of
-        // the second convolution's output, whose last reader runs before the delta that writes it.
+        // fp32 without a border (both convolution outputs, a2, the gradient at the first normalised output)
         const int64_t padded = m * B * (c->cv_H + 2) * (c->cv_W + 2) * c->cv_C;
         const int64_t act = m * B * c->cv_H * c->cv_W * c->cv_C * 4;
         c->off_x0 = take(padded * 2);
@@ -341,12 +358,19 @@ void plan_workspace(ols_ctx* c) {
         c->off_z1 = take(act);
         c->off_z2 = take(act);
         c->off_a2 = take(act);
-        c->off_dn = c->off_z2;
-        c->off_gate = take(act / 16);     // sign of a1: a byte per pixel and four channels
+        c->off_dn = take(act);
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
         const int64_t splits = conv3x3_bf16_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
-        c->off_cpartial = take(splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4);
+        const int64_t cpartial = splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4;
+        c->off_cpartial = take(cpartial);
+        // The sign of a1 (a byte per pixel and four channels, from the first normalisation to the delta) has no place of its own:
+        // behind what the tail keeps in a2's; without a tail in that of the kernel gradients' partial sums, which come after
+        // the delta; where that is too small in the gradient's, which then takes z2's, whose last reader precedes the delta
+        // (that alone would do, but blocks of 60 to 150 us per step are 1 to 3 % slower with it).
+        if (bn_has_tail(c)) c->off_gate = c->off_a2 + align256(bn_tail_layout(c).floats * 4);
+        else if (act / 16 <= cpartial) c->off_gate = c->off_cpartial;
+        else { c->off_gate = c->off_dn; c->off_dn = c->off_z2; }
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_bnstats = take(2 * m * 2 * c->cv_C * 4);
@@ -356,21 +380,24 @@ void plan_workspace(ols_ctx* c) {
         c->off_shadow = take(m * c->ld * 2);
     } else if (c->model == MODEL_CONV && c->gemm_dtype == 1) {
         // operand tensors are bf16 and carry their zero border; a2's place holds the pooling's partial sums (or, for
-        // images of fewer than 64 padded pixels, the second convolution's fp32 output with the border) until they are
-        // added up, and the delta at a1 afterwards
+        // images of fewer than 64 padded pixels, the second convolution's fp32 output with the border)
         const int64_t padded = m * B * (c->cv_H + 2) * (c->cv_W + 2) * c->cv_C;
         c->off_x0 = take(padded * 2);
         c->off_a1 = take(padded * 2);
         c->off_a2 = take(padded * 4);
         c->off_z1 = take(padded / 4);     // sign bytes of a2
         c->off_dz2 = take(padded * 2);
-        c->off_dz1 = c->off_a2;
-        // sign bytes of a1, where a kernel reads them
-        if (!conv3x3_bf16_slices_fits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C)) c->off_gate = take(padded / 4);
+        c->off_dz1 = take(padded * 2);
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
         const int64_t splits = conv3x3_bf16_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
-        c->off_cpartial = take(splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4);
+        const int64_t cpartial = splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4;
+        c->off_cpartial = take(cpartial);
+        // The sign of a1, as above: behind the pooling's partial sums; or in the kernel gradients' place; or in dz1's, which then
+        // takes that of the fp32 output, added up before the delta.
+        if ((c->cv_H + 2) * (c->cv_W + 2) >= 64) c->off_gate = c->off_a2 + align256(m * conv3x3_bf16_pool_part_floats(c->B, c->cv_H, c->cv_W, c->cv_C) * 4);
+        else if (padded / 4 <= cpartial) c->off_gate = c->off_cpartial;
+        else { c->off_gate = c->off_dz1; c->off_dz1 = c->off_a2; }
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_shadow = take(m * c->ld * 2);
@@ -555,7 +582,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     float* z1 = (float*)(c->ws + c->off_z1);
     float* z2 = (float*)(c->ws + c->off_z2);
     float* a2 = (float*)(c->ws + c->off_a2);
-    float* dn = (float*)(c->ws + c->off_dn);          // over z2
+    float* dn = (float*)(c->ws + c->off_dn);
     float* pooled = (float*)(c->ws + c->off_pooled);
     float* dpool = (float*)(c->ws + c->off_dpool);
     ConvBArgs base = {};
@@ -574,14 +601,13 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     // the convolutions leave the statistics of their output per wavefront (64 padded pixels): the normalisations merge those
     float* wstat = (float*)(c->ws + c->off_wstat);
     const int waves = (int)(conv3x3_bf16_stat_part_floats(B, H, W, C) / (3 * C));
-    // Images of at least 64 pixels: a2 is never stored -- the second normalisation leaves its sign (a byte per pixel and
-    // four channels) and its sums per 64 pixels; both live in a2's place
-    const bool tail = H * W >= 64;
-    const int64_t tail_units = ((int64_t)B * H * W + 63) / 64;
+    // images of at least 64 pixels: a2 is never stored, its place holds what the second normalisation leaves of it
+    const bool tail = bn_has_tail(c);
+    const BnTail layout = bn_tail_layout(c);
+    const int64_t tail_units = layout.units;
     uint8_t* sign = (uint8_t*)a2;
-    // (all three fit: m act / 16 floats of sign bytes, at most 3 / 16 of m act for the parts and 1 / 32 for the samples' sums)
-    float* tail_part = a2 + round_up((int64_t)m * (act / 4), 16) / 4;   // behind the sign bytes of all workers
-    float* sample_sums = tail_part + m * tail_units * 6 * C;
+    float* tail_part = a2 + layout.part;
+    float* sample_sums = a2 + layout.sums;
     int rc;
     if ((rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
              return launch_pad_cast_bf16(c->X, c->xs, xb, padded, m, B, H, W, C, images, s);
@@ -708,14 +734,13 @@ int conv_gradients(ols_ctx* c) {
     nbase.sums = (float*)(c->ws + c->off_bnsums);
     float* stats1 = (float*)(c->ws + c->off_bnstats);
     float* stats2 = stats1 + (int64_t)m * 2 * C;
-    // Normalised block on images of at least 64 pixels: a2 is never stored -- the second normalisation leaves its sign (a
-    // byte per pixel and four channels) and its sums per 64 pixels; both live in a2's place
-    const bool tail = bn && H * W >= 64;
-    const int64_t tail_units = ((int64_t)B * H * W + 63) / 64;
+    // normalised block on images of at least 64 pixels: a2 is never stored, its place holds what the normalisation leaves of it
+    const bool tail = bn && bn_has_tail(c);
+    const BnTail layout = bn_tail_layout(c);
+    const int64_t tail_units = layout.units;
     uint8_t* sign = (uint8_t*)a2;
-    // (all three fit: m act / 16 floats of sign bytes, at most 3 / 16 of m act for the parts and 1 / 32 for the samples' sums)
-    float* tail_part = a2 + round_up((int64_t)m * (act / 4), 16) / 4;   // behind the sign bytes of all workers
-    float* sample_sums = tail_part + m * tail_units * 6 * C;
+    float* tail_part = a2 + layout.part;
+    float* sample_sums = a2 + layout.sums;
     int rc;
     {   // first convolution
         ConvArgs a = base;
