@@ -273,6 +273,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_bf16_kernel(ConvBDev p) {
             }
             if (MODE == 0 && threadIdx.x < BN) bias_lds[threadIdx.x] = p.bias ? p.bias[(int64_t)group * p.s_bias + n0 + threadIdx.x] : 0.0f;
         }
+        // Loads into LDS count as vector loads, and the barrier alone waits for no wavefront's: each waits for its own rows first
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         OLS_TP(2);   // the strip is in LDS
         load_fa(0, 0);
