@@ -434,14 +434,16 @@ hipError_t slices_launch(const ConvBArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// The rule, from whole steps of 60 plain blocks on either path, by tiles of 512 pixels x 64 channels (us for two rounds, there /
+// The rule, from whole steps of 74 plain blocks on either path, by tiles of 512 pixels x 64 channels (us for two rounds, there /
 // here).  64 channels: 192 tiles 258 / 261, 200 271 / 267, 220 549 / 527; 264 896 / 914, 308 319 / 320, 330 326 / 325; 512 816 / 806,
 // 574 916 / 885, 960 1896 / 1815, 1125 740 / 697, 1504 2614 / 2542, 2260 2528 / 2477, 2604 2875 / 2806; 3542 3610 / 3674, 4624 4660 /
-// 4790.  128 channels: 224 384 / 370, 340 875 / 860, 368 1357 / 1305; 480 1060 / 1075, 656 1334 / 1346, 1808 2955 / 3054.  Fewer
-// tiles: there by 1 to 7 %.
+// 4790.  128 channels: 224 384 / 370, 340 875 / 860, 368 1357 / 1305; 480 1060 / 1075, 656 1334 / 1346, 1808 2955 / 3054.  192: 90 560
+// / 586, 144 666 / 706, 225 822 / 815, 288 1004 / 1025, 384 1143 / 1102 and 1178 / 1142, 684 1830 / 1880.  256, never taken: 112 646 / 676,
+// 160 798 / 858, 256 1053 / 1038, 272 1089 / 1163, 324 1211 / 1243, 512 1677 / 1747, 992 2809 / 2945.  Fewer tiles: there by 1 to 7 %.
 bool conv3x3_bf16_slices_fits(int groups, int B, int H, int W, int C) {
     const int64_t tiles = (int64_t)groups * (((int64_t)B * (H + 2) * (W + 2) + 511) / 512) * (C / kCB);
     if ((H + 2) * (W + 2) < 64) return false;   // (the unfused tail needs the fp32 output)
+    if (C > 192) return false;
     return C == kCB ? (tiles >= 200 && tiles <= 256) || (tiles >= 500 && tiles <= 3072) : tiles >= 200 && tiles <= 400;
 }
 hipError_t launch_conv3x3_bf16_slices_fwd(const ConvBArgs& a, hipStream_t s) { return slices_launch<0>(a, s); }

@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     ((64, 6, 6, 3), 64, 65),       # images of 64 padded pixels, the smallest with the fused tail
     ((64, 9, 33, 3), 12, 22),      # 220 tiles
     ((128, 13, 15, 7), 20, 11),    # two contraction chunks, two output tiles
+    ((192, 14, 14, 5), 16, 12),    # three of each
     ((64, 30, 30, 5), 8, 31),      # 496: the other kernels
 ])
 def test_middling_launch(dims, batch, m):

@@ -29,6 +29,8 @@ def one_step(cfg, dims, batch, m, X, labels, x0, batch_norm):
     ((64, 14, 50, 4), 10, 26),     # one column more: 256 x 64
     ((64, 9, 33, 3), 12, 45),      # 4620 padded pixels: a last tile of 12 pixels
     ((128, 13, 15, 7), 20, 21),    # two contraction chunks, two output tiles
+    ((256, 14, 14, 5), 16, 8),     # four of each; 256 tiles, where fewer channels would take the kernel slices through LDS
+    ((256, 14, 14, 5), 16, 13),    # 416 tiles
 ])
 def test_tile_of_a_large_launch(dims, batch, m):
     cfg, X, labels, x0 = conv_case(1, dims, batch, 1, seed=717)
