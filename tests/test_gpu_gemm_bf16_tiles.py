@@ -1,5 +1,5 @@
-"""The bf16 MLP's GEMMs take smaller tiles where the large ones would leave compute units idle: parity on either side of
-the lines of that rule, with ragged last tiles."""
+"""The bf16 MLP's GEMMs on small launches: parity on either side of the line between the weight gradient's tiles, and of forward and
+delta GEMMs by the kernel of small launches, which takes all of these (test_gpu_gemm_tiles.py has those above its limits)."""
 import numpy as np
 import pytest
 
@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,dims,batch", [
-    (3, (72, 136, 72, 10), 72),        # ragged in every dimension of a 64 x 64 tile
-    (1, (64, 64, 64, 10), 64),         # one tile
-    (255, (64, 128, 8, 4), 16),        # 255 tiles of the forward GEMM: the most that take the small ones
-    (256, (64, 128, 8, 4), 16),        # 256: the large ones
+    (3, (72, 136, 72, 10), 72),        # ragged in every dimension of a tile
+    (1, (64, 64, 64, 10), 64),         # one tile of the weight gradient
+    (255, (64, 128, 8, 4), 16),        # many workers: 2,040 steps of the forward GEMM
+    (256, (64, 128, 8, 4), 16),        # 2,048
     (8, (1024, 1024, 16, 4), 24),      # 1024 tiles of the weight gradient: the most that take the small ones
     (8, (1032, 1024, 16, 4), 24),      # one tile row more
 ])

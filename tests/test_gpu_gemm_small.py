@@ -34,7 +34,7 @@ def test_gradient_and_loss_match_oracle(m, dims, batch):
 
 def test_infinite_weight_stays_in_its_column():
     """Lanes past the contraction's end (20 indices: a second step of four) and past the last row or column hold zeros, not a
-    neighbour's value: an infinite weight reaches its own unit only."""
+    neighbour's value: an infinite weight reaches its own units only, forward and back."""
     m, dims, batch = 2, (20, 20, 20, 4), 4
     cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=422)
     inf = 20 * 20 + 20                   # second layer's weight [0][0], right behind the first layer's bias
@@ -43,13 +43,15 @@ def test_infinite_weight_stays_in_its_column():
     x0[20 * 20 + 1:inf] = 1.0            # .. but those after the first
     x0[inf] = np.inf
     g, losses = one_step(cfg, dims, batch, X, labels, x0)
-    # 0 * inf is a NaN in the second layer's first unit, which the ReLU takes to 0 as before; everything else stays finite
+    # 0 * inf is a NaN in the second layer's first unit, which the ReLU takes to 0 as before, and going back in the delta of the
+    # first layer's first unit, which is gated to 0; everything else is as with both units inactive
     ref = x0.copy()
     ref[inf] = 0.0
     ref[inf + 20 * 20] = -1e6            # that unit inactive
     for i in range(m):
         loss, grad = O.mlp_loss_grad(ref, dims, X[i, 0], labels[i, 0])
         assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
+        assert max_norm_ratio(g[i], grad) <= GRAD_TOL
 
 
 @pytest.mark.parametrize("m,batch,width,features", [

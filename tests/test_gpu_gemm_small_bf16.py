@@ -49,7 +49,7 @@ def test_gradient_and_loss_match_oracle(m, dims, batch):
 
 def test_infinite_weight_stays_in_its_column():
     """Lanes past the contraction's end or past the last row or column hold zeros, and the two columns of a pair stay apart: an
-    infinite weight reaches its own unit only."""
+    infinite weight reaches its own units only, forward and back."""
     m, dims, batch = 2, (24, 24, 24, 4), 8
     cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=432)
     inf = 24 * 24 + 24                   # second layer's weight [0][0], right behind the first layer's bias
@@ -57,11 +57,13 @@ def test_infinite_weight_stays_in_its_column():
     x0[24 * 24:inf] = -100.0             # first layer: no unit is active ..
     x0[24 * 24 + 1:inf] = 1.0            # .. but those after the first
     x0[inf] = np.inf
-    _, losses = one_step(m, dims, batch, cfg, X, labels, x0)
-    # 0 * inf is a NaN in the second layer's first unit, which the ReLU takes to 0; everything else stays finite
+    g, losses = one_step(m, dims, batch, cfg, X, labels, x0)
+    # 0 * inf is a NaN in the second layer's first unit, which the ReLU takes to 0, and going back in the delta of the first
+    # layer's first unit, which is gated to 0; everything else is as with both units inactive
     ref = x0.copy()
     ref[inf] = 0.0
     ref[inf + 24 * 24] = -1e6            # that unit inactive
     for i in range(m):
-        loss, _ = O.mlp_loss_grad(ref, dims, X[i, 0], labels[i, 0], bf16_operands=True)
+        loss, grad = O.mlp_loss_grad(ref, dims, X[i, 0], labels[i, 0], bf16_operands=True)
         assert abs(losses[i] - loss) <= 1e-3 * abs(loss)
+        assert l2_ratio(g[i], grad) <= 2e-2

@@ -280,11 +280,12 @@ def test_library_driven_loop_equals_one_call_per_step(dtype):
 
 
 @pytest.mark.parametrize("m,dims,batch", [(2, (3072, 512, 10), 128),          # configuration 2: split-K forward GEMM
-                                          (3, (1024, 256, 128, 10), 64),    # delta GEMM, single tile row
+                                          (3, (1024, 256, 128, 10), 64),    # the kernel of small launches either way
                                           (2, (3072, 1024, 10), 64)])       # configuration 5
 def test_f32_full_tile_kernels_match_bounds_checked_kernels_bit_for_bit(m, dims, batch):
     """Layer shapes that are whole numbers of tiles take the fp32 GEMM kernels without bounds checks (uniform base
-    plus fixed lane offsets); forcing the bounds-checked kernels on the same shapes must give identical bits."""
+    plus fixed lane offsets); forcing the bounds-checked kernels on the same shapes must give identical bits.  (The delta
+    GEMM's: test_gpu_gemm_tiles.py.)"""
     cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 2, seed=1010)
     states = []
     for force in (0, 1):
@@ -324,8 +325,9 @@ def test_pipelined_weight_gradient_kernel_is_bit_identical(m, dims, batch, tau):
 
 
 def test_bf16_full_tile_kernel_matches_bounds_checked_kernel_bit_for_bit():
-    """Configuration 3's layer shapes take the branch-free full-tile forward / delta kernels; forcing the
-    bounds-checked kernel on the same shapes must give identical bits (same slices, same MFMA order)."""
+    """Two workers on configuration 3's layer shapes take the branch-free full-tile forward / delta kernels (64 x 64; the
+    larger tiles: test_gpu_gemm_tiles.py); forcing the bounds-checked kernel on the same shapes must give identical bits
+    (same slices, same MFMA order)."""
     m, dims, batch, K = 2, (3072, 2048, 2048, 2048, 10), 256, 3
     cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 2, seed=606)
     states = []
