@@ -6,13 +6,17 @@
 //   DA   C[M][N] = (A[M][K] B[N][K]^T) * [mask > 0]
 //
 // A workgroup owns a 32 x 16 tile (32 x 32 in larger launches); its four wavefronts share out the contraction (wavefront w
-// takes steps w, w + 4, .. of 16 indices) and load their MFMA fragments (v_mfma_f32_16x16x4_f32) straight from memory, up to
-// eight steps in one round trip: no LDS and no barrier before the wavefronts' sums meet in LDS, in wavefront order.  Lane l of
-// a fragment holds indices 4 (l / 16) .. + 3 of its step, one per MFMA, for both operands: 16-byte loads where the contraction
-// index is contiguous, four dwords of 64 contiguous bytes per 16 lanes where it is not.  Buffer descriptors return zeros past
-// the operands' ends.  How many steps a round trip takes is a template parameter, so that no load is issued for nothing (with
-// twelve always requested, 5 x (36 x 124 x 300) took 8.0 us instead of 4.0); eight or sixteen wavefronts per tile are no
-// faster on any of 70 shapes by more than 8 % and slower on most.
+// takes steps w, w + 4, .. of 16 indices) and load their MFMA fragments (v_mfma_f32_16x16x4_f32) straight from memory: no LDS
+// and no barrier before the wavefronts' sums meet in LDS, in wavefront order.  Lane l of a fragment holds indices
+// 4 (l / 16) .. + 3 of its step, one per MFMA, for both operands: 16-byte loads where the contraction index is contiguous, four
+// dwords of 64 contiguous bytes per 16 lanes where it is not.  Buffer descriptors return zeros past the operands' ends.  How many
+// steps, up to eight, are requested together is a template parameter, so that no load is issued for nothing (with twelve
+// always requested, 5 x (36 x 124 x 300) took 8.0 us instead of 4.0).  In the forward kernels they are one round trip, and the
+// registers grow with their number (24 to 114 and the sums).  Not so in the delta's: the compiler moves the loads of a step
+// between the products of the steps before it, so that about two steps are in flight whatever the number (36 registers from
+// three on) and a wavefront waits once per step.  The rules below and the following figures were measured on these kernels as
+// they are; so was that eight or sixteen wavefronts per tile are no faster on any of 70 shapes by more than 8 % and slower on
+// most.
 //
 // us per launch, 64 x 64 tiles (forward with the pass that adds their K ranges) / here:
 //   workers x (M x N x K)     forward       delta
@@ -156,8 +160,10 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
 // The same for bf16 operands, fp32 accumulation and bf16 results (v_mfma_f32_16x16x32_bf16: lane l of a fragment holds indices
 // 8 (l / 16) .. + 7 of a step of 32).  A tile is 32 x 32; its two column blocks are interleaved (columns 2 (l % 16) and + 1), so
 // that the forward pass, whose weights are contiguous along the columns, takes both blocks' fragments from eight dwords of
-// neighbouring columns and puts them together with byte permutations, and results leave as pairs.  Up to six steps a round trip
-// (a step is ten loads in the forward pass).
+// neighbouring columns and puts them together with byte permutations, and results leave as pairs.  Up to six steps are
+// requested together (a step is ten loads in the forward pass): one round trip in the delta.  In the forward kernels the choice
+// between an offset and the end of the range has become a branch per step that waits for all loads before it, so there a
+// step is a round trip of its own, up to six in a row; the figures and the rule are of these kernels.
 //
 // us per launch, 64 x 64 tiles of kernels_gemm_bf16.hip, whose time is their chain of slices through LDS / here:
 //   workers x (M x N x K)     forward       delta
@@ -308,7 +314,7 @@ bool gemm_small_da_fits(int groups, int M, int N, int K) {
 
 template <int MODE, int TN>
 static void small_start(const SmallDev& p, int steps, hipStream_t s) {
-    // as few round trips of up to eight steps as there have to be, and as short as they then can be
+    // as few trips of up to eight steps (requested together) as there have to be, and as short as they then can be
     const int per = (steps + kW - 1) / kW, trips = (per + 7) / 8, S = (per + trips - 1) / trips;
     const unsigned grid = (unsigned)(p.chunk * kXcds);
 #define OLS_SMALL(S, CHAINS, MORE) gemm_f32_small_kernel<MODE, 2, TN, S, CHAINS, MORE><<<grid, kThreads, 0, s>>>(p)

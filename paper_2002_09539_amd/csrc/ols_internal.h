@@ -12,11 +12,20 @@ namespace ols {
 // themselves live in the matching kernels_*.hip file.  All pointers are device pointers.
 // ---------------------------------------------------------------------------------------------
 
-// Whether the kernels that stream over [m][ld] state use non-temporal accesses.  Up to 25 million elements, parameters, momenta
-// and gradients are worth leaving in the 256 MiB memory-side cache.  Two rounds, non-temporal over plain, by millions of elements
-// (8 workers, momentum; steps alone with pull-back and refresh | stale-average rule):
-//   tau 1   3: 1.10 | 1.06   9: 1.07 | 1.10   18: 1.06 | 1.09   25: 1.00 | 0.98   36: 1.02 | 0.97
-//   tau 4   3: 1.10 | 1.06   9: 1.09 | 1.11   18: 1.07 | 1.08   25: 1.07 | 1.05   36: 0.93 | 0.92
+// Whether the kernels that stream over [m][ld] state (local step, with and without the pull-back; step + pull-back + mean;
+// stale average) use non-temporal accesses.  Up to 25 million elements, parameters, momenta and gradients are worth leaving in the
+// 256 MiB memory-side cache.  Two rounds, non-temporal over plain, by millions of elements (8 workers, momentum 0.9), and the same
+// without momentum, where the state is a third smaller and the line could lie higher:
+//                          3     9    18    25    30    36    50          3     9    18    25    30    36    50
+//   paper     tau 1     1.08  1.06  1.07  1.06  1.03  1.02  0.99       1.03  1.05  1.07  1.06  1.05  1.04  1.01
+//             tau 4     1.03  1.09  1.08  1.08  0.98  0.93  0.93       0.99  1.11  1.07  1.07  1.06  1.04  0.98
+//   one pass  tau 1     1.03  1.08  1.03  1.07  0.96  0.86  0.87       1.00  1.11  1.11  1.05  1.07  1.06  0.89
+//             tau 4     1.13  1.10  1.07  1.08  1.03  0.95  0.92       1.01  1.10  1.09  1.06  1.09  1.08  0.99
+//   stale     tau 1     1.00  1.09  1.09  1.00  0.99  0.97  0.96       1.01  1.09  1.12  1.05  1.00  0.98  0.96
+//             tau 4     1.06  1.10  1.09  1.06  0.98  0.93  0.93       0.99  1.10  1.09  1.05  1.05  1.02  0.95
+//   mixing    tau 1     0.99  1.03  1.08  1.08  1.07  1.02  0.99       0.93  1.00  1.04  1.06  1.06  1.06  1.06
+//   (steps)   tau 4     1.09  1.06  1.06  1.08  1.00  0.93  0.93       1.01  1.04  1.05  1.06  1.07  1.07  0.98
+// (3 million elements without momentum take 20 to 114 us for all the calls of two rounds: the host's time.)
 inline bool state_streams(int64_t m, int64_t ld) { return m * ld > 25000000; }
 
 struct UpdateArgs {

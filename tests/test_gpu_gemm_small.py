@@ -1,5 +1,5 @@
 """GPU parity of the fp32 MLP where its forward and delta GEMMs take the kernel of small launches: tiles, contraction steps and
-round trips of steps that are whole or not, both tile widths, and an infinite weight."""
+groups of steps requested together that are whole or not, both tile widths, and an infinite weight."""
 import numpy as np
 import pytest
 
@@ -16,11 +16,11 @@ pytestmark = pytest.mark.gpu
     (2, (4, 4, 4, 3), 4),                # a quarter of one step, four rows
     (3, (128, 36, 20, 5), 36),           # two steps per wavefront; four rows and four columns more than a tile
     (2, (132, 300, 124, 7), 36),         # one step of four indices more
-    (1, (512, 16, 516, 3), 32),          # a whole round trip of eight steps; contractions of one step and of 33
-    (2, (520, 48, 16, 3), 20),           # nine steps per wavefront: two round trips of five
-    (2, (2060, 24, 8, 4), 20),           # 33 steps per wavefront: five round trips of seven
+    (1, (512, 16, 516, 3), 32),          # a whole group of eight steps; contractions of one step and of 33
+    (2, (520, 48, 16, 3), 20),           # nine steps per wavefront: two groups of five
+    (2, (2060, 24, 8, 4), 20),           # 33 steps per wavefront: five groups of seven
     (32, (360, 444, 8, 4), 24),          # 32 x 32 tiles, the last with 28 columns
-    (9, (760, 384, 92, 6), 164),         # 32 x 32 tiles over two round trips, rows no multiple of a tile
+    (9, (760, 384, 92, 6), 164),         # 32 x 32 tiles over two groups of steps, rows no multiple of a tile
 ])
 def test_gradient_and_loss_match_oracle(m, dims, batch):
     cfg, X, labels, x0 = small_mlp_case(m, dims, batch, 1, seed=421)
@@ -55,8 +55,8 @@ def test_infinite_weight_stays_in_its_column():
 
 
 @pytest.mark.parametrize("m,batch,width,features", [
-    (8, 24, 236, 2936),      # 32 x 16 tiles, round trips that overlap
-    (3, 32, 1200, 912),      # 32 x 16 tiles, round trips one behind the other
+    (8, 24, 236, 2936),      # 32 x 16 tiles, groups of steps that overlap
+    (3, 32, 1200, 912),      # 32 x 16 tiles, groups one behind the other
     (4, 28, 1924, 1872),     # 32 x 32 tiles
 ])
 def test_long_contractions_are_added_in_eight_parts(m, batch, width, features):

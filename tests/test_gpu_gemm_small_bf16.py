@@ -1,5 +1,5 @@
 """GPU parity of the bf16 MLP where its forward and delta GEMMs take the kernel of small launches: rows, columns and
-contractions that are whole tiles, steps and round trips or not, both sides of the rule's lines, and an infinite weight."""
+contractions that are whole tiles, steps and groups of steps or not, both sides of the rule's lines, and an infinite weight."""
 import numpy as np
 import pytest
 
@@ -28,9 +28,9 @@ def one_step(m, dims, batch, cfg, X, labels, x0):
     (2, (8, 8, 8, 3), 8),                # a quarter of one step, eight rows and columns
     (3, (128, 40, 24, 5), 40),           # one step per wavefront; eight rows and eight columns more than a tile
     (2, (136, 296, 136, 7), 40),         # a step of eight indices more
-    (1, (768, 16, 520, 3), 32),          # a whole round trip of six steps
-    (2, (776, 48, 16, 3), 24),           # seven steps per wavefront: two round trips of four
-    (2, (2056, 24, 8, 4), 24),           # 17 steps per wavefront: three round trips of six
+    (1, (768, 16, 520, 3), 32),          # a whole group of six steps
+    (2, (776, 48, 16, 3), 24),           # seven steps per wavefront: two groups of four
+    (2, (2056, 24, 8, 4), 24),           # 17 steps per wavefront: three groups of six
     (25, (320, 1024, 8, 4), 32),         # 8,000 steps of the forward pass, the most that it takes
     (25, (328, 1024, 8, 4), 32),         # 8,800: the 64 x 64 tiles
     (7, (16, 1280, 800, 4), 32),         # 7,000 steps of the delta, the most that it takes
