@@ -278,7 +278,8 @@ OLS_API int ols_attach_convblock_bn_bf16(ols_handle h, int channels, int height,
 /* Bytes of caller-provided device workspace the attached model needs (activations, deltas, per-sample
  * losses, bf16 operand copies).  0 when no model is attached. */
 OLS_API int64_t ols_workspace_bytes(ols_handle h);
-OLS_API int ols_bind_workspace(ols_handle h, void* ws_dev, int64_t bytes); /* 256-byte aligned; OLS_ENOMEM if short */
+OLS_API int ols_bind_workspace(ols_handle h, void* ws_dev, int64_t bytes); /* 256-byte aligned; OLS_ENOMEM if short.
+ * An fp32 MLP some of whose forward GEMMs are a little faster with scratch also takes a workspace without it. */
 
 /* Mini-batches for the NEXT local step: worker i reads X_dev + i * x_worker_stride (elements) and
  * y_dev + i * y_worker_stride (elements of int32 labels or fp32 targets).  Pointers only; no copy. */
@@ -338,8 +339,8 @@ OLS_API int ols_run_steps(ols_handle h, int64_t steps, const float* X_dev, const
  * caller-provided buffer.  The call allocates nothing (no hipMalloc / hipFree, no events); the handle must have
  * been bound and initialised beforehand, and state, data and streams remain the caller's.
  *   - The array holds ols_static_workspace_bytes() = 64 MiB, one copy per GPU, kept until the process ends;
- *     OLS_ENOMEM if ols_workspace_bytes(h) is larger -- except that an fp32 convolutional block which fits with the
- *     kernels that need the least scratch takes those (the same results within the rounding of fp32 sums) until
+ *     OLS_ENOMEM if ols_workspace_bytes(h) is larger -- except that an fp32 convolutional block or MLP which fits with
+ *     the kernels that need the least scratch takes those (the same results within the rounding of fp32 sums) until
  *     ols_bind_workspace is given the bytes that ols_workspace_bytes asked for before; meanwhile it asks for the less.
  *   - fp32 models only (least squares, fp32 MLP, fp32 convolutional blocks): the bf16 MLP keeps weights in its workspace (OLS_EINVAL).
  *   - OLS_ESTATE while OLS_OPT_KERNEL_TIMING is on (timing creates events).

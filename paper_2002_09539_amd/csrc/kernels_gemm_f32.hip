@@ -706,13 +706,11 @@ static hipError_t dw_pipelined_launch(const GemmArgs& g, hipStream_t s) {
 // Large launches run on the bf16 matrix cores with split operands (variant 32, kernels_gemm_split.hip: 234 -> 187 us and
 // 76 -> 61 us on configurations 5 and 2).  What is left is small: there a K range may be as short as 96 indices (5 workers
 // x (36 x 300 x 788): eight ranges 13.8 us, two 17.3), unless the contraction is too short for the second launch that
-// adds the ranges up.  Smaller launches still have a kernel without slices (variant 33, kernels_gemm_small.hip).
-void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* splits) {
+// adds the ranges up.  Smaller launches still have a kernel without slices and without scratch (variant 33,
+// kernels_gemm_small.hip); lean: also where K ranges are a little faster.
+void gemm_f32_fwd_plan(int groups, int M, int N, int K, bool lean, int* variant, int* splits) {
     *variant = 32;
     if (gemm_split_fwd_plan(groups, M, N, K, splits)) return;
-    *variant = 33;
-    *splits = 1;
-    if (gemm_small_fwd_fits(groups, M, N, K)) return;
     *variant = 2;
     int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 63) / 64);
     if (tiles >= 1024 && N >= 128) {
@@ -722,12 +720,15 @@ void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* split
     int s = 1;
     while (K >= 512 && tiles * s < 512 && K / (2 * s) >= 96 && s < 8) s *= 2;
     *splits = s;
+    if (!gemm_small_fwd_fits(groups, M, N, K, lean && s > 1 ? 0 : s)) return;
+    *variant = 33;
+    *splits = 1;
 }
 
 hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant) {
     if (variant == 0) {
         int sp;
-        gemm_f32_fwd_plan(g.groups, g.M, g.N, g.K, &variant, &sp);
+        gemm_f32_fwd_plan(g.groups, g.M, g.N, g.K, false, &variant, &sp);
     }
     switch (variant) {
         case 32: return launch_gemm_split_fwd(g, s);

@@ -296,19 +296,28 @@ bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) ==
 
 }  // namespace
 
-// The rule, from both sides measured on 110 shapes (2 - 64 workers, M 16 - 252, N 64 - 2000, K 64 - 3072): work in steps of 16
-// indices of a 32 x 16 tile.  Forward up to 80,000 (faster on all but three, 2 - 5 % slower there; beyond, 64 x 64 tiles read less),
-// long contractions only up to 30,000 (their K ranges spread better: 13 x (40 x 476 x 2612), 128,000, 40.5 and 45.4).  Delta, whose 64 x 64
+// The rules, from both sides measured on 110 shapes (2 - 64 workers, M 16 - 252, N 64 - 2000, K 64 - 3072) and again on 440, most of
+// them near the lines: work in steps of 16 indices of a 32 x 16 tile.  Forward up to 80,000; beyond, 64 x 64 tiles read less; long
+// contractions only up to 30,000 (their K ranges spread better: 13 x (40 x 476 x 2612), 128,000, 40.5 and 45.4).  Delta, whose 64 x 64
 // tiles have no K ranges, the same without that and up to 160,000 from K = 1024 on (7 x (76 x 1348 x 1396) 63.0 and 54.5;
 // 22 x (64 x 536 x 2256), 211,000: 56.9 and 66.4).
+// Where the 64 x 64 tiles come close to whole rounds of 256 they are at their best: with more than 1,250 tiles here (1,230 in the
+// delta) for each of their rounds, only up to 50,000 (70,000).  Forward 20 x (52 x 236 x 1984) 27.8 and 34.4, 11 x (64 x 412 x 1804) 28.6
+// and 34.5, 9 x (100 x 1680 x 300) 21.3 and 23.4, but below 6 x (52 x 644 x 1564), 48,200, 1.21 times as fast; delta
+// 6 x (80 x 1160 x 1376) 39.9 and 46.4, 14 x (156 x 364 x 704) 26.9 and 30.6, but 38 x (180 x 492 x 136), 63,600, 1.67 times.  Of 360 other
+// shapes that the rules take, the forward ones 1.31 times as fast in the geometric mean and the delta ones 1.70, two forward ones
+// lose 3 and 6 % (2 x (84 x 276 x 2536), 18.4 and 19.5).
 static int64_t small_tiles(int groups, int M, int N) { return (int64_t)groups * ((M + 31) / 32) * ((N + 15) / 16); }
+static int64_t tile_rounds(int groups, int M, int N, int ranges) { return ((int64_t)groups * ((M + 63) / 64) * ((N + 63) / 64) * ranges + 255) / 256; }
 static bool small_offsets(int64_t a_elems, int64_t b_elems) { return a_elems < (1 << 28) && b_elems < (1 << 28); }   // 32-bit byte offsets
-bool gemm_small_fwd_fits(int groups, int M, int N, int K) {
-    const int64_t work = small_tiles(groups, M, N) * ((K + 15) / 16);
+bool gemm_small_fwd_fits(int groups, int M, int N, int K, int ranges) {
+    const int64_t tiles = small_tiles(groups, M, N), work = tiles * ((K + 15) / 16);
+    if (tiles * ranges > 1250 * tile_rounds(groups, M, N, ranges) && work > 50000) return false;   // (never with no ranges)
     return work <= (K <= 2048 ? 80000 : 30000) && small_offsets((int64_t)M * K, (int64_t)K * N);
 }
 bool gemm_small_da_fits(int groups, int M, int N, int K) {
-    const int64_t work = small_tiles(groups, M, N) * ((K + 15) / 16);
+    const int64_t tiles = small_tiles(groups, M, N), work = tiles * ((K + 15) / 16);
+    if (tiles > 1230 * tile_rounds(groups, M, N, 1) && work > 70000) return false;
     return work <= (K >= 1024 ? 160000 : 80000) && small_offsets((int64_t)M * K, (int64_t)K * N);
 }
 
@@ -384,17 +393,27 @@ static hipError_t small_launch(int mode, const GemmArgs& g, hipStream_t s) {
 hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s) { return small_launch(kFwd, g, s); }
 hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s) { return small_launch(kDa, g, s); }
 
-// The bf16 rule, from both sides measured on 120 shapes (2 - 61 workers, M 16 - 250, N 64 - 2000, K 64 - 3000): work in steps of 32
-// indices of a 32 x 32 tile.  Forward up to 8,000, where it is faster on every shape (1.07 - 2.3 times), and up to 15,000 from K = 640
-// on (1.01 - 1.44 times; shorter contractions of that size lose: 14 x (168 x 536 x 192), 8,570, 5.5 and 6.0; a step of
-// 3 x 2016-512-1264-4 at batch 208, whose second layer is 13,440 with K = 512, 2 % of its time).
-// Delta up to 7,000 (1.02 - 1.7 times), up to 15,000 from K = 1024 on (6 x (72 x 520 x 1032), 10,100: 8.2 and 7.4; 4 x (32 x 1928 x
-// 1872), 14,400: 11.4 and 7.8; but 6 x (224 x 608 x 608), 15,200: 6.3 and 9.3).
+// The bf16 rules, from both sides measured on 120 shapes (2 - 61 workers, M 16 - 250, N 64 - 2000, K 64 - 3000) and again on 550, most
+// of them near the lines: work in steps of 32 indices of a 32 x 32 tile.
+// Forward up to 8,000, and up to 15,000 from K = 640 on and with up to 500 tiles (1.01 - 1.44 times; shorter contractions of that
+// size lose: 14 x (168 x 536 x 192), 8,570, 5.5 and 6.0; a step of 3 x 2016-512-1264-4 at batch 208, whose second layer is 13,440
+// with K = 512, 2 % of its time; 5 x (240 x 392 x 896), 520 tiles, 10.8 and 11.8).
+// Delta up to 7,000 where the tiles are at most 490 for each round of 256 of the 64 x 64 ones (beyond, 0.86 to 1.09 times:
+// 16 x (184 x 216 x 320) 7.6 and 8.8, 38 x (64 x 568 x 160) 8.3 and 8.9); from K = 1024 on up to 15,000, with one tile per compute unit
+// at most: up to 256 tiles 1.16 - 1.67 times on 80 shapes, with 257 and more 0.83 - 1.13 on 30 (2 x (72 x 1376 x 1088), 258 tiles,
+// 10.7 and 12.9).  Of 360 other shapes that the rules take (1.18 and 1.17 times), one forward one loses 5 %, one delta one 8 %
+// (5 x (56 x 1736 x 424) 8.6 and 9.1, 3 x (72 x 1304 x 576) 8.7 and 9.5), the rest 3 % at most.
 static int64_t small_tiles_bf16(int groups, int M, int N) { return (int64_t)groups * ((M + 31) / 32) * ((N + 31) / 32); }
 bool gemm_small_bf16_fits(const GemmArgs& g, bool fwd) {
-    const int64_t work = small_tiles_bf16(g.groups, g.M, g.N) * ((g.K + 31) / 32);
-    const int64_t most = fwd ? (g.K >= 640 ? 15000 : 8000) : (g.K >= 1024 ? 15000 : 7000);
-    return work <= most && small_offsets((int64_t)g.M * g.lda, (int64_t)(fwd ? g.K : g.N) * g.ldb);
+    const int64_t tiles = small_tiles_bf16(g.groups, g.M, g.N), work = tiles * ((g.K + 31) / 32);
+    if (fwd) {
+        if (work > (g.K >= 640 && tiles <= 500 ? 15000 : 8000)) return false;
+    } else if (g.K >= 1024) {
+        if (tiles > 256 || work > 15000) return false;
+    } else if (tiles > 490 * tile_rounds(g.groups, g.M, g.N, 1) || work > 7000) {
+        return false;
+    }
+    return small_offsets((int64_t)g.M * g.lda, (int64_t)(fwd ? g.K : g.N) * g.ldb);
 }
 
 template <int MODE>

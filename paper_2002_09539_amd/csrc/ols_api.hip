@@ -75,7 +75,7 @@ struct ols_ctx {
     int splitk = 0;                   // 0: from the shape
     bool gemm_force_general = false;
     bool head_dw_guest = true;        // output-layer gradients ride in the last hidden layer's weight-gradient launch
-    std::vector<int> fwd_splits;      // planned K ranges per hidden layer (fp32 forward GEMM)
+    std::vector<int> fwd_variant, fwd_splits;   // planned kernel and K ranges per hidden layer (fp32 forward GEMM)
     int64_t off_partial = 0;
     // schedule
     int64_t k = 0;
@@ -99,7 +99,7 @@ struct ols_ctx {
     int64_t off_a1 = 0, off_a2 = 0, off_dz1 = 0, off_dz2 = 0, off_pooled = 0, off_dpool = 0, off_cpartial = 0;
     int64_t off_z1 = 0, off_z2 = 0, off_bnstats = 0, off_bnsums = 0, off_bnpart = 0, off_dn = 0, off_wstat = 0;
     int cv_dw_splits = 1;      // fp32 block: pixel ranges of the kernel gradients
-    bool cv_lean = false;      // fp32 block: the kernels that need the least scratch (see ols_run_steps_static)
+    bool lean = false;         // fp32 MLP or block: the kernels that need the least scratch (see ols_bind_workspace, ols_run_steps_static)
     int64_t off_wsplit = -1;   // fp32 block: split kernels (-1: the shape takes the fp32 matrix cores)
     const float* X = nullptr;
     const void* y = nullptr;
@@ -329,11 +329,13 @@ void plan_workspace(ols_ctx* c) {
             c->off_dz[l] = take(m * B * c->dims[l] * es);
         }
         c->fwd_splits.assign(L, 1);
+        c->fwd_variant.assign(L, 0);
         if (!bf) {  // scratch for the split-K forward GEMMs: room for up to 8 K ranges where splitting is planned
             int64_t need_partial = 0;
             for (int l = 0; l < L - 1; ++l) {
                 int variant, splits;
-                gemm_f32_fwd_plan(c->m, c->B, c->dims[l + 1], c->dims[l], &variant, &splits);
+                gemm_f32_fwd_plan(c->m, c->B, c->dims[l + 1], c->dims[l], c->lean, &variant, &splits);
+                c->fwd_variant[l] = variant;
                 c->fwd_splits[l] = splits;
                 if (splits > 1) need_partial = std::max<int64_t>(need_partial, 8 * m * B * c->dims[l + 1] * 4);
             }
@@ -409,9 +411,9 @@ void plan_workspace(ols_ctx* c) {
         c->off_dz1 = take(act);
         c->off_pooled = take(m * B * c->cv_C * 4);
         c->off_dpool = take(m * B * c->cv_C * 4);
-        const bool split = !c->cv_lean && conv3x3_split_fits(c->B, c->cv_H, c->cv_W, c->cv_C);
+        const bool split = !c->lean && conv3x3_split_fits(c->B, c->cv_H, c->cv_W, c->cv_C);
         c->cv_dw_splits = split ? conv3x3_split_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C)
-                                : conv3x3_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->cv_lean ? 1024 : 256);
+                                : conv3x3_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->lean ? 1024 : 256);
         const int64_t cpartial = c->cv_dw_splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4;
         c->off_cpartial = take(cpartial);
         c->off_dlogits = take(m * B * c->cv_classes * 4);
@@ -424,7 +426,7 @@ void plan_workspace(ols_ctx* c) {
             c->off_bnsums = take(m * 2 * c->cv_C * 4);
             // (lean: in the place of the kernel gradient's partial sums, which are read before the next normalisation's are written)
             const int64_t bnpart = bn_partial_floats(c->m, c->B * c->cv_H * c->cv_W, c->cv_C) * 4;
-            c->off_bnpart = c->cv_lean && bnpart <= cpartial ? c->off_cpartial : take(bnpart);
+            c->off_bnpart = c->lean && bnpart <= cpartial ? c->off_cpartial : take(bnpart);
             // the split convolutions leave partial statistics of their output (one convolution's at a time)
             c->off_wstat = split && c->cv_C % 64 == 0 ? take(m * conv3x3_split_stat_parts(c->B, c->cv_H, c->cv_W) * 3 * c->cv_C * 4) : -1;
         }
@@ -903,7 +905,7 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
             ga.partial = (float*)(c->ws + c->off_partial);
         }
         rc = enqueue(c, OLS_K_GEMM_FWD, 0, c->cur, -1,
-                     [&](hipStream_t s) { return bf ? launch_gemm_bf16_fwd(ga, s) : launch_gemm_f32_fwd(ga, s, c->gemm_variant[0]); });
+                     [&](hipStream_t s) { return bf ? launch_gemm_bf16_fwd(ga, s) : launch_gemm_f32_fwd(ga, s, c->gemm_variant[0] ? c->gemm_variant[0] : c->fwd_variant[l]); });
         if (rc) return rc;
     }
     // output layer, loss, and its gradients
@@ -1229,6 +1231,7 @@ int ols_attach_lsq(ols_handle c, int batch) {
     if (c->k != 0) return fail(OLS_ESTATE, "models are attached before the first local step");
     c->model = MODEL_LSQ;
     c->B = batch;
+    c->lean = false;
     c->ws = nullptr;
     c->batch_set = false;
     plan_workspace(c);
@@ -1267,6 +1270,7 @@ int ols_attach_mlp(ols_handle c, int n_layers, const int* dims, int batch, int g
     c->dims.assign(dims, dims + n_layers + 1);
     c->w_off = w_off;
     c->b_off = b_off;
+    c->lean = false;
     c->ws = nullptr;
     c->batch_set = false;
     plan_workspace(c);
@@ -1302,7 +1306,7 @@ int attach_convblock(ols_ctx* c, int channels, int height, int width, int classe
     c->cv_classes = classes;
     c->cv_bn = bn;
     c->cv_eps = eps;
-    c->cv_lean = false;
+    c->lean = false;
     c->ws = nullptr;
     c->batch_set = false;
     plan_workspace(c);
@@ -1332,11 +1336,18 @@ int ols_bind_workspace(ols_handle c, void* ws, int64_t bytes) {
     if (int rc = need(c)) return rc;
     if (c->model == MODEL_NONE) return fail(OLS_ESTATE, "no model attached");
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u)) return fail(OLS_EINVAL, "workspace must be non-null and 256-byte aligned");
-    if (c->cv_lean) {   // chosen for the static workspace: one that holds the kernels ols_run_steps prefers takes them again
-        c->cv_lean = false;
+    // Chosen for the static workspace: one that holds the kernels ols_run_steps prefers takes them again.  An fp32 MLP whose
+    // workspace does not hold them takes those that need the least here as well.
+    const bool was_lean = c->lean;
+    if (was_lean || (c->model == MODEL_MLP && bytes < c->ws_need)) {
+        c->lean = false;
         plan_workspace(c);
         if (bytes < c->ws_need) {
-            c->cv_lean = true;
+            c->lean = was_lean || c->model == MODEL_MLP;
+            plan_workspace(c);
+        }
+        if (bytes < c->ws_need && c->lean != was_lean) {   // refused: the plan stays the bound workspace's
+            c->lean = was_lean;
             plan_workspace(c);
         }
     }
@@ -1630,13 +1641,13 @@ int ols_run_steps_static(ols_handle c, int64_t steps, const float* X, const void
         return fail(OLS_EINVAL, "the bf16 model keeps its bf16 weights in the workspace, which must then outlive the call: "
                                 "bind a caller-owned workspace and use ols_run_steps");
     if (c->timing) return fail(OLS_ESTATE, "per-kernel timing creates events; switch OLS_OPT_KERNEL_TIMING off first");
-    if (c->ws_need > kStaticWorkspaceBytes && c->model == MODEL_CONV && !c->cv_lean) {
+    if (c->ws_need > kStaticWorkspaceBytes && (c->model == MODEL_CONV || c->model == MODEL_MLP) && !c->lean) {
         // the split kernels' images and their many partial sums are what may not fit (1 worker x 16 x 32 x 32 x 128: 71 MiB
         // against 41 MiB): the fp32 matrix cores and fewer ranges then, until a workspace that holds the others is bound
-        c->cv_lean = true;
+        c->lean = true;
         plan_workspace(c);
         if (c->ws_need > kStaticWorkspaceBytes) {
-            c->cv_lean = false;
+            c->lean = false;
             plan_workspace(c);
         }
     }

@@ -183,12 +183,13 @@ struct GemmArgs {
 // fp32 MFMA.  fwd: C[M][N] = relu(A[M][K] W[K][N] + bias);  dw: C[M][N] = A[K][M]^T B[K][N];
 // da: C[M][N] = (A[M][K] B[N][K]^T) * (mask > 0)
 hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant);
-void gemm_f32_fwd_plan(int groups, int M, int N, int K, int* variant, int* splits);
+void gemm_f32_fwd_plan(int groups, int M, int N, int K, bool lean, int* variant, int* splits);   // lean: with little scratch
 hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_gemm_f32_da(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_splitk_finish(const float* partial, int splits, const GemmArgs& g, hipStream_t s);
-// forward and delta of small launches (kernels_gemm_small.hip), and whether a shape takes them
-bool gemm_small_fwd_fits(int groups, int M, int N, int K);
+// forward and delta of small launches (kernels_gemm_small.hip), and whether a shape takes them (forward: `ranges`, the K ranges
+// over which the 64 x 64 tiles would add it; 0: as if they were not at their best)
+bool gemm_small_fwd_fits(int groups, int M, int N, int K, int ranges);
 bool gemm_small_da_fits(int groups, int M, int N, int K);
 hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s);
