@@ -91,7 +91,7 @@ struct ols_ctx {
     int64_t ws_bytes = 0, ws_need = 0;
     // workspace sub-buffers (byte offsets)
     std::vector<int64_t> off_act, off_dz;
-    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_gate = 0, off_x0 = 0, off_flags = 0;
+    int64_t off_dlogits = 0, off_loss = 0, off_resid = 0, off_shadow = 0, off_gate = 0, off_images = -1, off_x0 = 0, off_flags = 0;
     // residual convolutional block: channels, image size, classes; workspace sub-buffers
     int cv_C = 0, cv_H = 0, cv_W = 0, cv_classes = 0;
     bool cv_bn = false;     // convolutions without bias, each followed by batch normalisation
@@ -304,6 +304,13 @@ BnTail bn_tail_layout(const ols_ctx* c) {
     return t;
 }
 
+// The bf16 blocks' images of a step's kernels (three times 9 C C values per worker) in what is left of a place of the workspace
+// between two offsets, or -1: too little (kernel_images).
+int64_t images_behind(const ols_ctx* c, int64_t from, int64_t to) {
+    from = align256(from);
+    return from + (int64_t)3 * c->m * 9 * c->cv_C * c->cv_C * 2 <= to ? from : -1;
+}
+
 void plan_workspace(ols_ctx* c) {
     int64_t off = 0;
     auto take = [&](int64_t bytes) {
@@ -373,6 +380,7 @@ void plan_workspace(ols_ctx* c) {
         if (bn_has_tail(c)) c->off_gate = c->off_a2 + align256(bn_tail_layout(c).floats * 4);
         else if (act / 16 <= cpartial) c->off_gate = c->off_cpartial;
         else { c->off_gate = c->off_dn; c->off_dn = c->off_z2; }
+        c->off_images = bn_has_tail(c) ? images_behind(c, c->off_gate + act / 16, c->off_a2 + act) : -1;
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_bnstats = take(2 * m * 2 * c->cv_C * 4);
@@ -400,6 +408,7 @@ void plan_workspace(ols_ctx* c) {
         if ((c->cv_H + 2) * (c->cv_W + 2) >= 64) c->off_gate = c->off_a2 + align256(m * conv3x3_bf16_pool_part_floats(c->B, c->cv_H, c->cv_W, c->cv_C) * 4);
         else if (padded / 4 <= cpartial) c->off_gate = c->off_cpartial;
         else { c->off_gate = c->off_dz1; c->off_dz1 = c->off_a2; }
+        c->off_images = (c->cv_H + 2) * (c->cv_W + 2) >= 64 ? images_behind(c, c->off_gate + padded / 4, c->off_a2 + padded * 4) : -1;
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
         c->off_shadow = take(m * c->ld * 2);
@@ -434,19 +443,28 @@ void plan_workspace(ols_ctx* c) {
     c->ws_need = off;
 }
 
-// Where the bf16 blocks keep the images of a step's kernels: in the kernels' gradients, which are written later in the step --
-// the second convolution's by its weight-gradient launch, behind both forward launches, and the first's at the step's end,
-// behind the delta.  (A kernel's gradient holds two images: 9 C C floats.)
+// Where the bf16 blocks keep the images of a step's kernels: in a2's place behind the sign bytes of a1, or, where they do not fit
+// (batches of few pixels), in the kernels' gradients, which are written later in the step -- the second convolution's by its
+// weight-gradient launch, behind both forward launches, and the first's at the step's end, behind the delta.  (A kernel's
+// gradient holds two images: 9 C C floats.  Us for six rounds with all in the gradients and as it is: 11 x 26 x 6 x 8 x 64 plain
+// 574 and 568, 11 x 26 x 8 x 8 x 64 normalised 865 and 857.)
 ConvBImages kernel_images(ols_ctx* c, const uint16_t* shadow, int64_t wa, int64_t wb) {
     const int64_t n_w = (int64_t)9 * c->cv_C * c->cv_C;
     ConvBImages im = {};
     im.wa = shadow + wa;
     im.wb = shadow + wb;
-    im.fwd_a = (uint16_t*)(c->g + wb);
-    im.fwd_b = im.fwd_a + n_w;
-    im.dx_b = (uint16_t*)(c->g + wa);
     im.s_w = c->ld;
-    im.s_image = 2 * c->ld;
+    if (c->off_images >= 0) {
+        im.fwd_a = (uint16_t*)(c->ws + c->off_images);
+        im.fwd_b = im.fwd_a + c->m * n_w;
+        im.dx_b = im.fwd_b + c->m * n_w;
+        im.s_image = n_w;
+    } else {
+        im.fwd_a = (uint16_t*)(c->g + wb);
+        im.fwd_b = im.fwd_a + n_w;
+        im.dx_b = (uint16_t*)(c->g + wa);
+        im.s_image = 2 * c->ld;
+    }
     return im;
 }
 
