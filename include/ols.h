@@ -95,7 +95,9 @@ enum {
                                       With an MLP both routes execute the same fp32 operation sequence per element
                                       (identical bits); the one-launch least-squares kernel sums in another order. */
     OLS_OPT_GEMM_FORCE_GENERAL = 14, /* 1: the GEMMs always take their bounds-checked kernel, also on
-                                      shapes the full-tile kernel covers (both give identical bits); default 0     */
+                                      shapes the full-tile kernel covers (both give identical bits); default 0.
+                                      Forward and delta GEMMs of small launches have one kernel, which checks its
+                                      bounds, either way                                                           */
     OLS_OPT_ANCHOR_DELAY_US = 15,  /* emulated communication latency, 0 (default) .. 1000000 microseconds: a kernel
                                       that only waits that long runs ahead of every anchor refresh on the refresh's
                                       stream, standing in for the all-reduce time of a real cluster (Section 2: the
