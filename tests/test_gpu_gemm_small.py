@@ -20,6 +20,9 @@ pytestmark = pytest.mark.gpu
     (2, (520, 48, 16, 3), 20),           # nine steps per wavefront: two groups of five
     (2, (2060, 24, 8, 4), 20),           # 33 steps per wavefront: five groups of seven
     (32, (360, 444, 8, 4), 24),          # 32 x 32 tiles, the last with 28 columns
+    (2, (764, 40, 16, 3), 20),           # twelve steps per wavefront in one sum ..
+    (2, (768, 40, 16, 3), 20),           # .. and in two
+    (6, (32, 1160, 1376, 4), 80),        # a delta of 1314 tiles, 113,004 steps: one round of 64 x 64 tiles instead
     (6, (760, 384, 92, 6), 164),         # 32 x 32 tiles over two groups of steps, rows no multiple of a tile
 ])
 def test_gradient_and_loss_match_oracle(m, dims, batch):

@@ -35,6 +35,11 @@ def one_step(m, dims, batch, cfg, X, labels, x0):
     (25, (328, 1024, 8, 4), 32),         # 8,800: the 64 x 64 tiles
     (7, (16, 1280, 800, 4), 32),         # 7,000 steps of the delta, the most that it takes
     (8, (1032, 520, 264, 6), 72),        # 13,464 of a long contraction
+    (8, (16, 1024, 1032, 4), 32),        # 256 tiles of the delta over a long contraction, the most that it takes
+    (8, (16, 1032, 1032, 4), 32),        # 264: the 64 x 64 tiles
+    (14, (16, 1112, 80, 4), 32),         # 490 tiles of the delta beside one round of the 64 x 64 ones, the most that it takes
+    (38, (16, 568, 160, 4), 64),         # 1368 and two: the 64 x 64 tiles
+    (5, (896, 392, 8, 4), 240),          # 520 tiles of the forward pass, 14,560 steps: the 64 x 64 tiles
 ])
 def test_gradient_and_loss_match_oracle(m, dims, batch):
     """2e-2 in L2: a value on a bf16 rounding boundary may fall on either side of it."""
