@@ -581,7 +581,7 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     constexpr size_t lds = GemmShape<MODE, BM, BN, BK>::kLdsBytes;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     void (*kern)(GemmDevB) = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH, true>;
-    if (MODE == kDw && p.upd.cached) kern = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH, MODE != kDw>;
+    if (MODE == kDw && !update_streams(p.upd, p.upd_w_off, p.N)) kern = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH, MODE != kDw>;
     unsigned threads = kThreads;
     if constexpr (MODE != kDw && BK == 64) {
         // full tiles and 32-bit lane offsets: the branch-free, interleaved kernel

@@ -616,7 +616,7 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     }
     if (!full) {
         // (only the weight gradient touches state)
-        if (MODE == kDw && p.upd.cached) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false, MODE != kDw><<<grid, kThreads, 0, s>>>(p);
+        if (MODE == kDw && !update_streams(p.upd, p.upd_w_off, p.N)) gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false, MODE != kDw><<<grid, kThreads, 0, s>>>(p);
         else gemm_f32_kernel<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false, true><<<grid, kThreads, 0, s>>>(p);
     }
     hipError_t e = hipGetLastError();
@@ -757,7 +757,7 @@ hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant) {
         // The persistent kernel that spreads a tile's update over the next tile's K loop wins where a tile has
         // enough K slices to hide the state's latency behind (K = 128, configuration 2: 0.1853 -> 0.1826 ms per
         // step); with K = 64 (configuration 5) it loses (665 us against 585 us per launch).
-        if (g.upd.enabled && g.K == 128 && dw_pipelined_fits(g)) variant = 16;
+        if (g.upd.enabled && g.K == 128 && g.upd_w_off % 32 == 0 && dw_pipelined_fits(g)) variant = 16;   // (it streams)
         else if (!g.upd.enabled) variant = 1;
         else variant = (int64_t)g.groups * ((g.M + 127) / 128) * ((g.N + 127) / 128) < 4096 ? 11 : 8;
     }

@@ -116,6 +116,14 @@ inline bool state_cached(int64_t elements, int more, bool in_place) {
     return elements * (8 + more) <= (int64_t)205000000 || (in_place && elements * (4 + more) <= (int64_t)185000000);
 }
 
+// Whether a weight gradient with the fused update accesses a layer's state non-temporally (n columns; its weights start w_off
+// elements into a replica row).  Only where a row of it is whole 128-byte lines: else two tiles side by side share a line, and
+// what the first leaves of it non-temporally does not wait in L2 for the second.  State of 2 arrays in place, tiles of 64 x 64, us
+// non-temporal / plain: 22 x (1636 x 692) 108 / 58, x 688 81 / 58, x 704 75 / 59; 29 x (1592 x 996) 233 / 148, x 992 137 / 140.
+// Two rounds, us: 12 x (2096-924-64-1100-6, batch 16) tau 8 1347 / 709;  29 x (1592-996-14, 32) tau 2 1284 / 1022;  14 x
+// (2464-1928-1040-156-7, 24) tau 8 5361 / 4723;  bf16, 43 x (1184-456-13, 96) tau 8 2266 / 1873.
+inline bool update_streams(const FusedUpdate& u, int64_t w_off, int n) { return !u.cached && n % 32 == 0 && w_off % 32 == 0; }
+
 #if defined(__HIPCC__)
 }  // namespace ols
 #include "update_rule.h"

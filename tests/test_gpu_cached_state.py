@@ -31,3 +31,20 @@ def test_either_side_of_the_line(dtype, dims, batch, below, above):
     assert not np.array_equal(a[0], x0)
     for i in (0, below - 1):
         assert np.array_equal(a[i], b[i])
+
+
+@pytest.mark.parametrize("dtype,dims,batch,m", [
+    ("f32", (1024, 1028, 10), 64, 20),          # 254 MB; rows of 32 lines and 16 bytes
+    ("f32", (68, 100, 128, 192, 10), 128, 3),   # the third layer's rows are whole lines that start inside one
+    ("bf16", (1024, 1048, 10), 64, 20),
+])
+def test_rows_that_are_no_whole_lines(dtype, dims, batch, m):
+    """Their state is accessed plainly at any size: worker by worker the bits of a single worker's run."""
+    cfg, X, labels, x0 = small_mlp_case(1, dims, batch, 2, seed=433)
+    x0 = x0 + G.generic_normal(3, 1, x0.shape, sigma=0.02)
+    a = two_steps(m, dims, batch, dtype, X, labels, x0)
+    assert not np.array_equal(a[0], x0)
+    for i in range(1, m):
+        assert np.array_equal(a[0], a[i])
+    b = two_steps(m + 1, dims, batch, dtype, X, labels, x0)
+    assert np.array_equal(a[m - 1], b[0])
