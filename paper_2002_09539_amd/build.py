@@ -23,6 +23,7 @@ SOURCES = [
     "kernels_gemm_f32.hip",
     "kernels_gemm_small.hip",
     "kernels_gemm_split.hip",
+    "kernels_mlp_strip.hip",
     "kernels_gemm_bf16.hip",
     "kernels_conv.hip",
     "kernels_conv_split.hip",

@@ -66,11 +66,11 @@ struct STile {
         for (int q = 0; q < kVecs; ++q) {
             const int v = threadIdx.x + q * kThreads, line = v / kVecLine, e = 8 * (v % kVecLine);
             const int row = KC ? row0 + line : row0 + e;
-            l.k[q] = KC ? e : line;
+            l.k[q] = KC ? 16 * (e / 16) + e % 16 / 2 : line;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const bool ok = KC ? row < rows : row + 4 * h < rows;
-                l.off[q][h] = ok ? 4u * (unsigned)(KC ? row * ld + e + 4 * h : line * ld + row + 4 * h) : kNowhere;
+                l.off[q][h] = ok ? 4u * (unsigned)(KC ? row * ld + l.k[q] + 8 * h : line * ld + row + 4 * h) : kNowhere;
             }
         }
     }
@@ -80,7 +80,7 @@ struct STile {
         for (int q = 0; q < kVecs; ++q)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const bool in = l.k[q] + (KC ? 4 * h : 0) < klen;
+                const bool in = l.k[q] + (KC ? 8 * h : 0) < klen;
                 r[q][h] = __builtin_bit_cast(f4, buf_load(rs, in ? l.off[q][h] : kNowhere, first));
             }
     }
@@ -102,7 +102,8 @@ struct STile {
             *(u4*)(d + 2 * kTerm) = s.lo;
         }
     }
-    // rows r0 .. r0 + 31 (a multiple of 32), k-step s: lane holds k = 16 s + 8 (lane / 32) + 0 .. 7 of row lane % 32
+    // rows r0 .. r0 + 31 (a multiple of 32), k-step s: lane holds k = 16 s + 4 (lane / 32) + 0 .. 3 and 8 further on, of row lane %
+    // 32: the order of the same product in kernels_mlp_strip.hip, so that both leave the same bits
     __device__ static void frag(SplitFrag& f, const uint8_t* lds, int r0, int s, int lane) {
         if constexpr (KC) {
             const int row = r0 + lane % 32, slot = 2 * s + lane / 32;
@@ -113,12 +114,12 @@ struct STile {
         } else {
             typedef s4v __attribute__((address_space(3))) * lds_s4_ptr;
             const int blk = lane / 16, j = lane % 16;
-            const int line = 16 * s + 8 * (blk / 2) + j / 4;
-            const int key = ROWS == 128 ? line & 3 : (line >> 1) & 1;   // the same four lines on
+            const int line = 16 * s + 4 * (blk / 2) + j / 4;
+            const int key = ROWS == 128 ? line & 3 : (line >> 1) & 1;   // the same eight lines on
             const uint8_t* p = lds + line * kLine + (((r0 / 32) ^ key) << 6) + (16 * (blk % 2) + 4 * (j % 4)) * 2;
             auto term = [&](int t) {
                 const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(p + t * kTerm));
-                const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(p + t * kTerm + 4 * kLine));
+                const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(p + t * kTerm + 8 * kLine));
                 return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             };
             f.hi = term(0);
@@ -279,7 +280,8 @@ hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     p.k_chunk = g.K;
     if (g.splits > 1) {
         if (!g.partial) return hipErrorInvalidValue;
-        p.k_chunk = (int)round_up((g.K + g.splits - 1) / g.splits, kBK);
+        p.k_chunk = g.k_chunk ? g.k_chunk : (int)round_up((g.K + g.splits - 1) / g.splits, kBK);
+        if (p.k_chunk % kBK) return hipErrorInvalidValue;
         p.splits = (g.K + p.k_chunk - 1) / p.k_chunk;   // never an empty split
         p.partial = g.partial;
     }

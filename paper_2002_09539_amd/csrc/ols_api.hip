@@ -77,6 +77,11 @@ struct ols_ctx {
     bool head_dw_guest = true;        // output-layer gradients ride in the last hidden layer's weight-gradient launch
     std::vector<int> fwd_variant, fwd_splits;   // planned kernel and K ranges per hidden layer (fp32 forward GEMM)
     int64_t off_partial = 0;
+    // fp32 MLP: the first hidden layer's weight gradient goes by column strips, over strip_ranges ranges of the weights' rows (0: it
+    // does not).  Inside ols_run_steps its launch then also forms the next step's product, on next_X; fwd_ready: it has.
+    int strip_ranges = 0;
+    const float* next_X = nullptr;
+    bool fwd_ready = false;
     // schedule
     int64_t k = 0;
     bool pull_due = false, pending_update = false, anchor_due = false, anchor_inflight = false,
@@ -337,6 +342,7 @@ void plan_workspace(ols_ctx* c) {
         }
         c->fwd_splits.assign(L, 1);
         c->fwd_variant.assign(L, 0);
+        c->strip_ranges = 0;
         if (!bf) {  // scratch for the split-K forward GEMMs: room for up to 8 K ranges where splitting is planned
             int64_t need_partial = 0;
             for (int l = 0; l < L - 1; ++l) {
@@ -344,7 +350,14 @@ void plan_workspace(ols_ctx* c) {
                 gemm_f32_fwd_plan(c->m, c->B, c->dims[l + 1], c->dims[l], c->lean, &variant, &splits);
                 c->fwd_variant[l] = variant;
                 c->fwd_splits[l] = splits;
-                if (splits > 1) need_partial = std::max<int64_t>(need_partial, 8 * m * B * c->dims[l + 1] * 4);
+                const bool scratch = splits > 1;
+                int ranges;
+                if (l == 0 && variant != 33 && mlp_strip_plan(c->m, c->B, c->dims[1], c->dims[0], scratch ? 8 : 1, &ranges)) {
+                    c->strip_ranges = ranges;   // and the forward kernel with the same products in the same order
+                    c->fwd_variant[0] = 32;
+                    c->fwd_splits[0] = ranges;
+                }
+                if (scratch) need_partial = std::max<int64_t>(need_partial, 8 * m * B * c->dims[l + 1] * 4);
             }
             if (need_partial) c->off_partial = take(need_partial);
         }
@@ -900,7 +913,10 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
         if (rc) return rc;
     }
     // hidden layers forward
+    const bool fwd_ready = c->fwd_ready;
+    c->fwd_ready = false;
     for (int l = 0; l < L - 1; ++l) {
+        if (l == 0 && fwd_ready) continue;
         GemmArgs ga = {};
         ga.a = act(l);
         ga.sa = act_stride(l);
@@ -922,6 +938,7 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
             ga.splits = c->splitk > 0 ? c->splitk : c->fwd_splits[l];
             ga.partial = (float*)(c->ws + c->off_partial);
         }
+        if (l == 0 && c->strip_ranges && !c->splitk && ga.splits > 1) ga.k_chunk = mlp_strip_range_rows(ga.K, ga.splits);
         rc = enqueue(c, OLS_K_GEMM_FWD, 0, c->cur, -1,
                      [&](hipStream_t s) { return bf ? launch_gemm_bf16_fwd(ga, s) : launch_gemm_f32_fwd(ga, s, c->gemm_variant[0] ? c->gemm_variant[0] : c->fwd_variant[l]); });
         if (rc) return rc;
@@ -1011,6 +1028,27 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
         gw.K = B;
         if (upd) {   // first updating launch when the output layer's gradients ride in it
             if ((rc = wait_if_update_must(c))) return rc;
+        }
+        if (l == 0 && c->strip_ranges && !c->gemm_variant[1]) {
+            gw.splits = c->strip_ranges;
+            MlpStripNext next = {};
+            const bool ahead = upd && c->next_X && !c->gemm_variant[0] && !c->splitk;
+            // with one range the product takes the place of the delta that the same workgroups have read: the guests still read
+            // the activations
+            const bool in_place = c->strip_ranges == 1;
+            if (ahead) {
+                next.x = c->next_X;
+                next.out = (float*)(c->ws + (in_place ? c->off_dz[1] : c->off_act[1]));
+                next.partial = (float*)(c->ws + c->off_partial);
+                next.bias = c->x[dst_buf] + c->b_off[0];
+                next.ranges = c->strip_ranges;
+            }
+            rc = enqueue(c, OLS_K_GEMM_DW, 0, upd ? src_buf : -1, upd ? dst_buf : -1,
+                         [&](hipStream_t s) { return launch_mlp_strip(gw, ahead ? &next : nullptr, s); });
+            if (rc) return rc;
+            if (ahead && in_place) std::swap(c->off_act[1], c->off_dz[1]);
+            c->fwd_ready = ahead;
+            continue;
         }
         rc = enqueue(c, OLS_K_GEMM_DW, 0, upd ? src_buf : -1, upd ? dst_buf : -1,
                      [&](hipStream_t s) { return bf ? launch_gemm_bf16_dw(gw, s, c->gemm_variant[1]) : launch_gemm_f32_dw(gw, s, c->gemm_variant[1]); });
@@ -1626,6 +1664,13 @@ int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, in
     const int64_t row = sample_elems(c);
     const int64_t x_batch = (int64_t)c->B * row, y_batch = c->B;   // elements per batch
     const size_t y_elem = 4;                                          // int32 labels and fp32 targets alike
+    // Whether a step's weight-gradient launch may form the next step's first product: nobody counts or times the launches, and
+    // (below) nothing rewrites the models between the two.
+    const bool look_ahead = !c->dry && !c->trace && !c->timing;
+    struct Ahead {
+        ols_ctx* c;
+        ~Ahead() { c->next_X = nullptr; c->fwd_ready = false; }
+    } ahead{c};
     for (int64_t it = 0; it < steps; ++it) {
         LsqRoundPlan plan;
         lsq_round_plan(c, steps - it, X, x_batch, &plan);
@@ -1638,6 +1683,8 @@ int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, in
         int rc = ols_set_batch(c, X + b * x_batch, (int64_t)nb * x_batch, (const char*)y + (size_t)(b * y_batch) * y_elem,
                                (int64_t)nb * y_batch);
         if (rc) return rc;
+        const bool rewritten = (c->k + 1) % c->tau == 0 && (c->mix_w || c->snap);
+        c->next_X = look_ahead && it + 1 < steps && !rewritten ? X + (c->k + 1) % nb * x_batch : nullptr;
         rc = ols_local_step(c);
         if (rc) return rc;
         if (c->pull_due) {

@@ -176,6 +176,7 @@ struct GemmArgs {
     const void* mask;   // dA: activations whose sign gates the output, same shape as c, stride smask
     float* colsum;      // dw: optional [N] per group, receives the column sums of B (the bias gradient)
     float* partial;     // fp32 fwd with splits > 1: scratch of splits * groups * M * N floats
+    int k_chunk;        // split forward with splits > 1: contraction indices of a range, a multiple of 32 (0: an even share)
     int splits;         // fp32 fwd: number of K ranges contracted by separate workgroups (<= 1: none)
     int force_general;  // use the bounds-checked kernel even where the full-tile kernel applies
     const HeadArgs* guest;  // dw: the output layer's weight / bias gradients (launch_head_bwd's work) are computed by
@@ -209,6 +210,18 @@ hipError_t launch_gemm_small_bf16_da(const GemmArgs& g, hipStream_t s);
 bool gemm_split_fits(int64_t a_elems, int64_t b_elems);   // elements a group's operand spans
 bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits);
 hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s);
+// Weight gradient of an fp32 MLP's first hidden layer by column strips (kernels_mlp_strip.hip); with the fused update it can form
+// the next step's forward product as well.  Whether a shape takes it, and over how many ranges of the weights' rows.
+struct MlpStripNext {
+    const float* x;       // the next step's batch, strides as GemmArgs::a
+    float* out;           // relu(x W + bias) with the updated parameters, [B][N] per worker
+    float* partial;       // ranges > 1: ranges * groups * B * N floats
+    const float* bias;    // where the update leaves the bias, upd.ld between workers
+    int ranges;
+};
+bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int* ranges);
+int mlp_strip_range_rows(int K, int ranges);
+hipError_t launch_mlp_strip(const GemmArgs& g, const MlpStripNext* next, hipStream_t s);
 // bf16 operands, fp32 accumulate.  fwd: A[M][K], W[K][N];  dw: A[K][M], B[K][N] (K = batch);  da: A[M][K], W[N][K]
 hipError_t launch_gemm_bf16_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant);

@@ -1,0 +1,118 @@
+"""The fp32 MLP's first hidden layer by column strips: the gradients against the oracle, and the loop inside the library, whose
+launches form the next step's product from the weights that they have just updated, against one call per step -- to the bit, over
+ragged rows, columns and batches, one range of rows and several, and every rule of synchronisation."""
+import numpy as np
+import pytest
+
+from ols_inputs import generate as G
+from oracle import ols_oracle as O
+from tests.helpers import max_norm_ratio
+from tests.test_gpu_mlp import GRAD_TOL, make_session, small_mlp_case
+
+from paper_2002_09539_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    (64, (324, 388, 10), 36),           # one range; six tiles, the last of four rows; a last strip of four columns
+    (60, (520, 260, 36, 7), 64),        # whole batch blocks; another hidden layer; a last tile of eight rows
+    (48, (840, 516, 5), 100),           # by halves of the samples; the last block of the batch is four samples
+    (10, (2060, 388, 10), 72),          # several ranges, the last one short
+    (12, (1856, 380, 24), 128),         # several ranges, whole batch; more than 16 classes
+    (32, (1028, 640, 9), 4),            # the smallest batch
+]
+
+
+def case(m, dims, batch, nb, seed):
+    cfg, X, labels, x0 = small_mlp_case(m, dims, batch, nb, seed)
+    return cfg, X, labels, x0 + G.generic_normal(3, 1, x0.shape, sigma=0.02)
+
+
+@pytest.mark.parametrize("m,dims,batch", SHAPES)
+def test_gradient_and_loss_match_oracle(m, dims, batch):
+    cfg, X, labels, x0 = case(m, dims, batch, 1, 511)
+    with make_session(m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+        s.set_option(B.OLS_OPT_FUSE_GEMM_UPDATE, 0)     # keep the gradients in g so they can be read
+        s.attach_mlp(dims, batch, "f32")
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        g, losses = s.gradient(), s.losses()
+    for i in (0, m // 2, m - 1):
+        loss, grad = O.mlp_loss_grad(x0, dims, X[i, 0], labels[i, 0])
+        assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
+        assert max_norm_ratio(g[i], grad) <= GRAD_TOL
+
+
+def run(m, dims, batch, X, labels, x0, tau, K, library, mu=0.9, setup=lambda s: None, rule=None, beta_z=0.0, second=True):
+    with make_session(m, x0.size, tau, 0.6, 0.05, mu, overlap_buffer=second) as s:
+        if beta_z:
+            s.set_anchor_momentum(beta_z)
+        s.attach_mlp(dims, batch, "f32")
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        if rule == "stale":
+            s.set_stale_average()
+        elif rule == "mixing":
+            w = np.zeros((m + 1, m + 1))
+            w[:m, :m] = 0.5 * np.eye(m) + 0.5 / m
+            w[:m, m] = 1.0 / m
+            s.set_mixing(w)
+        elif rule == "one_pass":
+            s.set_option(B.OLS_OPT_FUSE_MEAN, 1)
+        setup(s)
+        if library:
+            s.run_resident(K - 2, Xd, yd)
+            s.run_resident(2, Xd, yd)
+        else:
+            s.run(K, lambda k: s.set_batch(Xd[:, k % X.shape[1]], yd[:, k % X.shape[1]]))
+        out = [s.all_params(), s.params(-1), s.losses()]
+        return out + ([s.momentum()] if mu else [])
+
+
+def same(a, b):
+    return all(np.array_equal(p, q, equal_nan=True) for p, q in zip(a, b))
+
+
+@pytest.mark.parametrize("m,dims,batch", SHAPES)
+@pytest.mark.parametrize("tau,mu", [(2, 0.9), (1, 0.0)])
+def test_library_loop_equals_one_call_per_step(m, dims, batch, tau, mu):
+    cfg, X, labels, x0 = case(m, dims, batch, 3, 512)
+    a = run(m, dims, batch, X, labels, x0, tau, 7, True, mu)
+    b = run(m, dims, batch, X, labels, x0, tau, 7, False, mu)
+    assert same(a, b) and np.isfinite(a[0]).all() and not np.array_equal(a[0][0], x0)
+
+
+@pytest.mark.parametrize("rule,kw", [
+    ("stale", {}), ("mixing", {}), ("one_pass", {}), (None, dict(beta_z=0.7)), (None, dict(second=False)),
+    (None, dict(setup=lambda s: s.set_option(B.OLS_OPT_NESTEROV, 0))),
+    (None, dict(setup=lambda s: s.set_option(B.OLS_OPT_SERIALIZE, 0))),
+    (None, dict(setup=lambda s: s.set_option(B.OLS_OPT_HEAD_DW_GUEST, 0))),
+    (None, dict(setup=lambda s: s.set_option(B.OLS_OPT_FUSE_GEMM_UPDATE, 0))),
+    (None, dict(setup=lambda s: s.set_option(B.OLS_OPT_KERNEL_TIMING, 1))),
+])
+@pytest.mark.parametrize("shape", [0, 3])
+def test_every_rule_and_schedule(rule, kw, shape):
+    m, dims, batch = SHAPES[shape]
+    cfg, X, labels, x0 = case(m, dims, batch, 3, 513)
+    a = run(m, dims, batch, X, labels, x0, 3, 8, True, rule=rule, **kw)
+    b = run(m, dims, batch, X, labels, x0, 3, 8, False, rule=rule, **kw)
+    assert same(a, b)
+
+
+@pytest.mark.parametrize("shape", [0, 2])
+def test_infinite_and_huge_values(shape):
+    """Inputs and weights that round to a bf16 infinity, and infinities: the same bits, finite where they do not reach."""
+    m, dims, batch = SHAPES[shape]
+    cfg, X, labels, x0 = case(m, dims, batch, 2, 514)
+    X = X.copy()
+    X[0, 1, 1, 3] = 3.4e38
+    X[1, 1, 2, dims[0] - 1] = np.inf
+    X[2, 0, 0, 0] = -np.inf
+    a = run(m, dims, batch, X, labels, x0, 2, 4, True)
+    b = run(m, dims, batch, X, labels, x0, 2, 4, False)
+    assert same(a, b)
+    assert np.isnan(a[0][2]).any()
+    solo = run(m, dims, batch, X, labels, x0, 4, 2, True)     # before any synchronisation the other workers are untouched
+    assert np.isfinite(solo[0][3]).all() and np.isfinite(solo[0][m - 1]).all()
