@@ -80,7 +80,7 @@ struct GemmShape {
 };
 
 template <int MODE, int BM, int BN, int BK, int DEPTH, bool STREAM>   // STREAM: DW, non-temporal accesses to the state
-__global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
+__device__ __forceinline__ void gemm_bf16_tile(const GemmDevB& p, int bid, uint16_t* lds_all) {
     constexpr int WM = BM / 2, WN = BN / 2;     // 2 x 2 wavefronts
     constexpr int TM = WM / 32, TN = WN / 32;
     constexpr int S = BK / 16;                  // MFMA steps per K slice
@@ -89,13 +89,11 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
     using Shape = GemmShape<MODE, BM, BN, BK>;
     using TA = typename Shape::TA;
     using TB = typename Shape::TB;
-    extern __shared__ __attribute__((aligned(16))) uint16_t lds_all[];
     auto lds_a = [&](int buf) { return lds_all + buf * TA::kElems; };
     auto lds_b = [&](int buf) { return lds_all + 2 * TA::kElems + buf * TB::kElems; };
 
     // Guest workgroups come first in the launch, so they start at once and their latency-bound work runs
     // beside the tiles of the GEMM.  Their number is a multiple of 8: the tiles keep their XCD assignment.
-    int bid = blockIdx.x;
     if (MODE == kDw) {
         if (bid < p.guest.blocks) {
             head_dw_guest<(int)(Shape::kLdsBytes / sizeof(float))>(p.guest, (float*)lds_all, bid);
@@ -330,6 +328,25 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
 }
 
 
+template <int MODE, int BM, int BN, int BK, int DEPTH, bool STREAM>
+__global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmDevB p) {
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds_all[];
+    gemm_bf16_tile<MODE, BM, BN, BK, DEPTH, STREAM>(p, blockIdx.x, lds_all);
+}
+
+// The weight gradients of several layers in one launch.
+struct GemmDwLayersB {
+    GemmDevB layer[kDwMostLayers];
+    int end[kDwMostLayers];   // workgroups up to and with a layer's
+};
+template <int BM, int BN, int BK, int DEPTH, bool STREAM>
+__global__ __launch_bounds__(kThreads) void gemm_bf16_dw_layers_kernel(GemmDwLayersB q) {
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds_all[];
+    int l = 0, first = 0;
+    while (l + 1 < kDwMostLayers && (int)blockIdx.x >= q.end[l]) first = q.end[l++];
+    gemm_bf16_tile<kDw, BM, BN, BK, DEPTH, STREAM>(q.layer[l], blockIdx.x - first, lds_all);
+}
+
 // ---------------------------------------------------------------------------------------------
 // FWD / DA on full tiles: M % BM == 0, N % BN == 0, K % (NSETS BK) == 0.  One workgroup per compute unit with one
 // or two wavefronts per SIMD (THREADS = 256 or 512): little else is resident to fill a stall, and a wavefront that
@@ -531,8 +548,9 @@ __global__ __launch_bounds__(THREADS) void gemm_bf16_full_kernel(GemmDevB p) {
 
 static bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
-template <int MODE, int BM, int BN, int BK, int DEPTH>
-static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
+// checks the operands' shapes and fills in what the kernel takes
+template <int MODE, int BM, int BN, int BK>
+static hipError_t gemm_prepare(const GemmArgs& g, GemmDevB* out) {
     if (!g.a || !g.b || !g.c || g.groups < 1 || g.M < 1 || g.N < 1 || g.K < 1) return hipErrorInvalidValue;
     // 16-byte vectors of 8 bf16 along each operand's contiguous dimension: aligned bases, leading
     // dimensions and extents in multiples of 8
@@ -548,7 +566,8 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
         if (!aligned16(g.c) || g.ldc % 8 || g.sc % 8) return hipErrorInvalidValue;
     }
     if (g.ldc < g.N) return hipErrorInvalidValue;
-    GemmDevB p = {};
+    GemmDevB& p = *out;
+    p = GemmDevB{};
     if (g.guest) {
         if (MODE != kDw) return hipErrorInvalidValue;
         hipError_t ge = head_dw_prepare(*g.guest, &p.guest);
@@ -578,6 +597,14 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     if (total > (1 << 30)) return hipErrorInvalidValue;
     p.total_tiles = (int)total;
     p.chunk = (int)((total + kXcds - 1) / kXcds);
+    return hipSuccess;
+}
+
+template <int MODE, int BM, int BN, int BK, int DEPTH>
+static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
+    GemmDevB p;
+    hipError_t pe = gemm_prepare<MODE, BM, BN, BK>(g, &p);
+    if (pe != hipSuccess) return pe;
     constexpr size_t lds = GemmShape<MODE, BM, BN, BK>::kLdsBytes;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     void (*kern)(GemmDevB) = gemm_bf16_kernel<MODE, BM, BN, BK, DEPTH, true>;
@@ -625,13 +652,16 @@ hipError_t launch_gemm_bf16_da(const GemmArgs& g, hipStream_t s) {
     if (g.M > 128) return gemm_launch<kDa, 256, 128, 64, 2>(g, s);
     return gemm_launch<kDa, 128, 128, 64, 2>(g, s);
 }
-hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant) {
+static int dw_variant(const GemmArgs& g) {
     // Measured on configuration 3 (K = batch = 256, fused update): 64 x 128 x 32 tiles leave four workgroups per
     // compute unit and take 284 us per launch; 128 x 128: 309, 128 x 64: 294, 64 x 64: 295, BK = 64: 319-341.
     // Up to 1024 of those tiles -- one round at four per compute unit -- 64 x 64 x 32 fills the chip better: 2 workers 64 x
     // 512-256 10.6 -> 8.2 us, 8 workers 200 x 1000-136 15.5 -> 14.2, 16 workers 128 x 1024-512 37.8 -> 35.9; 4 workers 256 x
     // 3072-2048-1024 (3072 tiles) 67.7 -> 71.5.
-    if (variant == 0) variant = (int64_t)g.groups * ((g.M + 63) / 64) * ((g.N + 127) / 128) <= 1024 ? 3 : 1;
+    return (int64_t)g.groups * ((g.M + 63) / 64) * ((g.N + 127) / 128) <= 1024 ? 3 : 1;
+}
+hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant) {
+    if (variant == 0) variant = dw_variant(g);
     switch (variant) {
         case 1: return gemm_launch<kDw, 64, 128, 32, 1>(g, s);
         case 3: return gemm_launch<kDw, 64, 64, 32, 1>(g, s);
@@ -643,6 +673,38 @@ hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant) {
 #endif
         default: return hipErrorInvalidValue;
     }
+}
+
+template <int BN>
+static hipError_t dw_layers(const GemmArgs* g, int n, hipStream_t s) {
+    GemmDwLayersB q = {};
+    unsigned grid = 0;
+    for (int j = 0; j < kDwMostLayers; ++j) {
+        if (j < n) {
+            hipError_t e = gemm_prepare<kDw, 64, BN, 32>(g[j], &q.layer[j]);
+            if (e != hipSuccess) return e;
+            grid += (unsigned)(q.layer[j].guest.blocks + q.layer[j].chunk * kXcds);
+        }
+        q.end[j] = (int)grid;
+    }
+    constexpr size_t lds = GemmShape<kDw, 64, BN, 32>::kLdsBytes;
+    static_assert(lds <= 64 * 1024, "no more LDS than any launch may have");
+    if (update_streams(g[0].upd, g[0].upd_w_off, g[0].N)) gemm_bf16_dw_layers_kernel<64, BN, 32, 1, true><<<grid, kThreads, lds, s>>>(q);
+    else gemm_bf16_dw_layers_kernel<64, BN, 32, 1, false><<<grid, kThreads, lds, s>>>(q);
+    return hipGetLastError();
+}
+// Layers that access their state alike share a launch, in the larger tiles if one of them takes those.
+hipError_t launch_gemm_bf16_dw_layers(const GemmArgs* g, int n, hipStream_t s) {
+    for (int i = 0; i < n;) {
+        auto streams = [&](int j) { return update_streams(g[j].upd, g[j].upd_w_off, g[j].N); };
+        int variant = dw_variant(g[i]), k = i + 1;
+        for (; k < n && k - i < kDwMostLayers && !g[k].guest && streams(k) == streams(i); ++k)
+            if (dw_variant(g[k]) == 1) variant = 1;
+        hipError_t e = k == i + 1 ? launch_gemm_bf16_dw(g[i], s, variant) : variant == 3 ? dw_layers<64>(g + i, k - i, s) : dw_layers<128>(g + i, k - i, s);
+        if (e != hipSuccess) return e;
+        i = k;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -48,8 +48,11 @@ struct GemmDev {
     HeadDwDev guest;     // DW: output-layer gradients computed by the first guest.blocks workgroups (0: none)
 };
 
+template <int MODE, int BM, int BN, int BK>
+constexpr int gemm_lds_floats() { return 2 * Tile<BM, BK, MODE != kDw>::kFloats + 2 * Tile<BN, BK, MODE == kDa>::kFloats; }
+
 template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH, bool FULL, bool STREAM>
-__global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDev p) {
+__device__ __forceinline__ void gemm_f32_tile(const GemmDev& p, int bid, float* lds_all) {
     constexpr bool A_KC = MODE != kDw;   // FWD, DA: A[M][K];  DW: A[K][M]
     constexpr bool B_KC = MODE == kDa;   // DA: B[N][K];  FWD, DW: B[K][N]
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -59,14 +62,12 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDev p) {
     static_assert(DEPTH == 1 || DEPTH == 2, "global prefetch distance in K slices");
     using TA = Tile<BM, BK, A_KC>;
     using TB = Tile<BN, BK, B_KC>;
-    constexpr int kLdsFloats = 2 * TA::kFloats + 2 * TB::kFloats;
-    __shared__ __attribute__((aligned(16))) float lds_all[kLdsFloats];
+    constexpr int kLdsFloats = gemm_lds_floats<MODE, BM, BN, BK>();
     auto lds_a = [&](int buf) { return lds_all + buf * TA::kFloats; };
     auto lds_b = [&](int buf) { return lds_all + 2 * TA::kFloats + buf * TB::kFloats; };
 
     // Guest workgroups come first in the launch, so they start at once and their latency-bound work runs
     // beside the tiles of the GEMM.  Their number is a multiple of 8: the tiles keep their XCD assignment.
-    int bid = blockIdx.x;
     if (MODE == kDw) {
         if (bid < p.guest.blocks) {
             head_dw_guest<kLdsFloats>(p.guest, lds_all, bid);
@@ -295,6 +296,25 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDev p) {
             }
         }
     }
+}
+
+template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH, bool FULL, bool STREAM>
+__global__ __launch_bounds__(kThreads) void gemm_f32_kernel(GemmDev p) {
+    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<MODE, BM, BN, BK>()];
+    gemm_f32_tile<MODE, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, FULL, STREAM>(p, blockIdx.x, lds);
+}
+
+// The weight gradients of several layers in one launch.
+struct GemmDwLayers {
+    GemmDev layer[kDwMostLayers];
+    int end[kDwMostLayers];   // workgroups up to and with a layer's
+};
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH, bool STREAM>
+__global__ __launch_bounds__(kThreads) void gemm_f32_dw_layers_kernel(GemmDwLayers q) {
+    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<kDw, BM, BN, BK>()];
+    int l = 0, first = 0;
+    while (l + 1 < kDwMostLayers && (int)blockIdx.x >= q.end[l]) first = q.end[l++];
+    gemm_f32_tile<kDw, BM, BN, BK, WAVES_M, WAVES_N, DEPTH, false, STREAM>(q.layer[l], blockIdx.x - first, lds);
 }
 
 // Weight gradient with the fused update as a persistent, software-pipelined kernel.
@@ -551,8 +571,9 @@ hipError_t launch_splitk_finish(const float* partial, int splits, const GemmArgs
 
 static bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
-template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH>
-static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
+// checks the operands' shapes and fills in what the kernel takes
+template <int MODE, int BM, int BN, int BK>
+static hipError_t gemm_prepare(const GemmArgs& g, GemmDev* out) {
     if (!g.a || !g.b || !g.c || g.groups < 1 || g.M < 1 || g.N < 1 || g.K < 1) return hipErrorInvalidValue;
     // 16-byte vector loads: every line start must be aligned and extents multiples of 4
     if (!aligned16(g.a) || !aligned16(g.b) || g.lda % 4 || g.ldb % 4 || g.sa % 4 || g.sb % 4) return hipErrorInvalidValue;
@@ -561,7 +582,8 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     if (g.lda < (a_kc ? g.K : g.M) || g.ldb < (b_kc ? g.K : g.N) || g.ldc < g.N) return hipErrorInvalidValue;
     if (MODE == kFwd && !g.bias) return hipErrorInvalidValue;
     if (MODE == kDa && !g.mask) return hipErrorInvalidValue;
-    GemmDev p = {};
+    GemmDev& p = *out;
+    p = GemmDev{};
     if (g.guest) {
         if (MODE != kDw) return hipErrorInvalidValue;
         hipError_t ge = head_dw_prepare(*g.guest, &p.guest);
@@ -600,6 +622,14 @@ static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     if (total > (1 << 30)) return hipErrorInvalidValue;
     p.total_tiles = (int)total;
     p.chunk = (int)((total + kXcds - 1) / kXcds);
+    return hipSuccess;
+}
+
+template <int MODE, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int DEPTH>
+static hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
+    GemmDev p;
+    hipError_t pe = gemm_prepare<MODE, BM, BN, BK>(g, &p);
+    if (pe != hipSuccess) return pe;
     // Full tiles, K ranges that are whole (for DEPTH 2: even) numbers of slices, and operands small enough for
     // 32-bit lane offsets take the kernel without bounds checks; same arithmetic, identical bits.
     constexpr bool a_kc_ = MODE != kDw, b_kc_ = MODE == kDa;
@@ -747,20 +777,21 @@ hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant) {
         default: return hipErrorInvalidValue;
     }
 }
+static int dw_variant(const GemmArgs& g) {
+    // Measured (configurations 2 and 5): writing the gradient out, 128 x 128 tiles are fastest; with
+    // the update fused into the epilogue the kernel is bound by the HBM traffic of the state, and
+    // smaller tiles (more workgroups whose compute and epilogue phases interleave) win; with the small
+    // tiles a second K slice of global loads in flight costs one register and gains 3 % (configuration 2:
+    // 103.3 -> 100.3 us).
+    // The persistent kernel that spreads a tile's update over the next tile's K loop wins where a tile has
+    // enough K slices to hide the state's latency behind (K = 128, configuration 2: 0.1853 -> 0.1826 ms per
+    // step); with K = 64 (configuration 5) it loses (665 us against 585 us per launch).
+    if (g.upd.enabled && g.K == 128 && g.upd_w_off % 32 == 0 && dw_pipelined_fits(g)) return 16;   // (it streams)
+    if (!g.upd.enabled) return 1;
+    return (int64_t)g.groups * ((g.M + 127) / 128) * ((g.N + 127) / 128) < 4096 ? 11 : 8;
+}
 hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant) {
-    if (variant == 0) {
-        // Measured (configurations 2 and 5): writing the gradient out, 128 x 128 tiles are fastest; with
-        // the update fused into the epilogue the kernel is bound by the HBM traffic of the state, and
-        // smaller tiles (more workgroups whose compute and epilogue phases interleave) win; with the small
-        // tiles a second K slice of global loads in flight costs one register and gains 3 % (configuration 2:
-        // 103.3 -> 100.3 us).
-        // The persistent kernel that spreads a tile's update over the next tile's K loop wins where a tile has
-        // enough K slices to hide the state's latency behind (K = 128, configuration 2: 0.1853 -> 0.1826 ms per
-        // step); with K = 64 (configuration 5) it loses (665 us against 585 us per launch).
-        if (g.upd.enabled && g.K == 128 && g.upd_w_off % 32 == 0 && dw_pipelined_fits(g)) variant = 16;   // (it streams)
-        else if (!g.upd.enabled) variant = 1;
-        else variant = (int64_t)g.groups * ((g.M + 127) / 128) * ((g.N + 127) / 128) < 4096 ? 11 : 8;
-    }
+    if (variant == 0) variant = dw_variant(g);
     switch (variant) {
         case 1: return gemm_launch<kDw, 128, 128, 16, 2, 2, 1>(g, s);
         case 8: return gemm_launch<kDw, 64, 128, 16, 2, 2, 1>(g, s);
@@ -779,6 +810,36 @@ hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant) {
 #endif
         default: return hipErrorInvalidValue;
     }
+}
+template <int BN, int DEPTH>
+static hipError_t dw_layers(const GemmArgs* g, int n, hipStream_t s) {
+    GemmDwLayers q = {};
+    unsigned grid = 0;
+    for (int j = 0; j < kDwMostLayers; ++j) {
+        if (j < n) {
+            hipError_t e = gemm_prepare<kDw, 64, BN, 16>(g[j], &q.layer[j]);
+            if (e != hipSuccess) return e;
+            grid += (unsigned)(q.layer[j].guest.blocks + q.layer[j].chunk * kXcds);
+        }
+        q.end[j] = (int)grid;
+    }
+    if (update_streams(g[0].upd, g[0].upd_w_off, g[0].N)) gemm_f32_dw_layers_kernel<64, BN, 16, 2, 2, DEPTH, true><<<grid, kThreads, 0, s>>>(q);
+    else gemm_f32_dw_layers_kernel<64, BN, 16, 2, 2, DEPTH, false><<<grid, kThreads, 0, s>>>(q);
+    return hipGetLastError();
+}
+// Layers that access their state alike share a launch, in the larger tiles if one of them takes those; the persistent kernel has
+// one of its own.
+hipError_t launch_gemm_f32_dw_layers(const GemmArgs* g, int n, hipStream_t s) {
+    for (int i = 0; i < n;) {
+        auto streams = [&](int j) { return update_streams(g[j].upd, g[j].upd_w_off, g[j].N); };
+        int variant = dw_variant(g[i]), k = i + 1;
+        for (; variant != 16 && k < n && k - i < kDwMostLayers && !g[k].guest && dw_variant(g[k]) != 16 && streams(k) == streams(i); ++k)
+            if (dw_variant(g[k]) == 8) variant = 8;
+        hipError_t e = k == i + 1 ? launch_gemm_f32_dw(g[i], s, variant) : variant == 8 ? dw_layers<128, 1>(g + i, k - i, s) : dw_layers<64, 2>(g + i, k - i, s);
+        if (e != hipSuccess) return e;
+        i = k;
+    }
+    return hipSuccess;
 }
 hipError_t launch_gemm_f32_da(const GemmArgs& g, hipStream_t s, int variant) {
     if (variant == 0 && gemm_small_da_fits(g.groups, g.M, g.N, g.K)) return launch_gemm_small_da(g, s);

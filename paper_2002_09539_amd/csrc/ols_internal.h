@@ -222,6 +222,11 @@ struct MlpStripNext {
 bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int* ranges);
 int mlp_strip_range_rows(int K, int ranges);
 hipError_t launch_mlp_strip(const GemmArgs& g, const MlpStripNext* next, hipStream_t s);
+// The weight gradients of n layers with the fused update, whose deltas are all there: up to kDwMostLayers in a launch, the bits of
+// one launch each.  Only the first may have a guest.
+constexpr int kDwMostLayers = 4;
+hipError_t launch_gemm_f32_dw_layers(const GemmArgs* g, int n, hipStream_t s);
+hipError_t launch_gemm_bf16_dw_layers(const GemmArgs* g, int n, hipStream_t s);
 // bf16 operands, fp32 accumulate.  fwd: A[M][K], W[K][N];  dw: A[K][M], B[K][N] (K = batch);  da: A[M][K], W[N][K]
 hipError_t launch_gemm_bf16_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_bf16_dw(const GemmArgs& g, hipStream_t s, int variant);
