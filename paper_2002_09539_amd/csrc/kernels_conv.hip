@@ -437,13 +437,13 @@ __global__ __launch_bounds__(kThreads, OLS_CONV_DW_WAVES) void conv3x3_dw_kernel
 
 // Sums the parts of every kernel / bias entry over the pixel ranges in range order and writes the gradient.  One lane per
 // four consecutive entries (the kernel's and the bias's counts are multiples of four), eight ranges' loads in flight.
-__global__ __launch_bounds__(256) void conv_dw_finish_kernel(const float* __restrict__ partial, int splits, int groups,
-                                                             int64_t per_group, int64_t n_w, float* g, int64_t ld,
-                                                             int64_t w_off, int64_t b_off) {
+__global__ __launch_bounds__(256) void conv_dw_finish_kernel(ConvDwParts first, ConvDwParts second, int splits, int groups,
+                                                             int64_t per_group, int64_t n_w, float* g, int64_t ld) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= per_group) return;
     const int group = blockIdx.y;
-    const float* P = partial + (int64_t)group * per_group + i;
+    const ConvDwParts l = blockIdx.z ? second : first;
+    const float* P = l.partial + (int64_t)group * per_group + i;
     const int64_t step = (int64_t)groups * per_group;
     f4 s = {0.f, 0.f, 0.f, 0.f};
     constexpr int kFly = 8;
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void conv_dw_finish_kernel(const float* __rest
         for (int t = 0; t < kFly; ++t)
             if (sp0 + t < splits) s = s + v[t];
     }
-    float* dst = i < n_w ? g + (int64_t)group * ld + w_off + i : b_off >= 0 ? g + (int64_t)group * ld + b_off + (i - n_w) : nullptr;
+    float* dst = i < n_w ? g + (int64_t)group * ld + l.w_off + i : l.b_off >= 0 ? g + (int64_t)group * ld + l.b_off + (i - n_w) : nullptr;
     if (dst) {   // a convolution without bias has b_off < 0
 #pragma unroll
         for (int e = 0; e < 4; ++e) dst[e] = s[e];
@@ -600,16 +600,17 @@ hipError_t launch_conv3x3_dw(const ConvArgs& a, hipStream_t s) {
     conv3x3_dw_kernel<BK, OLS_CONV_DW_DEPTH><<<(unsigned)(p.chunk * kXcds), kThreads, 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_conv_dw_finish(a.partial, p.splits, a.groups, a.C, a.g, a.ld, a.g_w_off, a.g_b_off, s);
+    const ConvDwParts parts = {a.partial, a.g_w_off, a.g_b_off};
+    return launch_conv_dw_finish(&parts, 1, p.splits, a.groups, a.C, a.g, a.ld, s);
 }
 
-hipError_t launch_conv_dw_finish(const float* partial, int splits, int groups, int C, float* g, int64_t ld, int64_t w_off,
-                                 int64_t b_off, hipStream_t s) {
-    if (!partial || !g || splits < 1 || groups < 1 || groups > 65535 || C < 1) return hipErrorInvalidValue;
+hipError_t launch_conv_dw_finish(const ConvDwParts* layers, int n, int splits, int groups, int C, float* g, int64_t ld, hipStream_t s) {
+    if (!layers || n < 1 || n > 2 || !g || splits < 1 || groups < 1 || groups > 65535 || C < 1 || C % 4) return hipErrorInvalidValue;
+    for (int l = 0; l < n; ++l)
+        if (!layers[l].partial || !aligned16(layers[l].partial)) return hipErrorInvalidValue;
     const int64_t n_w = (int64_t)9 * C * C, per_group = n_w + C;
-    if (C % 4 || (reinterpret_cast<uintptr_t>(partial) & 15u)) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((per_group / 4 + 255) / 256), (unsigned)groups);
-    conv_dw_finish_kernel<<<grid, 256, 0, s>>>(partial, splits, groups, per_group, n_w, g, ld, w_off, b_off);
+    dim3 grid((unsigned)((per_group / 4 + 255) / 256), (unsigned)groups, (unsigned)n);
+    conv_dw_finish_kernel<<<grid, 256, 0, s>>>(layers[0], layers[n - 1], splits, groups, per_group, n_w, g, ld);
     return hipGetLastError();
 }
 

@@ -660,7 +660,8 @@ hipError_t launch_conv3x3_split_dw(const ConvArgs& a, hipStream_t s) {
     conv3x3_split_dw_kernel<<<(unsigned)(p.chunk * kXcds), kDwThreads, kDwRing * kDwRow + 2 * kDwBK * kDwRow, s>>>(p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_conv_dw_finish(a.partial, p.splits, a.groups, a.C, a.g, a.ld, a.g_w_off, a.g_b_off, s);
+    const ConvDwParts parts = {a.partial, a.g_w_off, a.g_b_off};
+    return launch_conv_dw_finish(&parts, 1, p.splits, a.groups, a.C, a.g, a.ld, s);
 }
 
 hipError_t launch_conv3x3_split_fwd(const ConvArgs& a, hipStream_t s) { return conv_launch<0>(a, s); }

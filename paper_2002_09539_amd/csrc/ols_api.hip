@@ -104,6 +104,8 @@ struct ols_ctx {
     int64_t off_a1 = 0, off_a2 = 0, off_dz1 = 0, off_dz2 = 0, off_pooled = 0, off_dpool = 0, off_cpartial = 0;
     int64_t off_z1 = 0, off_z2 = 0, off_bnstats = 0, off_bnsums = 0, off_bnpart = 0, off_dn = 0, off_wstat = 0;
     int cv_dw_splits = 1;      // fp32 block: pixel ranges of the kernel gradients
+    int cv_dw_pair = 0;        // bf16 blocks: pixel ranges of a launch for both kernels' gradients, 0: a launch for each
+    int64_t off_cpartial_b = 0;   // its second layer's partial sums, in places that nobody reads any more by then
     bool lean = false;         // fp32 MLP or block: the kernels that need the least scratch (see ols_bind_workspace, ols_run_steps_static)
     int64_t off_wsplit = -1;   // fp32 block: split kernels (-1: the shape takes the fp32 matrix cores)
     const float* X = nullptr;
@@ -386,6 +388,10 @@ void plan_workspace(ols_ctx* c) {
         const int64_t splits = conv3x3_bf16_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
         const int64_t cpartial = splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4;
         c->off_cpartial = take(cpartial);
+        c->off_cpartial_b = c->off_z1;   // what the normalisations, pooling and classifier read and wrote
+        // (Tensors beyond the memory-side cache keep two launches: the second layer's lets the delta's stores drain before the
+        // normalisation reads them; 16 x 128 x 32 x 32 x 64 two rounds 8333 us so and 8385 with one.)
+        c->cv_dw_pair = tensors_stream(c->m, act / 4 / m) ? 0 : conv3x3_bf16_dw_pair_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->off_cpartial - c->off_z1);
         // The sign of a1 (a byte per pixel and four channels, from the first normalisation to the delta) has no place of its own:
         // behind what the tail keeps in a2's; without a tail in that of the kernel gradients' partial sums, which come after
         // the delta; where that is too small in the gradient's, which then takes z2's, whose last reader precedes the delta
@@ -421,6 +427,8 @@ void plan_workspace(ols_ctx* c) {
         if ((c->cv_H + 2) * (c->cv_W + 2) >= 64) c->off_gate = c->off_a2 + align256(m * conv3x3_bf16_pool_part_floats(c->B, c->cv_H, c->cv_W, c->cv_C) * 4);
         else if (padded / 4 <= cpartial) c->off_gate = c->off_cpartial;
         else { c->off_gate = c->off_dz1; c->off_dz1 = c->off_a2; }
+        c->off_cpartial_b = c->off_dz1 == c->off_a2 ? align256(c->off_a2 + padded * 2) : c->off_a2;   // to the end of a2's signs
+        c->cv_dw_pair = conv3x3_bf16_dw_pair_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->off_dz2 - c->off_cpartial_b);
         c->off_images = (c->cv_H + 2) * (c->cv_W + 2) >= 64 ? images_behind(c, c->off_gate + padded / 4, c->off_a2 + padded * 4) : -1;
         c->off_dlogits = take(m * B * c->cv_classes * 4);
         c->off_loss = take(m * B * 4);
@@ -479,6 +487,18 @@ ConvBImages kernel_images(ols_ctx* c, const uint16_t* shadow, int64_t wa, int64_
         im.s_image = 2 * c->ld;
     }
     return im;
+}
+
+// The bf16 blocks' kernel gradients.  The second layer's could run as soon as its delta is there; where one launch for both layers
+// fills the chip better (conv3x3_bf16_dw_pair_splits) it waits for the first layer's, and its own place in the schedule stays empty.
+int second_kernel_gradient(ols_ctx* c, const ConvBArgs& a) {
+    return enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return c->cv_dw_pair ? hipSuccess : launch_conv3x3_bf16_dw(a, s); });
+}
+int first_kernel_gradient(ols_ctx* c, const ConvBArgs& a, ConvBArgs second) {
+    second.partial = (float*)(c->ws + c->off_cpartial_b);
+    return enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) {
+        return c->cv_dw_pair ? launch_conv3x3_bf16_dw_pair(a, second, c->cv_dw_pair, s) : launch_conv3x3_bf16_dw(a, s);
+    });
 }
 
 // The plain residual block with bf16 operands: the input batch is converted (and given its zero border) first, the
@@ -581,17 +601,11 @@ int conv_gradients_bf16(ols_ctx* c) {
         else { a.w = images.dx_b; a.gate = gate; a.s_gate = act / 4; }
         if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return slices ? launch_conv3x3_bf16_slices_dx(a, s) : launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }
-    {
-        ConvBArgs a = base;
-        a.in = a1; a.s_in = act; a.dout = dz2; a.s_dout = act; a.g_w_off = wb; a.g_b_off = bb;
-        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dw(a, s); }))) return rc;
-    }
-    {
-        ConvBArgs a = base;
-        a.in = xb; a.s_in = act; a.dout = dz1; a.s_dout = act; a.g_w_off = wa; a.g_b_off = ba;
-        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dw(a, s); }))) return rc;
-    }
-    return OLS_OK;
+    ConvBArgs da = base, db = base;
+    da.in = xb; da.s_in = act; da.dout = dz1; da.s_dout = act; da.g_w_off = wa; da.g_b_off = ba;
+    db.in = a1; db.s_in = act; db.dout = dz2; db.s_dout = act; db.g_w_off = wb; db.g_b_off = bb;
+    if ((rc = second_kernel_gradient(c, db))) return rc;
+    return first_kernel_gradient(c, da, db);
 }
 
 // Forward + backward of the residual convolutional block on the main stream; gradients go to g.
@@ -709,22 +723,17 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
         a.out_f32 = 1; a.out_unpadded = 1;
         if ((rc = enqueue(c, OLS_K_CONV_DX, 0, c->cur, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dx(a, s); }))) return rc;
     }
-    {   // gradients of the second convolution
-        ConvBArgs a = base;
-        a.in = a1; a.s_in = padded; a.dout = dz2; a.s_dout = padded; a.g_w_off = wb; a.g_b_off = -1;
-        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dw(a, s); }))) return rc;
-    }
+    ConvBArgs db = base;
+    db.in = a1; db.s_in = padded; db.dout = dz2; db.s_dout = padded; db.g_w_off = wb; db.g_b_off = -1;
+    if ((rc = second_kernel_gradient(c, db))) return rc;
     {   // through the first normalisation
         BnArgs a = nbase;
         a.z = z1; a.dy = dn; a.out_bf16 = dz1; a.stats = stats1; a.gamma = xc + ga; a.g_gamma_off = ga; a.g_beta_off = ba;
         if ((rc = enqueue(c, OLS_K_BN_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_backward(a, s); }))) return rc;
     }
-    {   // gradients of the first convolution (its input is data: no delta beyond it)
-        ConvBArgs a = base;
-        a.in = xb; a.s_in = padded; a.dout = dz1; a.s_dout = padded; a.g_w_off = wa; a.g_b_off = -1;
-        if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dw(a, s); }))) return rc;
-    }
-    return OLS_OK;
+    ConvBArgs da = base;   // (its input is data: no delta beyond it)
+    da.in = xb; da.s_in = padded; da.dout = dz1; da.s_dout = padded; da.g_w_off = wa; da.g_b_off = -1;
+    return first_kernel_gradient(c, da, db);
 }
 
 // Plain block:       a1 = relu(conv(X; Wa) + ba);        a2 = relu(conv(a1; Wb) + bb + X)

@@ -297,9 +297,13 @@ hipError_t launch_conv3x3_split_fwd(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_split_dx(const ConvArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_split_dw(const ConvArgs& a, hipStream_t s);   // (two launches)
 int conv3x3_split_dw_splits(int groups, int B, int H, int W, int C);
-// second pass of the kernel gradient: sums the pixel ranges' parts [splits][groups][9 C C + C] in range order into g
-hipError_t launch_conv_dw_finish(const float* partial, int splits, int groups, int C, float* g, int64_t ld, int64_t w_off,
-                                 int64_t b_off, hipStream_t s);
+// second pass of the kernel gradients of one or two layers: sums the pixel ranges' parts [splits][groups][9 C C + C] in range
+// order into g
+struct ConvDwParts {
+    const float* partial;
+    int64_t w_off, b_off;   // b_off < 0: no bias
+};
+hipError_t launch_conv_dw_finish(const ConvDwParts* layers, int n, int splits, int groups, int C, float* g, int64_t ld, hipStream_t s);
 // pooled = scale * sum over the HW positions of every sample (scale = 1 / HW: global average pooling), and the backward
 // of the average through the ReLU in front of it
 hipError_t launch_pool_mean(const float* a, int64_t s_a, float* pooled, int64_t s_p, int groups, int B, int HW, int C,
@@ -350,6 +354,10 @@ bool conv3x3_bf16_slices_fits(int groups, int B, int H, int W, int C);
 hipError_t launch_conv3x3_bf16_slices_fwd(const ConvBArgs& a, hipStream_t s);
 hipError_t launch_conv3x3_bf16_slices_dx(const ConvBArgs& a, hipStream_t s);
 int conv3x3_bf16_dw_splits(int groups, int B, int H, int W, int C);
+// the kernel gradients of two layers of one shape in one launch: its pixel ranges, each layer's `partial` as large as they make
+// it (the second layer's in scratch_bytes, the first's never larger than for conv3x3_bf16_dw_splits), or 0: two launches instead
+int conv3x3_bf16_dw_pair_splits(int groups, int B, int H, int W, int C, int64_t scratch_bytes);
+hipError_t launch_conv3x3_bf16_dw_pair(const ConvBArgs& a, const ConvBArgs& b, int splits, hipStream_t s);
 int64_t conv3x3_bf16_pool_part_floats(int B, int H, int W, int C);   // per group
 int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C);   // per group
 // pooled[g][sample][c] = inv * the sum over the sample's positions, from partial sums [group][w][2][C] per 64 consecutive
