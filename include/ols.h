@@ -109,7 +109,9 @@ enum {
                                       weight / bias gradients (and their fused update) are computed by extra
                                       workgroups at the front of the launch of the last hidden layer's
                                       weight-gradient GEMM instead of a kernel of their own (OLS_K_HEAD_BWD then
-                                      does not appear); same arithmetic, identical bits                          */
+                                      does not appear); a convolutional block's classifier gradients in the launch
+                                      that ends its last kernel gradient (OLS_K_HEAD_BWD's place in the schedule is
+                                      empty then); same arithmetic, identical bits                               */
 };
 
 /* kernel kinds for ols_kernel_stats / the launch trace */

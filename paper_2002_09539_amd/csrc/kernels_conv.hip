@@ -32,6 +32,7 @@
 #include <algorithm>
 
 #include "gemm_f32_tile.h"
+#include "head_dw_body.h"
 #include "ols_internal.h"
 
 namespace ols {
@@ -436,12 +437,20 @@ __global__ __launch_bounds__(kThreads, OLS_CONV_DW_WAVES) void conv3x3_dw_kernel
 }
 
 // Sums the parts of every kernel / bias entry over the pixel ranges in range order and writes the gradient.  One lane per
-// four consecutive entries (the kernel's and the bias's counts are multiples of four), eight ranges' loads in flight.
+// four consecutive entries (the kernel's and the bias's counts are multiples of four), eight ranges' loads in flight.  In front
+// of the first layer's workgroups, guest.grid_x per group compute the classifier's gradients (see head_dw_body.h): a launch of
+// its own took 4 to 5 us of a small block's step, here it ends with the others.
+constexpr int kFinishLds = head_dw_lds_floats(32, 32);
 __global__ __launch_bounds__(256) void conv_dw_finish_kernel(ConvDwParts first, ConvDwParts second, int splits, int groups,
-                                                             int64_t per_group, int64_t n_w, float* g, int64_t ld) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= per_group) return;
+                                                             int64_t per_group, int64_t n_w, float* g, int64_t ld, HeadDwDev guest) {
+    __shared__ __attribute__((aligned(16))) float lds[kFinishLds];
     const int group = blockIdx.y;
+    if ((int)blockIdx.x < guest.grid_x) {
+        if (blockIdx.z == 0) head_dw_guest<kFinishLds>(guest, lds, group * guest.grid_x + blockIdx.x);
+        return;
+    }
+    const int64_t i = ((int64_t)(blockIdx.x - guest.grid_x) * 256 + threadIdx.x) * 4;
+    if (i >= per_group) return;
     const ConvDwParts l = blockIdx.z ? second : first;
     const float* P = l.partial + (int64_t)group * per_group + i;
     const int64_t step = (int64_t)groups * per_group;
@@ -601,16 +610,23 @@ hipError_t launch_conv3x3_dw(const ConvArgs& a, hipStream_t s) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const ConvDwParts parts = {a.partial, a.g_w_off, a.g_b_off};
-    return launch_conv_dw_finish(&parts, 1, p.splits, a.groups, a.C, a.g, a.ld, s);
+    return launch_conv_dw_finish(&parts, 1, p.splits, a.groups, a.C, a.g, a.ld, a.guest, s);
 }
 
-hipError_t launch_conv_dw_finish(const ConvDwParts* layers, int n, int splits, int groups, int C, float* g, int64_t ld, hipStream_t s) {
+hipError_t launch_conv_dw_finish(const ConvDwParts* layers, int n, int splits, int groups, int C, float* g, int64_t ld,
+                                 const HeadArgs* guest, hipStream_t s) {
     if (!layers || n < 1 || n > 2 || !g || splits < 1 || groups < 1 || groups > 65535 || C < 1 || C % 4) return hipErrorInvalidValue;
     for (int l = 0; l < n; ++l)
         if (!layers[l].partial || !aligned16(layers[l].partial)) return hipErrorInvalidValue;
     const int64_t n_w = (int64_t)9 * C * C, per_group = n_w + C;
-    dim3 grid((unsigned)((per_group / 4 + 255) / 256), (unsigned)groups, (unsigned)n);
-    conv_dw_finish_kernel<<<grid, 256, 0, s>>>(layers[0], layers[n - 1], splits, groups, per_group, n_w, g, ld);
+    HeadDwDev head = {};
+    if (guest) {
+        if (guest->m != groups) return hipErrorInvalidValue;
+        hipError_t e = head_dw_prepare(*guest, &head);
+        if (e != hipSuccess) return e;
+    }
+    dim3 grid((unsigned)(head.grid_x + (per_group / 4 + 255) / 256), (unsigned)groups, (unsigned)n);
+    conv_dw_finish_kernel<<<grid, 256, 0, s>>>(layers[0], layers[n - 1], splits, groups, per_group, n_w, g, ld, head);
     return hipGetLastError();
 }
 

@@ -1078,7 +1078,7 @@ hipError_t dw_launch(const ConvBArgs& a, const ConvBArgs* b, int splits, hipStre
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const ConvDwParts parts[2] = {{a.partial, a.g_w_off, a.g_b_off}, b ? ConvDwParts{b->partial, b->g_w_off, b->g_b_off} : ConvDwParts{}};
-    return launch_conv_dw_finish(parts, b ? 2 : 1, p.splits, a.groups, a.C, a.g, a.ld, s);
+    return launch_conv_dw_finish(parts, b ? 2 : 1, p.splits, a.groups, a.C, a.g, a.ld, a.guest, s);
 }
 
 }  // namespace

@@ -661,7 +661,7 @@ hipError_t launch_conv3x3_split_dw(const ConvArgs& a, hipStream_t s) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const ConvDwParts parts = {a.partial, a.g_w_off, a.g_b_off};
-    return launch_conv_dw_finish(&parts, 1, p.splits, a.groups, a.C, a.g, a.ld, s);
+    return launch_conv_dw_finish(&parts, 1, p.splits, a.groups, a.C, a.g, a.ld, a.guest, s);
 }
 
 hipError_t launch_conv3x3_split_fwd(const ConvArgs& a, hipStream_t s) { return conv_launch<0>(a, s); }

@@ -74,7 +74,7 @@ struct ols_ctx {
     int gemm_variant[3] = {0, 0, 0};  // fwd, dw, da
     int splitk = 0;                   // 0: from the shape
     bool gemm_force_general = false;
-    bool head_dw_guest = true;        // output-layer gradients ride in the last hidden layer's weight-gradient launch
+    bool head_dw_guest = true;        // output-layer gradients ride in the last hidden layer's weight-gradient launch (block: the last of its kernels')
     std::vector<int> fwd_variant, fwd_splits;   // planned kernel and K ranges per hidden layer (fp32 forward GEMM)
     int64_t off_partial = 0;
     // fp32 MLP: the first hidden layer's weight gradient goes by column strips, over strip_ranges ranges of the weights' rows (0: it
@@ -388,10 +388,10 @@ void plan_workspace(ols_ctx* c) {
         const int64_t splits = conv3x3_bf16_dw_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C);
         const int64_t cpartial = splits * m * ((int64_t)9 * c->cv_C * c->cv_C + c->cv_C) * 4;
         c->off_cpartial = take(cpartial);
-        c->off_cpartial_b = c->off_z1;   // what the normalisations, pooling and classifier read and wrote
+        c->off_cpartial_b = c->off_z1;   // what the normalisations read and wrote (the classifier's gradients still read the pooled)
         // (Tensors beyond the memory-side cache keep two launches: the second layer's lets the delta's stores drain before the
         // normalisation reads them; 16 x 128 x 32 x 32 x 64 two rounds 8333 us so and 8385 with one.)
-        c->cv_dw_pair = tensors_stream(c->m, act / 4 / m) ? 0 : conv3x3_bf16_dw_pair_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->off_cpartial - c->off_z1);
+        c->cv_dw_pair = tensors_stream(c->m, act / 4 / m) ? 0 : conv3x3_bf16_dw_pair_splits(c->m, c->B, c->cv_H, c->cv_W, c->cv_C, c->off_pooled - c->off_z1);
         // The sign of a1 (a byte per pixel and four channels, from the first normalisation to the delta) has no place of its own:
         // behind what the tail keeps in a2's; without a tail in that of the kernel gradients' partial sums, which come after
         // the delta; where that is too small in the gradient's, which then takes z2's, whose last reader precedes the delta
@@ -487,6 +487,11 @@ ConvBImages kernel_images(ols_ctx* c, const uint16_t* shadow, int64_t wa, int64_
         im.s_image = 2 * c->ld;
     }
     return im;
+}
+
+// A block's classifier gradients ride in the launch that ends the first kernel's (ConvArgs::guest); their place stays empty then.
+int classifier_gradient(ols_ctx* c, const HeadArgs& ha) {
+    return enqueue(c, OLS_K_HEAD_BWD, 0, c->cur, -1, [&](hipStream_t s) { return c->head_dw_guest ? hipSuccess : launch_head_bwd(ha, s); });
 }
 
 // The bf16 blocks' kernel gradients.  The second layer's could run as soon as its delta is there; where one launch for both layers
@@ -589,7 +594,7 @@ int conv_gradients_bf16(ols_ctx* c) {
     ha.H = C;
     ha.C = c->cv_classes;
     if ((rc = enqueue(c, OLS_K_HEAD_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_fwd(ha, s); }))) return rc;
-    if ((rc = enqueue(c, OLS_K_HEAD_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_bwd(ha, s); }))) return rc;
+    if ((rc = classifier_gradient(c, ha))) return rc;
     if ((rc = enqueue(c, OLS_K_POOL_BWD, 0, -1, -1, [&](hipStream_t s) {
              return launch_pool_bwd_bf16(dpool, (int64_t)B * C, sign, act / 4, dz2, act, m, B, positions, C, 1.0f / (float)(H * W), s);
          })))
@@ -603,6 +608,7 @@ int conv_gradients_bf16(ols_ctx* c) {
     }
     ConvBArgs da = base, db = base;
     da.in = xb; da.s_in = act; da.dout = dz1; da.s_dout = act; da.g_w_off = wa; da.g_b_off = ba;
+    da.guest = c->head_dw_guest ? &ha : nullptr;
     db.in = a1; db.s_in = act; db.dout = dz2; db.s_dout = act; db.g_w_off = wb; db.g_b_off = bb;
     if ((rc = second_kernel_gradient(c, db))) return rc;
     return first_kernel_gradient(c, da, db);
@@ -707,7 +713,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     ha.H = C;
     ha.C = c->cv_classes;
     if ((rc = enqueue(c, OLS_K_HEAD_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_fwd(ha, s); }))) return rc;
-    if ((rc = enqueue(c, OLS_K_HEAD_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_bwd(ha, s); }))) return rc;
+    if ((rc = classifier_gradient(c, ha))) return rc;
     {   // through the pooling, the second ReLU and the second normalisation: the gradient at the normalised output is
         // dpool / positions where a2 > 0 and is formed on the fly; scale / shift gradients; the gradient at z2 goes out as
         // the bf16 operand dz2
@@ -733,6 +739,7 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
     }
     ConvBArgs da = base;   // (its input is data: no delta beyond it)
     da.in = xb; da.s_in = padded; da.dout = dz1; da.s_dout = padded; da.g_w_off = wa; da.g_b_off = -1;
+    da.guest = c->head_dw_guest ? &ha : nullptr;
     return first_kernel_gradient(c, da, db);
 }
 
@@ -840,7 +847,7 @@ int conv_gradients(ols_ctx* c) {
     ha.H = C;
     ha.C = c->cv_classes;
     if ((rc = enqueue(c, OLS_K_HEAD_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_fwd(ha, s); }))) return rc;
-    if ((rc = enqueue(c, OLS_K_HEAD_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_bwd(ha, s); }))) return rc;
+    if ((rc = classifier_gradient(c, ha))) return rc;
     if (!bn) {
         if ((rc = enqueue(c, OLS_K_POOL_BWD, 0, -1, -1, [&](hipStream_t s) {
                  return launch_pool_bwd(dpool, (int64_t)B * C, a2, act, dz2, act, m, B, H * W, C, s);
@@ -873,6 +880,7 @@ int conv_gradients(ols_ctx* c) {
     {   // gradients of the first convolution (its input is data: no delta beyond it)
         ConvArgs a = base;
         a.in = c->X; a.s_in = c->xs; a.dout = dz1; a.s_dout = act; a.g_w_off = wa; a.g_b_off = bn ? -1 : ba;
+        a.guest = c->head_dw_guest ? &ha : nullptr;
         if ((rc = enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return split ? launch_conv3x3_split_dw(a, s) : launch_conv3x3_dw(a, s); }))) return rc;
     }
     return OLS_OK;

@@ -272,6 +272,7 @@ struct ConvArgs {
     float* g;               // dw: gradients [groups][ld]; kernel gradient at g_w_off, bias gradient at g_b_off of a row
                             // (g_b_off < 0: no bias, nothing written for it)
     int64_t ld, g_w_off, g_b_off;
+    const HeadArgs* guest;  // dw, optional: the classifier's gradients (launch_head_bwd's work), in the finish pass's launch
     int64_t s_in, s_w, s_dout, s_out, s_bias, s_res, s_mask;   // group strides (elements)
     int groups, B, H, W, C;
     int relu;               // fwd: apply max(., 0)
@@ -303,7 +304,8 @@ struct ConvDwParts {
     const float* partial;
     int64_t w_off, b_off;   // b_off < 0: no bias
 };
-hipError_t launch_conv_dw_finish(const ConvDwParts* layers, int n, int splits, int groups, int C, float* g, int64_t ld, hipStream_t s);
+hipError_t launch_conv_dw_finish(const ConvDwParts* layers, int n, int splits, int groups, int C, float* g, int64_t ld,
+                                 const HeadArgs* guest, hipStream_t s);
 // pooled = scale * sum over the HW positions of every sample (scale = 1 / HW: global average pooling), and the backward
 // of the average through the ReLU in front of it
 hipError_t launch_pool_mean(const float* a, int64_t s_a, float* pooled, int64_t s_p, int groups, int B, int HW, int C,
@@ -332,6 +334,7 @@ struct ConvBArgs {
     float* partial;         // dw: scratch of conv3x3_bf16_dw_splits(...) * groups * (9 C C + C) floats
     float* g;               // dw: gradients [groups][ld]
     int64_t ld, g_w_off, g_b_off;   // g_b_off < 0: no bias
+    const HeadArgs* guest;  // dw, optional: the classifier's gradients (launch_head_bwd's work), in the finish pass's launch
     int64_t s_in, s_w, s_dout, s_out, s_bias, s_gate, s_mask;   // group strides (elements of the tensor's own type)
     int groups, B, H, W, C;
     int relu;               // fwd with bf16 output: max(., 0) is applied, and has to be asked for
