@@ -144,21 +144,17 @@ __device__ __forceinline__ void merge_moments(float& n, float& mean, float& m2, 
     }
 }
 
-// grid (chunks, groups, C / 64)
-__global__ __launch_bounds__(kThreads) void bn_stats_waves_kernel(const float* __restrict__ wpart, int64_t s_wpart, float* cpart,
-                                                                  int C, int waves, int chunks) {
-    __shared__ float lds[3][kThreads];
+// The four stripes' (or more) walk over the parts lo .. hi - 1 of a channel, each every STRIPES-th in order, and the merge of their
+// results in stripe order, valid in stripe 0.
+template <int STRIPES>
+__device__ __forceinline__ void merge_parts(const float* __restrict__ P, int C, int lo, int hi, float (*lds)[STRIPES * kWaveStatChannels], float& n, float& mean, float& m2) {
     const int cl = threadIdx.x % kWaveStatChannels, stripe = threadIdx.x / kWaveStatChannels;
-    const int c = blockIdx.z * kWaveStatChannels + cl, g = blockIdx.y, k = blockIdx.x;
-    const int per = (waves + chunks - 1) / chunks;
-    const int lo = k * per, hi = min(waves, lo + per);
-    float n = 0.0f, mean = 0.0f, m2 = 0.0f;
-    const float* P = wpart + (int64_t)g * s_wpart + c;
-    for (int w0 = lo + stripe; w0 < hi; w0 += kWaveStatStripes * kWaveStatBatch) {
+    n = mean = m2 = 0.0f;
+    for (int w0 = lo + stripe; w0 < hi; w0 += STRIPES * kWaveStatBatch) {
         float nr[kWaveStatBatch], mr[kWaveStatBatch], qr[kWaveStatBatch];
 #pragma unroll
         for (int u = 0; u < kWaveStatBatch; ++u) {
-            const int w = w0 + u * kWaveStatStripes;
+            const int w = w0 + u * STRIPES;
             const float* o = P + (int64_t)(w < hi ? w : lo) * 3 * C;   // past the chunk: an in-range part, not merged
             nr[u] = w < hi ? o[0] : 0.0f;
             mr[u] = o[C];
@@ -171,14 +167,44 @@ __global__ __launch_bounds__(kThreads) void bn_stats_waves_kernel(const float* _
     lds[1][threadIdx.x] = mean;
     lds[2][threadIdx.x] = m2;
     __syncthreads();
-    if (stripe == 0) {
-        for (int s = 1; s < kWaveStatStripes; ++s)
+    if (stripe == 0)
+        for (int s = 1; s < STRIPES; ++s)
             merge_moments(n, mean, m2, lds[0][s * kWaveStatChannels + cl], lds[1][s * kWaveStatChannels + cl], lds[2][s * kWaveStatChannels + cl]);
+}
+
+__device__ __forceinline__ void store_stats(float* stats, int g, int C, int c, float n, float mean, float m2, float eps) {
+    const float var = fmaxf(m2 / n, 0.0f);
+    stats[((int64_t)g * 2) * C + c] = mean;
+    stats[((int64_t)g * 2 + 1) * C + c] = 1.0f / sqrtf(var + eps);
+}
+
+// grid (chunks, groups, C / 64)
+__global__ __launch_bounds__(kThreads) void bn_stats_waves_kernel(const float* __restrict__ wpart, int64_t s_wpart, float* cpart,
+                                                                  int C, int waves, int chunks) {
+    __shared__ float lds[3][kThreads];
+    const int c = blockIdx.z * kWaveStatChannels + threadIdx.x % kWaveStatChannels, g = blockIdx.y, k = blockIdx.x;
+    const int per = (waves + chunks - 1) / chunks;
+    float n, mean, m2;
+    merge_parts<kWaveStatStripes>(wpart + (int64_t)g * s_wpart + c, C, k * per, min(waves, k * per + per), lds, n, mean, m2);
+    if (threadIdx.x < kWaveStatChannels) {
         float* o = cpart + (((int64_t)g * chunks + k) * 3) * C + c;
         o[0] = n;
         o[C] = mean;
         o[2 * C] = m2;
     }
+}
+
+// Up to 384 parts (two batches of twelve for each of sixteen stripes): one level and one launch, grid (C / 64, groups).  Two rounds,
+// us, two levels / one: 10 samples of 10 x 8 x 128 channels (20 parts) 811 / 755 with the classifier's gradients moved as well, 45
+// of 12 x 34 x 64 (356) 1651 / 1642, 24 of 32 x 32 x 64 (436) 1244 / 1244, 38 of the same (688) 998 / 1024.
+constexpr int kOneLevelParts = 384, kOneLevelThreads = 1024;
+__global__ __launch_bounds__(kOneLevelThreads) void bn_stats_one_level_kernel(const float* __restrict__ wpart, int64_t s_wpart, float* stats, int C,
+                                                                              int waves, float eps) {
+    __shared__ float lds[3][kOneLevelThreads];
+    const int c = blockIdx.x * kWaveStatChannels + threadIdx.x % kWaveStatChannels, g = blockIdx.y;
+    float n, mean, m2;
+    merge_parts<kOneLevelThreads / kWaveStatChannels>(wpart + (int64_t)g * s_wpart + c, C, 0, waves, lds, n, mean, m2);
+    if (threadIdx.x < kWaveStatChannels) store_stats(stats, g, C, c, n, mean, m2, eps);
 }
 
 // grid (ceil(C / 256), groups): one lane per channel merges its chunks in chunk order
@@ -197,9 +223,7 @@ __global__ __launch_bounds__(kThreads) void bn_stats_chunks_kernel(const float* 
     }
 #pragma unroll
     for (int k = 0; k < kWaveStatChunks; ++k) merge_moments(n, mean, m2, nr[k], mr[k], qr[k]);
-    const float var = fmaxf(m2 / n, 0.0f);
-    stats[((int64_t)g * 2) * C + c] = mean;
-    stats[((int64_t)g * 2 + 1) * C + c] = 1.0f / sqrtf(var + eps);
+    store_stats(stats, g, C, c, n, mean, m2, eps);
 }
 
 // Where a result becomes the operand of a bf16 convolution it is written as bf16 (to nearest even) into that operand's
@@ -549,14 +573,21 @@ hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s) {
     hipError_t e;
     if (a.wave_part) {   // the producer of z left per-wavefront statistics: z is not read for them
         if (a.waves < 1 || !aligned16(a.wave_part) || a.C % kWaveStatChannels) return hipErrorInvalidValue;
-        const int chunks = wave_stat_chunks(a.groups, a.P);   // their results fit the ranges' buffer: chunks <= bn_ranges(groups, P)
-        bn_stats_waves_kernel<<<dim3((unsigned)chunks, (unsigned)a.groups, (unsigned)(a.C / kWaveStatChannels)), kThreads, 0, s>>>(
-            a.wave_part, (int64_t)a.waves * 3 * a.C, a.part, a.C, a.waves, chunks);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        bn_stats_chunks_kernel<<<dim3((unsigned)((a.C + kThreads - 1) / kThreads), (unsigned)a.groups), kThreads, 0, s>>>(a.part, a.stats, a.C, chunks, a.eps);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        if (a.waves <= kOneLevelParts) {
+            bn_stats_one_level_kernel<<<dim3((unsigned)(a.C / kWaveStatChannels), (unsigned)a.groups), kOneLevelThreads, 0, s>>>(
+                a.wave_part, (int64_t)a.waves * 3 * a.C, a.stats, a.C, a.waves, a.eps);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        } else {
+            const int chunks = wave_stat_chunks(a.groups, a.P);   // their results fit the ranges' buffer: chunks <= bn_ranges(groups, P)
+            bn_stats_waves_kernel<<<dim3((unsigned)chunks, (unsigned)a.groups, (unsigned)(a.C / kWaveStatChannels)), kThreads, 0, s>>>(
+                a.wave_part, (int64_t)a.waves * 3 * a.C, a.part, a.C, a.waves, chunks);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            bn_stats_chunks_kernel<<<dim3((unsigned)((a.C + kThreads - 1) / kThreads), (unsigned)a.groups), kThreads, 0, s>>>(a.part, a.stats, a.C, chunks, a.eps);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     } else {
         const int ranges = bn_ranges(a.groups, a.P);
         bn_stats_partial_kernel<<<dim3((unsigned)ranges, (unsigned)a.groups), kThreads, 0, s>>>(a.z, a.s_z, a.part, a.P, a.C, ranges);
