@@ -871,48 +871,6 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_bf16_kernel(const float* __
     }
 }
 
-// pooled[g][n][c] = inv * sum of the partial sums that a fused tail left for sample n: part w covers the pixels
-// 64 w .. 64 w + 63 (padded pixels for the convolution's tail, image pixels for the normalisation's), its first sample
-// is floor(64 w / per) with per pixels per sample, and its two slots are that sample and the next.  A slot holds SUMS
-// sums of C channels; those after the first go to more[g][SUMS - 1][n][c] as they are.
-// Added in order of w; one lane per (sample, channel quad).
-template <int SUMS>
-__global__ __launch_bounds__(kThreads) void pool_finish_kernel(const float* __restrict__ part, int64_t s_part, float* pooled,
-                                                               int64_t s_p, float* more, int B, int per, int C, float inv) {
-    const int v = blockIdx.x * kThreads + threadIdx.x;
-    const int c4n = C / 4;
-    if (v >= B * c4n) return;
-    const int n = v / c4n, c4 = v % c4n, g = blockIdx.y;
-    const f4* P = (const f4*)(part + (int64_t)g * s_part) + c4;
-    const int w_lo = (n * per) / 64, w_hi = ((n + 1) * per - 1) / 64;
-    f4 acc[SUMS];
-#pragma unroll
-    for (int k = 0; k < SUMS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
-    constexpr int kFly = 8;   // the loads of eight parts ahead of their additions
-    for (int w0 = w_lo; w0 <= w_hi; w0 += kFly) {
-        f4 v[kFly][SUMS];
-#pragma unroll
-        for (int t = 0; t < kFly; ++t) {
-            const int w = w0 + t <= w_hi ? w0 + t : w_hi;
-            const int slot = n - (64 * w) / per;   // 0 or 1
-#pragma unroll
-            for (int k = 0; k < SUMS; ++k) v[t][k] = P[((int64_t)(2 * w + slot) * SUMS + k) * c4n];
-        }
-#pragma unroll
-        for (int t = 0; t < kFly; ++t)
-            if (w0 + t <= w_hi) {
-#pragma unroll
-                for (int k = 0; k < SUMS; ++k) acc[k] = acc[k] + v[t][k];
-            }
-    }
-    f4 o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = acc[0][e] * inv;
-    *(f4*)(pooled + (int64_t)g * s_p + (int64_t)n * C + 4 * c4) = o;
-#pragma unroll
-    for (int k = 1; k < SUMS; ++k) *(f4*)(more + (((int64_t)g * (SUMS - 1) + k - 1) * B + n) * C + 4 * c4) = acc[k];
-}
-
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 bool shape_ok(const ConvBArgs& a) {
@@ -1148,18 +1106,6 @@ int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C) {
 int64_t conv3x3_bf16_pool_part_floats(int B, int H, int W, int C) {
     const int64_t Pp = (int64_t)B * (H + 2) * (W + 2);
     return ((Pp + 255) / 256) * 4 * 2 * C;   // per group
-}
-
-hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, float* more, int groups, int B, int per,
-                              int C, float inv, hipStream_t s) {
-    if (!part || !pooled || groups < 1 || groups > 65535 || B < 1 || C < 4 || C % 4 || !aligned16(part) || !aligned16(pooled) ||
-        !aligned16(more) || s_part % 4 || s_p % 4 || per < 64 || (int64_t)B * per >= ((int64_t)1 << 31) - 64)
-        return hipErrorInvalidValue;
-    const int64_t lanes = (int64_t)B * (C / 4);
-    if (lanes > 0x7FFFFFFF) return hipErrorInvalidValue;
-    auto kern = more ? pool_finish_kernel<3> : pool_finish_kernel<1>;
-    kern<<<dim3((unsigned)((lanes + kThreads - 1) / kThreads), (unsigned)groups), kThreads, 0, s>>>(part, s_part, pooled, s_p, more, B, per, C, inv);
-    return hipGetLastError();
 }
 
 hipError_t launch_pool_bwd_bf16(const float* dpool, int64_t s_dp, const uint8_t* sign, int64_t s_sign, uint16_t* dz, int64_t s_dz,

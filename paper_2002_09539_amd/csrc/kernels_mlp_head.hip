@@ -60,7 +60,48 @@ struct HeadDev {
     void* dz;
     int64_t h_stride, ld, w_off, b_off, label_stride;
     int B, H, C;
+    PoolParts pool;
 };
+
+// A block's pooled features from the partial sums that its fused tail left: pooled[n][c] = inv * the sum for sample n.  Part w
+// covers the pixels 64 w .. 64 w + 63 (padded pixels for the convolution's tail, image pixels for the normalisation's), its first
+// sample is floor(64 w / per) with per pixels per sample, and its two slots are that sample and the next.  A slot holds SUMS sums of
+// C channels; those after the first go to more[SUMS - 1][n][c] as they are.  Added in order of w; one lane per (sample, channel quad).
+// The workgroup that classifies a sample adds up its parts; as a launch of its own that took 4 to 9 us.  Two rounds, us: plain
+// 4 x 17 x 13 x 13 x 64 295 -> 284, 12 x 8 x 9 x 14 x 64 tau 3 441 -> 427, normalised 3 x 12 x 35 x 36 x 64 589 -> 581; 16 random bf16 blocks
+// 1.014 times as fast (0.995 the least).
+template <int SUMS>
+__device__ __forceinline__ void pool_finish(const HeadDev& p, int i, int n, int c4) {
+    const int C = p.H, c4n = C / 4, per = p.pool.per;
+    const f4* P = (const f4*)(p.pool.part + (int64_t)i * p.pool.s_part) + c4;
+    const int w_lo = (n * per) / 64, w_hi = ((n + 1) * per - 1) / 64;
+    f4 acc[SUMS];
+#pragma unroll
+    for (int k = 0; k < SUMS; ++k) acc[k] = f4{0.f, 0.f, 0.f, 0.f};
+    constexpr int kFly = 8;   // the loads of eight parts ahead of their additions
+    for (int w0 = w_lo; w0 <= w_hi; w0 += kFly) {
+        f4 v[kFly][SUMS];
+#pragma unroll
+        for (int t = 0; t < kFly; ++t) {
+            const int w = w0 + t <= w_hi ? w0 + t : w_hi;
+            const int slot = n - (64 * w) / per;   // 0 or 1
+#pragma unroll
+            for (int k = 0; k < SUMS; ++k) v[t][k] = P[((int64_t)(2 * w + slot) * SUMS + k) * c4n];
+        }
+#pragma unroll
+        for (int t = 0; t < kFly; ++t)
+            if (w0 + t <= w_hi) {
+#pragma unroll
+                for (int k = 0; k < SUMS; ++k) acc[k] = acc[k] + v[t][k];
+            }
+    }
+    f4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = acc[0][e] * p.pool.inv;
+    *(f4*)((float*)p.h + (int64_t)i * p.h_stride + (int64_t)n * C + 4 * c4) = o;
+#pragma unroll
+    for (int k = 1; k < SUMS; ++k) *(f4*)(p.pool.more + (((int64_t)i * (SUMS - 1) + k - 1) * p.B + n) * C + 4 * c4) = acc[k];
+}
 
 // Measured against a kernel that staged weights and activations in LDS and formed both products on the vector ALUs, us per
 // launch: 14.9 -> 12.0 (16 workers x 128 samples x 512 units), 27.9 -> 18.0 (64 x 64 x 1024), 52.7 -> 24.1 (16 x 256 x 2048, bf16),
@@ -95,6 +136,17 @@ __global__ __launch_bounds__(64 * WAVES) void head_fwd_kernel(HeadDev p) {
 #pragma unroll
     for (int c0 = 0; c0 < CT; ++c0) bias[c0] = soft && kRow * c0 + sub < C ? p.x[(int64_t)i * p.ld + p.b_off + kRow * c0 + sub] : 0.0f;
     const int label = live ? p.labels[(int64_t)i * p.label_stride + s] : 0;
+
+    if constexpr (!BF) {
+        if (p.pool.part) {   // the workgroup's own samples; its loads of them below come behind the barrier
+            for (int v = threadIdx.x; v < rows * (H / 4); v += 64 * WAVES) {
+                const int n = v / (H / 4), c4 = v - n * (H / 4);
+                if (p.pool.more) pool_finish<3>(p, i, s0 + n, c4);
+                else pool_finish<1>(p, i, s0 + n, c4);
+            }
+            __syncthreads();
+        }
+    }
 
     f4 hv[BF ? 1 : T];
     u2 hb[BF ? T : 1];
@@ -249,17 +301,19 @@ static hipError_t head_fwd_launch(const HeadDev& p, int m, hipStream_t s) {
     head_fwd_kernel<BF, CMAX, T, WAVES><<<grid, 64 * WAVES, 0, s>>>(p);
     return hipGetLastError();
 }
-// One pass over the layer where the registers of up to 16 wavefronts hold it: T = 8 tiles of 16 units each, with fp32
+// With partial sums to add up first, as many wavefronts as make that one item per lane (16 samples x H / 4 channel quads; wavefronts
+// without units add zeros to the logits, the same bits).  One pass over the layer where the registers of up to 16 wavefronts hold it: T = 8 tiles of 16 units each, with fp32
 // activations beyond 1024 units or with more than 16 classes four (eight spill).
 template <bool BF>
 static hipError_t head_fwd_dispatch(const HeadDev& p, int m, hipStream_t s) {
+    const int units = p.pool.part ? 4 * p.H : p.H;
     if (p.C > 16) {
-        if (p.H <= 256) return head_fwd_launch<BF, 32, 4, 4>(p, m, s);
+        if (units <= 256) return head_fwd_launch<BF, 32, 4, 4>(p, m, s);
         return head_fwd_launch<BF, 32, 4, 8>(p, m, s);
     }
-    if (p.H <= 256) return head_fwd_launch<BF, 16, 4, 4>(p, m, s);
-    if (p.H <= 512) return head_fwd_launch<BF, 16, 4, 8>(p, m, s);
-    if (p.H <= 1024) return head_fwd_launch<BF, 16, 8, 8>(p, m, s);
+    if (units <= 256) return head_fwd_launch<BF, 16, 4, 4>(p, m, s);
+    if (units <= 512) return head_fwd_launch<BF, 16, 4, 8>(p, m, s);
+    if (p.H <= 1024 && !p.pool.part) return head_fwd_launch<BF, 16, 8, 8>(p, m, s);
     if constexpr (BF) return head_fwd_launch<BF, 16, 8, 16>(p, m, s);
     return head_fwd_launch<BF, 16, 4, 16>(p, m, s);
 }
@@ -270,7 +324,11 @@ hipError_t launch_head_fwd(const HeadArgs& a, hipStream_t s) {
     // 16-byte activation vectors: 4 floats or 8 bf16
     if (a.h_bf16 && (a.H % 8 || a.h_stride % 8)) return hipErrorInvalidValue;
     if (a.dz && (reinterpret_cast<uintptr_t>(a.dz) & 15u)) return hipErrorInvalidValue;
+    if (a.pool.part && (a.h_bf16 || a.pool.per < 64 || (int64_t)a.B * a.pool.per >= ((int64_t)1 << 31) - 64 || a.pool.s_part % 4 ||
+                        (reinterpret_cast<uintptr_t>(a.pool.part) & 15u) || (reinterpret_cast<uintptr_t>(a.pool.more) & 15u)))
+        return hipErrorInvalidValue;
     HeadDev p;
+    p.pool = a.pool;
     p.h = a.h;
     p.x = a.x;
     p.labels = a.labels;

@@ -550,6 +550,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         a.gate = gate; a.s_gate = act / 4;
         if ((rc = conv_fwd(a, shadow + wa, images.fwd_a))) return rc;
     }
+    PoolParts parts = {};
     if (positions >= 64) {
         // conv(a1; Wb) + bb with the block's tail in its epilogue: a2 = relu(. + X) is never stored -- its sign bytes and
         // partial sums of the pooling are (the partial sums take the place the fp32 output has without the fusion)
@@ -558,11 +559,8 @@ int conv_gradients_bf16(ols_ctx* c) {
         a.in = a1; a.s_in = act; a.bias = xc + bb; a.tail = 1;
         a.xres = c->X; a.s_x = c->xs; a.sign = sign; a.s_sign = act / 4; a.pool_part = pool_part;
         if ((rc = conv_fwd(a, shadow + wb, images.fwd_b))) return rc;
-        if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-                 return launch_pool_finish(pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), pooled, (int64_t)B * C, nullptr, m, B, positions, C,
-                                           1.0f / (float)(H * W), s);
-             })))
-            return rc;
+        parts = {pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), nullptr, positions, 1.0f / (float)(H * W)};
+        if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t) { return hipSuccess; }))) return rc;   // added up by the classifier's launch
     } else {   // images too small for the fused tail's two-samples-per-wavefront bookkeeping
         {   // y = conv(a1; Wb) + bb, fp32
             ConvBArgs a = base;
@@ -577,6 +575,7 @@ int conv_gradients_bf16(ols_ctx* c) {
     }
     HeadArgs ha = {};
     ha.h = pooled;
+    ha.pool = parts;
     ha.h_stride = (int64_t)B * C;
     ha.h_bf16 = false;
     ha.x = xc;
@@ -690,12 +689,13 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
     if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-             return tail ? launch_pool_finish(tail_part, tail_units * 6 * C, pooled, (int64_t)B * C, sample_sums, m, B, H * W, C, 1.0f / (float)(H * W), s)
+             return tail ? hipSuccess   // added up by the classifier's launch
                          : launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
          })))
         return rc;
     HeadArgs ha = {};
     ha.h = pooled;
+    if (tail) ha.pool = {tail_part, tail_units * 6 * C, sample_sums, H * W, 1.0f / (float)(H * W)};
     ha.h_stride = (int64_t)B * C;
     ha.h_bf16 = false;
     ha.x = xc;
@@ -824,12 +824,13 @@ int conv_gradients(ols_ctx* c) {
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
     if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-             return tail ? launch_pool_finish(tail_part, tail_units * 6 * C, pooled, (int64_t)B * C, sample_sums, m, B, H * W, C, 1.0f / (float)(H * W), s)
+             return tail ? hipSuccess   // added up by the classifier's launch
                          : launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
          })))
         return rc;
     HeadArgs ha = {};
     ha.h = pooled;
+    if (tail) ha.pool = {tail_part, tail_units * 6 * C, sample_sums, H * W, 1.0f / (float)(H * W)};
     ha.h_stride = (int64_t)B * C;
     ha.h_bf16 = false;
     ha.x = xc;

@@ -235,7 +235,17 @@ hipError_t launch_cast_bf16(const float* src, int64_t src_stride, uint16_t* dst,
                             hipStream_t s);
 
 // output layer (N = classes <= 32) on plain vector ALUs
+// Partial sums of a fused tail per 64 consecutive pixels, [group][w][2][SUMS][C] (slot 0: the sample of pixel 64 w, slot 1: the
+// next one), with `per` (>= 64) pixels per sample; launch_head_fwd adds them up into its h first.
+struct PoolParts {
+    const float* part;    // nullptr: h is there
+    int64_t s_part;       // floats between groups
+    float* more;          // SUMS = 3: the sums after the first, [group][2][sample][C]; nullptr: SUMS = 1
+    int per;
+    float inv;            // h = inv * the first sum
+};
 struct HeadArgs {
+    PoolParts pool;       // launch_head_fwd, fp32 h
     const void* h;        // [m][B][H] last hidden activations (fp32, or bf16 when h_bf16)
     int64_t h_stride;     // elements between workers in h
     bool h_bf16;
@@ -341,7 +351,7 @@ struct ConvBArgs {
     // fwd with the residual block's tail fused in (tail != 0; out unused, no relu, padded images of at least 64 pixels):
     // a2 = relu(convolution + bias + xres) is never stored -- sign[padded pixel][C / 4] gets one byte per four channels
     // with bit e set iff a2 > 0 (border: 0), and pool_part (conv3x3_bf16_pool_part_floats(...) floats per group) the
-    // partial sums that launch_pool_finish turns into the mean over the positions.
+    // partial sums that launch_head_fwd turns into the mean over the positions (PoolParts).
     int tail;
     const float* xres;      // fp32 [B H W][C], not padded
     uint8_t* sign;
@@ -363,10 +373,6 @@ int conv3x3_bf16_dw_pair_splits(int groups, int B, int H, int W, int C, int64_t 
 hipError_t launch_conv3x3_bf16_dw_pair(const ConvBArgs& a, const ConvBArgs& b, int splits, hipStream_t s);
 int64_t conv3x3_bf16_pool_part_floats(int B, int H, int W, int C);   // per group
 int64_t conv3x3_bf16_stat_part_floats(int B, int H, int W, int C);   // per group
-// pooled[g][sample][c] = inv * the sum over the sample's positions, from partial sums [group][w][2][C] per 64 consecutive
-// pixels (slot 0: the sample of pixel 64 w, slot 1: the next one) with `per` (>= 64) pixels per sample
-hipError_t launch_pool_finish(const float* part, int64_t s_part, float* pooled, int64_t s_p, float* more, int groups, int B, int per,
-                              int C, float inv, hipStream_t s);
 // The step's kernels in fragment order, which launch_conv3x3_bf16_fwd / _dx take as ConvBArgs::w: 9 C C values per group for the
 // first convolution, the second, and the second's delta.  All nullptr: none are made.
 struct ConvBImages {
@@ -425,9 +431,9 @@ struct BnArgs {
     // Optional (fwd, with shortcut / relu as given; H * W >= 64): the block's tail.  The activation is not stored: `sign`
     // gets one byte per pixel and four channels ([group][P][C / 4], bit e set iff the activation is positive) and
     // `pool_part` ([group][ceil(P / 64)][2][3][C] floats) per 64 pixels the activation's sums, the number of positive
-    // activations and their sums of xhat, for launch_pool_finish (with `more`).
+    // activations and their sums of xhat, for PoolParts (with `more`).
     // (bwd) `sign` in place of `gate`: the same bytes say where the activation was positive; `sample_sums`
-    // ([group][2][sample][C]: numbers and sums of xhat, launch_pool_finish's `more`) then has to be given.
+    // ([group][2][sample][C]: numbers and sums of xhat, PoolParts' `more`) then has to be given.
     uint8_t* sign;
     float* pool_part;
     const float* sample_sums;
