@@ -64,7 +64,9 @@ enum {
                                   (the paper's schedule); 1: on the main stream (blocking); 2 (default): overlapped
                                   unless the refresh moves at most 1 MiB ((4 m + 4) ld bytes), where the two
                                   cross-stream synchronisations of a round cost more than the refresh they would
-                                  hide.  Results are identical bit for bit in all three.                        */
+                                  hide -- and, with tau = 1 and up to 16 MiB, unless another step follows in the
+                                  same ols_run_steps (the refresh that a call leaves behind is overlapped).
+                                  Results are identical bit for bit in all three.                               */
     OLS_OPT_DRY_RUN = 4,       /* 1: advance the schedule and record the launch trace but launch nothing
                                   (host-logic tests on machines without a GPU); default 0                     */
     OLS_OPT_KERNEL_TIMING = 5, /* 1: bracket every kernel with HIP events on its own stream and accumulate
