@@ -34,7 +34,7 @@ namespace ols {
 
 namespace {
 
-enum { kFwd = 0, kDa = 1 };
+enum { kFwd = 0, kDa = 1, kFwdCast = 2 };   // kFwdCast (bf16): forward from the fp32 batch, see SmallDevB::a32
 constexpr int kXcds = 8;
 constexpr int kW = 4, kThreads = 64 * kW;          // wavefronts that share a tile's contraction
 
@@ -173,8 +173,16 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
 //   6 x (72 x 520 x 1032)     9.2 / 6.7     8.2 / 7.4
 //   2 x (32 x 168 x 2224)    15.1 / 7.0    12.6 / 8.0
 //   24 x (224 x 168 x 120)    4.4 / 3.9     4.4 / 3.8
+//
+// The first layer's forward GEMM takes the batch as it comes (kFwdCast): a lane loads its eight indices in fp32 and rounds them, and
+// the workgroups of a row's first column tile leave the rounded batch for the weight gradient.  The pass that did this alone took
+// 4 us and a launch of a small step.  Two rounds, us, one state / three in turn: 44 x (360-64-12, 184) tau 3 202 -> 180 / 127 -> 119,
+// 6 x (264-280-7, 104) tau 3 140 -> 125 / 131 -> 121, 9 x (2032-168-384-3, 72) 216 -> 211 / 174 -> 171, 6 x (1032-520-264-10, 72) 169 -> 167
+// (three in turn); none slower.
 struct SmallDevB {
     const uint16_t* a;
+    const float* a32;        // kFwdCast: A in fp32, in place of a
+    uint16_t* a_out;         // kFwdCast: [M][K] per group, the rounded A
     const uint16_t* b;
     uint16_t* c;
     const float* bias;
@@ -186,6 +194,7 @@ struct SmallDevB {
 
 template <int MODE, int S>
 __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) {
+    constexpr bool FWD = MODE != kDa, CAST = MODE == kFwdCast;
     __shared__ float red[kW][2][2][256];   // [wavefront][row block][column block][register, lane]
     const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
     const int tile = xcd * p.chunk + slot;
@@ -200,7 +209,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
     float bias[2] = {0.0f, 0.0f};
     unsigned gate[2] = {0u, 0u};
     if (col < p.N) {
-        if constexpr (MODE == kFwd) {
+        if constexpr (FWD) {
             bias[0] = p.bias[(int64_t)group * p.sbias + col];
             bias[1] = p.bias[(int64_t)group * p.sbias + col + 1];
         } else {
@@ -210,19 +219,23 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
         }
     }
 
-    const rsrc_t a_rs = make_rsrc(p.a + (int64_t)group * p.sa, (unsigned)((p.M - 1) * p.lda + p.K) * 2u);
-    const rsrc_t b_rs = make_rsrc(p.b + (int64_t)group * p.sb, (unsigned)(MODE == kFwd ? (p.K - 1) * p.ldb + p.N : (p.N - 1) * p.ldb + p.K) * 2u);
+    const void* A = CAST ? (const void*)(p.a32 + (int64_t)group * p.sa) : (const void*)(p.a + (int64_t)group * p.sa);
+    constexpr unsigned kEs = CAST ? 4u : 2u;
+    const rsrc_t a_rs = make_rsrc(A, (unsigned)((p.M - 1) * p.lda + p.K) * kEs);
+    const rsrc_t b_rs = make_rsrc(p.b + (int64_t)group * p.sb, (unsigned)(FWD ? (p.K - 1) * p.ldb + p.N : (p.N - 1) * p.ldb + p.K) * 2u);
     constexpr unsigned kOutside = 0x80000000u;   // beyond every range
-    struct Step { u4 a[2], b[2]; };   // b: FWD, rows k .. k + 7 of the column pair; DA, eight indices of either column
+    struct Step { u4 a[CAST ? 4 : 2], b[2]; };   // b: FWD, rows k .. k + 7 of the column pair; DA, eight indices of either column
     auto load = [&](Step& r, int step) {
         const int k = 32 * step + k8;
         const bool in = k < p.K;                 // K is a multiple of eight
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int row = m0 + 16 * i + l16;
-            r.a[i] = buf_load(a_rs, in && row < p.M ? 2u * (unsigned)(row * p.lda + k) : kOutside, 0u);
+            const unsigned off = in && row < p.M ? kEs * (unsigned)(row * p.lda + k) : kOutside;
+            r.a[i] = buf_load(a_rs, off, 0u);
+            if constexpr (CAST) r.a[2 + i] = buf_load(a_rs, off, 16u);
         }
-        if constexpr (MODE == kFwd) {
+        if constexpr (FWD) {
             const unsigned off = in && col < p.N ? 2u * (unsigned)(k * p.ldb + col) : kOutside;
 #pragma unroll
             for (int e = 0; e < 8; ++e) r.b[e / 4][e % 4] = __builtin_amdgcn_raw_buffer_load_b32(b_rs, (int)(off + 2u * (unsigned)(e * p.ldb)), 0, 0);
@@ -236,9 +249,23 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    auto mfma = [&](const Step& r) {
-        u4 fb[2];
-        if constexpr (MODE == kFwd) {
+    auto mfma = [&](const Step& r, int step) {
+        u4 fa[2], fb[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            fa[i] = r.a[i];
+            if constexpr (CAST) {
+                const f4 lo = __builtin_bit_cast(f4, r.a[i]), hi = __builtin_bit_cast(f4, r.a[2 + i]);
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    fa[i][w] = bf16_bits_rne(lo[2 * w]) | bf16_bits_rne(lo[2 * w + 1]) << 16;
+                    fa[i][2 + w] = bf16_bits_rne(hi[2 * w]) | bf16_bits_rne(hi[2 * w + 1]) << 16;
+                }
+                const int row = m0 + 16 * i + l16, k = 32 * step + k8;
+                if (n0 == 0 && row < p.M && k < p.K) *(u4*)(p.a_out + (int64_t)group * p.M * p.K + (int64_t)row * p.K + k) = fa[i];
+            }
+        }
+        if constexpr (FWD) {
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 const unsigned lo = r.b[w / 2][2 * (w % 2)], hi = r.b[w / 2][2 * (w % 2) + 1];   // rows k + 2 w and k + 2 w + 1
@@ -253,7 +280,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.a[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0, 0);
     };
     const int steps = (p.K + 31) / 32;
     for (int s0 = wave; s0 < steps; s0 += S * kW) {
@@ -261,7 +288,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
 #pragma unroll
         for (int t = 0; t < S; ++t) load(r[t], s0 + t * kW);   // (steps past the end: zeros, no traffic)
 #pragma unroll
-        for (int t = 0; t < S; ++t) mfma(r[t]);
+        for (int t = 0; t < S; ++t) mfma(r[t], s0 + t * kW);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -281,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
             v[j] = red[0][i][j][threadIdx.x];
 #pragma unroll
             for (int w = 1; w < kW; ++w) v[j] += red[w][i][j][threadIdx.x];
-            if constexpr (MODE == kFwd) v[j] = fmaxf(v[j] + bias[j], 0.0f);
+            if constexpr (FWD) v[j] = fmaxf(v[j] + bias[j], 0.0f);
         }
         unsigned o = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{v[0], v[1]}, bf16x2));   // to nearest even
         if constexpr (MODE == kDa) {   // a bf16 is positive iff its sign bit is clear and it is not zero
@@ -418,15 +445,16 @@ bool gemm_small_bf16_fits(const GemmArgs& g, bool fwd) {
 
 template <int MODE>
 static hipError_t small_bf16(const GemmArgs& g, hipStream_t s) {
-    constexpr bool fwd = MODE == kFwd;
+    constexpr bool fwd = MODE != kDa, cast = MODE == kFwdCast;
     if (!g.a || !g.b || !g.c || g.groups < 1 || g.M < 1 || g.N < 1 || g.K < 1 || (fwd ? !g.bias : !g.mask)) return hipErrorInvalidValue;
-    if (!aligned16(g.a) || !aligned16(g.b) || !aligned16(g.c) || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || g.sa % 8 || g.sb % 8 || g.sc % 8 || g.K % 8 || g.N % 8)
+    if (!aligned16(g.a) || !aligned16(g.b) || !aligned16(g.c) || g.lda % 8 || g.ldb % 8 || g.ldc % 8 || g.sa % (cast ? 4 : 8) || g.sb % 8 || g.sc % 8 || g.K % 8 || g.N % 8)
         return hipErrorInvalidValue;
     if (!fwd && (!aligned16(g.mask) || g.smask % 8)) return hipErrorInvalidValue;
     if (g.lda < g.K || g.ldb < (fwd ? g.N : g.K) || g.ldc < g.N) return hipErrorInvalidValue;
     if (!small_offsets((int64_t)g.M * g.lda, (int64_t)(fwd ? g.K : g.N) * g.ldb)) return hipErrorInvalidValue;
+    if (cast && (!g.a_rounded || !aligned16(g.a_rounded) || (int64_t)g.M * g.lda >= ((int64_t)1 << 29))) return hipErrorInvalidValue;
     SmallDevB p = {};
-    p.a = (const uint16_t*)g.a; p.b = (const uint16_t*)g.b; p.c = (uint16_t*)g.c; p.bias = g.bias; p.mask = (const uint16_t*)g.mask;
+    p.a = (const uint16_t*)g.a; p.a32 = (const float*)g.a; p.a_out = (uint16_t*)g.a_rounded; p.b = (const uint16_t*)g.b; p.c = (uint16_t*)g.c; p.bias = g.bias; p.mask = (const uint16_t*)g.mask;
     p.sa = g.sa; p.sb = g.sb; p.sc = g.sc; p.sbias = g.sbias; p.smask = g.smask;
     p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
     p.tiles_m = (g.M + 31) / 32;
@@ -447,7 +475,7 @@ static hipError_t small_bf16(const GemmArgs& g, hipStream_t s) {
     }
     return hipGetLastError();
 }
-hipError_t launch_gemm_small_bf16_fwd(const GemmArgs& g, hipStream_t s) { return small_bf16<kFwd>(g, s); }
+hipError_t launch_gemm_small_bf16_fwd(const GemmArgs& g, hipStream_t s) { return g.a_rounded ? small_bf16<kFwdCast>(g, s) : small_bf16<kFwd>(g, s); }
 hipError_t launch_gemm_small_bf16_da(const GemmArgs& g, hipStream_t s) { return small_bf16<kDa>(g, s); }
 
 }  // namespace ols

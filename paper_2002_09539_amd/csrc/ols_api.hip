@@ -937,9 +937,13 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
     auto act_stride = [&](int l) -> int64_t { return (l == 0 && !bf) ? c->xs : (int64_t)B * c->dims[l]; };
     (void)es;
     int rc;
+    // the batch in bf16: by a pass of its own, or by the first forward GEMM where that is a small one
+    GemmArgs first = {};
+    first.groups = m; first.M = B; first.K = first.lda = c->dims[0]; first.N = first.ldb = c->dims[1];
+    const bool cast_in_gemm = bf && L > 1 && gemm_small_bf16_fits(first, true);
     if (bf) {
         rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-            return launch_cast_bf16(c->X, c->xs, (uint16_t*)(c->ws + c->off_x0), m, B, c->dims[0], s);
+            return cast_in_gemm ? hipSuccess : launch_cast_bf16(c->X, c->xs, (uint16_t*)(c->ws + c->off_x0), m, B, c->dims[0], s);
         });
         if (rc) return rc;
     }
@@ -951,6 +955,11 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
         GemmArgs ga = {};
         ga.a = act(l);
         ga.sa = act_stride(l);
+        if (l == 0 && cast_in_gemm) {
+            ga.a = c->X;
+            ga.sa = c->xs;
+            ga.a_rounded = c->ws + c->off_x0;
+        }
         ga.lda = c->dims[l];
         ga.b = bf ? (const void*)(shadow + c->w_off[l]) : (const void*)(xc + c->w_off[l]);
         ga.sb = c->ld;

@@ -172,6 +172,8 @@ struct GemmArgs {
     const void* a;      // operand A, group stride sa
     const void* b;      // operand B, group stride sb
     void* c;            // output, group stride sc
+    void* a_rounded;    // bf16 fwd of a small launch (gemm_small_bf16_fits), optional: a is fp32, and its bf16 values, which the
+                        // product takes, go here as well ([M][K] per group)
     const float* bias;  // fwd: [N] per group, stride sbias
     const void* mask;   // dA: activations whose sign gates the output, same shape as c, stride smask
     float* colsum;      // dw: optional [N] per group, receives the column sums of B (the bias gradient)

@@ -16,6 +16,7 @@ def outcome(m, dims, tau, calls, options, setup):
     from paper_2002_09539_amd.session import Session
     cfg = I.get(2).scaled(m=m, dims=dims, batch=20, nb=3, tau=tau, seed=611)
     X, labels = G.mlp_data(cfg)
+    labels = (labels % dims[-1]).astype(labels.dtype)
     with Session(m, cfg.d, tau, 0.6, 0.05, 0.9) as s:
         for key, value in options:
             s.set_option(key, value)
