@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f32_small_kernel(SmallDev p) {
 //
 // The first layer's forward GEMM takes the batch as it comes (kFwdCast): a lane loads its eight indices in fp32 and rounds them, and
 // the workgroups of a row's first column tile leave the rounded batch for the weight gradient.  The pass that did this alone took
-// 4 us and a launch of a small step.  Two rounds, us, one state / three in turn: 44 x (360-64-12, 184) tau 3 202 -> 180 / 127 -> 119,
+// 4 us and a launch of a small step (6 x (72 x 520 x 1032): 4.0 and 9.3 us then, 13.3 now, so what it saves is the launch).  Two rounds, us, one state / three in turn: 44 x (360-64-12, 184) tau 3 202 -> 180 / 127 -> 119,
 // 6 x (264-280-7, 104) tau 3 140 -> 125 / 131 -> 121, 9 x (2032-168-384-3, 72) 216 -> 211 / 174 -> 171, 6 x (1032-520-264-10, 72) 169 -> 167
 // (three in turn); none slower.
 struct SmallDevB {
