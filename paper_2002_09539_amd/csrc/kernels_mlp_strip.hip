@@ -25,6 +25,7 @@
 // 651 -> 567; 80 random fp32 MLPs that take it 1.09 times as fast in the geometric mean.
 #include "gemm_f32_tile.h"
 #include "head_dw_body.h"
+#include "mlp_strip_plan.h"
 #include "ols_internal.h"
 #include "split_bf16.h"
 
@@ -34,11 +35,11 @@ namespace {
 
 constexpr int kXcds = 8;
 constexpr int kThreads = 512;                // eight wavefronts: 2 halves x 4 of 32 columns
-constexpr int kRows = 64, kCols = 128;       // weight rows of a tile, columns of a strip
+constexpr int kRows = kStripRows, kCols = kStripCols;
 constexpr int kLine = 3 * 2 * kRows;         // bytes of a sample's rows of a tile in three bf16 terms
 constexpr int kWxBytes = 8 * 6 * 1024;       // the wavefronts' new weights as fragments of the products
 constexpr int kGxBytes = 8 * 4 * 1024;       // half sums of the gradient on their way to the wavefront that owns their rows
-constexpr unsigned kNowhere = 0x80000000u;   // a byte offset that the range checks answer with zeros (operands are smaller)
+constexpr unsigned kNowhere = kStripNowhere;
 
 struct StripDev {
     const float* xa;     // batch of the step, [B][M] per worker
@@ -127,8 +128,8 @@ __global__ __launch_bounds__(kThreads, 2) void strip_kernel(StripDev p) {
     const rsrc_t xn_rs = make_rsrc(FWD ? p.xn + (int64_t)group * p.sxn : nullptr, FWD ? x_bytes : 0u);
 
     // weight element r of the lane (accumulator order): row 8 (r / 4) + 4 half + r % 4 of the wavefront's 32, column lane % 32
-    const unsigned w_lane = col < N ? (unsigned)(32 * wr + 4 * half) * n4 + 4u * (unsigned)col : kNowhere;
-    auto w_off = [&](int row0, int r) { return w_lane + (unsigned)(row0 + 8 * (r / 4) + r % 4) * n4; };
+    const unsigned w_lane = col < N ? strip_offset(4u * (unsigned)col, (unsigned)(32 * wr + 4 * half), n4) : kNowhere;
+    auto w_off = [&](int row0, int r) { return strip_offset(w_lane, (unsigned)(row0 + 8 * (r / 4) + r % 4), n4); };
     float sx[16], sb[MOM ? 16 : 1], sz[PULL ? 16 : 1];
     auto state_request = [&](int row0) {
         if constexpr (UPD) {
@@ -151,9 +152,9 @@ __global__ __launch_bounds__(kThreads, 2) void strip_kernel(StripDev p) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int k = row0 + 8 * x_slot + 4 * h;
-            const unsigned o = k < M ? (unsigned)x_line * m4 + 4u * (unsigned)k : kNowhere;
+            const unsigned o = k < M ? strip_offset(4u * (unsigned)k, (unsigned)x_line, m4) : kNowhere;
 #pragma unroll
-            for (int t = 0; t < kVecs; ++t) xt[t][h] = __builtin_bit_cast(f4, buf_load(xa_rs, o + (unsigned)(kThreads / 8 * t) * m4, 0));
+            for (int t = 0; t < kVecs; ++t) xt[t][h] = __builtin_bit_cast(f4, buf_load(xa_rs, strip_offset(o, (unsigned)(kThreads / 8 * t), m4), 0));
         }
     };
     auto next_request = [&](int row0) {
@@ -161,9 +162,9 @@ __global__ __launch_bounds__(kThreads, 2) void strip_kernel(StripDev p) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int k = row0 + 16 * (x_slot / 2) + 4 * (x_slot % 2) + 8 * h;
-                const unsigned o = k < M ? (unsigned)x_line * m4 + 4u * (unsigned)k : kNowhere;
+                const unsigned o = k < M ? strip_offset(4u * (unsigned)k, (unsigned)x_line, m4) : kNowhere;
 #pragma unroll
-                for (int t = 0; t < kVecs; ++t) xr[t][h] = __builtin_bit_cast(f4, buf_load(xn_rs, o + (unsigned)(kThreads / 8 * t) * m4, 0));
+                for (int t = 0; t < kVecs; ++t) xr[t][h] = __builtin_bit_cast(f4, buf_load(xn_rs, strip_offset(o, (unsigned)(kThreads / 8 * t), m4), 0));
             }
         }
     };
@@ -206,10 +207,10 @@ __global__ __launch_bounds__(kThreads, 2) void strip_kernel(StripDev p) {
         constexpr int kVecLine = kCols / 4, kDv = kBatch * kVecLine / kThreads;
         const rsrc_t dz_rs = make_rsrc(p.dz + (int64_t)group * p.sdz, (unsigned)p.B * n4);
         const int line = threadIdx.x / kVecLine, c4 = 4 * (threadIdx.x % kVecLine);
-        const unsigned o = n0 + c4 < N ? (unsigned)line * n4 + 4u * (unsigned)(n0 + c4) : kNowhere;
+        const unsigned o = n0 + c4 < N ? strip_offset(4u * (unsigned)(n0 + c4), (unsigned)line, n4) : kNowhere;
         f4 dv[kDv];
 #pragma unroll
-        for (int t = 0; t < kDv; ++t) dv[t] = __builtin_bit_cast(f4, buf_load(dz_rs, o + (unsigned)(kThreads / kVecLine * t) * n4, 0));
+        for (int t = 0; t < kDv; ++t) dv[t] = __builtin_bit_cast(f4, buf_load(dz_rs, strip_offset(o, (unsigned)(kThreads / kVecLine * t), n4), 0));
         batch_request(tile0 * kRows);
         next_request(tile0 * kRows);
 #pragma unroll
@@ -377,14 +378,14 @@ __global__ __launch_bounds__(kThreads, 2) void strip_kernel(StripDev p) {
         const bool raw = p.ranges > 1;
         const rsrc_t out_rs = make_rsrc(p.out + (raw ? ((int64_t)range * p.groups + group) * p.B * N : (int64_t)group * p.sout), (unsigned)p.B * n4);
         const float bias = raw || col >= N ? 0.0f : bs[32 * wc + lane32];
-        const unsigned o = col < N ? (unsigned)(32 * HB * wr + 4 * half) * n4 + 4u * (unsigned)col : kNowhere;
+        const unsigned o = col < N ? strip_offset(4u * (unsigned)col, (unsigned)(32 * HB * wr + 4 * half), n4) : kNowhere;
 #pragma unroll
         for (int i = 0; i < HB; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 float v = split_sum(acc[i][r], low[i][r]);
                 if (!raw) v = fmaxf(v + bias, 0.0f);
-                state_store<false>(v, out_rs, o + (unsigned)(32 * i + 8 * (r / 4) + r % 4) * n4);   // samples past the batch are dropped
+                state_store<false>(v, out_rs, strip_offset(o, (unsigned)(32 * i + 8 * (r / 4) + r % 4), n4));   // samples past the batch are dropped
             }
     }
 }
@@ -409,43 +410,12 @@ hipError_t strip_dispatch(const StripDev& p, hipStream_t s) {
 #undef OLS_STRIP
 }
 
-constexpr int64_t kMostElements = ((int64_t)1 << 29) - 65536;   // byte offsets of a worker's operand below 2^31
-
 }  // namespace
-
-// The rule.  A workgroup takes a compute unit; its time is its tiles and about one and a half more for its start and end.  Ranges
-// are chosen for the fewest such times, within one round of the compute units if half of it is work (0.6 where that is more than
-// eight tiles; columns that a last strip does not have count as none), else over several rounds if 0.72 of them is: a last round that is nearly empty costs more than the saved
-// pass over the weights.  Contractions of up to 1024 stay in one range.  Two rounds, us without / with it.  One round, share: 0.51: 2
-// x (2544-1364-10, batch 92) 337 / 302;  0.65: 15 x (2368-352-448-10, 108) 635 / 534;  0.68: 3 x (2488-1188-10, 48) 600 / 480;  0.86:
-// 64 x (2164-240-10, 48) 767 / 603;  0.45 (not taken): 55 x (2660-144-10, 28) 306 / 340.  Several rounds: 0.72: 15 x (1664-1536-480-10,
-// 112) 1566 / 1496, 52 x (1524-1800-10, 20) 2832 / 2903;  0.73: 21 x (1492-1060-10, 48) 845 / 743;  0.82: 33 x (1868-1704-428-2016-5, 16)
-// 5387 / 5034;  not taken: 0.62: 22 x (1888-692-10, 96) 1730 / 2018;  0.69: 18 x (1312-1024-10, 88) 1338 / 1432 (0.53 in one round: the same), 10 x (1952-1248-96-10,
-// 16) 1196 / 1040.
-bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int* ranges) {
-    if (B > 128 || N % 4 || K % 4) return false;
-    if ((int64_t)B * K >= kMostElements || (int64_t)K * N >= kMostElements || (int64_t)B * N >= kMostElements) return false;
-    const int64_t strips = (int64_t)groups * ((N + kCols - 1) / kCols), tiles = (K + kRows - 1) / kRows;
-    if (strips > (1 << 20)) return false;
-    const double work = (double)groups * N / kCols * (double)tiles / 256.0;
-    double one = 0.0, several = 0.0;
-    int r_one = 1, r_several = 1;
-    for (int r = 1; r <= (K > 1024 ? most_ranges : 1) && (r == 1 || tiles / r >= 3); ++r) {
-        const int64_t per = (tiles + r - 1) / r, used = (tiles + per - 1) / per, rounds = (strips * used + 255) / 256;
-        const double share = work / ((double)rounds * ((double)per + 1.5));
-        if (rounds == 1 && share > one) { one = share; r_one = (int)used; }
-        if (rounds > 1 && share > several) { several = share; r_several = (int)used; }
-    }
-    const bool fits_one = one >= (work > 8.0 ? 0.6 : 0.5);
-    *ranges = fits_one ? r_one : r_several;
-    return fits_one || several >= 0.72;
-}
-int mlp_strip_range_rows(int K, int ranges) { return ((K + kRows - 1) / kRows + ranges - 1) / ranges * kRows; }
 
 hipError_t launch_mlp_strip(const GemmArgs& g, const MlpStripNext* next, hipStream_t s) {
     if (!g.a || !g.b || !g.c || !g.colsum || g.groups < 1 || g.K < 1 || g.K > 128 || g.M < 4 || g.M % 4 || g.N < 4 || g.N % 4) return hipErrorInvalidValue;
     if (!aligned16(g.a) || g.sa % 4 || !aligned16(g.b) || g.sb % 4 || g.lda != g.M || g.ldb != g.N || g.ldc != g.N) return hipErrorInvalidValue;
-    if ((int64_t)g.K * g.M >= kMostElements || (int64_t)g.M * g.N >= kMostElements || (int64_t)g.K * g.N >= kMostElements) return hipErrorInvalidValue;
+    if (!mlp_strip_offsets_fit(g.K, g.N, g.M)) return hipErrorInvalidValue;
     if (next && (!g.upd.enabled || !next->x || !aligned16(next->x) || !next->out || !next->bias || next->ranges < 1 || (next->ranges > 1 && !next->partial)))
         return hipErrorInvalidValue;
     StripDev p = {};

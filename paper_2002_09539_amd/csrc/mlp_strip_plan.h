@@ -1,0 +1,54 @@
+// Which fp32 MLPs' first hidden layer goes by column strips (kernels_mlp_strip.hip), over how many ranges of the weights' rows, and
+// the byte offsets that its lanes form.  Plain host code, and callable from the kernel where it is constexpr.
+#pragma once
+#include <cstdint>
+
+namespace ols {
+
+constexpr int kStripRows = 64, kStripCols = 128;       // weight rows of a tile, columns of a strip
+constexpr unsigned kStripNowhere = 0x80000000u;        // a lane without a column or a sample's rows starts here: zeros, and nothing is stored
+
+// samples that a workgroup has places for (zeros past the batch)
+constexpr int strip_samples(int B) { return B <= 64 ? 64 : 128; }
+
+// Byte offset of row `row` of a lane whose column's offset (or kStripNowhere) is `lane`, in a matrix with `row_bytes` per row.
+constexpr unsigned strip_offset(unsigned lane, unsigned row, unsigned row_bytes) { return lane + row * row_bytes; }
+
+// The offsets are 32 bits, and lanes add rows that do not exist to them, also to kStripNowhere: rows of a last tile past the weights,
+// samples past the batch.  With every operand, rounded up to whole tiles of rows and to strip_samples, below 2^31 bytes no sum passes 2^32
+// (where it would be a place in the matrix again), and all of them lie past the operand's end.  The limit is gemm_split_fits's, whose
+// forward GEMM such a layer takes.  B samples, layer K -> N.
+inline bool mlp_strip_offsets_fit(int B, int N, int K) {
+    const int64_t most = ((int64_t)1 << 29) - 65536, rows = ((int64_t)K + kStripRows - 1) / kStripRows * kStripRows, samples = strip_samples(B);
+    return rows * N < most && samples * K < most && samples * N < most;
+}
+
+// The rule.  A workgroup takes a compute unit; its time is its tiles and about one and a half more for its start and end.  Ranges
+// are chosen for the fewest such times, within one round of the compute units if half of it is work (0.6 where that is more than
+// eight tiles; columns that a last strip does not have count as none), else over several rounds if 0.72 of them is: a last round that is nearly empty costs more than the saved
+// pass over the weights.  Contractions of up to 1024 stay in one range.  Two rounds, us without / with it.  One round, share: 0.51: 2
+// x (2544-1364-10, batch 92) 337 / 302;  0.65: 15 x (2368-352-448-10, 108) 635 / 534;  0.68: 3 x (2488-1188-10, 48) 600 / 480;  0.86:
+// 64 x (2164-240-10, 48) 767 / 603;  0.45 (not taken): 55 x (2660-144-10, 28) 306 / 340.  Several rounds: 0.72: 15 x (1664-1536-480-10,
+// 112) 1566 / 1496, 52 x (1524-1800-10, 20) 2832 / 2903;  0.73: 21 x (1492-1060-10, 48) 845 / 743;  0.82: 33 x (1868-1704-428-2016-5, 16)
+// 5387 / 5034;  not taken: 0.62: 22 x (1888-692-10, 96) 1730 / 2018;  0.69: 18 x (1312-1024-10, 88) 1338 / 1432 (0.53 in one round: the same), 10 x (1952-1248-96-10,
+// 16) 1196 / 1040.
+inline bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int* ranges) {
+    if (B > 128 || N % 4 || K % 4 || !mlp_strip_offsets_fit(B, N, K)) return false;
+    const int64_t strips = (int64_t)groups * ((N + kStripCols - 1) / kStripCols), tiles = (K + kStripRows - 1) / kStripRows;
+    if (strips > (1 << 20)) return false;
+    const double work = (double)groups * N / kStripCols * (double)tiles / 256.0;
+    double one = 0.0, several = 0.0;
+    int r_one = 1, r_several = 1;
+    for (int r = 1; r <= (K > 1024 ? most_ranges : 1) && (r == 1 || tiles / r >= 3); ++r) {
+        const int64_t per = (tiles + r - 1) / r, used = (tiles + per - 1) / per, rounds = (strips * used + 255) / 256;
+        const double share = work / ((double)rounds * ((double)per + 1.5));
+        if (rounds == 1 && share > one) { one = share; r_one = (int)used; }
+        if (rounds > 1 && share > several) { several = share; r_several = (int)used; }
+    }
+    const bool fits_one = one >= (work > 8.0 ? 0.6 : 0.5);
+    *ranges = fits_one ? r_one : r_several;
+    return fits_one || several >= 0.72;
+}
+inline int mlp_strip_range_rows(int K, int ranges) { return ((K + kStripRows - 1) / kStripRows + ranges - 1) / ranges * kStripRows; }
+
+}  // namespace ols

@@ -22,6 +22,7 @@
 #include <string>
 #include <vector>
 
+#include "mlp_strip_plan.h"
 #include "ols_internal.h"
 
 using namespace ols;

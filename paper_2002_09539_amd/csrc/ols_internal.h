@@ -213,7 +213,7 @@ bool gemm_split_fits(int64_t a_elems, int64_t b_elems);   // elements a group's 
 bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits);
 hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s);
 // Weight gradient of an fp32 MLP's first hidden layer by column strips (kernels_mlp_strip.hip); with the fused update it can form
-// the next step's forward product as well.  Whether a shape takes it, and over how many ranges of the weights' rows.
+// the next step's forward product as well.  Whether a shape takes it, and over how many ranges of the weights' rows: mlp_strip_plan.h.
 struct MlpStripNext {
     const float* x;       // the next step's batch, strides as GemmArgs::a
     float* out;           // relu(x W + bias) with the updated parameters, [B][N] per worker
@@ -221,8 +221,6 @@ struct MlpStripNext {
     const float* bias;    // where the update leaves the bias, upd.ld between workers
     int ranges;
 };
-bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int* ranges);
-int mlp_strip_range_rows(int K, int ranges);
 hipError_t launch_mlp_strip(const GemmArgs& g, const MlpStripNext* next, hipStream_t s);
 // The weight gradients of n layers with the fused update, whose deltas are all there: up to kDwMostLayers in a launch, the bits of
 // one launch each.  Only the first may have a guest.
