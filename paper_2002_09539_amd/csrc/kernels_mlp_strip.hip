@@ -316,6 +316,14 @@ __global__ __launch_bounds__(kThreads, 2) void strip_kernel(StripDev p) {
                 state_store<false>(g, wo_rs, o);
             }
         }
+        if constexpr (FWD) {   // rows that the last tile does not have: 0 times a delta, which an infinite one makes a NaN
+            const int left = M - row0 - 32 * __builtin_amdgcn_readfirstlane(wr);   // (lane masks in scalar registers: there are no vector ones)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {   // rows 8 (r / 4) + 4 half + 0 .. 3 are there together: M is a multiple of four
+                const uint64_t there = (left > 8 * (r / 4) ? 0xFFFFFFFFull : 0ull) | (left > 8 * (r / 4) + 4 ? 0xFFFFFFFFull << 32 : 0ull);
+                w[r] = __builtin_amdgcn_inverse_ballot_w64(there) ? w[r] : 0.0f;
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (FWD) {
             uint8_t* mine = wx + wave * 6144 + 16 * lane;

@@ -116,3 +116,20 @@ def test_infinite_and_huge_values(shape):
     assert np.isnan(a[0][2]).any()
     solo = run(m, dims, batch, X, labels, x0, 4, 2, True)     # before any synchronisation the other workers are untouched
     assert np.isfinite(solo[0][3]).all() and np.isfinite(solo[0][m - 1]).all()
+
+
+@pytest.mark.parametrize("m,dims,batch", [(64, (324, 388, 36, 10), 36), (10, (2060, 388, 36, 10), 72)])   # last tiles of 4 and 12 rows
+def test_infinite_delta(m, dims, batch):
+    """A delta that overflows to an infinity: the updated weights are infinite and so is the next step's first activation.  The
+    rows that the last tile does not have would be NaN (zero times the infinity) and must not reach it."""
+    cfg, X, labels, _ = case(m, dims, batch, 2, 515)
+    X, labels = np.abs(X) + np.float32(0.5), np.zeros_like(labels)
+    big = np.float32(1e20)
+    x0 = np.concatenate([np.concatenate([np.full(a * b, w, np.float32), np.full(b, v, np.float32)]) for a, b, w, v in
+                         zip(dims, dims[1:], (0.0, -big, 0.0), (1e-30, 1e3, 0.0))])
+    w3 = x0[-(dims[2] * dims[3] + dims[3]):-dims[3]].reshape(dims[2], dims[3])
+    w3[:, 0] = -big                      # class 0 is never predicted and always right: the delta is 1e20 times -1e20
+    a = run(m, dims, batch, X, labels, x0, 4, 2, True)
+    b = run(m, dims, batch, X, labels, x0, 4, 2, False)
+    assert np.isposinf(b[0][:, :dims[0] * dims[1]]).all()    # the weights that the infinite activations come from
+    assert same(a, b)
