@@ -786,7 +786,7 @@ static int dw_variant(const GemmArgs& g) {
     // The persistent kernel that spreads a tile's update over the next tile's K loop wins where a tile has
     // enough K slices to hide the state's latency behind (K = 128, configuration 2: 0.1853 -> 0.1826 ms per
     // step); with K = 64 (configuration 5) it loses (665 us against 585 us per launch).
-    if (g.upd.enabled && g.K == 128 && g.upd_w_off % 32 == 0 && dw_pipelined_fits(g)) return 16;   // (it streams)
+    if (g.upd.enabled && g.K == 128 && g.upd_w_off % 16 == 0 && dw_pipelined_fits(g)) return 16;   // (it streams)
     if (!g.upd.enabled) return 1;
     return (int64_t)g.groups * ((g.M + 127) / 128) * ((g.N + 127) / 128) < 4096 ? 11 : 8;
 }

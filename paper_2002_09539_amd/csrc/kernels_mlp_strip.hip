@@ -411,7 +411,11 @@ hipError_t strip_launch(const StripDev& p, hipStream_t s) {
 
 template <int NB, bool FWD>
 hipError_t strip_dispatch(const StripDev& p, hipStream_t s) {
-    const bool mom = p.upd.mu != 0.0f, pull = p.upd.pull != 0, stream = update_streams(p.upd, p.upd_w_off, p.N);
+    // A strip's rows are four lines: non-temporal only where a row is whole lines.  (Where it is halves, which the tiles of the other
+    // weight gradients stream, two rounds, us, three states in turn, non-temporal / plain: 12 x (3072-656-10, 64) tau 4 925 / 855, 16 x
+    // (3072-528-10, 128) 681 / 668, 50 x (1800-624-10, 64) tau 8 3647 / 3565, 64 x (756-1264-9, 24) tau 4 2159 / 2085.)
+    const bool stream = !p.upd.cached && p.N % 32 == 0 && p.upd_w_off % 32 == 0;
+    const bool mom = p.upd.mu != 0.0f, pull = p.upd.pull != 0;
 #define OLS_STRIP(P, Mo) (stream ? strip_launch<NB, FWD, true, P, Mo, true>(p, s) : strip_launch<NB, FWD, true, P, Mo, false>(p, s))
     if (pull) return mom ? OLS_STRIP(true, true) : OLS_STRIP(true, false);
     return mom ? OLS_STRIP(false, true) : OLS_STRIP(false, false);

@@ -117,12 +117,18 @@ inline bool state_cached(int64_t elements, int more, bool in_place) {
 }
 
 // Whether a weight gradient with the fused update accesses a layer's state non-temporally (n columns; its weights start w_off
-// elements into a replica row).  Only where a row of it is whole 128-byte lines: else two tiles side by side share a line, and
-// what the first leaves of it non-temporally does not wait in L2 for the second.  State of 2 arrays in place, tiles of 64 x 64, us
-// non-temporal / plain: 22 x (1636 x 692) 108 / 58, x 688 81 / 58, x 704 75 / 59; 29 x (1592 x 996) 233 / 148, x 992 137 / 140.
-// Two rounds, us: 12 x (2096-924-64-1100-6, batch 16) tau 8 1347 / 709;  29 x (1592-996-14, 32) tau 2 1284 / 1022;  14 x
-// (2464-1928-1040-156-7, 24) tau 8 5361 / 4723;  bf16, 43 x (1184-456-13, 96) tau 8 2266 / 1873.
-inline bool update_streams(const FusedUpdate& u, int64_t w_off, int n) { return !u.cached && n % 32 == 0 && w_off % 32 == 0; }
+// elements into a replica row).  fp32: only where rows are whole halves of a 128-byte line.  Else two tiles side by side share a
+// half, and what the first leaves of it non-temporally does not wait in L2 for the second.  Two rounds, us, three states in turn,
+// non-temporal / plain: 30 x (2000-N-10, batch 24) tau 4, N = 1252 3104 / 2765, 1256 2952 / 2745, 1272 2995 / 2775, but 1264 2665 /
+// 2750;  40 x (1500-N-10, 48), N = 1036 1382 / 1275, 1032 1330 / 1252, 1048 1340 / 1278, but 1040 1202 / 1251;  29 x (1592-996-14, 32)
+// 1108 / 851;  rows that start inside a half: 20 x (1200-648-1024-10, 160) tau 3 2079 / 2003.
+// bf16: at any width.  The copy goes out in 2 bytes a weight beside the state's 16, and where the state does not stay in the cache
+// plain accesses cost it more than the shared lines: 12 x (3072-N-10, 96) tau 4, N = 656 971 / 1035, 664 1056 / 1064, 648 1058 / 1031;
+// 8 x (2048-N-10, 96), N = 2008 686 / 716, 2032 607 / 698;  17 x (944-1264-624-5, 112) 397 / 438;  40 x (3072-216-10, 96) 610 / 649 (with one
+// state, which then half fits the cache, N = 648 1218 / 1030 and 43 x (1184-456-13, 96) tau 8 2273 / 1975).
+inline bool update_streams(const FusedUpdate& u, int64_t w_off, int n) {
+    return !u.cached && (u.shadow || (n % 16 == 0 && w_off % 16 == 0));
+}
 
 #if defined(__HIPCC__)
 }  // namespace ols

@@ -37,9 +37,12 @@ def test_either_side_of_the_line(dtype, dims, batch, below, above):
     ("f32", (1024, 1028, 10), 64, 17),          # 216 MB; rows of 32 lines and 16 bytes
     ("f32", (68, 100, 128, 192, 10), 128, 3),   # the third layer's rows are whole lines that start inside one
     ("bf16", (1024, 1048, 10), 64, 20),
+    ("f32", (1024, 1040, 10), 160, 17),         # halves of a line, streamed
+    ("f32", (72, 80, 1024, 1032, 10), 128, 20),    # a streamed layer whose first row starts in the middle of a line, and a plain one
 ])
 def test_rows_that_are_no_whole_lines(dtype, dims, batch, m):
-    """Their state is accessed plainly at any size: worker by worker the bits of a single worker's run."""
+    """Their state is accessed plainly at any size unless rows are whole half lines or the operands bf16: worker by worker the same
+    bits either way."""
     cfg, X, labels, x0 = small_mlp_case(1, dims, batch, 2, seed=433)
     x0 = x0 + G.generic_normal(3, 1, x0.shape, sigma=0.02)
     a = two_steps(m, dims, batch, dtype, X, labels, x0)
