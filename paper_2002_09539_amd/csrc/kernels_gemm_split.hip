@@ -48,8 +48,11 @@ struct GemmSDev {
 };
 
 // ROWS x 32 slice of an operand.  KC: memory [rows][K]; else memory [K][rows].
-template <int ROWS, bool KC>
+// Of the 16 contraction indices of a matrix instruction lane half h takes 8 h + 0 .. 7 -- or, in the strips' order (STRIP), 4 h + 0 .. 3
+// and 8 further on: the order in which the accumulators of kernels_mlp_strip.hip hold the weights, so that both leave the same bits.
+template <int ROWS, bool KC, bool STRIP>
 struct STile {
+    static constexpr int kSecond = STRIP ? 8 : 4;   // from the first four of a lane half's indices to the others
     static constexpr int kLine = KC ? 192 : 6 * ROWS;          // bytes of an LDS line: three terms
     static constexpr int kTerm = KC ? 64 : 2 * ROWS;           // bytes between terms
     static constexpr int kBytes = (KC ? ROWS : kBK) * kLine;
@@ -66,11 +69,11 @@ struct STile {
         for (int q = 0; q < kVecs; ++q) {
             const int v = threadIdx.x + q * kThreads, line = v / kVecLine, e = 8 * (v % kVecLine);
             const int row = KC ? row0 + line : row0 + e;
-            l.k[q] = KC ? 16 * (e / 16) + e % 16 / 2 : line;
+            l.k[q] = !KC ? line : STRIP ? 16 * (e / 16) + e % 16 / 2 : e;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const bool ok = KC ? row < rows : row + 4 * h < rows;
-                l.off[q][h] = ok ? 4u * (unsigned)(KC ? row * ld + l.k[q] + 8 * h : line * ld + row + 4 * h) : kNowhere;
+                l.off[q][h] = ok ? 4u * (unsigned)(KC ? row * ld + l.k[q] + kSecond * h : line * ld + row + 4 * h) : kNowhere;
             }
         }
     }
@@ -80,7 +83,7 @@ struct STile {
         for (int q = 0; q < kVecs; ++q)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const bool in = l.k[q] + (KC ? 8 * h : 0) < klen;
+                const bool in = l.k[q] + (KC ? kSecond * h : 0) < klen;
                 r[q][h] = __builtin_bit_cast(f4, buf_load(rs, in ? l.off[q][h] : kNowhere, first));
             }
     }
@@ -102,8 +105,7 @@ struct STile {
             *(u4*)(d + 2 * kTerm) = s.lo;
         }
     }
-    // rows r0 .. r0 + 31 (a multiple of 32), k-step s: lane holds k = 16 s + 4 (lane / 32) + 0 .. 3 and 8 further on, of row lane %
-    // 32: the order of the same product in kernels_mlp_strip.hip, so that both leave the same bits
+    // rows r0 .. r0 + 31 (a multiple of 32), k-step s: lane holds its half's eight indices of 16 s .. 16 s + 15, of row lane % 32
     __device__ static void frag(SplitFrag& f, const uint8_t* lds, int r0, int s, int lane) {
         if constexpr (KC) {
             const int row = r0 + lane % 32, slot = 2 * s + lane / 32;
@@ -114,12 +116,12 @@ struct STile {
         } else {
             typedef s4v __attribute__((address_space(3))) * lds_s4_ptr;
             const int blk = lane / 16, j = lane % 16;
-            const int line = 16 * s + 4 * (blk / 2) + j / 4;
-            const int key = ROWS == 128 ? line & 3 : (line >> 1) & 1;   // the same eight lines on
+            const int line = 16 * s + (STRIP ? 4 : 8) * (blk / 2) + j / 4;
+            const int key = ROWS == 128 ? line & 3 : (line >> 1) & 1;   // the same kSecond lines on
             const uint8_t* p = lds + line * kLine + (((r0 / 32) ^ key) << 6) + (16 * (blk % 2) + 4 * (j % 4)) * 2;
             auto term = [&](int t) {
                 const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(p + t * kTerm));
-                const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(p + t * kTerm + 8 * kLine));
+                const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_ptr)(p + t * kTerm + kSecond * kLine));
                 return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             };
             f.hi = term(0);
@@ -129,10 +131,10 @@ struct STile {
     }
 };
 
-template <int BM, int BN, int DEPTH>
+template <int BM, int BN, int DEPTH, bool STRIP>
 __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(GemmSDev p) {
-    using TA = STile<BM, true>;
-    using TB = STile<BN, false>;
+    using TA = STile<BM, true, STRIP>;
+    using TB = STile<BN, false, STRIP>;
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;   // 2 x 2 wavefronts
     constexpr int kSlice = TA::kBytes + TB::kBytes;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kSlice];
@@ -289,7 +291,9 @@ hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
     if (total > (1 << 30)) return hipErrorInvalidValue;
     p.total_tiles = (int)total;
     p.chunk = (int)((total + kXcds - 1) / kXcds);
-    gemm_split_kernel<BM, BN, DEPTH><<<(unsigned)(p.chunk * kXcds), kThreads, 0, s>>>(p);
+    const unsigned grid = (unsigned)(p.chunk * kXcds);
+    if (g.strip_order) gemm_split_kernel<BM, BN, DEPTH, true><<<grid, kThreads, 0, s>>>(p);
+    else gemm_split_kernel<BM, BN, DEPTH, false><<<grid, kThreads, 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits == 1) return e;
     return launch_splitk_finish(p.partial, p.splits, g, s);

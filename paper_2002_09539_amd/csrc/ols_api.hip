@@ -979,7 +979,10 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
             ga.splits = c->splitk > 0 ? c->splitk : c->fwd_splits[l];
             ga.partial = (float*)(c->ws + c->off_partial);
         }
-        if (l == 0 && c->strip_ranges && !c->splitk && ga.splits > 1) ga.k_chunk = mlp_strip_range_rows(ga.K, ga.splits);
+        if (l == 0 && c->strip_ranges) {
+            ga.strip_order = 1;
+            if (!c->splitk && ga.splits > 1) ga.k_chunk = mlp_strip_range_rows(ga.K, ga.splits);
+        }
         rc = enqueue(c, OLS_K_GEMM_FWD, 0, c->cur, -1,
                      [&](hipStream_t s) { return bf ? launch_gemm_bf16_fwd(ga, s) : launch_gemm_f32_fwd(ga, s, c->gemm_variant[0] ? c->gemm_variant[0] : c->fwd_variant[l]); });
         if (rc) return rc;

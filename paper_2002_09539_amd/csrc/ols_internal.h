@@ -185,6 +185,7 @@ struct GemmArgs {
     float* colsum;      // dw: optional [N] per group, receives the column sums of B (the bias gradient)
     float* partial;     // fp32 fwd with splits > 1: scratch of splits * groups * M * N floats
     int k_chunk;        // split forward with splits > 1: contraction indices of a range, a multiple of 32 (0: an even share)
+    int strip_order;    // split forward: add up the products as the column strips do (MlpStripNext)
     int splits;         // fp32 fwd: number of K ranges contracted by separate workgroups (<= 1: none)
     int force_general;  // use the bounds-checked kernel even where the full-tile kernel applies
     const HeadArgs* guest;  // dw: the output layer's weight / bias gradients (launch_head_bwd's work) are computed by

@@ -115,3 +115,19 @@ def test_every_unit_that_an_infinity_reaches(m, dims, batch):
         rows = [r for r in range(batch) if (i, r) not in ((0, 3), (1, 2))]
         ref = np.maximum(X[i, 0, rows].astype(np.float64) @ W.astype(np.float64) + bias, 0.0)
         assert max_norm_ratio(h[i, rows], ref) <= GRAD_TOL
+
+
+def test_order_of_the_products():
+    """A first layer that goes by column strips adds the indices 4 .. 7 and 8 .. 11 of every sixteen in each other's place; any other layer
+    adds them as they come.  So the strips' product of the first samples is, to the bit, the plain one with those places exchanged."""
+    m, dims, few, many = 64, (512, 512, 3), 64, 256       # strips take up to 128 samples
+    cfg, X, labels, x0 = small_mlp_case(m, dims, many, 1, seed=415)
+    n_w = dims[0] * dims[1]
+    place = np.arange(dims[0]).reshape(-1, 4, 4)[:, [0, 2, 1, 3]].reshape(-1)
+    moved = x0.copy()
+    moved[:n_w] = x0[:n_w].reshape(dims[0], dims[1])[place].reshape(-1)
+    strips = first_activations(cfg, dims, few, X[:, :, :few], labels[:, :, :few], x0)
+    plain = first_activations(cfg, dims, many, X, labels, x0)[:, :few]
+    exchanged = first_activations(cfg, dims, many, X[..., place], labels, moved)[:, :few]
+    assert np.array_equal(strips, exchanged)
+    assert not np.array_equal(strips, plain) and max_norm_ratio(strips, plain) <= GRAD_TOL
