@@ -366,14 +366,10 @@ void plan_workspace(ols_ctx* c) {
                 gemm_f32_fwd_plan(c->m, c->B, c->dims[l + 1], c->dims[l], c->lean, &variant, &splits);
                 c->fwd_variant[l] = variant;
                 c->fwd_splits[l] = splits;
-                const bool scratch = splits > 1;
                 int ranges;
-                if (l == 0 && variant != 33 && mlp_strip_plan(c->m, c->B, c->dims[1], c->dims[0], scratch ? 8 : 1, &ranges)) {
-                    c->strip_ranges = ranges;   // and the forward kernel with the same products in the same order
-                    c->fwd_variant[0] = 32;
-                    c->fwd_splits[0] = ranges;
-                }
-                if (scratch) need_partial = std::max<int64_t>(need_partial, 8 * m * B * c->dims[l + 1] * 4);
+                if (l == 0 && variant != 33 && mlp_strip_plan(c->m, c->B, c->dims[1], c->dims[0], splits > 1 ? 8 : 1, &ranges))
+                    c->strip_ranges = ranges;   // (the forward GEMM then takes the same products in the same order, see compute_gradients)
+                if (splits > 1) need_partial = std::max<int64_t>(need_partial, 8 * m * B * c->dims[l + 1] * 4);
             }
             if (need_partial) c->off_partial = take(need_partial);
         }
@@ -979,12 +975,15 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
             ga.splits = c->splitk > 0 ? c->splitk : c->fwd_splits[l];
             ga.partial = (float*)(c->ws + c->off_partial);
         }
-        if (l == 0 && c->strip_ranges) {
+        int variant = bf ? 0 : c->fwd_variant[l];
+        if (l == 0 && c->strip_ranges && !c->splitk && !c->gemm_variant[0]) {   // what the strips' launch adds up ahead inside ols_run_steps, to the bit
+            variant = 32;
             ga.strip_order = 1;
-            if (!c->splitk && ga.splits > 1) ga.k_chunk = mlp_strip_range_rows(ga.K, ga.splits);
+            ga.splits = c->strip_ranges;
+            ga.k_chunk = mlp_strip_range_rows(ga.K, ga.splits);
         }
         rc = enqueue(c, OLS_K_GEMM_FWD, 0, c->cur, -1,
-                     [&](hipStream_t s) { return bf ? launch_gemm_bf16_fwd(ga, s) : launch_gemm_f32_fwd(ga, s, c->gemm_variant[0] ? c->gemm_variant[0] : c->fwd_variant[l]); });
+                     [&](hipStream_t s) { return bf ? launch_gemm_bf16_fwd(ga, s) : launch_gemm_f32_fwd(ga, s, c->gemm_variant[0] ? c->gemm_variant[0] : variant); });
         if (rc) return rc;
     }
     // output layer, loss, and its gradients

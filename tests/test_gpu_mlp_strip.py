@@ -133,3 +133,25 @@ def test_infinite_delta(m, dims, batch):
     b = run(m, dims, batch, X, labels, x0, 4, 2, False)
     assert np.isposinf(b[0][:, :dims[0] * dims[1]]).all()    # the weights that the infinite activations come from
     assert same(a, b)
+
+
+def test_forced_ranges_of_the_forward_gemm():
+    """OLS_OPT_GEMM_SPLITK holds for a layer whose strips are one range and whose plan has scratch for several."""
+    m, dims, batch = 64, (520, 380, 36, 12, 7), 64
+    cfg, X, labels, x0 = case(m, dims, batch, 1, 516)
+    h = []
+    for count in (1, 2, 4):
+        with make_session(m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+            s.set_option(B.OLS_OPT_GEMM_SPLITK, count)
+            s.attach_mlp(dims, batch, "f32")
+            Xd, yd = s.upload(X), s.upload(labels)
+            s.init_params(x0)
+            s.set_batch(Xd[:, 0], yd[:, 0])
+            s.local_step()
+            s.sync()
+            h.append(s.ws[:4 * m * batch * dims[1]].cpu().numpy().view(np.float32).reshape(m, batch, dims[1]))
+    W = x0[:dims[0] * dims[1]].reshape(dims[0], dims[1]).astype(np.float64)
+    bias = x0[dims[0] * dims[1]:(dims[0] + 1) * dims[1]].astype(np.float64)
+    for a in h:
+        assert max_norm_ratio(a[3], np.maximum(X[3, 0].astype(np.float64) @ W + bias, 0.0)) <= GRAD_TOL
+    assert not np.array_equal(h[0], h[1]) and not np.array_equal(h[1], h[2])    # sums over other ranges
