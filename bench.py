@@ -143,10 +143,9 @@ def algorithmic_work(cfg, ld, fused_update=True):
             work["conv_dw_bytes"] = 1.0 * act                           # bf16 input and bf16 delta
             if (H + 2) * (W + 2) >= 64:
                 # the block's tail runs in the second convolution's epilogue: bf16 in, fp32 shortcut in, sign bytes out (the first one's too);
-                # what is left of the pooling is a pass over the wavefronts' partial sums (8 C floats per 256 padded pixels)
+                # the wavefronts' partial sums of the pooling are added up by the classifier's launch
                 work["conv_fwd_bytes"] = ((1.0 + 1.0 / 16) * act + (1.5 + 1.0 / 16) * act) / 2
-                tiles = -(-(cfg.batch * (H + 2) * (W + 2)) // 256)
-                work["pool"] = ("hbm", 4.0 * m * (tiles * 8 * C + cfg.batch * C))
+                work.pop("pool")
             else:
                 work["conv_fwd_bytes"] = ((1.0 + 1.0 / 16) * act + 1.5 * act) / 2   # first: bf16 in, bf16 and sign bytes out; second: bf16 in, fp32 out
                 work["pool"] = ("hbm", 2.0 * act + act / 16)            # shortcut + ReLU + pooling: conv output and shortcut in, sign bytes out
@@ -169,8 +168,8 @@ def algorithmic_work(cfg, ld, fused_update=True):
             gate = 1.0 / 16 if tail else 1.0
             out = 0.5 if bf else 1.0
             work["bn_bwd"] = ("hbm", (((1 if tail else 2) * (gate + 1.0) + out) + (4.0 + out)) / 2 * act)
-            if tail:   # the pooling is a pass over the sums per 64 pixels
-                work["pool"] = ("hbm", 4.0 * m * (-(-(cfg.batch * H * W) // 64) * 3 * C + 3 * cfg.batch * C))
+            if tail:   # the sums per 64 pixels are added up by the classifier's launch
+                work.pop("pool", None)
             work.pop("pool_bwd", None)   # no such pass in the normalised blocks
     return work
 
@@ -361,6 +360,9 @@ def measure(idx, args, K, W, cpu_seconds, side):
             entry = {"launches": n, "avg_us": 1e3 * ms / n, "total_ms": ms}
             if name in work:
                 bound, amount = work[name]
+                if name == "conv_dw" and n == K and "conv_dw_bytes" in work:   # bf16: one launch per step for the gradients of both kernels
+                    amount *= 2
+                    work["conv_dw_bytes"] *= 2
                 rate = amount / (ms / n * 1e-3)
                 if bound == "hbm":
                     entry.update(bound="hbm", achieved=rate / 1e9, peak=HBM_PEAK_GBS, unit="GB/s",

@@ -116,7 +116,11 @@ enum {
                                       empty then); same arithmetic, identical bits                               */
 };
 
-/* kernel kinds for ols_kernel_stats / the launch trace */
+/* kernel kinds for ols_kernel_stats / the launch trace.  A stage whose work rides in another kind's launch keeps its place in the
+ * trace, but is neither launched nor counted: a block's OLS_K_POOL where the pooling's partial sums are added up by OLS_K_HEAD_FWD
+ * (a fused tail: normalised blocks on images of at least 64 pixels, plain bf16 ones of at least 64 with a border of one) and its
+ * OLS_K_HEAD_BWD (OLS_OPT_HEAD_DW_GUEST); the first of a bf16 block's two OLS_K_CONV_DW where one launch computes both kernels'
+ * gradients; OLS_K_CAST of a bf16 MLP whose first forward GEMM is a small one and rounds the batch itself. */
 enum {
     OLS_K_INIT = 0,
     OLS_K_STEP = 1,       /* momentum / plain local step                */
@@ -141,7 +145,7 @@ enum {
     OLS_K_CONV_DW = 20,   /* kernel and bias gradient of a 3 x 3 convolution                 */
     OLS_K_POOL = 21,      /* global average pooling in front of the classifier               */
     OLS_K_POOL_BWD = 22,  /* its backward                                                    */
-    OLS_K_BN_FWD = 23,    /* batch normalisation: statistics (two launches) + normalise, shortcut, ReLU */
+    OLS_K_BN_FWD = 23,    /* batch normalisation: statistics (one or two launches) + normalise, shortcut, ReLU */
     OLS_K_BN_BWD = 24,    /* its backward: scale / shift gradients (two launches) + gradient at the input */
     OLS_K_COUNT = 25
 };

@@ -171,9 +171,7 @@ int get_timer_event(ols_ctx* c, hipEvent_t* ev) {
     return OLS_OK;
 }
 
-// Enqueue one kernel: trace entry, optional event bracket on the kernel's own stream, launch.
-template <class F>
-int enqueue(ols_ctx* c, int kind, int stream_id, int src_buf, int dst_buf, F&& launch) {
+void trace_entry(ols_ctx* c, int kind, int stream_id, int src_buf, int dst_buf) {
     if (c->trace && c->trace_log.size() < 65536) {
         ols_trace_entry t;
         t.kind = kind;
@@ -185,6 +183,18 @@ int enqueue(ols_ctx* c, int kind, int stream_id, int src_buf, int dst_buf, F&& l
         c->trace_log.push_back(t);
     }
     c->next_waited = false;
+}
+
+// A stage whose work rides in another launch: its place in the trace, and nothing that would be counted or timed.
+int no_launch(ols_ctx* c, int kind, int src_buf) {
+    trace_entry(c, kind, 0, src_buf, -1);
+    return OLS_OK;
+}
+
+// Enqueue one kernel: trace entry, optional event bracket on the kernel's own stream, launch.
+template <class F>
+int enqueue(ols_ctx* c, int kind, int stream_id, int src_buf, int dst_buf, F&& launch) {
+    trace_entry(c, kind, stream_id, src_buf, dst_buf);
     if (c->dry) return OLS_OK;
     hipStream_t s = c->stream[stream_id];
     TimedLaunch t;
@@ -501,13 +511,15 @@ ConvBImages kernel_images(ols_ctx* c, const uint16_t* shadow, int64_t wa, int64_
 
 // A block's classifier gradients ride in the launch that ends the first kernel's (ConvArgs::guest); their place stays empty then.
 int classifier_gradient(ols_ctx* c, const HeadArgs& ha) {
-    return enqueue(c, OLS_K_HEAD_BWD, 0, c->cur, -1, [&](hipStream_t s) { return c->head_dw_guest ? hipSuccess : launch_head_bwd(ha, s); });
+    if (c->head_dw_guest) return no_launch(c, OLS_K_HEAD_BWD, c->cur);
+    return enqueue(c, OLS_K_HEAD_BWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_head_bwd(ha, s); });
 }
 
 // The bf16 blocks' kernel gradients.  The second layer's could run as soon as its delta is there; where one launch for both layers
 // fills the chip better (conv3x3_bf16_dw_pair_splits) it waits for the first layer's, and its own place in the schedule stays empty.
 int second_kernel_gradient(ols_ctx* c, const ConvBArgs& a) {
-    return enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return c->cv_dw_pair ? hipSuccess : launch_conv3x3_bf16_dw(a, s); });
+    if (c->cv_dw_pair) return no_launch(c, OLS_K_CONV_DW, -1);
+    return enqueue(c, OLS_K_CONV_DW, 0, -1, -1, [&](hipStream_t s) { return launch_conv3x3_bf16_dw(a, s); });
 }
 int first_kernel_gradient(ols_ctx* c, const ConvBArgs& a, ConvBArgs second) {
     second.partial = (float*)(c->ws + c->off_cpartial_b);
@@ -570,7 +582,7 @@ int conv_gradients_bf16(ols_ctx* c) {
         a.xres = c->X; a.s_x = c->xs; a.sign = sign; a.s_sign = act / 4; a.pool_part = pool_part;
         if ((rc = conv_fwd(a, shadow + wb, images.fwd_b))) return rc;
         parts = {pool_part, conv3x3_bf16_pool_part_floats(B, H, W, C), nullptr, positions, 1.0f / (float)(H * W)};
-        if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t) { return hipSuccess; }))) return rc;   // added up by the classifier's launch
+        if ((rc = no_launch(c, OLS_K_POOL, -1))) return rc;   // added up by the classifier's launch
     } else {   // images too small for the fused tail's two-samples-per-wavefront bookkeeping
         {   // y = conv(a1; Wb) + bb, fp32
             ConvBArgs a = base;
@@ -698,11 +710,11 @@ int conv_gradients_bn_bf16(ols_ctx* c) {
         if (tail) { a.out = nullptr; a.sign = sign; a.s_sign = act / 4; a.pool_part = tail_part; a.positions = H * W; }
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
-    if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-             return tail ? hipSuccess   // added up by the classifier's launch
-                         : launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
-         })))
-        return rc;
+    if (tail) rc = no_launch(c, OLS_K_POOL, -1);   // added up by the classifier's launch
+    else rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
+        return launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
+    });
+    if (rc) return rc;
     HeadArgs ha = {};
     ha.h = pooled;
     if (tail) ha.pool = {tail_part, tail_units * 6 * C, sample_sums, H * W, 1.0f / (float)(H * W)};
@@ -833,11 +845,11 @@ int conv_gradients(ols_ctx* c) {
         if (tail) { a.out = nullptr; a.sign = sign; a.s_sign = act / 4; a.pool_part = tail_part; a.positions = H * W; }
         if ((rc = enqueue(c, OLS_K_BN_FWD, 0, c->cur, -1, [&](hipStream_t s) { return launch_bn_forward(a, s); }))) return rc;
     }
-    if ((rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
-             return tail ? hipSuccess   // added up by the classifier's launch
-                         : launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
-         })))
-        return rc;
+    if (tail) rc = no_launch(c, OLS_K_POOL, -1);   // added up by the classifier's launch
+    else rc = enqueue(c, OLS_K_POOL, 0, -1, -1, [&](hipStream_t s) {
+        return launch_pool_mean(a2, act, pooled, (int64_t)B * C, m, B, H * W, C, 1.0f / (float)(H * W), s);
+    });
+    if (rc) return rc;
     HeadArgs ha = {};
     ha.h = pooled;
     if (tail) ha.pool = {tail_part, tail_units * 6 * C, sample_sums, H * W, 1.0f / (float)(H * W)};
@@ -939,8 +951,9 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
     first.groups = m; first.M = B; first.K = first.lda = c->dims[0]; first.N = first.ldb = c->dims[1];
     const bool cast_in_gemm = bf && L > 1 && gemm_small_bf16_fits(first, true);
     if (bf) {
-        rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
-            return cast_in_gemm ? hipSuccess : launch_cast_bf16(c->X, c->xs, (uint16_t*)(c->ws + c->off_x0), m, B, c->dims[0], s);
+        if (cast_in_gemm) rc = no_launch(c, OLS_K_CAST, -1);
+        else rc = enqueue(c, OLS_K_CAST, 0, -1, -1, [&](hipStream_t s) {
+            return launch_cast_bf16(c->X, c->xs, (uint16_t*)(c->ws + c->off_x0), m, B, c->dims[0], s);
         });
         if (rc) return rc;
     }

@@ -446,7 +446,7 @@ struct BnArgs {
     const float* sample_sums;
     int64_t s_sign;
 };
-hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s);    // statistics (two launches) + normalise
+hipError_t launch_bn_forward(const BnArgs& a, hipStream_t s);    // statistics (one or two launches) + normalise
 hipError_t launch_bn_backward(const BnArgs& a, hipStream_t s);   // sums (two launches) + gradient at z
 int64_t bn_partial_floats(int groups, int P, int C);
 

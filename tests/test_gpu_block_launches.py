@@ -61,3 +61,43 @@ def test_statistics_levels(dims, batch):
     head = slice(-(dims[0] * dims[3] + dims[3]), None)
     assert l2_ratio(g[0][head], want[head]) <= 1e-3
     assert l2_ratio(g[0], want) <= 1e-2
+
+
+def counted(attach, d, m, X, labels, x0, options=()):
+    """Launches per kind of one timed local step."""
+    from paper_2002_09539_amd.session import Session
+    with Session(m, d, 2, 0.6, 0.05, 0.0) as s:
+        for key, value in options:
+            s.set_option(key, value)
+        attach(s)
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_option(B.OLS_OPT_KERNEL_TIMING, 1)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        s.sync()
+        return {kind: n for kind, (n, _) in s.kernel_stats().items()}
+
+
+@pytest.mark.parametrize("dims,batch,batch_norm,dtype,options,want", [
+    ((64, 8, 9, 10), 5, True, "bf16", (), dict(pool=0, head_bwd=0, conv_dw=1)),                        # a tail, one launch for both kernels
+    ((64, 8, 9, 10), 5, False, "bf16", [(B.OLS_OPT_HEAD_DW_GUEST, 0)], dict(pool=0, head_bwd=1, conv_dw=1)),
+    ((192, 5, 5, 3), 2, True, "bf16", (), dict(pool=1, head_bwd=0, conv_dw=2)),                        # no tail, two launches
+    ((48, 6, 5, 10), 9, False, "f32", (), dict(pool=1, head_bwd=0, conv_dw=2)),
+    ((64, 9, 8, 7), 4, True, "f32", (), dict(pool=0, head_bwd=0, conv_dw=2)),
+])
+def test_blocks_count_what_they_launch(dims, batch, batch_norm, dtype, options, want):
+    cfg = I.get((9 if dtype == "bf16" else 7) if batch_norm else (8 if dtype == "bf16" else 6)).scaled(m=2, dims=dims, batch=batch, nb=1, seed=79)
+    X, labels = G.conv_data(cfg)
+    got = counted(lambda s: s.attach_convblock(*dims, batch, batch_norm=batch_norm, gemm_dtype=dtype), cfg.d, 2, X, labels, G.conv_init(cfg), options)
+    assert {k: got.get(k, 0) for k in want} == want
+    assert got["conv_fwd"] == 2 and got["conv_dx"] == 1 and got["head_fwd"] == 1
+
+
+@pytest.mark.parametrize("m,casts", [(3, 0), (200, 1)])    # a small first forward GEMM, and one that takes the converted batch
+def test_mlps_count_the_conversion_that_they_launch(m, casts):
+    dims, batch = (264, 280, 7), 104
+    cfg = I.get(3).scaled(m=m, dims=dims, batch=batch, nb=1, seed=80)
+    X, labels = G.mlp_data(cfg)
+    got = counted(lambda s: s.attach_mlp(dims, batch, "bf16"), cfg.d, m, X, labels % 7, G.mlp_init(cfg))
+    assert got.get("cast_bf16", 0) == casts and got["gemm_fwd"] == 1
