@@ -78,8 +78,9 @@ def parse():
     return ap.parse_args()
 
 
-def algorithmic_work(cfg, ld, fused_update=True):
-    """Per-launch algorithmic bytes / flops of each kernel kind (element-replicas x bytes, 2 M N K)."""
+def algorithmic_work(cfg, ld, fused_update=True, ahead=False):
+    """Per-launch algorithmic bytes / flops of each kernel kind (element-replicas x bytes, 2 M N K).  ahead: the first layer's
+    weight gradient also forms the next step's product (fp32 MLPs with one hidden layer, inside the library's loop)."""
     m = cfg.m
     er = m * ld                        # element-replicas one streaming launch touches
     mom = 8 if cfg.mu != 0.0 else 0    # read + write of the momentum buffer
@@ -114,8 +115,10 @@ def algorithmic_work(cfg, ld, fused_update=True):
             es = 2 if cfg.gemm_dtype == "bf16" else 4
             per_elem = 8 + mom + shadow
             dw_bytes = [m * (dims[l] * dims[l + 1] * per_elem + B * (dims[l] + dims[l + 1]) * es) for l in range(L - 1)]
+            if ahead:   # the next batch in, its activations out, and as many products again
+                dw_bytes[0] += m * B * (dims[0] + dims[1]) * es
             work["gemm_dw"] = ("hbm", sum(dw_bytes) / len(dw_bytes))
-            work["gemm_dw_flops"] = sum(fwd) / len(fwd)
+            work["gemm_dw_flops"] = (sum(fwd) + (fwd[0] if ahead else 0.0)) / len(fwd)
         da = [2.0 * m * B * dims[l] * dims[l + 1] for l in range(1, L - 1)]
         if da:
             work["gemm_da"] = ("mfma", sum(da) / len(da))
@@ -355,7 +358,8 @@ def measure(idx, args, K, W, cpu_seconds, side):
         timed_elapsed = region(K)
         stats = sess.kernel_stats()
         sess.set_option(B.OLS_OPT_KERNEL_TIMING, 0)
-        work = algorithmic_work(cfg, sess.ld, fused_update=bool(fuse_gemm_update) and not fuse_mean)
+        ahead = cfg.kind == "mlp" and len(cfg.dims) == 3 and stats.get("gemm_fwd", (K, 0.0))[0] < K
+        work = algorithmic_work(cfg, sess.ld, fused_update=bool(fuse_gemm_update) and not fuse_mean, ahead=ahead)
         for name, (n, ms) in stats.items():
             entry = {"launches": n, "avg_us": 1e3 * ms / n, "total_ms": ms}
             if name in work:

@@ -337,10 +337,10 @@ OLS_API int ols_anchor_update_async(ols_handle h);
  * from a resident data set visited cyclically and unshuffled (Section 4: the data is partitioned and not
  * shuffled): iteration k reads batch k mod nb of X_dev [m][nb][B][row] fp32 and y_dev [m][nb][B]
  * (int32 labels or fp32 targets), k being the handle's iteration count.  Same results as the
- * separate calls, to the bit, and the same launches -- except that (not while OLS_OPT_TRACE or
- * OLS_OPT_KERNEL_TIMING is on) the steps of a round of a small least-squares problem whose refresh runs in line may
- * share one launch, and that the weight gradient of a large fp32 MLP's first hidden layer may form the next step's
- * first product in its launch; stops at the first error and returns it.  OLS_ESTATE without an attached model or
+ * separate calls, to the bit, and the same launches -- except that the steps of a round of a small least-squares
+ * problem whose refresh runs in line may share one launch (not while OLS_OPT_TRACE or OLS_OPT_KERNEL_TIMING is on), and
+ * that the weight gradient of a large fp32 MLP's first hidden layer may form the next step's first product in its launch
+ * (not while OLS_OPT_TRACE is on; OLS_K_GEMM_FWD is then counted for the first step of a call only); stops at the first error and returns it.  OLS_ESTATE without an attached model or
  * when a pull or an anchor refresh is due. */
 OLS_API int ols_run_steps(ols_handle h, int64_t steps, const float* X_dev, const void* y_dev, int nb);
 

@@ -1741,9 +1741,9 @@ int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, in
     const int64_t row = sample_elems(c);
     const int64_t x_batch = (int64_t)c->B * row, y_batch = c->B;   // elements per batch
     const size_t y_elem = 4;                                          // int32 labels and fp32 targets alike
-    // Whether a step's weight-gradient launch may form the next step's first product: nobody counts or times the launches, and
-    // (below) nothing rewrites the models between the two.
-    const bool look_ahead = !c->dry && !c->trace && !c->timing;
+    // Whether a step's weight-gradient launch may form the next step's first product: nobody asks for the schedule of single steps,
+    // and (below) nothing rewrites the models between the two.  Timed launches are the ones that run otherwise.
+    const bool look_ahead = !c->dry && !c->trace;
     struct Ahead {
         ols_ctx* c;
         ~Ahead() { c->next_X = nullptr; c->fwd_ready = false; c->refresh_in_line = false; }

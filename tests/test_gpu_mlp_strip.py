@@ -155,3 +155,20 @@ def test_forced_ranges_of_the_forward_gemm():
     for a in h:
         assert max_norm_ratio(a[3], np.maximum(X[3, 0].astype(np.float64) @ W + bias, 0.0)) <= GRAD_TOL
     assert not np.array_equal(h[0], h[1]) and not np.array_equal(h[1], h[2])    # sums over other ranges
+
+
+@pytest.mark.parametrize("shape", [0, 3])
+def test_timing_times_the_launches_of_the_loop(shape):
+    """Per-kernel timing leaves the library's loop as it is: the first product of every step but a call's first comes with the
+    weight gradient of the step before."""
+    m, dims, batch = SHAPES[shape]
+    cfg, X, labels, x0 = case(m, dims, batch, 2, 517)
+    with make_session(m, cfg.d, 4, 0.6, 0.05, 0.9) as s:
+        s.attach_mlp(dims, batch, "f32")
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_option(B.OLS_OPT_KERNEL_TIMING, 1)
+        s.run_resident(3, Xd, yd)
+        s.run_resident(2, Xd, yd)
+        stats = s.kernel_stats()
+        assert stats["gemm_fwd"][0] == 2 and stats["gemm_dw"][0] == 5 and stats["head_fwd"][0] == 5
