@@ -340,8 +340,10 @@ OLS_API int ols_anchor_update_async(ols_handle h);
  * separate calls, to the bit, and the same launches -- except that the steps of a round of a small least-squares
  * problem whose refresh runs in line may share one launch (not while OLS_OPT_TRACE or OLS_OPT_KERNEL_TIMING is on), and
  * that the weight gradient of a large fp32 MLP's first hidden layer may form the next step's first product in its launch
- * (not while OLS_OPT_TRACE is on; OLS_K_GEMM_FWD is then counted for the first step of a call only); stops at the first error and returns it.  OLS_ESTATE without an attached model or
- * when a pull or an anchor refresh is due. */
+ * (not while OLS_OPT_TRACE is on; OLS_K_GEMM_FWD is then counted for the first step of a call only).  Such a layer's
+ * kernels are chosen for this loop and taken by the separate calls as well, for the same bits; without the product ahead
+ * most shapes are still faster with them than with the other kernels, some take up to a tenth longer.  Stops at the first
+ * error and returns it.  OLS_ESTATE without an attached model or when a pull or an anchor refresh is due. */
 OLS_API int ols_run_steps(ols_handle h, int64_t steps, const float* X_dev, const void* y_dev, int nb);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses

@@ -321,6 +321,16 @@ bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits) {
     return tiles >= 512 || (tiles >= 256 && K >= 1024) || (tiles >= 128 && K >= 2048);
 }
 
-hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s) { return gemm_launch<64, 128, 4>(g, s); }
+// A first layer whose weight gradient goes by column strips has its products in the strips' ranges, few of them, whatever its own plan
+// would be; callers that drive the steps one by one form them here.  Where 64 x 128 tiles leave much of a round of two per compute
+// unit empty, 64 x 64 ones are faster on short contractions of one row of tiles (the same bits).  us per launch, 64 x 128 / 64 x 64: 45 x
+// (64 x 512 x 1556), 180 tiles, 65 / 62; 11 x (48 x 1076 x 1220), 198, 37.6 / 35.5; 13 x (40 x 432 x 1544), 208, 21.3 / 19.4; 64 x (24 x 1264 x
+// 756), 640, 107 / 94; but longer 14 x (20 x 1768 x 2428), 196, 55 / 60 and 64 x (64 x 1024 x 3072), 512, 189 / 240, more rows 39 x (72 x 300 x
+// 1536), 468, 55 / 59, full rounds 39 x (36 x 1620 x 632), 507 (a step with 4 % more).
+hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s) {
+    const int64_t tiles = (int64_t)g.groups * ((g.M + 63) / 64) * ((g.N + 127) / 128) * (g.splits > 1 ? g.splits : 1);
+    if (g.strip_order && g.M <= 64 && g.K <= 2048 && tiles <= 320 * ((tiles + 511) / 512)) return gemm_launch<64, 64, 2>(g, s);
+    return gemm_launch<64, 128, 4>(g, s);
+}
 
 }  // namespace ols

@@ -450,7 +450,7 @@ hipError_t launch_mlp_strip(const GemmArgs& g, const MlpStripNext* next, hipStre
     }
     p.strips = (g.N + kCols - 1) / kCols;
     p.tiles_m = (g.M + kRows - 1) / kRows;
-    const int ranges = next ? next->ranges : g.splits > 1 ? g.splits : 1;
+    const int ranges = next ? next->ranges : mlp_strip_alone_ranges(g.groups, g.N, g.M, g.splits > 1 ? g.splits : 1, g.upd.enabled != 0);
     p.tiles_per_range = (p.tiles_m + ranges - 1) / ranges;
     p.ranges = (p.tiles_m + p.tiles_per_range - 1) / p.tiles_per_range;
     const bool raw = next && p.ranges > 1;

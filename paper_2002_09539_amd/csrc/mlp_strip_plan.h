@@ -32,6 +32,9 @@ inline bool mlp_strip_offsets_fit(int B, int N, int K) {
 // 112) 1566 / 1496, 52 x (1524-1800-10, 20) 2832 / 2903;  0.73: 21 x (1492-1060-10, 48) 845 / 743;  0.82: 33 x (1868-1704-428-2016-5, 16)
 // 5387 / 5034;  not taken: 0.62: 22 x (1888-692-10, 96) 1730 / 2018;  0.69: 18 x (1312-1024-10, 88) 1338 / 1432 (0.53 in one round: the same), 10 x (1952-1248-96-10,
 // 16) 1196 / 1040.
+// Those figures are for ols_run_steps.  Callers that drive the steps one by one take the same two kernels without the product ahead,
+// for the same bits: 110 shapes 1.05 times as fast as without strips in the geometric mean, 0.90 the least (27 x (2400-184-11, 24)), where
+// ols_run_steps is 1.21 and 1.15 times as fast.
 inline bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int* ranges) {
     if (B > 128 || N % 4 || K % 4 || !mlp_strip_offsets_fit(B, N, K)) return false;
     const int64_t strips = (int64_t)groups * ((N + kStripCols - 1) / kStripCols), tiles = (K + kStripRows - 1) / kStripRows;
@@ -50,5 +53,15 @@ inline bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int
     return fits_one || several >= 0.72;
 }
 inline int mlp_strip_range_rows(int K, int ranges) { return ((K + kStripRows - 1) / kStripRows + ranges - 1) / ranges * kStripRows; }
+
+// The ranges of a launch without the next product, whose bits do not depend on them: the caller drives the steps one by one.  More
+// rounds than one end more evenly in four ranges: us per launch 64 x (3072 x 1024, batch 64) 598 / 590, 64 x (756 x 1264, 24) 211 / 199.  A
+// launch that only writes the gradient holds two workgroups per compute unit and takes eight: steps of 63 x (2752-252-5, 16) 257 / 237,
+// 11 x (2628-1108-5, 92) 294 / 253, 40 x (1900-688-10, 32) 319 / 299, 45 x (1556-512-2, 64) 238 / 218.
+inline int mlp_strip_alone_ranges(int groups, int N, int K, int ranges, bool update) {
+    const int64_t strips = (int64_t)groups * ((N + kStripCols - 1) / kStripCols), tiles = (K + kStripRows - 1) / kStripRows;
+    if (!update) return (int)(tiles < 8 ? tiles : 8);
+    return strips > 256 && ranges < 4 && tiles >= 12 ? 4 : ranges;
+}
 
 }  // namespace ols
