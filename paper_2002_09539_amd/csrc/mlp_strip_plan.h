@@ -31,7 +31,9 @@ inline bool mlp_strip_offsets_fit(int B, int N, int K) {
 // 64 x (2164-240-10, 48) 767 / 603;  0.45 (not taken): 55 x (2660-144-10, 28) 306 / 340.  Several rounds: 0.72: 15 x (1664-1536-480-10,
 // 112) 1566 / 1496, 52 x (1524-1800-10, 20) 2832 / 2903;  0.73: 21 x (1492-1060-10, 48) 845 / 743;  0.82: 33 x (1868-1704-428-2016-5, 16)
 // 5387 / 5034;  not taken: 0.62: 22 x (1888-692-10, 96) 1730 / 2018;  0.69: 18 x (1312-1024-10, 88) 1338 / 1432 (0.53 in one round: the same), 10 x (1952-1248-96-10,
-// 16) 1196 / 1040.
+// 16) 1196 / 1040.  Short contractions of more than 64 samples, whose tiles take longer, have to fill 0.56 of the one round: below it
+// 23 x (1492-404-2, 76) tau 1 0.90 times as fast, 32 x (1224-300-13, 124) tau 1 0.94, 44 x (296-492-6, 96) 0.97, 31 x (844-604-5, 108) 1.04,
+// but 9 x (2228-380-8, 124) 1.27, 2 x (1908-1512-9, 124) 1.23.
 // Those figures are for ols_run_steps.  Callers that drive the steps one by one take the same two kernels without the product ahead,
 // for the same bits: 110 shapes 1.05 times as fast as without strips in the geometric mean, 0.90 the least (27 x (2400-184-11, 24)), where
 // ols_run_steps is 1.21 and 1.15 times as fast.
@@ -48,7 +50,7 @@ inline bool mlp_strip_plan(int groups, int B, int N, int K, int most_ranges, int
         if (rounds == 1 && share > one) { one = share; r_one = (int)used; }
         if (rounds > 1 && share > several) { several = share; r_several = (int)used; }
     }
-    const bool fits_one = one >= (work > 8.0 ? 0.6 : 0.5);
+    const bool fits_one = one >= (work > 8.0 ? 0.6 : B > 64 && K < 1600 ? 0.56 : 0.5);
     *ranges = fits_one ? r_one : r_several;
     return fits_one || several >= 0.72;
 }
