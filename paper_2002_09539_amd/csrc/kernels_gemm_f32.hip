@@ -19,6 +19,7 @@
 // Workgroup ids are remapped so that consecutive tiles of one worker land on the same XCD (workgroups
 // are dealt round-robin to the 8 XCDs, each with its own L2), keeping a worker's weights in one L2.
 #include "gemm_epilogue.h"
+#include "gemm_f32_plan.h"
 #include "gemm_f32_tile.h"
 #include "head_dw_body.h"
 #include "ols_internal.h"
@@ -722,39 +723,6 @@ static hipError_t dw_pipelined_launch(const GemmArgs& g, hipStream_t s) {
 
 // Tile shapes.  Variant 0 is the default (for the forward GEMM: chosen from the shape); the others exist so
 // that the choice can be re-measured (OLS_OPT_TUNING; most of them only in builds with -DOLS_TUNING_VARIANTS).  LDS per workgroup stays below 80 KiB so two workgroups fit a compute unit.
-// Shape-driven choice for the forward GEMM.  Measured on configuration 2 (M = 128, N = 512, K = 3072,
-// 16 groups): every tile shape lands within a few percent once there are several workgroups per compute
-// unit, because the matrix pipe idles whenever a wavefront waits at the slice barrier or for its loads
-// and only other resident workgroups fill those gaps; so: 64 x 64 tiles, and K ranges until the launch
-// has about two workgroups per compute unit.  With the full-tile path, per launch including the pass that
-// sums the parts: one K range (256 workgroups) 70.8 us, two 69.1 us, four 71.3 us, eight 82 us; the step as a
-// whole 0.1808 / 0.1798 / 0.1828 / 0.194 ms (fewer parts to write and re-read, and the anchor refresh on the
-// side stream finds more room beside the smaller launch).
-// Where 64 x 64 tiles would give four or more workgroups per compute unit, 64 x 128 tiles (half as many, each
-// A slice loaded once for twice the columns) are faster: configuration 5 (M = 64, N = 1024, 64 groups) 232 us
-// against 238 us per launch, 0.8428 against 0.8504 ms per step.
-// Large launches run on the bf16 matrix cores with split operands (variant 32, kernels_gemm_split.hip: 234 -> 187 us and
-// 76 -> 61 us on configurations 5 and 2).  What is left is small: there a K range may be as short as 96 indices (5 workers
-// x (36 x 300 x 788): eight ranges 13.8 us, two 17.3), unless the contraction is too short for the second launch that
-// adds the ranges up.  Smaller launches still have a kernel without slices and without scratch (variant 33,
-// kernels_gemm_small.hip); lean: also where K ranges are a little faster.
-void gemm_f32_fwd_plan(int groups, int M, int N, int K, bool lean, int* variant, int* splits) {
-    *variant = 32;
-    if (gemm_split_fwd_plan(groups, M, N, K, splits)) return;
-    *variant = 2;
-    int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 63) / 64);
-    if (tiles >= 1024 && N >= 128) {
-        *variant = 6;
-        tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 127) / 128);
-    }
-    int s = 1;
-    while (K >= 512 && tiles * s < 512 && K / (2 * s) >= 96 && s < 8) s *= 2;
-    *splits = s;
-    if (!gemm_small_fwd_fits(groups, M, N, K, lean && s > 1 ? 0 : s)) return;
-    *variant = 33;
-    *splits = 1;
-}
-
 hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant) {
     if (variant == 0) {
         int sp;

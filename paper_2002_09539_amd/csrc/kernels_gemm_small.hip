@@ -28,6 +28,7 @@
 //   6 x (220 x 608 x 604)    28.4 / 19.1   20.7 / 19.9
 //   7 x (92 x 824 x 1580)    35.6 / 38.7 (not taken)   43.1 / 41.6
 #include "gemm_bf16_tile.h"
+#include "gemm_f32_plan.h"
 #include "ols_internal.h"
 
 namespace ols {
@@ -322,31 +323,6 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_small_kernel(SmallDevB p) 
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
 
 }  // namespace
-
-// The rules, from both sides measured on 110 shapes (2 - 64 workers, M 16 - 252, N 64 - 2000, K 64 - 3072) and again on 440, most of
-// them near the lines: work in steps of 16 indices of a 32 x 16 tile.  Forward up to 80,000; beyond, 64 x 64 tiles read less; long
-// contractions only up to 30,000 (their K ranges spread better: 13 x (40 x 476 x 2612), 128,000, 40.5 and 45.4).  Delta, whose 64 x 64
-// tiles have no K ranges, the same without that and up to 160,000 from K = 1024 on (7 x (76 x 1348 x 1396) 63.0 and 54.5;
-// 22 x (64 x 536 x 2256), 211,000: 56.9 and 66.4).
-// Where the 64 x 64 tiles come close to whole rounds of 256 they are at their best: with more than 1,250 tiles here (1,230 in the
-// delta) for each of their rounds, only up to 50,000 (70,000).  Forward 20 x (52 x 236 x 1984) 27.8 and 34.4, 11 x (64 x 412 x 1804) 28.6
-// and 34.5, 9 x (100 x 1680 x 300) 21.3 and 23.4, but below 6 x (52 x 644 x 1564), 48,200, 1.21 times as fast; delta
-// 6 x (80 x 1160 x 1376) 39.9 and 46.4, 14 x (156 x 364 x 704) 26.9 and 30.6, but 38 x (180 x 492 x 136), 63,600, 1.67 times.  Of 360 other
-// shapes that the rules take, the forward ones 1.31 times as fast in the geometric mean and the delta ones 1.70, two forward ones
-// lose 3 and 6 % (2 x (84 x 276 x 2536), 18.4 and 19.5).
-static int64_t small_tiles(int groups, int M, int N) { return (int64_t)groups * ((M + 31) / 32) * ((N + 15) / 16); }
-static int64_t tile_rounds(int groups, int M, int N, int ranges) { return ((int64_t)groups * ((M + 63) / 64) * ((N + 63) / 64) * ranges + 255) / 256; }
-static bool small_offsets(int64_t a_elems, int64_t b_elems) { return a_elems < (1 << 28) && b_elems < (1 << 28); }   // 32-bit byte offsets
-bool gemm_small_fwd_fits(int groups, int M, int N, int K, int ranges) {
-    const int64_t tiles = small_tiles(groups, M, N), work = tiles * ((K + 15) / 16);
-    if (tiles * ranges > 1250 * tile_rounds(groups, M, N, ranges) && work > 50000) return false;   // (never with no ranges)
-    return work <= (K <= 2048 ? 80000 : 30000) && small_offsets((int64_t)M * K, (int64_t)K * N);
-}
-bool gemm_small_da_fits(int groups, int M, int N, int K) {
-    const int64_t tiles = small_tiles(groups, M, N), work = tiles * ((K + 15) / 16);
-    if (tiles > 1230 * tile_rounds(groups, M, N, 1) && work > 70000) return false;
-    return work <= (K >= 1024 ? 160000 : 80000) && small_offsets((int64_t)M * K, (int64_t)K * N);
-}
 
 template <int MODE, int TN>
 static void small_start(const SmallDev& p, int steps, hipStream_t s) {

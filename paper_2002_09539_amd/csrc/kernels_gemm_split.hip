@@ -22,6 +22,7 @@
 // 103 against 585 and 102 for the fp32 kernels, 64 x 128 658 and 107: not kept.  In the delta GEMM no difference (12.5
 // against 12.7 us on 5 x (36 x 300 x 124)), nor with 64 x 64 tiles in small forward GEMMs.
 // Error of a step's gradients against 64 bits (relative 2-norm, median over workers): 1.7e-7 -> 1.4e-7 and 1.9e-7 -> 1.2e-7.
+#include "gemm_f32_plan.h"
 #include "ols_internal.h"
 #include "split_bf16.h"
 
@@ -300,26 +301,6 @@ hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
 }
 
 }  // namespace
-
-bool gemm_split_fits(int64_t a_elems, int64_t b_elems) {   // byte offsets of a group's operand below 2^31
-    return a_elems < ((int64_t)1 << 29) - 65536 && b_elems < ((int64_t)1 << 29) - 65536;
-}
-
-// The rule: 64 x 128 tiles, where they give two workgroups per compute unit, one with long contractions, or half of one over
-// four K ranges of at least 512 indices.  Below that the fp32 kernel's smaller tiles fill the chip better: 8 workers x (128 x
-// 1024 x 1024) 29 us with it, 28 over four ranges here; 4 x (112 x 120 .. 280 x 1084 .. 120) 13 against 17 us.  With 256 to
-// 511 tiles, the fp32 kernel's 64 x 64 tiles against this kernel: 32 x (128 x 512 x 1024) 49 and 47 us, 24 x (192 x 512 x
-// 2048) 116 and 107, 40 x (64 x 1024 x 1536) 99 and 95, 16 x (128 x 1024 x 3072) 135 and 135; two K ranges would take 48,
-// 105, 92 and 121 us but 64 MB and more of scratch, where these shapes need none.  Contractions are rounded up to groups of
-// four slices (128 indices); short ones gain all the same (us per two rounds of two steps, fp32 kernels and these: 64 x (64 x
-// 1028 x 36) 367 and 289, 64 x (128 x 2048 x 36) 831 and 632, 64 x (16 x 1024 x 64) 244 and 208, 64 x (64 x 1024 x 132) 399
-// and 352).
-bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits) {
-    if (N < 128 || !gemm_split_fits((int64_t)M * K, (int64_t)K * N)) return false;
-    const int64_t tiles = (int64_t)groups * ((M + 63) / 64) * ((N + 127) / 128);
-    *splits = tiles < 256 ? 4 : 1;
-    return tiles >= 512 || (tiles >= 256 && K >= 1024) || (tiles >= 128 && K >= 2048);
-}
 
 // A first layer whose weight gradient goes by column strips has its products in the strips' ranges, few of them, whatever its own plan
 // would be; callers that drive the steps one by one form them here.  Where 64 x 128 tiles leave much of a round of two per compute

@@ -22,7 +22,7 @@
 #include <string>
 #include <vector>
 
-#include "mlp_strip_plan.h"
+#include "gemm_f32_plan.h"
 #include "ols_internal.h"
 
 using namespace ols;
@@ -376,9 +376,7 @@ void plan_workspace(ols_ctx* c) {
                 gemm_f32_fwd_plan(c->m, c->B, c->dims[l + 1], c->dims[l], c->lean, &variant, &splits);
                 c->fwd_variant[l] = variant;
                 c->fwd_splits[l] = splits;
-                int ranges;
-                if (l == 0 && variant != 33 && mlp_strip_plan(c->m, c->B, c->dims[1], c->dims[0], splits > 1 ? 8 : 1, &ranges))
-                    c->strip_ranges = ranges;   // (the forward GEMM then takes the same products in the same order, see compute_gradients)
+                if (l == 0) c->strip_ranges = mlp_first_layer_strips(c->m, c->B, c->dims[1], c->dims[0], c->lean);
                 if (splits > 1) need_partial = std::max<int64_t>(need_partial, 8 * m * B * c->dims[l + 1] * 4);
             }
             if (need_partial) c->off_partial = take(need_partial);

@@ -201,23 +201,16 @@ struct GemmArgs {
 // fp32 MFMA.  fwd: C[M][N] = relu(A[M][K] W[K][N] + bias);  dw: C[M][N] = A[K][M]^T B[K][N];
 // da: C[M][N] = (A[M][K] B[N][K]^T) * (mask > 0)
 hipError_t launch_gemm_f32_fwd(const GemmArgs& g, hipStream_t s, int variant);
-void gemm_f32_fwd_plan(int groups, int M, int N, int K, bool lean, int* variant, int* splits);   // lean: with little scratch
 hipError_t launch_gemm_f32_dw(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_gemm_f32_da(const GemmArgs& g, hipStream_t s, int variant);
 hipError_t launch_splitk_finish(const float* partial, int splits, const GemmArgs& g, hipStream_t s);
-// forward and delta of small launches (kernels_gemm_small.hip), and whether a shape takes them (forward: `ranges`, the K ranges
-// over which the 64 x 64 tiles would add it; 0: as if they were not at their best)
-bool gemm_small_fwd_fits(int groups, int M, int N, int K, int ranges);
-bool gemm_small_da_fits(int groups, int M, int N, int K);
+// forward and delta of small launches (kernels_gemm_small.hip; gemm_f32_plan.h: whether an fp32 shape takes them)
 hipError_t launch_gemm_small_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_small_da(const GemmArgs& g, hipStream_t s);
 bool gemm_small_bf16_fits(const GemmArgs& g, bool fwd);
 hipError_t launch_gemm_small_bf16_fwd(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_small_bf16_da(const GemmArgs& g, hipStream_t s);
-// forward on the bf16 matrix cores with every operand split exactly into three bf16 terms (fp32 accuracy): whether, and
-// over how many K ranges, a shape takes it
-bool gemm_split_fits(int64_t a_elems, int64_t b_elems);   // elements a group's operand spans
-bool gemm_split_fwd_plan(int groups, int M, int N, int K, int* splits);
+// forward on the bf16 matrix cores with every operand split exactly into three bf16 terms (fp32 accuracy)
 hipError_t launch_gemm_split_fwd(const GemmArgs& g, hipStream_t s);
 // Weight gradient of an fp32 MLP's first hidden layer by column strips (kernels_mlp_strip.hip); with the fused update it can form
 // the next step's forward product as well.  Whether a shape takes it, and over how many ranges of the weights' rows: mlp_strip_plan.h.

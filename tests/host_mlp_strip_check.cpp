@@ -1,11 +1,13 @@
 // Host check of the strip kernel's byte offsets (csrc/mlp_strip_plan.h).  For every layer that the rule takes, near the largest
 // operands that it may: what its lanes form for rows and samples that exist is their place, and what they form for those that do
 // not -- rows of the last tile past the weights, samples past the batch, lanes without a column -- lies past the operand's end
-// and does not wrap.  Built with the host compiler by tests/test_mlp_strip_plan_cpu.py; prints the number of mismatches.
-#include "mlp_strip_plan.h"
+// and does not wrap.  Built with the host compiler by tests/test_mlp_strip_plan_cpu.py; prints the number of mismatches -- or, with
+// arguments "workers batch columns rows" for any number of first layers, over how many ranges each goes by column strips.
+#include "gemm_f32_plan.h"
 
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <initializer_list>
 
 using namespace ols;
@@ -37,7 +39,11 @@ static void check(int B, int N, int K) {
     operand("delta", 0, strip_samples(B) - 1, B, N, B, N, K);
 }
 
-int main() {
+int main(int argc, char** argv) {
+    if (argc > 1) {
+        for (int i = 1; i + 3 < argc; i += 4) std::printf("%d\n", mlp_first_layer_strips(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), false));
+        return 0;
+    }
     check(32, 9996, 53700);    // 2 x (53700-9996-10): 31 KiB per row, 60 rows of the last tile do not exist
     check(32, 3040, 176580);
     check(64, 512, 3072);

@@ -20,7 +20,14 @@ SHAPES = [
     (10, (2060, 388, 10), 72),          # several ranges, the last one short
     (12, (1856, 380, 24), 128),         # several ranges, whole batch; more than 16 classes
     (32, (1028, 640, 9), 4),            # the smallest batch
+    (64, (520, 380, 36, 12, 7), 64),    # whole batch blocks and other hidden layers again
+    (32, (1028, 896, 9), 4),            # the smallest batch again, on state beyond the memory-side cache in whole lines
+    (60, (324, 1024, 10), 36),          # several rounds of strips, the same state
+    (28, (616, 1024, 9), 128),          # by halves of a whole batch, the same state
+    (108, (2000, 100, 10), 20),         # fewer columns than a strip; two ranges
 ]
+# over how many ranges of the weights' rows they go by column strips (0: by other kernels), which test_mlp_strip_plan_cpu.py checks
+RANGES = [1, 0, 1, 6, 6, 0, 1, 1, 1, 1, 2]
 
 
 def case(m, dims, batch, nb, seed):
@@ -116,6 +123,34 @@ def test_infinite_and_huge_values(shape):
     assert np.isnan(a[0][2]).any()
     solo = run(m, dims, batch, X, labels, x0, 4, 2, True)     # before any synchronisation the other workers are untouched
     assert np.isfinite(solo[0][3]).all() and np.isfinite(solo[0][m - 1]).all()
+
+
+@pytest.mark.parametrize("e", [60, 100])
+@pytest.mark.parametrize("small", ["batch", "delta"])
+def test_gradients_over_the_exponent_range(small, e):
+    """A batch scaled down and first-layer weights scaled up by 2^e, or the output layer's weights, and with them the delta, scaled
+    down by 2^e: the split operands keep their bits while their last term is a normal bf16."""
+    m, dims, batch = SHAPES[0]
+    cfg, X, labels, x0 = case(m, dims, batch, 1, 518)
+    X, x0, n_w = X.copy(), x0.copy(), dims[0] * dims[1]
+    if small == "batch":
+        X, x0[:n_w] = np.ldexp(X, -e).astype(np.float32), np.ldexp(x0[:n_w], e)
+    else:
+        w2 = slice(n_w + dims[1], n_w + dims[1] + dims[1] * dims[2])
+        x0[w2] = np.ldexp(x0[w2], -e)
+    with make_session(m, cfg.d, 2, 0.6, 0.05, 0.0) as s:
+        s.set_option(B.OLS_OPT_FUSE_GEMM_UPDATE, 0)
+        s.attach_mlp(dims, batch, "f32")
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_batch(Xd[:, 0], yd[:, 0])
+        s.local_step()
+        g, losses = s.gradient(), s.losses()
+    for i in (0, m - 1):
+        loss, grad = O.mlp_loss_grad(x0, dims, X[i, 0], labels[i, 0])
+        assert abs(losses[i] - loss) <= 1e-5 * abs(loss)
+        for sl in (slice(0, n_w), slice(n_w, n_w + dims[1]), slice(n_w + dims[1], None)):
+            assert np.abs(grad[sl]).max() > 0.0 and max_norm_ratio(g[i][sl], grad[sl]) <= GRAD_TOL
 
 
 @pytest.mark.parametrize("m,dims,batch", [(64, (324, 388, 36, 10), 36), (10, (2060, 388, 36, 10), 72)])   # last tiles of 4 and 12 rows
