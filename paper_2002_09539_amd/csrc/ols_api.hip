@@ -263,6 +263,8 @@ int wait_if_update_must(ols_ctx* c) {
     return main_waits_for_anchor(c);
 }
 
+constexpr int kMostLayers = 64;   // of an MLP
+
 int64_t align256(int64_t v) { return round_up(v, 256); }
 
 // Static model workspace for callers that cannot allocate (ols_run_steps_static).  One copy per GPU, held until the
@@ -1035,14 +1037,15 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
     // tau 2 178 -> 169, 2 x (848-136-120-10, 184) fp32 182 -> 133, bf16 186 -> 144, 4 x (1208-2032-464-10, 224) bf16 874 -> 824; three
     // large layers, 16 x (3072-2048-2048-2048-10, 256), the same (8847 and 8838).
     const bool together = upd && !c->dry && !c->trace && !c->timing && !c->gemm_variant[1];
-    std::vector<GemmArgs> waiting;
+    GemmArgs waiting[kMostLayers];   // (on the stack: nothing here may throw)
+    int n_waiting = 0;
     auto launch_waiting = [&]() -> int {
-        if (waiting.empty()) return OLS_OK;
+        if (!n_waiting) return OLS_OK;
         if (int e = wait_if_update_must(c)) return e;
         const int e = enqueue(c, OLS_K_GEMM_DW, 0, src_buf, dst_buf, [&](hipStream_t s) {
-            return bf ? launch_gemm_bf16_dw_layers(waiting.data(), (int)waiting.size(), s) : launch_gemm_f32_dw_layers(waiting.data(), (int)waiting.size(), s);
+            return bf ? launch_gemm_bf16_dw_layers(waiting, n_waiting, s) : launch_gemm_f32_dw_layers(waiting, n_waiting, s);
         });
-        waiting.clear();
+        n_waiting = 0;
         return e;
     };
     for (int l = L - 2; l >= 0; --l) {
@@ -1096,7 +1099,7 @@ int compute_gradients(ols_ctx* c, const FusedUpdate* upd, int src_buf, int dst_b
         gw.K = B;
         const bool strip = l == 0 && c->strip_ranges && !c->gemm_variant[1];
         if (together && !strip) {
-            waiting.push_back(gw);
+            waiting[n_waiting++] = gw;
             continue;
         }
         if ((rc = launch_waiting())) return rc;
@@ -1371,7 +1374,7 @@ int ols_attach_lsq(ols_handle c, int batch) {
 int ols_attach_mlp(ols_handle c, int n_layers, const int* dims, int batch, int gemm_dtype) {
     if (int rc = need(c)) return rc;
     if (c->k != 0) return fail(OLS_ESTATE, "models are attached before the first local step");
-    if (n_layers < 1 || n_layers > 64 || !dims) return fail(OLS_EINVAL, "n_layers must be in [1, 64]");
+    if (n_layers < 1 || n_layers > kMostLayers || !dims) return fail(OLS_EINVAL, "n_layers must be in [1, %d]", kMostLayers);
     if (gemm_dtype != 0 && gemm_dtype != 1) return fail(OLS_EINVAL, "gemm_dtype must be 0 (fp32) or 1 (bf16)");
     if (gemm_dtype == 1 && c->inited)
         return fail(OLS_ESTATE, "a bf16 model is attached (and its workspace bound) before ols_init_params");
