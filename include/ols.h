@@ -70,7 +70,9 @@ enum {
     OLS_OPT_DRY_RUN = 4,       /* 1: advance the schedule and record the launch trace but launch nothing
                                   (host-logic tests on machines without a GPU); default 0                     */
     OLS_OPT_KERNEL_TIMING = 5, /* 1: bracket every kernel with HIP events on its own stream and accumulate
-                                  per-kernel durations (see ols_kernel_stats); default 0                      */
+                                  per-kernel durations (see ols_kernel_stats); default 0.  The weight gradients of
+                                  an MLP's layers, several of which share a launch otherwise, then (and with
+                                  OLS_OPT_TRACE) have one each; same bits                                     */
     OLS_OPT_TRACE = 6,         /* 1: keep a host-side log of launches (see ols_trace_get); default 0          */
     OLS_OPT_MEAN_SPLIT = 7,    /* anchor-mean kernel: 0 = choose from (m, d); 1, 2, 4, 8 or 16 = number of
                                   lane groups / wavefronts of a workgroup sharing the replica axis (combined by
@@ -340,7 +342,8 @@ OLS_API int ols_anchor_update_async(ols_handle h);
  * separate calls, to the bit, and the same launches -- except that the steps of a round of a small least-squares
  * problem whose refresh runs in line may share one launch (not while OLS_OPT_TRACE or OLS_OPT_KERNEL_TIMING is on), and
  * that the weight gradient of a large fp32 MLP's first hidden layer may form the next step's first product in its launch
- * (not while OLS_OPT_TRACE is on; OLS_K_GEMM_FWD is then counted for the first step of a call only).  Such a layer's
+ * (not while OLS_OPT_TRACE is on, nor at the end of a round where OLS_OPT_ANCHOR_DELAY_US outlasts the round's other steps;
+ * OLS_K_GEMM_FWD is otherwise counted for the first step of a call only).  Such a layer's
  * kernels are chosen for this loop and taken by the separate calls as well, for the same bits; without the product ahead
  * most shapes are still faster with them than with the other kernels, some take up to a tenth longer.  Stops at the first
  * error and returns it.  OLS_ESTATE without an attached model or when a pull or an anchor refresh is due. */

@@ -242,6 +242,15 @@ bool refresh_fits_in_line(const ols_ctx* c) {
            (4 * (int64_t)c->m + 4) * c->ld <= kInLineRefreshBytes;
 }
 
+// An emulated latency that outlasts the round's other steps is hidden behind the next round's first forward GEMM as well, which the
+// main stream passes before it waits for the anchor: the last step of a round then leaves that product to it.  The steps are taken as
+// 16 bytes per element-replica at 2 TB/s: nearer the line the launch that leaves the product out costs more than is hidden.  us per
+// step of 16 x (3072-512-10, 128), product formed ahead / left: tau 1, 10 us 168 / 168, 50 us 208 / 180, 200 us 358 / 330; tau 2 (the line
+// is at 202), 150 us 167 / 181, 200 us 179 / 181, 400 us 279 / 267; 64 x (3072-1024-10, 64) tau 8 (11,300), 6400 us 899 / 903.
+bool refresh_outlasts_round(const ols_ctx* c) {
+    return c->anchor_delay_us > 0 && !serialized(c) && c->stream[1] != c->stream[0] && (double)c->anchor_delay_us > (double)(c->tau - 1) * 16.0 * (double)c->m * (double)c->d / 2e6;
+}
+
 // The main stream must not pass this point before the in-flight anchor refresh has finished.
 int main_waits_for_anchor(ols_ctx* c) {
     if (!c->anchor_inflight) return OLS_OK;
@@ -1761,8 +1770,8 @@ int ols_run_steps(ols_handle c, int64_t steps, const float* X, const void* y, in
         int rc = ols_set_batch(c, X + b * x_batch, (int64_t)nb * x_batch, (const char*)y + (size_t)(b * y_batch) * y_elem,
                                (int64_t)nb * y_batch);
         if (rc) return rc;
-        const bool rewritten = (c->k + 1) % c->tau == 0 && (c->mix_w || c->snap);
-        c->next_X = look_ahead && it + 1 < steps && !rewritten ? X + (c->k + 1) % nb * x_batch : nullptr;
+        const bool apart = (c->k + 1) % c->tau == 0 && (c->mix_w || c->snap || refresh_outlasts_round(c));   // models rewritten, or the product waits
+        c->next_X = look_ahead && it + 1 < steps && !apart ? X + (c->k + 1) % nb * x_batch : nullptr;
         rc = ols_local_step(c);
         if (rc) return rc;
         if (c->pull_due) {

@@ -207,3 +207,28 @@ def test_timing_times_the_launches_of_the_loop(shape):
         s.run_resident(2, Xd, yd)
         stats = s.kernel_stats()
         assert stats["gemm_fwd"][0] == 2 and stats["gemm_dw"][0] == 5 and stats["head_fwd"][0] == 5
+
+
+@pytest.mark.parametrize("tau,delay,serialize,products", [
+    (1, 50, 0, 4),     # nothing else of a round to hide behind: every step's forward GEMM beside the refresh
+    (1, 50, 1, 1),     # blocking: nothing to hide
+    (2, 200, 0, 2),    # longer than the round's other step (64 x 130,000 element-replicas, 67 us at the rule's rate): the first step of each round
+    (2, 10, 0, 1),     # shorter
+    (1, 0, 0, 1),
+])
+def test_forward_gemms_that_an_emulated_latency_hides_behind(tau, delay, serialize, products):
+    m, dims, batch = SHAPES[0]
+    cfg, X, labels, x0 = case(m, dims, batch, 2, 519)
+    options = [(B.OLS_OPT_SERIALIZE, serialize), (B.OLS_OPT_ANCHOR_DELAY_US, delay)]
+    with make_session(m, cfg.d, tau, 0.6, 0.05, 0.9) as s:
+        for key, value in options:
+            s.set_option(key, value)
+        s.attach_mlp(dims, batch, "f32")
+        Xd, yd = s.upload(X), s.upload(labels)
+        s.init_params(x0)
+        s.set_option(B.OLS_OPT_KERNEL_TIMING, 1)
+        s.run_resident(4, Xd, yd)
+        assert s.kernel_stats()["gemm_fwd"][0] == products
+    setup = lambda s: [s.set_option(key, value) for key, value in options]   # noqa: E731
+    a = run(m, dims, batch, X, labels, x0, tau, 6, True, setup=setup)
+    assert same(a, run(m, dims, batch, X, labels, x0, tau, 6, False, setup=setup)) and same(a, run(m, dims, batch, X, labels, x0, tau, 6, True))
