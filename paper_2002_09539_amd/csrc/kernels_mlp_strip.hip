@@ -16,13 +16,20 @@
 //
 // What bounds it: the state, 16 bytes per weight with momentum, walked down in strips: a probe that only streams it in this order
 // takes 579 us for 64 x (3072 x 1024) and 80 for 16 x (3072 x 512) (whole tiles side by side 537 and 72; strips of 64 columns 640 and
-// 81).  Us per launch, batch 64 and 128: 580 - 640 and 118 - 122, where the weight gradient alone took 582 - 602 and 100 - 105 and
-// the forward GEMM 187 and 59 + 6; without the next product 600 - 627 and 102.  At batch 128 the products are next: the launch takes
-// 103 us with no state at all, vector ALU (splitting, update), LDS and matrix work in phases that eight wavefronts in step do not
-// overlap.  Not kept: two elements per access, which costs the exchange of two lanes and touches four rows (654 and 144 us);
-// fp32 matrix products for the gradient (631 and 140); at batch 128 the delta split anew for every tile instead of by halves (134),
-// at batch 64 by halves as well (601).  Two rounds: 64 x (3072-1024-10, 64) tau 8 12770 -> 10150, 16 x (3072-512-10, 128) tau 2
-// 651 -> 567; 80 random fp32 MLPs that take it 1.09 times as fast in the geometric mean.
+// 81).  Us per launch, batch 64 and 128: 580 - 640 and 118 - 124 (up to 147 where the clock is still rising), where the weight gradient
+// alone took 582 - 602 and 100 - 105 and the forward GEMM 187 and 59 + 6; without the next product 590 - 627 and 102 - 105.  Counters, with
+// the product: matrix pipes busy 27 % and 22 - 27 %, 3.44 GB and 0.51 GB moved (3.25 and 0.46 of state and operands).  At batch 128 the
+// products are next: the launch takes 103 us with no state at all, vector ALU (splitting, update), LDS and matrix work in phases that
+// eight wavefronts in step do not overlap.  Not kept: two elements per access, which costs the exchange of two lanes and touches four
+// rows (654 and 144 us); fp32 matrix products for the gradient (631 and 140); at batch 128 the delta split anew for every tile instead of
+// by halves (134), at batch 64 by halves as well (601).  Two rounds: 64 x (3072-1024-10, 64) tau 8 12900 -> 10190, 16 x (3072-512-10, 128)
+// tau 2 644 -> 567; 40 random MLPs with one hidden layer that take it 1.15 times as fast in the geometric mean, one 2 % slower (20 x
+// (1772-672-7, 20) tau 1, 285 and 290 us).
+//
+// Accuracy: six of the nine bf16 products of every fp32 one, for operands of at least 2^-109 (below, up to 2^-133 of an operand is
+// missing; split_bf16.h).  From the same operands, relative 2-norm against 64 bits, over 42 layers (3 - 64 workers, 520 - 3072 x 84 - 2044,
+// batch 16 - 128): gradients 2.7e-8 - 4.7e-8, 0.34 - 0.53 times the error of the fp32 matrix cores' 128 x 128 tiles, products 1.0e-7 -
+// 3.4e-7, 0.30 - 0.47 times that of their 64 x 64 tiles.
 #include "gemm_f32_tile.h"
 #include "head_dw_body.h"
 #include "mlp_strip_plan.h"
